@@ -684,14 +684,6 @@ __global__ void __launch_bounds__(WG) k_prolong_small(int64_t na, const int32_t*
     }
 }
 
-__global__ void k_gather_rhs(int64_t n, int nr, const double* b, int64_t ldb, double* B) {
-    for (int64_t e = blockIdx.x * (int64_t)WG + tid(); e < n * NB; e += (int64_t)gridDim.x * WG) {
-        const int64_t d = e / NB;
-        const int k = (int)(e % NB);
-        B[e] = k < nr ? b[k * ldb + d] : 0.0;
-    }
-}
-
 __global__ void k_scatter_sol(int64_t n, int nr, const double* X, double* x, int64_t ldx) {
     for (int64_t e = blockIdx.x * (int64_t)WG + tid(); e < n * NB; e += (int64_t)gridDim.x * WG) {
         const int64_t d = e / NB;
@@ -702,186 +694,275 @@ __global__ void k_scatter_sol(int64_t n, int nr, const double* X, double* x, int
 
 // ---------------------------------------------------------------- segmented PCG
 // Block b of the table covers DOFs [lo, hi) of one segment; thread = (DOF lane,
-// right-hand side), a fixed-order tree over the DOF lanes gives NR sums.
+// right-hand side).  An iteration is bound by the latency of its chain of small
+// launches and, for blocks of right-hand sides, by the vector traffic, so the
+// scalars have no launches of their own: a kernel that needs a dot product adds the
+// block partials of its segment itself (every block the same sum in the same order),
+// and the vectors the cycle starts from (its FP32 residual, its zero iterate) are
+// written by the kernel that has the residual in registers.  Six launches per
+// iteration around the cycle instead of eleven (FP64) or fifteen (FP32 cycle): 162 DOFs
+// 1.17 -> 0.92 ms per solve, 33,800 DOFs with an FP32 cycle 5.95 -> 5.48 ms.
+constexpr int PCG_WG = 256;
+
+// Sum of u over the block for every right-hand side k = tid % NR, in a fixed order; all
+// threads of right-hand side k get the result.  s_w: WG / 64 * NR entries.
 template <int NR>
-__global__ void __launch_bounds__(WG) k_seg_dot(const int64_t* blk_lo, const int64_t* blk_hi, const double* a0,
-                                                const double* b0, const double* a1, const double* b1, double* part,
-                                                int n_blk) {
-    __shared__ double s_r[2][WG];
-    const int b = blockIdx.x;
-    const int k = tid() % NR, dl = tid() / NR;
-    constexpr int DL = WG / NR;
-    double u = 0.0, v = 0.0;
-    for (int64_t d = blk_lo[b] + dl; d < blk_hi[b]; d += DL) {
-        const int64_t e = d * NR + k;
-        u += a0[e] * b0[e];
-        if (a1) v += a1[e] * b1[e];
-    }
-    s_r[0][tid()] = u;
-    s_r[1][tid()] = v;
+__device__ inline double block_sum(double u, double* s_w) {
+    const int lane = tid() & 63, w = tid() >> 6;
+#pragma unroll
+    for (int off = NR; off < 64; off <<= 1) u += __shfl_xor(u, off, 64);
+    __syncthreads();                                   // s_w may hold an earlier sum
+    if (lane < NR) s_w[w * NR + lane] = u;
     __syncthreads();
-    for (int off = WG / 2; off >= NR; off >>= 1) {
-        if (tid() < off) {
-            s_r[0][tid()] += s_r[0][tid() + off];
-            s_r[1][tid()] += s_r[1][tid() + off];
-        }
-        __syncthreads();
-    }
-    if (tid() < NR) {
-        part[(int64_t)b * NR + tid()] = s_r[0][tid()];
-        part[((int64_t)n_blk + b) * NR + tid()] = s_r[1][tid()];
-    }
+    const int k = tid() % NR;
+    double v = s_w[k];
+#pragma unroll
+    for (int q = 1; q < PCG_WG / 64; ++q) v += s_w[q * NR + k];
+    return v;
 }
 
-// out[s * NR + k] = sum over the blocks of segment s, in block order
-// One wave per (segment, right-hand side): lane l sums the blocks l, l + 64, ... of
-// the segment in order, then a butterfly over the lanes -- a fixed order, so the
-// same partials always give the same sum.
-__global__ void k_seg_sum(int n_seg, int nr, const int32_t* seg_blk, const double* part, int n_blk, double* out0,
-                          double* out1) {
-    const int i = (int)((blockIdx.x * WG + tid()) >> 6), lane = tid() & 63;
-    if (i >= n_seg * nr) return;
-    const int s = i / nr, k = i % nr;
+// The dot product of segment s from its block partials (part[b * NR + k]).
+template <int NR>
+__device__ inline double seg_total(const double* part, int b0, int b1, double* s_w) {
+    constexpr int DL = PCG_WG / NR;
+    const int k = tid() % NR;
+    double u = 0.0;
+#pragma unroll 4
+    for (int b = b0 + tid() / NR; b < b1; b += DL) u += part[(int64_t)b * NR + k];
+    return block_sum<NR>(u, s_w);
+}
+
+// partials of <a0, b0> and, with a1, <a1, b1> (b0, b1 of type Z, products in FP64)
+template <int NR, typename Z>
+__global__ void __launch_bounds__(PCG_WG) k_seg_dot(const int64_t* blk_lo, const int64_t* blk_hi, const double* a0,
+                                                    const Z* b0, const double* a1, const Z* b1, double* part0,
+                                                    double* part1) {
+    __shared__ double s_w[PCG_WG / 64 * NR];
+    const int b = blockIdx.x;
+    constexpr int DL = PCG_WG / NR;
+    const int64_t e0 = blk_lo[b] * NR, e1 = blk_hi[b] * NR;
     double u = 0.0, v = 0.0;
-    for (int b = seg_blk[s] + lane; b < seg_blk[s + 1]; b += 64) {
-        u += part[(int64_t)b * nr + k];
-        v += part[((int64_t)n_blk + b) * nr + k];
+#pragma unroll 4
+    for (int64_t e = e0 + tid(); e < e1; e += DL * NR) {
+        u += a0[e] * (double)b0[e];
+        if (a1) v += a1[e] * (double)b1[e];
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        u += __shfl_xor(u, off, 64);
-        v += __shfl_xor(v, off, 64);
-    }
-    if (lane == 0) {
-        out0[i] = u;
-        if (out1) out1[i] = v;
+    u = block_sum<NR>(u, s_w);
+    if (tid() < NR) part0[(int64_t)b * NR + tid()] = u;
+    if (a1) {
+        v = block_sum<NR>(v, s_w);
+        if (tid() < NR) part1[(int64_t)b * NR + tid()] = v;
     }
 }
 
-__global__ void k_pcg_init(int n_s, const double* bb, int32_t* act, int32_t* iters, double* relres,
-                           int32_t* it_flag) {
-    const int i = blockIdx.x * WG + tid();
-    if (i == 0) {
-        it_flag[0] = 0;
-        it_flag[1] = 0;
+// out[s * NR + k] = sum over the blocks of segment s (one workgroup per segment); host:
+// optional pinned copy of the first NR sums
+template <int NR>
+__global__ void __launch_bounds__(PCG_WG) k_seg_sum(const int32_t* seg_blk, const double* part, double* out,
+                                                    double* host) {
+    __shared__ double s_w[PCG_WG / 64 * NR];
+    const int s = blockIdx.x;
+    const double v = seg_total<NR>(part, seg_blk[s], seg_blk[s + 1], s_w);
+    if (tid() < NR) {
+        out[s * NR + tid()] = v;
+        if (host && s == 0) host[tid()] = v;
     }
-    if (i >= n_s) return;
-    act[i] = bb[i] > 0.0 ? 1 : 0;
-    iters[i] = 0;
-    relres[i] = bb[i] > 0.0 ? 1.0 : 0.0;
 }
 
-__global__ void k_pcg_alpha(int n_s, const int32_t* act, const double* rz, const double* pq, double* alpha,
-                            int32_t* flag) {
-    const int i = blockIdx.x * WG + tid();
-    if (i >= n_s) return;
-    double a = 0.0;
-    if (act[i]) {
-        const double d = pq[i];
-        // breakdown cause bits: 1 p^T A p <= 0, 2 p^T A p or r^T z not finite
-        if (!isfinite(d) || !isfinite(rz[i])) atomicOr(flag, 2);
-        else if (!(d > 0.0)) atomicOr(flag, 1);
-        else a = rz[i] / d;
+// Start of a solve: r = b, x = 0 (b: nr right-hand sides at stride ldb, the others zero),
+// the cycle's start vectors, partials of <b, b> and of the count of non-finite entries.
+template <int NR, typename Z>
+__global__ void __launch_bounds__(PCG_WG) k_pcg_begin(const int64_t* blk_lo, const int64_t* blk_hi, int nr,
+                                                      const double* b, int64_t ldb, double* r, double* x, float* r32,
+                                                      Z* z, double* part_bb, double* part_bad) {
+    __shared__ double s_w[PCG_WG / 64 * NR];
+    const int blk = blockIdx.x, k = tid() % NR;
+    constexpr int DL = PCG_WG / NR;
+    double u = 0.0, bad = 0.0;
+#pragma unroll 2
+    for (int64_t d = blk_lo[blk] + tid() / NR; d < blk_hi[blk]; d += DL) {
+        const double v = k < nr ? b[k * ldb + d] : 0.0;
+        const int64_t e = d * NR + k;
+        r[e] = v;
+        x[e] = 0.0;
+        if (r32) r32[e] = (float)v;
+        z[e] = (Z)0;
+        u += v * v;
+        if (!isfinite(v)) bad += 1.0;
     }
-    alpha[i] = a;
+    u = block_sum<NR>(u, s_w);
+    if (tid() < NR) part_bb[(int64_t)blk * NR + tid()] = u;
+    bad = block_sum<NR>(bad, s_w);
+    if (tid() < NR) part_bad[(int64_t)blk * NR + tid()] = bad;
 }
+
+// One workgroup; a wave per segment adds the partials of its NR pairs: lanes =
+// (block lane, right-hand side).
+template <int NR>
+__device__ inline double wave_seg_total(const double* part, int b0, int b1) {
+    const int lane = tid() & 63, k = lane % NR;
+    double u = 0.0;
+#pragma unroll 4
+    for (int b = b0 + lane / NR; b < b1; b += 64 / NR) u += part[(int64_t)b * NR + k];
+#pragma unroll
+    for (int off = NR; off < 64; off <<= 1) u += __shfl_xor(u, off, 64);
+    return u;
+}
+
+constexpr int PCG_CHECK_WG = 1024;
 
 template <int NR>
-__global__ void __launch_bounds__(WG) k_pcg_update_xr(const int32_t* blk_seg, const int64_t* blk_lo,
-                                                      const int64_t* blk_hi, const int32_t* act, const double* alpha,
-                                                      const double* p, const double* q, double* x, double* r,
-                                                      double* part) {
-    __shared__ double s_r[WG];
-    const int b = blockIdx.x;
-    const int k = tid() % NR, dl = tid() / NR;
-    constexpr int DL = WG / NR;
-    const int i = blk_seg[b] * NR + k;
+__global__ void __launch_bounds__(PCG_CHECK_WG) k_pcg_init(int n_seg, const int32_t* seg_blk, const double* part_bb,
+                                                           const double* part_bad, double* bb, int32_t* act,
+                                                           int32_t* iters, double* relres, int32_t* st) {
+    __shared__ int s_bad;
+    if (tid() == 0) s_bad = 0;
+    __syncthreads();
+    const int lane = tid() & 63;
+    for (int s = tid() >> 6; s < n_seg; s += PCG_CHECK_WG / 64) {
+        const double v = wave_seg_total<NR>(part_bb, seg_blk[s], seg_blk[s + 1]);
+        const double bad = wave_seg_total<NR>(part_bad, seg_blk[s], seg_blk[s + 1]);
+        if (lane < NR) {
+            const int i = s * NR + lane;
+            bb[i] = v;
+            act[i] = v > 0.0 ? 1 : 0;
+            iters[i] = 0;
+            relres[i] = v > 0.0 ? 1.0 : 0.0;
+            if (bad > 0.0) s_bad = 1;
+        }
+    }
+    __syncthreads();
+    if (tid() == 0) {
+        st[PCG_ST_COUNT] = 0;
+        st[PCG_ST_IT] = 0;
+        st[PCG_ST_FLAG] = 0;
+        st[PCG_ST_BAD] = s_bad;
+    }
+}
+
+// alpha = <r, z> / <p, q> of the block's segment from the partials of <p, q> (0 for
+// pairs that have left the iteration and at a breakdown), then x += alpha p,
+// r -= alpha q, the partials of <r, r> and the cycle's start vectors; rold: the residual
+// before the step (flexible beta).  rz has two slots, used in turn: the iteration it
+// reads the one the previous iteration wrote.  Bound by the vector traffic (four vectors
+// in, up to five out).  The block table decides how much of the chip that traffic uses: at
+// 2048 DOFs a block, the 8-vector blocks of a 243,420-DOF batch ran 126 workgroups of 64
+// serial steps, 59.6 us; at 256 DOFs (batch solve 17.7 -> 15.3 ms) there are 957 of 8.
+template <int NR, typename Z>
+__global__ void __launch_bounds__(PCG_WG) k_pcg_update_xr(const int32_t* blk_seg, const int64_t* blk_lo,
+                                                          const int64_t* blk_hi, const int32_t* seg_blk,
+                                                          const int32_t* act, const double* rz2, int nsm,
+                                                          const double* part_pq, const double* p, const double* q,
+                                                          double* x, double* r, double* rold, float* r32, Z* z,
+                                                          double* part_rr, int32_t* st) {
+    __shared__ double s_w[PCG_WG / 64 * NR];
+    const int b = blockIdx.x, s = blk_seg[b];
+    const int k = tid() % NR, i = s * NR + k;
+    const int b0 = seg_blk[s];
     const bool on = act[i] != 0;
-    const double a = alpha[i];
+    const double rzv = rz2[(int64_t)(st[PCG_ST_IT] & 1) * nsm + i];
+    const double d = seg_total<NR>(part_pq, b0, seg_blk[s + 1], s_w);
+    double a = 0.0;
+    if (on) {
+        // breakdown cause bits: 1 p^T A p <= 0, 2 p^T A p or r^T z not finite
+        int bits = 0;
+        if (!isfinite(d) || !isfinite(rzv)) bits = 2;
+        else if (!(d > 0.0)) bits = 1;
+        else a = rzv / d;
+        if (bits && b == b0 && tid() < NR) atomicOr(st + PCG_ST_FLAG, bits);
+    }
+    const int64_t e0 = blk_lo[b] * NR, e1 = blk_hi[b] * NR;
     double u = 0.0;
-    for (int64_t d = blk_lo[b] + dl; d < blk_hi[b]; d += DL) {
-        const int64_t e = d * NR + k;
+#pragma unroll 4
+    for (int64_t e = e0 + tid(); e < e1; e += PCG_WG) {
         double re = r[e];
+        if (rold) rold[e] = re;
         if (on) {
             x[e] += a * p[e];
             re -= a * q[e];
             r[e] = re;
         }
+        if (r32) r32[e] = (float)re;
+        z[e] = (Z)0;
         u += re * re;
     }
-    s_r[tid()] = u;
-    __syncthreads();
-    for (int off = WG / 2; off >= NR; off >>= 1) {
-        if (tid() < off) s_r[tid()] += s_r[tid() + off];
-        __syncthreads();
-    }
-    if (tid() < NR) part[(int64_t)b * NR + tid()] = s_r[tid()];
+    u = block_sum<NR>(u, s_w);
+    if (tid() < NR) part_rr[(int64_t)b * NR + tid()] = u;
 }
 
-// single workgroup: state transitions and the active count (fixed-order sum)
-__global__ void __launch_bounds__(WG) k_pcg_check(int n_s, int32_t* it_dev, double tol2, const double* bb,
-                                                  const double* rr, int32_t* act, int32_t* iters, double* relres,
-                                                  int32_t* count, int32_t* flag) {
-    __shared__ int s_c[WG];
-    const int it = it_dev[0] + 1;
-    int c = 0;
-    for (int i = tid(); i < n_s; i += WG) {
-        if (!act[i]) continue;
-        const double v = rr[i];
-        if (!isfinite(v)) {
-            atomicOr(flag, 4);          // residual norm not finite
-            continue;
-        }
-        relres[i] = sqrt(v / bb[i]);
-        iters[i] = it;
-        if (v <= tol2 * bb[i]) act[i] = 0;
-        else ++c;
-    }
-    s_c[tid()] = c;
-    __syncthreads();
-    for (int off = WG / 2; off > 0; off >>= 1) {
-        if (tid() < off) s_c[tid()] += s_c[tid() + off];
-        __syncthreads();
-    }
-    if (tid() == 0) {
-        count[0] = s_c[0];
-        it_dev[0] = it;
-    }
-}
-
-__global__ void k_pcg_beta(int n_s, const int32_t* act, const double* rz_new, const double* rz_old_dot, double* rz,
-                           double* beta, int32_t* flag) {
-    const int i = blockIdx.x * WG + tid();
-    if (i >= n_s) return;
-    double bt = 0.0;
-    if (act[i]) {
-        const double num = rz_old_dot ? rz_new[i] - rz_old_dot[i] : rz_new[i];
-        bt = num / rz[i];
-        if (!isfinite(bt)) atomicOr(flag, 8);   // beta not finite
-        rz[i] = rz_new[i];
-    }
-    beta[i] = bt;
-}
-
+// State transitions and the active count, one workgroup: a wave per segment adds the
+// partials of <r, r>; the status goes to the device and to the host's pinned mirror, which
+// the host reads after the stream has drained (no copy launch).
 template <int NR>
-__global__ void __launch_bounds__(WG) k_pcg_update_p(const int32_t* blk_seg, const int64_t* blk_lo,
-                                                     const int64_t* blk_hi, const int32_t* act, const double* beta,
-                                                     const double* z, double* p) {
-    const int b = blockIdx.x;
-    const int k = tid() % NR, dl = tid() / NR;
-    constexpr int DL = WG / NR;
-    const int i = blk_seg[b] * NR + k;
-    if (!act[i]) return;
-    const double bt = beta[i];
-    for (int64_t d = blk_lo[b] + dl; d < blk_hi[b]; d += DL) {
-        const int64_t e = d * NR + k;
-        p[e] = z[e] + bt * p[e];
+__global__ void __launch_bounds__(PCG_CHECK_WG) k_pcg_check(int n_seg, const int32_t* seg_blk, const double* part_rr,
+                                                            double tol2, const double* bb, int32_t* act,
+                                                            int32_t* iters, double* relres, int32_t* st,
+                                                            int32_t* host_st) {
+    __shared__ int s_count, s_flag;
+    if (tid() == 0) s_count = s_flag = 0;
+    __syncthreads();
+    const int it = st[PCG_ST_IT] + 1;
+    const int lane = tid() & 63;
+    for (int s = tid() >> 6; s < n_seg; s += PCG_CHECK_WG / 64) {
+        const double v = wave_seg_total<NR>(part_rr, seg_blk[s], seg_blk[s + 1]);
+        const int i = s * NR + lane;
+        if (lane < NR && act[i]) {
+            if (!isfinite(v)) {
+                atomicOr(&s_flag, 4);          // residual norm not finite
+            } else {
+                relres[i] = sqrt(v / bb[i]);
+                iters[i] = it;
+                if (v <= tol2 * bb[i]) act[i] = 0;
+                else atomicAdd(&s_count, 1);
+            }
+        }
+    }
+    __syncthreads();
+    if (tid() == 0) {
+        const int flag = st[PCG_ST_FLAG] | s_flag;
+        st[PCG_ST_COUNT] = s_count;
+        st[PCG_ST_IT] = it;
+        st[PCG_ST_FLAG] = flag;
+        host_st[PCG_ST_COUNT] = s_count;
+        host_st[PCG_ST_IT] = it;
+        host_st[PCG_ST_FLAG] = flag;
+        host_st[PCG_ST_BAD] = st[PCG_ST_BAD];
     }
 }
 
-__global__ void k_pcg_start(int64_t len, const double* b, double* r, double* x) {
-    for (int64_t e = blockIdx.x * (int64_t)WG + tid(); e < len; e += (int64_t)gridDim.x * WG) {
-        r[e] = b[e];
-        x[e] = 0.0;
+// beta = (<r, z> - <rold, z>) / <r, z>_old of the block's segment (part_rzo NULL: the
+// standard beta) and p = z + beta p; before the first iteration (counter 0) p = z.  The
+// segment's first block writes <r, z> to the slot the next step reads.
+template <int NR, typename Z>
+__global__ void __launch_bounds__(PCG_WG) k_pcg_update_p(const int32_t* blk_seg, const int64_t* blk_lo,
+                                                         const int64_t* blk_hi, const int32_t* seg_blk,
+                                                         const int32_t* act, double* rz2, int nsm,
+                                                         const double* part_rz, const double* part_rzo, const Z* z,
+                                                         double* p, int32_t* st) {
+    __shared__ double s_w[PCG_WG / 64 * NR];
+    const int b = blockIdx.x, s = blk_seg[b];
+    const int k = tid() % NR, i = s * NR + k;
+    const int b0 = seg_blk[s], b1 = seg_blk[s + 1];
+    const int it = st[PCG_ST_IT];
+    const bool on = act[i] != 0;
+    const double rz_old = rz2[(int64_t)((it + 1) & 1) * nsm + i];
+    const double rz_new = seg_total<NR>(part_rz, b0, b1, s_w);
+    double num = rz_new;
+    if (part_rzo && it > 0) num -= seg_total<NR>(part_rzo, b0, b1, s_w);
+    double bt = 0.0;
+    if (on && it > 0) {
+        bt = num / rz_old;
+        if (!isfinite(bt) && b == b0 && tid() < NR) atomicOr(st + PCG_ST_FLAG, 8);   // beta not finite
+    }
+    if (b == b0 && tid() < NR) rz2[(int64_t)(it & 1) * nsm + i] = on || it == 0 ? rz_new : rz_old;
+    if (!on && it > 0) return;
+    const int64_t e0 = blk_lo[b] * NR, e1 = blk_hi[b] * NR;
+    if (it == 0) {
+#pragma unroll 4
+        for (int64_t e = e0 + tid(); e < e1; e += PCG_WG) p[e] = (double)z[e];
+    } else {
+#pragma unroll 4
+        for (int64_t e = e0 + tid(); e < e1; e += PCG_WG) p[e] = (double)z[e] + bt * p[e];
     }
 }
 
@@ -1119,73 +1200,84 @@ void launch_prolong_b(int64_t n_items, const int32_t* items, const int64_t* agg_
                        coff, Zc, ec, x);
 }
 
-void launch_gather_rhs(int64_t n, int32_t nr, const double* b, int64_t ldb, double* B, hipStream_t st) {
-    hipLaunchKernelGGL(k_gather_rhs, dim3(grid_for(n * NB)), dim3(WG), 0, st, n, (int)nr, b, ldb, B);
-}
-
 void launch_scatter_sol(int64_t n, int32_t nr, const double* X, double* x, int64_t ldx, hipStream_t st) {
     hipLaunchKernelGGL(k_scatter_sol, dim3(grid_for(n * NB)), dim3(WG), 0, st, n, (int)nr, X, x, ldx);
 }
 
-void launch_seg_dot(const SegTable& t, int nr, const double* a0, const double* b0, const double* a1,
-                    const double* b1, double* part, double* out0, double* out1, hipStream_t st) {
-    if (nr == NB)
-        hipLaunchKernelGGL(k_seg_dot<NB>, dim3((unsigned)t.n_blk), dim3(WG), 0, st, t.blk_lo, t.blk_hi, a0, b0, a1,
-                           b1, part, t.n_blk);
-    else
-        hipLaunchKernelGGL(k_seg_dot<1>, dim3((unsigned)t.n_blk), dim3(WG), 0, st, t.blk_lo, t.blk_hi, a0, b0, a1, b1,
-                           part, t.n_blk);
-    hipLaunchKernelGGL(k_seg_sum, dim3(grid_for((int64_t)t.n_seg * nr * 64)), dim3(WG), 0, st, t.n_seg, nr, t.seg_blk,
-                       part, t.n_blk, out0, a1 ? out1 : nullptr);
+static_assert(PCG_WG % NB == 0 && 64 % NB == 0, "a thread keeps its right-hand side from step to step");
+
+namespace {
+
+// f(std::integral_constant<int, NR>) for NR = 1 or NB
+template <class F>
+void with_nr(int nr, F&& f) {
+    if (nr == NB) f(std::integral_constant<int, NB>{});
+    else f(std::integral_constant<int, 1>{});
 }
 
-void launch_pcg_init(int n_s, const double* bb, int32_t* act, int32_t* iters, double* relres, int32_t* it_flag,
-                     hipStream_t st) {
-    hipLaunchKernelGGL(k_pcg_init, dim3(grid_for(n_s)), dim3(WG), 0, st, n_s, bb, act, iters, relres, it_flag);
+template <int NR, typename Z>
+void seg_dot_parts(const SegTable& t, const double* a0, const Z* b0, const double* a1, const Z* b1, double* part0,
+                   double* part1, hipStream_t st) {
+    hipLaunchKernelGGL((k_seg_dot<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.blk_lo, t.blk_hi, a0, b0, a1,
+                       b1, part0, part1);
 }
 
-void launch_pcg_alpha(int n_s, const int32_t* act, const double* rz, const double* pq, double* alpha, int32_t* flag,
-                      hipStream_t st) {
-    hipLaunchKernelGGL(k_pcg_alpha, dim3(grid_for(n_s)), dim3(WG), 0, st, n_s, act, rz, pq, alpha, flag);
+}  // namespace
+
+void launch_seg_dot(const SegTable& t, int nr, const double* a, const double* b, double* part, double* out,
+                    double* host, hipStream_t st) {
+    with_nr(nr, [&](auto c) {
+        constexpr int NR = decltype(c)::value;
+        seg_dot_parts<NR, double>(t, a, b, nullptr, nullptr, part, nullptr, st);
+        hipLaunchKernelGGL(k_seg_sum<NR>, dim3((unsigned)t.n_seg), dim3(PCG_WG), 0, st, t.seg_blk, part, out, host);
+    });
 }
 
-void launch_pcg_update_xr(const SegTable& t, int nr, const int32_t* act, const double* alpha, const double* p,
-                          const double* q, double* x, double* r, double* part, double* rr, hipStream_t st) {
-    if (nr == NB)
-        hipLaunchKernelGGL(k_pcg_update_xr<NB>, dim3((unsigned)t.n_blk), dim3(WG), 0, st, t.blk_seg, t.blk_lo,
-                           t.blk_hi, act, alpha, p, q, x, r, part);
-    else
-        hipLaunchKernelGGL(k_pcg_update_xr<1>, dim3((unsigned)t.n_blk), dim3(WG), 0, st, t.blk_seg, t.blk_lo,
-                           t.blk_hi, act, alpha, p, q, x, r, part);
-    hipLaunchKernelGGL(k_seg_sum, dim3(grid_for((int64_t)t.n_seg * nr * 64)), dim3(WG), 0, st, t.n_seg, nr, t.seg_blk,
-                       part, 0, rr, nullptr);
+template <typename Z>
+void launch_pcg_begin(const PcgArgs<Z>& a, int nrhs, const double* b, int64_t ldb, hipStream_t st) {
+    with_nr(a.nr, [&](auto c) {
+        constexpr int NR = decltype(c)::value;
+        const SegTable& t = a.seg;
+        hipLaunchKernelGGL((k_pcg_begin<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.blk_lo, t.blk_hi, nrhs,
+                           b, ldb, a.r, a.x, a.r32, a.z, a.part_rr, a.part_pq);
+        hipLaunchKernelGGL(k_pcg_init<NR>, dim3(1), dim3(PCG_CHECK_WG), 0, st, t.n_seg, t.seg_blk, a.part_rr, a.part_pq,
+                           a.bb, a.act, a.iters, a.relres, a.st);
+    });
 }
 
-void launch_pcg_check(int n_s, int32_t* it_dev, double tol2, const double* bb, const double* rr, int32_t* act,
-                      int32_t* iters, double* relres, int32_t* count, int32_t* flag, hipStream_t st) {
-    hipLaunchKernelGGL(k_pcg_check, dim3(1), dim3(WG), 0, st, n_s, it_dev, tol2, bb, rr, act, iters, relres, count,
-                       flag);
+template <typename Z>
+void launch_pcg_step(const PcgArgs<Z>& a, double tol2, int32_t* host_st, hipStream_t st) {
+    with_nr(a.nr, [&](auto c) {
+        constexpr int NR = decltype(c)::value;
+        const SegTable& t = a.seg;
+        seg_dot_parts<NR, double>(t, a.p, a.q, nullptr, nullptr, a.part_pq, nullptr, st);
+        hipLaunchKernelGGL((k_pcg_update_xr<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.blk_seg, t.blk_lo,
+                           t.blk_hi, t.seg_blk, a.act, a.rz2, a.nsm, a.part_pq, a.p, a.q, a.x, a.r, a.rold, a.r32, a.z,
+                           a.part_rr, a.st);
+        hipLaunchKernelGGL(k_pcg_check<NR>, dim3(1), dim3(PCG_CHECK_WG), 0, st, t.n_seg, t.seg_blk, a.part_rr, tol2,
+                           a.bb, a.act, a.iters, a.relres, a.st, host_st);
+    });
 }
 
-void launch_pcg_beta(int n_s, const int32_t* act, const double* rz_new, const double* rz_old_dot, double* rz,
-                     double* beta, int32_t* flag, hipStream_t st) {
-    hipLaunchKernelGGL(k_pcg_beta, dim3(grid_for(n_s)), dim3(WG), 0, st, n_s, act, rz_new, rz_old_dot, rz, beta,
-                       flag);
+template <typename Z>
+void launch_pcg_direction(const PcgArgs<Z>& a, bool first, hipStream_t st) {
+    with_nr(a.nr, [&](auto c) {
+        constexpr int NR = decltype(c)::value;
+        const SegTable& t = a.seg;
+        const bool flex = a.rold && !first;
+        seg_dot_parts<NR, Z>(t, a.r, a.z, flex ? a.rold : nullptr, flex ? a.z : nullptr, a.part_pq, a.part_rr, st);
+        hipLaunchKernelGGL((k_pcg_update_p<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.blk_seg, t.blk_lo,
+                           t.blk_hi, t.seg_blk, a.act, a.rz2, a.nsm, a.part_pq, flex ? a.part_rr : nullptr, a.z, a.p,
+                           a.st);
+    });
 }
 
-void launch_pcg_update_p(const SegTable& t, int nr, const int32_t* act, const double* beta, const double* z,
-                         double* p, hipStream_t st) {
-    if (nr == NB)
-        hipLaunchKernelGGL(k_pcg_update_p<NB>, dim3((unsigned)t.n_blk), dim3(WG), 0, st, t.blk_seg, t.blk_lo,
-                           t.blk_hi, act, beta, z, p);
-    else
-        hipLaunchKernelGGL(k_pcg_update_p<1>, dim3((unsigned)t.n_blk), dim3(WG), 0, st, t.blk_seg, t.blk_lo,
-                           t.blk_hi, act, beta, z, p);
-}
-
-void launch_pcg_start(int64_t len, const double* b, double* r, double* x, hipStream_t st) {
-    hipLaunchKernelGGL(k_pcg_start, dim3(grid_for(len)), dim3(WG), 0, st, len, b, r, x);
-}
+#define LSDD_PCG_INST(Z)                                                                                     \
+    template void launch_pcg_begin<Z>(const PcgArgs<Z>&, int, const double*, int64_t, hipStream_t);         \
+    template void launch_pcg_step<Z>(const PcgArgs<Z>&, double, int32_t*, hipStream_t);                     \
+    template void launch_pcg_direction<Z>(const PcgArgs<Z>&, bool, hipStream_t);
+LSDD_PCG_INST(double)
+LSDD_PCG_INST(float)
 
 template <typename T, int NR>
 void launch_small_sub(int64_t s0, int64_t n_sub, const int64_t* sub_off, const int32_t* sub_dofs,

@@ -71,8 +71,7 @@ void launch_prolong_small(int64_t na, const int32_t* agg_of_p, const int64_t* ag
                           const int64_t* zoff, const int32_t* k, const int64_t* coff, const T* Zc, const T* ec, T* x,
                           hipStream_t st);
 
-// B[d * NRB + k] = k < nr ? b[k * ldb + d] : 0 (d < n); and the inverse copy
-void launch_gather_rhs(int64_t n, int32_t nr, const double* b, int64_t ldb, double* B, hipStream_t st);
+// x[k * ldx + d] = X[d * NRB + k] (d < n, k < nr)
 void launch_scatter_sol(int64_t n, int32_t nr, const double* X, double* x, int64_t ldx, hipStream_t st);
 
 // ---------------------------------------------------------------- segmented PCG
@@ -89,31 +88,40 @@ struct SegTable {
     const int32_t* seg_blk = nullptr;   // [n_seg + 1] blocks of segment s
 };
 
-// out0[i] = <a0, b0>_i and, when a1 != NULL, out1[i] = <a1, b1>_i;
-// part holds 2 * n_blk * NR doubles
-void launch_seg_dot(const SegTable& t, int nr, const double* a0, const double* b0, const double* a1,
-                    const double* b1, double* part, double* out0, double* out1, hipStream_t st);
-// state of the recurrences: act (1 = still iterating), iters, relres; it_flag[0]
-// (iteration counter) and it_flag[1] (breakdown flag) are cleared
-void launch_pcg_init(int n_s, const double* bb, int32_t* act, int32_t* iters, double* relres, int32_t* it_flag,
-                     hipStream_t st);
-// alpha_i = rz_i / pq_i for active pairs (0 otherwise); flag[0] = 1 on breakdown
-void launch_pcg_alpha(int n_s, const int32_t* act, const double* rz, const double* pq, double* alpha,
-                      int32_t* flag, hipStream_t st);
-// x += alpha p, r -= alpha q on active pairs; rr_i = <r, r>_i (fused)
-void launch_pcg_update_xr(const SegTable& t, int nr, const int32_t* act, const double* alpha, const double* p,
-                          const double* q, double* x, double* r, double* part, double* rr, hipStream_t st);
-// it_dev[0] += 1; converged pairs (rr <= tol2 * bb) leave the active set at that
-// iteration; count[0] = number of active pairs; flag[0] = 1 on a non-finite residual
-void launch_pcg_check(int n_s, int32_t* it_dev, double tol2, const double* bb, const double* rr, int32_t* act,
-                      int32_t* iters, double* relres, int32_t* count, int32_t* flag, hipStream_t st);
-// beta_i = (rz_new_i - rzold_i) / rz_i (rzold = NULL: standard beta); rz_i <- rz_new_i
-void launch_pcg_beta(int n_s, const int32_t* act, const double* rz_new, const double* rz_old_dot, double* rz,
-                     double* beta, int32_t* flag, hipStream_t st);
-// p = z + beta p on active pairs
-void launch_pcg_update_p(const SegTable& t, int nr, const int32_t* act, const double* beta, const double* z,
-                         double* p, hipStream_t st);
-// x = 0 and r = b on every pair (r, x block or single vectors)
-void launch_pcg_start(int64_t len, const double* b, double* r, double* x, hipStream_t st);
+// Status words of a solve: active pairs, iterations, breakdown cause bits (1 p^T A p <= 0,
+// 2 p^T A p or r^T z not finite, 4 residual not finite, 8 beta not finite), 1 when the
+// right-hand side holds a NaN or an infinity.
+enum { PCG_ST_COUNT = 0, PCG_ST_IT = 1, PCG_ST_FLAG = 2, PCG_ST_BAD = 3, PCG_ST_WORDS = 4 };
+
+// Vectors and scalars of a solve (blocks of nr = 1 or NRB vectors).  Z: type of the
+// cycle's output (float: an FP32 cycle, whose input r32 the kernels fill from r).
+template <typename Z>
+struct PcgArgs {
+    SegTable seg;
+    int nr;
+    double *x, *r, *p, *q;
+    double* rold;                 // residual before the step (flexible beta), or NULL
+    float* r32;                   // FP32 residual for the cycle, or NULL
+    Z* z;                         // cycle output; zeroed where the residual is formed
+    int nsm;                      // stride of the per-pair arrays
+    double *bb, *rz2, *relres;    // rz2: two slots of nsm
+    int32_t *act, *iters, *st;
+    double *part_pq, *part_rr;    // n_blk * nr partials each
+};
+
+// out[i] = <a, b>_i (and, for the first segment, host[k]); part holds n_blk * nr doubles
+void launch_seg_dot(const SegTable& t, int nr, const double* a, const double* b, double* part, double* out,
+                    double* host, hipStream_t st);
+// r = b, x = 0, z = 0 and the state of the recurrences (nrhs <= nr right-hand sides at
+// stride ldb, the others zero)
+template <typename Z>
+void launch_pcg_begin(const PcgArgs<Z>& a, int nrhs, const double* b, int64_t ldb, hipStream_t st);
+// with q = A p: the step along p on the active pairs; pairs with <r, r> <= tol2 <b, b>
+// leave the iteration; z = 0; the status words go to a.st and host_st
+template <typename Z>
+void launch_pcg_step(const PcgArgs<Z>& a, double tol2, int32_t* host_st, hipStream_t st);
+// with z = cycle(r): the next direction (first: p = z)
+template <typename Z>
+void launch_pcg_direction(const PcgArgs<Z>& a, bool first, hipStream_t st);
 
 }  // namespace lsdd

@@ -1466,42 +1466,6 @@ __global__ void k_zero(int64_t n, T* x) {
 
 // ---------------------------------------------------------------- PCG helpers
 
-__global__ void __launch_bounds__(WG) k_dot_partial(int64_t n, const double* a, const double* b, double* partials) {
-    __shared__ double red[WG / 64];
-    double s = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)WG + tid(); i < n; i += (int64_t)gridDim.x * WG) s += a[i] * b[i];
-    s = wg_sum(s, red);
-    if (tid() == 0) partials[blockIdx.x] = s;
-}
-
-__global__ void __launch_bounds__(WG) k_sum_partials(int np, const double* partials, double* out) {
-    __shared__ double red[WG / 64];
-    double s = 0.0;
-    for (int i = tid(); i < np; i += WG) s += partials[i];
-    s = wg_sum(s, red);
-    if (tid() == 0) *out = s;
-}
-
-__global__ void __launch_bounds__(WG) k_update_xr(int64_t n, const double* s_num, const double* s_den, const double* p,
-                                                  const double* q, double* x, double* r, double* partials) {
-    __shared__ double red[WG / 64];
-    const double alpha = *s_num / *s_den;
-    double s = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)WG + tid(); i < n; i += (int64_t)gridDim.x * WG) {
-        x[i] += alpha * p[i];
-        double ri = r[i] - alpha * q[i];
-        r[i] = ri;
-        s += ri * ri;
-    }
-    s = wg_sum(s, red);
-    if (tid() == 0) partials[blockIdx.x] = s;
-}
-
-__global__ void k_update_p(int64_t n, const double* s_num, const double* s_den, const double* z, double* p) {
-    const double beta = *s_num / *s_den;
-    for (int64_t i = blockIdx.x * (int64_t)WG + tid(); i < n; i += (int64_t)gridDim.x * WG) p[i] = z[i] + beta * p[i];
-}
-
 __global__ void k_copy(int64_t n, const double* a, double* b) {
     for (int64_t i = blockIdx.x * (int64_t)WG + tid(); i < n; i += (int64_t)gridDim.x * WG) b[i] = a[i];
 }
@@ -1514,8 +1478,6 @@ __global__ void k_check_finite(int64_t n, const double* a, int32_t* flag) {
     for (int64_t i = blockIdx.x * (int64_t)WG + tid(); i < n; i += (int64_t)gridDim.x * WG)
         if (!isfinite(a[i])) *flag = 1;
 }
-
-constexpr int NPART = 1024;
 
 }  // namespace
 
@@ -1891,25 +1853,6 @@ template <typename T>
 void launch_zero(int64_t n, T* x, hipStream_t st) {
     if (n <= 0) return;
     hipLaunchKernelGGL(k_zero<T>, dim3(grid_for(n)), dim3(WG), 0, st, n, x);
-}
-
-void launch_dot(int64_t n, const double* a, const double* b, double* partials, double* out, hipStream_t st) {
-    unsigned nb = grid_for(n);
-    if (nb > NPART) nb = NPART;
-    hipLaunchKernelGGL(k_dot_partial, dim3(nb), dim3(WG), 0, st, n, a, b, partials);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(WG), 0, st, (int)nb, partials, out);
-}
-
-void launch_update_xr(int64_t n, const double* s_num, const double* s_den, const double* p, const double* q, double* x,
-                      double* r, double* partials, double* out_rr, hipStream_t st) {
-    unsigned nb = grid_for(n);
-    if (nb > NPART) nb = NPART;
-    hipLaunchKernelGGL(k_update_xr, dim3(nb), dim3(WG), 0, st, n, s_num, s_den, p, q, x, r, partials);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(WG), 0, st, (int)nb, partials, out_rr);
-}
-
-void launch_update_p(int64_t n, const double* s_num, const double* s_den, const double* z, double* p, hipStream_t st) {
-    hipLaunchKernelGGL(k_update_p, dim3(grid_for(n)), dim3(WG), 0, st, n, s_num, s_den, z, p);
 }
 
 void launch_copy(int64_t n, const double* a, double* b, hipStream_t st) {

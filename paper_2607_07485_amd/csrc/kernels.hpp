@@ -234,14 +234,6 @@ void launch_prolong(int64_t n_items, const int32_t* items, const int64_t* agg_pt
 template <typename T>
 void launch_zero(int64_t n, T* x, hipStream_t st);
 
-// PCG helpers (FP64).  `partials` holds at least 1024 doubles.
-void launch_dot(int64_t n, const double* a, const double* b, double* partials, double* out, hipStream_t st);
-// x += alpha p; r -= alpha q with alpha = s[0] / s[1]; out = ||r||^2
-void launch_update_xr(int64_t n, const double* s_num, const double* s_den, const double* p, const double* q,
-                      double* x, double* r, double* partials, double* out_rr, hipStream_t st);
-// p = z + (s_num / s_den) p
-void launch_update_p(int64_t n, const double* s_num, const double* s_den, const double* z, double* p,
-                     hipStream_t st);
 void launch_copy(int64_t n, const double* a, double* b, hipStream_t st);
 // Timing events the next launch of the subdomain product records at the kernel's own
 // start and end (hipExtLaunchKernel), instead of separate event packets around it;

@@ -344,16 +344,19 @@ struct lsdd_hierarchy {
     double setup_s = 0.0;
     // PCG work vectors: [0] single vectors, [1] blocks of NRB right-hand sides
     struct PcgBuf {
-        double *B = nullptr, *X = nullptr, *r = nullptr, *p = nullptr, *q = nullptr, *z = nullptr, *rold = nullptr;
+        double *X = nullptr, *r = nullptr, *p = nullptr, *q = nullptr, *z = nullptr, *rold = nullptr;
     } pb[2];
     // segments of the level-0 vector (one per problem instance) and the reduction table
     std::vector<int64_t> seg_off;
-    lsdd::SegTable seg;
+    lsdd::SegTable seg[2];        // reduction blocks for single vectors, for blocks of NRB
     int32_t nsm = 0;              // n_seg * NRB: stride of the per-pair scalar arrays
-    double* sc = nullptr;         // per-pair scalars: bb rz pq rr rzn rzo alpha beta relres
-    int32_t* ic = nullptr;        // act, iters (nsm each), then count, it, flag, finite-check flag
-    double* part = nullptr;       // reduction partials, 2 * n_blk * NRB
-    int32_t* h_ic = nullptr;      // pinned host mirror of count, it, flag
+    double* sc = nullptr;         // per-pair scalars: bb, rz (two slots), relres; then act, iters (int32)
+    int32_t* act() const { return reinterpret_cast<int32_t*>(sc + 4 * (size_t)nsm); }
+    int32_t* ic = nullptr;        // status words of the solve
+    double* part = nullptr;       // reduction partials, two sets
+    size_t part_len = 0;          // doubles per set
+    int32_t* h_ic = nullptr;      // pinned: mirror of the status words, then a residual norm (double)
+    void* h_res = nullptr;        // pinned: relres, act, iters of a finished solve
     // element coefficients the level-0 blocks were scaled with at setup (NULL: none)
     double* d_scale0 = nullptr;
     double* d_factor = nullptr;   // scratch for lsdd_update_theta
@@ -1791,8 +1794,9 @@ void terminal_solve(lsdd_hierarchy* h, Level& lv, const double* r, double* x) {
                  h->st);
 }
 
+// x_zero: the caller has zeroed x
 template <typename T, int NR>
-void vcycle(lsdd_hierarchy* h, size_t l, const T* r, T* x) {
+void vcycle(lsdd_hierarchy* h, size_t l, const T* r, T* x, bool x_zero = false) {
     using O = LvOps<T>;
     using C = Cyc<T, NR>;
     constexpr int b = NR > 1 ? 1 : 0;
@@ -1816,7 +1820,7 @@ void vcycle(lsdd_hierarchy* h, size_t l, const T* r, T* x) {
     Level& nx = *h->L[l + 1];
     VecSet<T>& v = O::v(lv, b);
     VecSet<T>& vn = O::v(nx, b);
-    launch_zero<T>(lv.n * NR, x, h->st);
+    if (!x_zero) launch_zero<T>(lv.n * NR, x, h->st);
     if (!lv.term.empty()) terminal();     // instances whose hierarchy ends on this level
     sweep<T, NR>(h, lv, r, x, true, true);
     bool mixed = false;
@@ -1871,7 +1875,6 @@ void alloc_pcg(lsdd_hierarchy* h, int b) {
     Arena& a = h->arena;
     const int64_t len = h->L[0]->n * (b ? NRB : 1);
     auto& B = h->pb[b];
-    B.B = a.alloc<double>(len);
     B.X = a.alloc<double>(len);
     B.r = a.alloc<double>(len);
     B.p = a.alloc<double>(len);
@@ -1880,35 +1883,45 @@ void alloc_pcg(lsdd_hierarchy* h, int b) {
     B.rold = a.alloc<double>(len);
 }
 
-// Segment table: DOF ranges [seg_off[s], seg_off[s+1]) cut into reduction
-// blocks of at most 2048 DOFs.
+// Segment tables: DOF ranges [seg_off[s], seg_off[s+1]) cut into reduction blocks of at
+// most 1024 entries of a single vector, 2048 of a block of NRB.  Smaller blocks leave
+// fewer serial steps per workgroup but more partials for every reader of a dot product to
+// add (one workgroup adds up to 512 in two to sixteen loads per thread), so a segment is
+// cut into at most 512.
 void init_segments(lsdd_hierarchy* h, const std::vector<int64_t>& seg_off) {
     Arena& a = h->arena;
     const int32_t ns = (int32_t)seg_off.size() - 1;
-    constexpr int64_t CH = 2048;
-    std::vector<int32_t> bseg, sblk(1, 0);
-    std::vector<int64_t> blo, bhi;
-    for (int32_t s = 0; s < ns; ++s) {
-        if (seg_off[s + 1] <= seg_off[s]) throw Error(LSDD_E_INVAL, "empty segment");
-        for (int64_t d = seg_off[s]; d < seg_off[s + 1]; d += CH) {
-            bseg.push_back(s);
-            blo.push_back(d);
-            bhi.push_back(std::min(d + CH, seg_off[s + 1]));
-        }
-        sblk.push_back((int32_t)bseg.size());
-    }
     h->seg_off = seg_off;
-    h->seg.n_seg = ns;
-    h->seg.n_blk = (int32_t)bseg.size();
-    h->seg.blk_seg = a.upload(bseg, h->st);
-    h->seg.blk_lo = a.upload(blo, h->st);
-    h->seg.blk_hi = a.upload(bhi, h->st);
-    h->seg.seg_blk = a.upload(sblk, h->st);
+    for (int b = 0; b < 2; ++b) {
+        std::vector<int32_t> bseg, sblk(1, 0);
+        std::vector<int64_t> blo, bhi;
+        for (int32_t s = 0; s < ns; ++s) {
+            if (seg_off[s + 1] <= seg_off[s]) throw Error(LSDD_E_INVAL, "empty segment");
+            const int64_t ch = std::max<int64_t>(b ? 2048 / NRB : 1024, (seg_off[s + 1] - seg_off[s] + 511) / 512);
+            for (int64_t d = seg_off[s]; d < seg_off[s + 1]; d += ch) {
+                bseg.push_back(s);
+                blo.push_back(d);
+                bhi.push_back(std::min(d + ch, seg_off[s + 1]));
+            }
+            sblk.push_back((int32_t)bseg.size());
+        }
+        SegTable& t = h->seg[b];
+        t.n_seg = ns;
+        t.n_blk = (int32_t)bseg.size();
+        t.blk_seg = a.upload(bseg, h->st);
+        t.blk_lo = a.upload(blo, h->st);
+        t.blk_hi = a.upload(bhi, h->st);
+        t.seg_blk = a.upload(sblk, h->st);
+        sync(h->st);
+        h->part_len = std::max<size_t>(h->part_len, (size_t)t.n_blk * (b ? NRB : 1));
+    }
     h->nsm = ns * NRB;
-    h->sc = a.alloc<double>((size_t)9 * h->nsm);
-    h->ic = a.alloc<int32_t>((size_t)2 * h->nsm + 4);
-    h->part = a.alloc<double>((size_t)2 * h->seg.n_blk * NRB);
-    if (!h->h_ic) HIPCHK(hipHostMalloc((void**)&h->h_ic, 4 * sizeof(int32_t), hipHostMallocDefault));
+    h->sc = a.alloc<double>((size_t)5 * h->nsm);
+    h->ic = a.alloc<int32_t>(PCG_ST_WORDS);
+    h->part = a.alloc<double>(2 * h->part_len);
+    if (!h->h_ic)
+        HIPCHK(hipHostMalloc((void**)&h->h_ic, PCG_ST_WORDS * sizeof(int32_t) + sizeof(double), hipHostMallocDefault));
+    if (!h->h_res) HIPCHK(hipHostMalloc(&h->h_res, (size_t)h->nsm * 16, hipHostMallocDefault));
 }
 
 void reset_graphs(lsdd_hierarchy* h) {
@@ -1921,46 +1934,57 @@ void reset_graphs(lsdd_hierarchy* h) {
                 }
 }
 
-// PCG (x0 = 0) on the NR right-hand sides in pb[b].B, one recurrence per
-// (segment, right-hand side) pair, preconditioned by one V-cycle; the solution
-// is left in pb[b].X.  Returns true on breakdown.  Every scalar stays on the
-// device; the host reads the active count once per iteration.
-template <int NR>
-bool pcg_run(lsdd_hierarchy* h) {
+// PCG (x0 = 0) on up to NR right-hand sides b (nrhs of them at stride ldb), one
+// recurrence per (segment, right-hand side) pair, preconditioned by one V-cycle whose
+// output is of type Z; the solution is left in pb[].X.  Returns true on breakdown.
+// Every scalar stays on the device; the host reads the status once per iteration.
+template <int NR, typename Z>
+bool pcg_run(lsdd_hierarchy* h, const double* rhs, int32_t nrhs, int64_t ldb) {
     constexpr int b = NR > 1 ? 1 : 0;
     auto& B = h->pb[b];
     hipStream_t st = h->st;
     Level& l0 = *h->L[0];
     const int64_t n = l0.n;
-    const SegTable& T = h->seg;
-    const int ns = T.n_seg * NR, nsm = h->nsm;
-    double *bb = h->sc, *rz = bb + nsm, *pq = rz + nsm, *rr = pq + nsm, *rzn = rr + nsm, *rzo = rzn + nsm,
-           *alpha = rzo + nsm, *beta = alpha + nsm, *relres = beta + nsm;
-    int32_t *act = h->ic, *iters = act + nsm, *cnt = iters + nsm, *itf = cnt + 1;   // itf[0] it, itf[1] flag
-    const bool flex = h->cycle_prec >= 1;
+    const bool f32 = std::is_same<Z, float>::value;
+    PcgArgs<Z> A;
+    A.seg = h->seg[b];
+    A.nr = NR;
+    A.x = B.X;
+    A.r = B.r;
+    A.p = B.p;
+    A.q = B.q;
+    A.rold = f32 ? B.rold : nullptr;
+    A.r32 = f32 ? l0.v32[b].r : nullptr;
+    if constexpr (std::is_same<Z, float>::value) A.z = l0.v32[b].x;
+    else A.z = B.z;
+    A.nsm = h->nsm;
+    A.bb = h->sc;
+    A.rz2 = A.bb + h->nsm;
+    A.relres = A.rz2 + 2 * (size_t)h->nsm;
+    A.act = h->act();
+    A.iters = A.act + h->nsm;
+    A.st = h->ic;
+    A.part_pq = h->part;
+    A.part_rr = h->part + h->part_len;
     const double tol2 = h->prm.rtol * h->prm.rtol;
-    launch_seg_dot(T, NR, B.B, B.B, nullptr, nullptr, h->part, bb, nullptr, st);
-    launch_pcg_init(ns, bb, act, iters, relres, itf, st);
-    launch_pcg_start(n * NR, B.B, B.r, B.X, st);
-    precond<NR>(h, B.r, B.z);
-    launch_copy(n * NR, B.z, B.p, st);
-    launch_seg_dot(T, NR, B.r, B.z, nullptr, nullptr, h->part, rz, nullptr, st);
+    // z = 0 and, for an FP32 cycle, its residual are written by the PCG kernels
+    auto cycle = [&] {
+        if constexpr (std::is_same<Z, float>::value) vcycle<float, NR>(h, 0, l0.v32[b].r, l0.v32[b].x, true);
+        else vcycle<double, NR>(h, 0, B.r, B.z, true);
+    };
+    launch_pcg_begin(A, nrhs, rhs, ldb, st);
+    cycle();
+    launch_pcg_direction(A, true, st);
     auto half_a = [&] {
         traced(h, "pcg_spmv",
                NR == 1 ? full_apply_bytes(l0, 8.0, 8.0, false)
                        : (double)l0.nnz * ((l0.sup ? l0.sup_ib : 4.0) + 8.0) + (double)n * 8.0 * (1 + 2 * NR),
                [&] { Cyc<double, NR>::spmv(l0, l0.d_val, B.p, B.q, nullptr, st); });
-        launch_seg_dot(T, NR, B.p, B.q, nullptr, nullptr, h->part, pq, nullptr, st);
-        launch_pcg_alpha(ns, act, rz, pq, alpha, itf + 1, st);
-        if (flex) launch_copy(n * NR, B.r, B.rold, st);
-        launch_pcg_update_xr(T, NR, act, alpha, B.p, B.q, B.X, B.r, h->part, rr, st);
-        launch_pcg_check(ns, itf, tol2, bb, rr, act, iters, relres, cnt, itf + 1, st);
+        launch_pcg_step(A, tol2, h->h_ic, st);
     };
     auto half_b = [&] {
-        precond<NR>(h, B.r, B.z);
-        launch_seg_dot(T, NR, B.r, B.z, flex ? B.rold : nullptr, flex ? B.z : nullptr, h->part, rzn, rzo, st);
-        launch_pcg_beta(ns, act, rzn, flex ? rzo : nullptr, rz, beta, itf + 1, st);
-        launch_pcg_update_p(T, NR, act, beta, B.z, B.p, st);
+        cycle();
+        launch_pcg_direction(A, false, st);
     };
     auto run = [&](int half, auto&& fn) {
         if (!h->use_graph || h->tr.on || !st) {
@@ -1981,15 +2005,15 @@ bool pcg_run(lsdd_hierarchy* h) {
     bool breakdown = false;
     for (int it = 1; it <= h->prm.max_iter; ++it) {
         run(0, half_a);
-        HIPCHK(hipMemcpyAsync(h->h_ic, cnt, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
         sync(st);
         if (h->tr.on) h->tr.flush();
-        if (h->h_ic[2]) {
+        if (h->h_ic[PCG_ST_BAD]) throw Error(LSDD_E_INVAL, "right-hand side has NaN/Inf");
+        if (h->h_ic[PCG_ST_FLAG]) {
             breakdown = true;
-            h->breakdown_bits = h->h_ic[2];
+            h->breakdown_bits = h->h_ic[PCG_ST_FLAG];
             break;
         }
-        if (h->h_ic[0] == 0) break;
+        if (h->h_ic[PCG_ST_COUNT] == 0) break;
         run(1, half_b);
     }
     HIPCHK(hipGetLastError());
@@ -2643,6 +2667,7 @@ lsdd_status lsdd_destroy(lsdd_hierarchy* h) {
     h->tr.destroy();
     h->arena.clear();
     if (h->h_ic) (void)hipHostFree(h->h_ic);
+    if (h->h_res) (void)hipHostFree(h->h_res);
     delete h;
     return LSDD_OK;
     ABI_END
@@ -2704,18 +2729,26 @@ lsdd_status lsdd_solve(lsdd_hierarchy* h, const double* b, double* x, int32_t nr
     h->st = (hipStream_t)hip_stream;
     hipStream_t st = h->st;
     const int64_t n = h->L[0]->n;
-    const int32_t nseg = h->seg.n_seg;
+    const int32_t nseg = h->seg[0].n_seg;
     const double t0 = now_s();
-    int32_t* fin = h->ic + 2 * h->nsm + 3;
-    HIPCHK(hipMemsetAsync(fin, 0, sizeof(int32_t), st));
-    launch_check_finite(n * nrhs, b, fin, st);
-    if (download(fin, 1, st)[0]) throw Error(LSDD_E_INVAL, "right-hand side has NaN/Inf");
+    if (nrhs > NRB) {
+        // several blocks: the later ones are checked before the first one's solution is
+        // written (a single block is checked by its own solve)
+        HIPCHK(hipMemsetAsync(h->ic, 0, sizeof(int32_t), st));
+        launch_check_finite(n * nrhs, b, h->ic, st);
+        if (download(h->ic, 1, st)[0]) throw Error(LSDD_E_INVAL, "right-hand side has NaN/Inf");
+    }
     std::vector<lsdd_info> out((size_t)nrhs * nseg);
     bool breakdown = false;
+    // iterations and residuals of the block that starts at right-hand side k0: relres,
+    // act and iters lie side by side on the device, one copy to pinned memory
     auto collect = [&](int32_t k0, int32_t nr, int NR) {
-        std::vector<int32_t> it = download(h->ic + h->nsm, (size_t)nseg * NR, st);
-        std::vector<int32_t> act = download(h->ic, (size_t)nseg * NR, st);
-        std::vector<double> rel = download(h->sc + 8 * (size_t)h->nsm, (size_t)nseg * NR, st);
+        const size_t nsm = (size_t)h->nsm;
+        HIPCHK(hipMemcpyAsync(h->h_res, h->sc + 3 * nsm, nsm * 16, hipMemcpyDeviceToHost, st));
+        sync(st);
+        const double* rel = static_cast<const double*>(h->h_res);
+        const int32_t* act = reinterpret_cast<const int32_t*>(rel + nsm);
+        const int32_t* it = act + nsm;
         for (int32_t k = 0; k < nr; ++k)
             for (int32_t sg = 0; sg < nseg; ++sg) {
                 const size_t i = (size_t)sg * NR + k;
@@ -2727,25 +2760,23 @@ lsdd_status lsdd_solve(lsdd_hierarchy* h, const double* b, double* x, int32_t nr
             }
     };
     if (nrhs == 1) {
-        launch_copy(n, b, h->pb[0].B, st);
-        breakdown = pcg_run<1>(h);
+        breakdown = h->cycle_prec >= 1 ? pcg_run<1, float>(h, b, 1, n) : pcg_run<1, double>(h, b, 1, n);
         launch_copy(n, h->pb[0].X, x, st);
         collect(0, 1, 1);
     } else {
-        if (!h->pb[1].B) {
+        if (!h->pb[1].r) {
             ensure_block_vectors(h);
             alloc_pcg(h, 1);
         }
         for (int32_t k0 = 0; k0 < nrhs && !breakdown; k0 += NRB) {
             const int32_t nr = std::min<int32_t>(NRB, nrhs - k0);
-            launch_gather_rhs(n, nr, b + (int64_t)k0 * n, n, h->pb[1].B, st);
-            breakdown = pcg_run<NRB>(h);
+            const double* bk = b + (int64_t)k0 * n;
+            breakdown = h->cycle_prec >= 1 ? pcg_run<NRB, float>(h, bk, nr, n) : pcg_run<NRB, double>(h, bk, nr, n);
             launch_scatter_sol(n, nr, h->pb[1].X, x + (int64_t)k0 * n, n, st);
             collect(k0, nr, NRB);
         }
     }
     HIPCHK(hipGetLastError());
-    sync(st);
     const double ts = now_s() - t0;
     bool allconv = true;
     for (auto& f : out) {
@@ -2777,7 +2808,7 @@ lsdd_status lsdd_solve_batched(int32_t n_inst, lsdd_hierarchy* const* hs, const 
     for (int32_t i = 0; i < n_inst; ++i) {
         const lsdd_status s = lsdd_solve(hs[i], b[i], x[i], nrhs, hip_stream, info ? info + off : nullptr);
         if (s != LSDD_OK) return s;
-        off += (int64_t)nrhs * hs[i]->seg.n_seg;
+        off += (int64_t)nrhs * hs[i]->seg[0].n_seg;
     }
     return LSDD_OK;
 }
@@ -2785,20 +2816,20 @@ lsdd_status lsdd_solve_stationary(lsdd_hierarchy* h, const double* b, double* x,
                                   lsdd_info* info) {
     ABI_BEGIN
     if (!h || !b || !x || nrhs < 1) throw Error(LSDD_E_INVAL, "bad argument");
-    if (h->seg.n_seg != 1)
+    if (h->seg[0].n_seg != 1)
         throw Error(LSDD_E_UNSUPPORTED, "the standalone cycle iteration needs a single-problem hierarchy");
     h->st = (hipStream_t)hip_stream;
     hipStream_t st = h->st;
     Level& l0 = *h->L[0];
     const int64_t n = l0.n;
     const double t0 = now_s();
-    int32_t* fin = h->ic + 2 * h->nsm + 3;
-    HIPCHK(hipMemsetAsync(fin, 0, sizeof(int32_t), st));
-    launch_check_finite(n * nrhs, b, fin, st);
-    launch_check_finite(n * nrhs, x, fin, st);
-    if (download(fin, 1, st)[0]) throw Error(LSDD_E_INVAL, "right-hand side or initial iterate has NaN/Inf");
+    HIPCHK(hipMemsetAsync(h->ic, 0, sizeof(int32_t), st));
+    launch_check_finite(n * nrhs, b, h->ic, st);
+    launch_check_finite(n * nrhs, x, h->ic, st);
+    if (download(h->ic, 1, st)[0]) throw Error(LSDD_E_INVAL, "right-hand side or initial iterate has NaN/Inf");
     auto& B = h->pb[0];
     double* rr = h->sc;
+    double* h_rr = reinterpret_cast<double*>(h->h_ic + PCG_ST_WORDS);
     std::vector<lsdd_info> out((size_t)nrhs);
     bool breakdown = false;
     for (int32_t k = 0; k < nrhs && !breakdown; ++k) {
@@ -2810,8 +2841,9 @@ lsdd_status lsdd_solve_stationary(lsdd_hierarchy* h, const double* b, double* x,
         auto resid = [&] {
             traced(h, "pcg_spmv", full_apply_bytes(l0, 8.0, 8.0, true),
                    [&] { Cyc<double, 1>::spmv(l0, l0.d_val, xk, B.r, bk, st); });
-            launch_seg_dot(h->seg, 1, B.r, B.r, nullptr, nullptr, h->part, rr, nullptr, st);
-            const double v = std::sqrt(download(rr, 1, st)[0]);
+            launch_seg_dot(h->seg[0], 1, B.r, B.r, h->part, rr, h_rr, st);
+            sync(st);
+            const double v = std::sqrt(*h_rr);
             if (h->tr.on) h->tr.flush();
             return v;
         };
@@ -2896,7 +2928,7 @@ lsdd_status lsdd_set_graph(lsdd_hierarchy* h, int32_t on) {
 lsdd_status lsdd_segments(const lsdd_hierarchy* h, int32_t* n_seg, int64_t* seg_off) {
     ABI_BEGIN
     if (!h) throw Error(LSDD_E_INVAL, "NULL hierarchy");
-    if (n_seg) *n_seg = h->seg.n_seg;
+    if (n_seg) *n_seg = h->seg[0].n_seg;
     if (seg_off) std::copy(h->seg_off.begin(), h->seg_off.end(), seg_off);
     return LSDD_OK;
     ABI_END
@@ -2907,7 +2939,7 @@ lsdd_status lsdd_autotune(lsdd_hierarchy* h, int32_t block, void* hip_stream) {
     if (!h) throw Error(LSDD_E_INVAL, "NULL hierarchy");
     h->st = (hipStream_t)hip_stream;
     if (block) {
-        if (!h->pb[1].B) {
+        if (!h->pb[1].r) {
             ensure_block_vectors(h);
             alloc_pcg(h, 1);
         }
