@@ -358,8 +358,10 @@ lsdd_status lsdd_level_tuning(const lsdd_hierarchy* h, int32_t level, int32_t* o
  * DOFs, or shared column lists (row blocks) on a level without them ->
  * LSDD_E_UNSUPPORTED (the
  * triangles are built on first use).  Captured PCG graphs are
- * dropped and recaptured on the next solve.  Like lsdd_autotune, it changes only the
- * summation order of the sums involved. */
+ * dropped and recaptured on the next solve.  The shapes are those of a cycle in separate
+ * launches: a level that runs single vectors through the fused kernels goes back to
+ * separate launches, except with the shapes lsdd_autotune chose along with them.  Like
+ * lsdd_autotune, it changes only the summation order of the sums involved. */
 lsdd_status lsdd_set_level_tuning(lsdd_hierarchy* h, int32_t level, const int32_t* in);
 
 /* Per-kernel timing: on != 0 clears the counters and records a pair of HIP

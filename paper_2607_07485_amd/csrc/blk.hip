@@ -703,6 +703,7 @@ __global__ void k_scatter_sol(int64_t n, int nr, const double* X, double* x, int
 // iteration around the cycle instead of eleven (FP64) or fifteen (FP32 cycle): 162 DOFs
 // 1.17 -> 0.92 ms per solve, 33,800 DOFs with an FP32 cycle 5.95 -> 5.48 ms.
 constexpr int PCG_WG = 256;
+constexpr int PCG_U = 4;                               // vector entries per thread in flight
 
 // Sum of u over the block for every right-hand side k = tid % NR, in a fixed order; all
 // threads of right-hand side k get the result.  s_w: WG / 64 * NR entries.
@@ -849,19 +850,35 @@ __global__ void __launch_bounds__(PCG_CHECK_WG) k_pcg_init(int n_seg, const int3
 // 2048 DOFs a block, the 8-vector blocks of a 243,420-DOF batch ran 126 workgroups of 64
 // serial steps, 59.6 us; at 256 DOFs (batch solve 17.7 -> 15.3 ms) there are 957 of 8.
 template <int NR, typename Z>
-__global__ void __launch_bounds__(PCG_WG) k_pcg_update_xr(const int32_t* blk_seg, const int64_t* blk_lo,
-                                                          const int64_t* blk_hi, const int32_t* seg_blk,
+__global__ void __launch_bounds__(PCG_WG) k_pcg_update_xr(int n_seg, const int32_t* blk_seg,
+                                                          const int64_t* blk_lo, const int64_t* blk_hi,
+                                                          const int32_t* seg_blk,
                                                           const int32_t* act, const double* rz2, int nsm,
                                                           const double* part_pq, const double* p, const double* q,
                                                           double* x, double* r, double* rold, float* r32, Z* z,
                                                           double* part_rr, int32_t* st) {
     __shared__ double s_w[PCG_WG / 64 * NR];
-    const int b = blockIdx.x, s = blk_seg[b];
+    const int b = blockIdx.x;
+    // the first chunk of the vectors arrives while the scalars are formed
+    const int64_t e0 = blk_lo[b] * NR, e1 = blk_hi[b] * NR;
+    double pv[PCG_U], qv[PCG_U], xv[PCG_U], rv[PCG_U];
+    auto load = [&](int64_t e) {
+#pragma unroll
+        for (int j = 0; j < PCG_U; ++j) {
+            const int64_t ec = min(e + tid() + j * PCG_WG, e1 - 1);
+            pv[j] = p[ec];
+            qv[j] = q[ec];
+            xv[j] = x[ec];
+            rv[j] = r[ec];
+        }
+    };
+    load(e0);
+    const int s = n_seg == 1 ? 0 : blk_seg[b];
     const int k = tid() % NR, i = s * NR + k;
-    const int b0 = seg_blk[s];
+    const int b0 = n_seg == 1 ? 0 : seg_blk[s], b1 = n_seg == 1 ? (int)gridDim.x : seg_blk[s + 1];
     const bool on = act[i] != 0;
     const double rzv = rz2[(int64_t)(st[PCG_ST_IT] & 1) * nsm + i];
-    const double d = seg_total<NR>(part_pq, b0, seg_blk[s + 1], s_w);
+    const double d = seg_total<NR>(part_pq, b0, b1, s_w);
     double a = 0.0;
     if (on) {
         // breakdown cause bits: 1 p^T A p <= 0, 2 p^T A p or r^T z not finite
@@ -871,20 +888,24 @@ __global__ void __launch_bounds__(PCG_WG) k_pcg_update_xr(const int32_t* blk_seg
         else a = rzv / d;
         if (bits && b == b0 && tid() < NR) atomicOr(st + PCG_ST_FLAG, bits);
     }
-    const int64_t e0 = blk_lo[b] * NR, e1 = blk_hi[b] * NR;
     double u = 0.0;
-#pragma unroll 4
-    for (int64_t e = e0 + tid(); e < e1; e += PCG_WG) {
-        double re = r[e];
-        if (rold) rold[e] = re;
-        if (on) {
-            x[e] += a * p[e];
-            re -= a * q[e];
-            r[e] = re;
+    for (int64_t ec = e0; ec < e1; ec += PCG_U * PCG_WG) {
+        if (ec > e0) load(ec);
+#pragma unroll
+        for (int j = 0; j < PCG_U; ++j) {
+            const int64_t e = ec + tid() + j * PCG_WG;
+            if (e >= e1) break;
+            double re = rv[j];
+            if (rold) rold[e] = re;
+            if (on) {
+                x[e] = xv[j] + a * pv[j];
+                re -= a * qv[j];
+                r[e] = re;
+            }
+            if (r32) r32[e] = (float)re;
+            z[e] = (Z)0;
+            u += re * re;
         }
-        if (r32) r32[e] = (float)re;
-        z[e] = (Z)0;
-        u += re * re;
     }
     u = block_sum<NR>(u, s_w);
     if (tid() < NR) part_rr[(int64_t)b * NR + tid()] = u;
@@ -892,14 +913,16 @@ __global__ void __launch_bounds__(PCG_WG) k_pcg_update_xr(const int32_t* blk_seg
 
 // State transitions and the active count, one workgroup: a wave per segment adds the
 // partials of <r, r>; the status goes to the device and to the host's pinned mirror, which
-// the host reads after the stream has drained (no copy launch).
+// the host reads after the launch has ended (no copy launch); behind them the largest
+// |r|^2 / (tol^2 |b|^2) of the pairs still active.
 template <int NR>
 __global__ void __launch_bounds__(PCG_CHECK_WG) k_pcg_check(int n_seg, const int32_t* seg_blk, const double* part_rr,
                                                             double tol2, const double* bb, int32_t* act,
                                                             int32_t* iters, double* relres, int32_t* st,
                                                             int32_t* host_st) {
     __shared__ int s_count, s_flag;
-    if (tid() == 0) s_count = s_flag = 0;
+    __shared__ unsigned long long s_excess;             // non-negative doubles order like their bits
+    if (tid() == 0) s_count = s_flag = 0, s_excess = 0;
     __syncthreads();
     const int it = st[PCG_ST_IT] + 1;
     const int lane = tid() & 63;
@@ -913,7 +936,10 @@ __global__ void __launch_bounds__(PCG_CHECK_WG) k_pcg_check(int n_seg, const int
                 relres[i] = sqrt(v / bb[i]);
                 iters[i] = it;
                 if (v <= tol2 * bb[i]) act[i] = 0;
-                else atomicAdd(&s_count, 1);
+                else {
+                    atomicAdd(&s_count, 1);
+                    atomicMax(&s_excess, __double_as_longlong(v / (tol2 * bb[i])));
+                }
             }
         }
     }
@@ -927,6 +953,8 @@ __global__ void __launch_bounds__(PCG_CHECK_WG) k_pcg_check(int n_seg, const int
         host_st[PCG_ST_IT] = it;
         host_st[PCG_ST_FLAG] = flag;
         host_st[PCG_ST_BAD] = st[PCG_ST_BAD];
+        *reinterpret_cast<double*>(host_st + PCG_ST_WORDS) = __longlong_as_double((long long)s_excess);
+        __threadfence_system();
     }
 }
 
@@ -934,16 +962,31 @@ __global__ void __launch_bounds__(PCG_CHECK_WG) k_pcg_check(int n_seg, const int
 // standard beta) and p = z + beta p; before the first iteration (counter 0) p = z.  The
 // segment's first block writes <r, z> to the slot the next step reads.
 template <int NR, typename Z>
-__global__ void __launch_bounds__(PCG_WG) k_pcg_update_p(const int32_t* blk_seg, const int64_t* blk_lo,
-                                                         const int64_t* blk_hi, const int32_t* seg_blk,
+__global__ void __launch_bounds__(PCG_WG) k_pcg_update_p(int n_seg, const int32_t* blk_seg,
+                                                         const int64_t* blk_lo, const int64_t* blk_hi,
+                                                         const int32_t* seg_blk,
                                                          const int32_t* act, double* rz2, int nsm,
                                                          const double* part_rz, const double* part_rzo, const Z* z,
                                                          double* p, int32_t* st) {
     __shared__ double s_w[PCG_WG / 64 * NR];
-    const int b = blockIdx.x, s = blk_seg[b];
-    const int k = tid() % NR, i = s * NR + k;
-    const int b0 = seg_blk[s], b1 = seg_blk[s + 1];
+    const int b = blockIdx.x;
+    const int64_t e0 = blk_lo[b] * NR, e1 = blk_hi[b] * NR;
     const int it = st[PCG_ST_IT];
+    // the first chunk of the vectors arrives while the scalars are formed
+    Z zv[PCG_U];
+    double pv[PCG_U];
+    auto load = [&](int64_t e) {
+#pragma unroll
+        for (int j = 0; j < PCG_U; ++j) {
+            const int64_t ec = min(e + tid() + j * PCG_WG, e1 - 1);
+            zv[j] = z[ec];
+            pv[j] = p[ec];
+        }
+    };
+    load(e0);
+    const int s = n_seg == 1 ? 0 : blk_seg[b];
+    const int k = tid() % NR, i = s * NR + k;
+    const int b0 = n_seg == 1 ? 0 : seg_blk[s], b1 = n_seg == 1 ? (int)gridDim.x : seg_blk[s + 1];
     const bool on = act[i] != 0;
     const double rz_old = rz2[(int64_t)((it + 1) & 1) * nsm + i];
     const double rz_new = seg_total<NR>(part_rz, b0, b1, s_w);
@@ -956,13 +999,13 @@ __global__ void __launch_bounds__(PCG_WG) k_pcg_update_p(const int32_t* blk_seg,
     }
     if (b == b0 && tid() < NR) rz2[(int64_t)(it & 1) * nsm + i] = on || it == 0 ? rz_new : rz_old;
     if (!on && it > 0) return;
-    const int64_t e0 = blk_lo[b] * NR, e1 = blk_hi[b] * NR;
-    if (it == 0) {
-#pragma unroll 4
-        for (int64_t e = e0 + tid(); e < e1; e += PCG_WG) p[e] = (double)z[e];
-    } else {
-#pragma unroll 4
-        for (int64_t e = e0 + tid(); e < e1; e += PCG_WG) p[e] = (double)z[e] + bt * p[e];
+    for (int64_t ec = e0; ec < e1; ec += PCG_U * PCG_WG) {
+        if (ec > e0) load(ec);
+#pragma unroll
+        for (int j = 0; j < PCG_U; ++j) {
+            const int64_t e = ec + tid() + j * PCG_WG;
+            if (e < e1) p[e] = it == 0 ? (double)zv[j] : (double)zv[j] + bt * pv[j];   // p holds anything before
+        }
     }
 }
 
@@ -1251,7 +1294,7 @@ void launch_pcg_step(const PcgArgs<Z>& a, double tol2, int32_t* host_st, hipStre
         constexpr int NR = decltype(c)::value;
         const SegTable& t = a.seg;
         seg_dot_parts<NR, double>(t, a.p, a.q, nullptr, nullptr, a.part_pq, nullptr, st);
-        hipLaunchKernelGGL((k_pcg_update_xr<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.blk_seg, t.blk_lo,
+        hipLaunchKernelGGL((k_pcg_update_xr<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.n_seg, t.blk_seg, t.blk_lo,
                            t.blk_hi, t.seg_blk, a.act, a.rz2, a.nsm, a.part_pq, a.p, a.q, a.x, a.r, a.rold, a.r32, a.z,
                            a.part_rr, a.st);
         hipLaunchKernelGGL(k_pcg_check<NR>, dim3(1), dim3(PCG_CHECK_WG), 0, st, t.n_seg, t.seg_blk, a.part_rr, tol2,
@@ -1266,7 +1309,7 @@ void launch_pcg_direction(const PcgArgs<Z>& a, bool first, hipStream_t st) {
         const SegTable& t = a.seg;
         const bool flex = a.rold && !first;
         seg_dot_parts<NR, Z>(t, a.r, a.z, flex ? a.rold : nullptr, flex ? a.z : nullptr, a.part_pq, a.part_rr, st);
-        hipLaunchKernelGGL((k_pcg_update_p<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.blk_seg, t.blk_lo,
+        hipLaunchKernelGGL((k_pcg_update_p<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.n_seg, t.blk_seg, t.blk_lo,
                            t.blk_hi, t.seg_blk, a.act, a.rz2, a.nsm, a.part_pq, flex ? a.part_rr : nullptr, a.z, a.p,
                            a.st);
     });

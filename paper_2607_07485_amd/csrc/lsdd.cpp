@@ -21,6 +21,7 @@
 #include "graph.hpp"
 #include "kernels.hpp"
 #include "blk.hpp"
+#include "fuse.hpp"
 
 namespace {
 
@@ -212,6 +213,25 @@ struct Level {
     int32_t* d_pitems = nullptr;  // prolongation work items
     int64_t n_ritems = 0, n_pitems = 0;
     double* d_mu = nullptr;
+    // Single-vector cycle kernels of levels bound by launches (fuse.hip).  fuse: 0 separate
+    // launches (residual rows, tiled product, partial sums), 1 one launch per colour, 2
+    // residual rows and whole rows of the unpacked inverses; with 1 and 2 the transfers run
+    // fused with the level's residual.  fuse_has: the modes whose tables are there
+    int fuse = 0;
+    bool fuse_has[3] = {true, false, false};
+    SubItem* d_sitems = nullptr;      // subdomains in sweep order
+    int4* d_srows = nullptr;          // their row tables, spad entries each
+    AggItem* d_aitems = nullptr;
+    int4* d_arows = nullptr;          // row tables of the aggregates, apad entries each
+    RowItem* d_witems = nullptr;      // 16-row items in sweep order, by colour
+    std::vector<int64_t> color_witem0;
+    double* d_full = nullptr;         // unpacked inverses
+    float* d_full32 = nullptr;
+    int32_t spad = 0, apad = 0, max_k = 0, row_len = 0;
+    bool fuse_rr = false;             // an aggregate's rows are few enough for one workgroup
+    int tuned_fuse = 0;               // the autotuner's choice and the launch shapes it made it with
+    int32_t tuned[7] = {};
+    double* d_cfull = nullptr;        // coarsest level of at most DENSE_MAX DOFs: its inverse, unpacked
     // smoother, sweep order (colour-major, aggregate index within a colour)
     std::vector<int32_t> sweep;
     std::vector<int64_t> sw_sub_off;
@@ -356,6 +376,7 @@ struct lsdd_hierarchy {
     double* part = nullptr;       // reduction partials, two sets
     size_t part_len = 0;          // doubles per set
     int32_t* h_ic = nullptr;      // pinned: mirror of the status words, then a residual norm (double)
+    hipEvent_t ev_step = nullptr; // after the step of a PCG iteration
     void* h_res = nullptr;        // pinned: relres, act, iters of a finished solve
     // element coefficients the level-0 blocks were scaled with at setup (NULL: none)
     double* d_scale0 = nullptr;
@@ -625,6 +646,12 @@ void append_symv_items(const std::vector<int64_t>& sub_off, const std::vector<in
     for (size_t q : ord) items.insert(items.end(), {it[3 * q], it[3 * q + 1], it[3 * q + 2]});
 }
 
+// Coarsest levels up to this size keep their inverse unpacked as well, for a product in one
+// launch (launch_dense_apply).  It reads twice the bytes of the packed tiles, 72 MB at 3000
+// DOFs, some 7 us more than these, which is what the partial sums' launch and the longer
+// chain of the tiled product cost (2171 DOFs: 10 us against 24 us with its conversions).
+constexpr int64_t DENSE_MAX = 3000;
+
 // Terminal blocks of a level: the dense Cholesky factorisation and explicit
 // inverse of the instance blocks of A_l listed in `term` (on the coarsest level:
 // every instance present, i.e. the whole level for a single problem), packed into
@@ -706,12 +733,102 @@ void make_terminal(lsdd_hierarchy* h, Level& lv, const std::vector<int32_t>& ter
     HIPCHK(hipGetLastError());
     sync(h->st);
     ar.release(d_inv_off);
-    ar.release(inv);
+    if (coarsest && nb == 1 && lv.n <= DENSE_MAX) lv.d_cfull = inv;
+    else ar.release(inv);
     lv.c_scr_len = scr_off[nb];
     if (coarsest) {
         lv.coarsest = true;
         alloc_vectors(h, lv, 0);
     }
+}
+
+// Bytes of a colour's unpacked inverses up to which a level keeps them: reading them
+// instead of the packed ones costs half of them at about 5 TB/s, 8 us here, and saves the
+// partial sums' launch and the tiled product's longer chain, 8 us per colour where it was
+// measured (k_sub_rows).
+constexpr double FULL_MAX_COLOUR = 80e6;
+
+// Tables of the fused single-vector kernels of a level, and the mode it starts out with.
+// inv, inv_off: the unpacked inverses (aggregate order), kept by the level in mode 2's
+// range; returns whether it took them over.  RAS masks entries of its sweep lists, which the
+// row tables cannot express.
+bool build_fused(lsdd_hierarchy* h, Level& lv, const std::vector<int64_t>& sw_tp_off,
+                 const std::vector<int64_t>& sw_pk_off, double* inv, const std::vector<int64_t>& inv_off) {
+    Arena& ar = h->arena;
+    hipStream_t st = h->st;
+    const int32_t n_sub = (int32_t)lv.sweep.size();
+    const Closure& C = lv.cl;
+    if (lv.smoother == 1 || n_sub < 1) return false;
+    int32_t max_sub = 0, max_nw = 0;
+    std::vector<double> full(lv.n_colors, 0.0);
+    for (int32_t s = 0; s < n_sub; ++s) {
+        const int32_t m = (int32_t)(lv.sw_sub_off[s + 1] - lv.sw_sub_off[s]);
+        max_sub = std::max(max_sub, m);
+        full[lv.colors[lv.sweep[s]]] += 8.0 * m * m;
+        max_nw = std::max<int32_t>(max_nw, (int32_t)(C.agg_ptr[s + 1] - C.agg_ptr[s]));
+        lv.max_k = std::max(lv.max_k, lv.k[s]);
+    }
+    lv.spad = (max_sub + 63) & ~63;
+    lv.apad = (max_nw + 63) & ~63;
+    const int64_t rows = lv.sw_sub_off[n_sub];
+    const double full_max = *std::max_element(full.begin(), full.end());
+    if (lv.nnz > INT32_MAX || rows > INT32_MAX || lv.coff[n_sub] > INT32_MAX) return false;
+    lv.fuse_has[1] = lv.spad <= FUSE_M;
+    lv.fuse_has[2] = full_max <= FULL_MAX_COLOUR;
+    if (!lv.fuse_has[1] && !lv.fuse_has[2]) return false;
+    lv.row_len = (int32_t)(lv.nnz / std::max<int64_t>(lv.n, 1));
+    std::vector<AggItem> ai(n_sub);
+    for (int32_t s = 0; s < n_sub; ++s)
+        ai[s] = AggItem{(int32_t)(C.agg_ptr[s + 1] - C.agg_ptr[s]), (int32_t)lv.coff[s], lv.k[s], 0, lv.zoff[s]};
+    lv.d_aitems = ar.upload(ai, st);
+    lv.d_arows = ar.alloc<int4>((size_t)n_sub * lv.apad);
+    launch_row_table(n_sub, lv.d_agg_ptr, lv.d_agg_dofs, lv.d_rowptr, lv.d_scoff, lv.apad, lv.d_arows, st);
+    if (lv.fuse_has[1]) {
+        std::vector<SubItem> si(n_sub);
+        for (int32_t s = 0; s < n_sub; ++s) {
+            const int32_t m = (int32_t)(lv.sw_sub_off[s + 1] - lv.sw_sub_off[s]);
+            si[s] = SubItem{m, 0, m <= SMALL_M ? sw_pk_off[s] : sw_tp_off[s]};
+        }
+        lv.d_sitems = ar.upload(si, st);
+        lv.d_srows = ar.alloc<int4>((size_t)n_sub * lv.spad);
+        launch_row_table(n_sub, lv.d_sw_sub_off, lv.d_sw_sub_dofs, lv.d_rowptr, lv.d_scoff, lv.spad, lv.d_srows, st);
+    }
+    if (lv.fuse_has[2]) {
+        std::vector<RowItem> wi;
+        lv.color_witem0.assign(lv.n_colors + 1, 0);
+        for (int32_t c = 0; c < lv.n_colors; ++c) {
+            for (int32_t s = lv.color_sub0[c]; s < lv.color_sub0[c + 1]; ++s) {
+                const int32_t m = (int32_t)(lv.sw_sub_off[s + 1] - lv.sw_sub_off[s]);
+                for (int32_t r0 = 0; r0 < m; r0 += 16)
+                    wi.push_back(RowItem{(int32_t)lv.sw_sub_off[s], m, r0, 0, inv_off[lv.sweep[s]]});
+            }
+            lv.color_witem0[c + 1] = (int64_t)wi.size();
+        }
+        lv.d_witems = ar.upload(wi, st);
+        lv.d_full = inv;
+        if (h->prm.precision >= 1) {
+            lv.d_full32 = ar.alloc<float>(std::max<int64_t>(lv.inv_len, 1));
+            launch_to_f32(lv.inv_len, inv, lv.d_full32, st);
+        }
+    }
+    HIPCHK(hipGetLastError());
+    sync(st);
+    // Until the autotuner has timed the modes: one launch per colour up to |Omega| = 128 (ms
+    // per sweep, one launch against two against three: |Omega| <= 50 0.019 / 0.028 / 0.040,
+    // <= 123 0.041 / 0.053 / 0.081), two above (<= 141 0.036 / 0.029 / 0.072, <= 161 0.060 /
+    // 0.030 / 0.063, <= 552 0.094 / 0.046 / 0.062), where a workgroup per subdomain leaves
+    // most CUs idle.  Past some 24 MB per colour the matrix entries set the time of all three
+    // and the packed ones are the fewest.
+    double bytes = 0.0;
+    for (int32_t c = 0; c < lv.n_colors; ++c)
+        bytes = std::max(bytes, 8.0 * (lv.color_m2[c] + lv.color_pk[c]) + 12.0 * lv.color_nnz[c]);
+    lv.fuse = lv.fuse_has[1] && max_sub <= 128 && bytes <= 24e6 ? 1 : lv.fuse_has[2] ? 2 : 0;
+    // 16 aggregates of 441 rows x 376 entries: 52 us in one workgroup each, 10.7 us as a
+    // product and a restriction; 100 of 80 x 46 entries: 6.4 against 14 us
+    lv.fuse_rr = (double)max_nw * lv.row_len <= 16384.0;
+    vlog("level %d: single-vector mode %d (%.1f MB per colour, overlaps up to %d, %d entries per row)", lv.level,
+         lv.fuse, bytes * 1e-6, max_sub, lv.row_len);
+    return lv.fuse_has[2];
 }
 
 // Build level l+1 from level l; returns nullptr when no mode is retained.
@@ -1330,7 +1447,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         }
         ar.release(d_tp_agg);
         ar.release(d_pk_agg);
-        ar.release(lv.d_inv);
+        if (!build_fused(h, lv, sw_tp_off, sw_pk_off, lv.d_inv, msq)) ar.release(lv.d_inv);
         lv.d_inv = nullptr;
     }
     lv.rloc_len = (int64_t)sw_dofs.size();
@@ -1524,6 +1641,7 @@ struct LvOps<double> {
     static const double* Z(Level& l) { return l.d_Zc; }
     static const double* inv(Level& l) { return l.d_tiles; }
     static const double* pk(Level& l) { return l.d_pk; }
+    static const double* full(Level& l) { return l.d_full; }
     static const double* etri(Level& l) { return l.d_etri; }
     static double* ebuf(Level& l) { return l.d_ebuf; }
 };
@@ -1534,6 +1652,7 @@ struct LvOps<float> {
     static const float* Z(Level& l) { return l.d_Zc32; }
     static const float* inv(Level& l) { return l.d_tiles32; }
     static const float* pk(Level& l) { return l.d_pk32; }
+    static const float* full(Level& l) { return l.d_full32; }
     static const float* etri(Level& l) { return l.d_etri32; }
     static float* ebuf(Level& l) { return l.d_ebuf32; }
 };
@@ -1742,6 +1861,34 @@ void sweep(lsdd_hierarchy* h, Level& lv, const T* r, T* x, bool forward, bool x_
             return;
         }
     }
+    if constexpr (NR == 1) {
+        if (lv.fuse) {
+            for (int32_t cc = 0; cc < lv.n_colors; ++cc) {
+                const int32_t c = forward ? cc : lv.n_colors - 1 - cc;
+                const bool xz = x_zero_first && cc == 0;
+                const double ab = xz ? 0.0 : lv.color_nnz[c] * ((lv.d_scoff ? lv.sup_ib : 4.0) + w);
+                if (lv.fuse == 2) {
+                    traced(h, "csr_resid_rows", lv.color_m[c] * (4 + 8 + 3 * w) + ab, [&] {
+                        C::template resid_colour<T>(lv, c, O::val(lv), x, r, v.rloc, xz, h->st);
+                    });
+                    traced(h, "sub_rows", 2 * (lv.color_m2[c] + lv.color_pk[c]) * w + lv.color_m[c] * (4 + 3 * w), [&] {
+                        const int64_t w0 = lv.color_witem0[c];
+                        launch_sub_rows<T>(lv.color_witem0[c + 1] - w0, lv.d_witems + w0, O::full(lv), v.rloc,
+                                           lv.d_sw_sub_dofs, x, h->st);
+                    });
+                    continue;
+                }
+                const int64_t s0 = lv.color_sub0[c], ns = lv.color_sub0[c + 1] - s0;
+                const double cb = (lv.color_m2[c] + lv.color_pk[c]) * w + lv.color_m[c] * (16 + 3 * w) + ab;
+                traced(h, "colour_step", cb, [&] {
+                    launch_colour_step<T>(ns, lv.d_sitems + s0, lv.d_srows + s0 * lv.spad,
+                                          lv.d_scoff ? lv.d_scol : lv.d_col, O::val(lv), O::pk(lv), O::inv(lv), r, x, xz,
+                                          lv.spad, lv.row_len, h->st);
+                });
+            }
+            return;
+        }
+    }
     for (int32_t cc = 0; cc < lv.n_colors; ++cc) {
         int32_t c = forward ? cc : lv.n_colors - 1 - cc;
         const int64_t r0 = lv.color_row0[c], r1 = lv.color_row0[c + 1], rm = lv.color_rmid[c];
@@ -1804,6 +1951,13 @@ void vcycle(lsdd_hierarchy* h, size_t l, const T* r, T* x, bool x_zero = false) 
     const double w = (double)sizeof(T), wv = w * NR;
     // terminal blocks (all of the coarsest level) in FP64
     auto terminal = [&] {
+        if constexpr (NR == 1) {
+            if (lv.coarsest && lv.d_cfull) {
+                traced(h, "coarse_dense", (double)lv.n * lv.n * 8.0 + 2.0 * lv.n * w,
+                       [&] { launch_dense_apply<T>(lv.n, lv.d_cfull, r, x, h->st); });
+                return;
+            }
+        }
         if constexpr (std::is_same<T, double>::value) {
             terminal_solve<NR>(h, lv, r, x);
         } else {
@@ -1823,6 +1977,28 @@ void vcycle(lsdd_hierarchy* h, size_t l, const T* r, T* x, bool x_zero = false) 
     if (!x_zero) launch_zero<T>(lv.n * NR, x, h->st);
     if (!lv.term.empty()) terminal();     // instances whose hierarchy ends on this level
     sweep<T, NR>(h, lv, r, x, true, true);
+    if constexpr (NR == 1) {
+        if (lv.fuse && h->cycle_prec != 2) {
+            const double tb = (double)lv.zoff.back() * w + (double)lv.n * 16 + (double)nx.n * w;
+            if (lv.fuse_rr) {
+                traced(h, "resid_restrict", tb + full_apply_bytes(lv, w, w, true), [&] {
+                    launch_resid_restrict<T>(lv.cl.n_agg, lv.d_aitems, lv.d_arows, lv.d_scoff ? lv.d_scol : lv.d_col,
+                                             O::val(lv), O::Z(lv), r, x, vn.r, vn.x, lv.apad, lv.row_len, h->st);
+                });
+            } else {
+                traced(h, "csr_spmv", full_apply_bytes(lv, w, w, true),
+                       [&] { C::spmv(lv, O::val(lv), x, v.t, r, h->st); });
+                traced(h, "restrict", tb, [&] { C::restrict_(lv, O::Z(lv), v.t, vn.r, h->st); });
+            }
+            vcycle<T, NR>(h, l + 1, vn.r, vn.x, lv.fuse_rr);
+            traced(h, "prolong_agg", tb + (double)lv.n * w, [&] {
+                launch_prolong_agg<T>(lv.cl.n_agg, lv.d_aitems, lv.d_arows, O::Z(lv), vn.x, x, lv.apad, lv.max_k,
+                                      h->st);
+            });
+            sweep<T, NR>(h, lv, r, x, false, false);
+            return;
+        }
+    }
     bool mixed = false;
     if constexpr (std::is_same<T, float>::value && NR == 1) {
         if (h->cycle_prec == 2) {
@@ -1921,6 +2097,7 @@ void init_segments(lsdd_hierarchy* h, const std::vector<int64_t>& seg_off) {
     h->part = a.alloc<double>(2 * h->part_len);
     if (!h->h_ic)
         HIPCHK(hipHostMalloc((void**)&h->h_ic, PCG_ST_WORDS * sizeof(int32_t) + sizeof(double), hipHostMallocDefault));
+    if (!h->ev_step) HIPCHK(hipEventCreateWithFlags(&h->ev_step, hipEventDisableTiming));
     if (!h->h_res) HIPCHK(hipHostMalloc(&h->h_res, (size_t)h->nsm * 16, hipHostMallocDefault));
 }
 
@@ -2003,9 +2180,22 @@ bool pcg_run(lsdd_hierarchy* h, const double* rhs, int32_t nrhs, int64_t ldb) {
         HIPCHK(hipGraphLaunch(g, st));
     };
     bool breakdown = false;
+    // While the residual is far from the tolerance the cycle is enqueued behind the step
+    // without waiting for its outcome, so that the stream does not run dry while the host
+    // reads the status (11 us a wait).  An iteration that converges all the same leaves x
+    // alone in what follows; one cycle was then for nothing.
+    double excess = 1.0 / tol2;                  // largest |r|^2 / (tol^2 |b|^2) before the step
     for (int it = 1; it <= h->prm.max_iter; ++it) {
         run(0, half_a);
-        sync(st);
+        const bool ahead = excess > 1e6 && !h->tr.on;
+        if (ahead) {
+            HIPCHK(hipEventRecord(h->ev_step, st));
+            run(1, half_b);
+            HIPCHK(hipEventSynchronize(h->ev_step));
+        } else {
+            sync(st);
+        }
+        excess = *reinterpret_cast<const double*>(h->h_ic + PCG_ST_WORDS);
         if (h->tr.on) h->tr.flush();
         if (h->h_ic[PCG_ST_BAD]) throw Error(LSDD_E_INVAL, "right-hand side has NaN/Inf");
         if (h->h_ic[PCG_ST_FLAG]) {
@@ -2014,7 +2204,7 @@ bool pcg_run(lsdd_hierarchy* h, const double* rhs, int32_t nrhs, int64_t ldb) {
             break;
         }
         if (h->h_ic[PCG_ST_COUNT] == 0) break;
-        run(1, half_b);
+        if (!ahead) run(1, half_b);
     }
     HIPCHK(hipGetLastError());
     return breakdown;
@@ -2089,6 +2279,17 @@ double time_ms(lsdd_hierarchy* h, F&& fn, int reps = 5) {
     return best;
 }
 
+// the level's launch shapes in the layout of lsdd_level_tuning
+void level_shapes(const Level& lv, int32_t* out) {
+    out[0] = lv.lanes;
+    out[1] = lv.lanes_b;
+    out[2] = lv.chl;
+    out[3] = lv.fl;
+    out[4] = lv.eapply;
+    out[5] = lv.sup;
+    out[6] = lv.fact_stash;
+}
+
 // Time the candidates of every per-level launch shape on the level's own data
 // and keep the fastest.  Values in the work vectors are irrelevant (zeroed).
 template <typename T, int NR>
@@ -2158,7 +2359,28 @@ void autotune_levels(lsdd_hierarchy* h) {
             }
             lv.eapply = pick_e;
         }
-        if (lv.color_item0.back() == 0) continue;   // no large overlap on this level
+        // last: the fused kernels against the launches chosen above, a cycle's sweep each
+        auto pick_fused = [&] {
+            if constexpr (NR == 1) {
+                lv.tuned_fuse = 0;
+                if (h->cycle_prec == 2) return;
+                double low = 1e300;
+                int pick_f = 0;
+                for (int f : {0, 1, 2}) {
+                    if (!lv.fuse_has[f]) continue;
+                    lv.fuse = f;
+                    const double ms = time_ms(h, [&] { sweep<T, NR>(h, lv, v.r, v.x, true, false); });
+                    vlog("autotune level %d: sweep in mode %d: %.3f ms", lv.level, f, ms);
+                    if (ms < low) low = ms, pick_f = f;
+                }
+                lv.fuse = lv.tuned_fuse = pick_f;
+                level_shapes(lv, lv.tuned);
+            }
+        };
+        if (lv.color_item0.back() == 0) {           // no large overlap on this level
+            pick_fused();
+            continue;
+        }
         auto run_large = [&] {
             for (int32_t c = 0; c < lv.n_colors; ++c) {
                 const int64_t i0 = lv.color_item0[c], i1 = lv.color_item0[c + 1];
@@ -2210,6 +2432,7 @@ void autotune_levels(lsdd_hierarchy* h) {
                 lv.fact_stash = pick_fs;
             }
         }
+        pick_fused();
     }
     sync(h->st);
 }
@@ -2668,6 +2891,7 @@ lsdd_status lsdd_destroy(lsdd_hierarchy* h) {
     h->arena.clear();
     if (h->h_ic) (void)hipHostFree(h->h_ic);
     if (h->h_res) (void)hipHostFree(h->h_res);
+    if (h->ev_step) (void)hipEventDestroy(h->ev_step);
     delete h;
     return LSDD_OK;
     ABI_END
@@ -2973,6 +3197,9 @@ lsdd_status lsdd_set_level_tuning(lsdd_hierarchy* h, int32_t level, const int32_
     if (in[4] && !build_elem_apply(h, lv))
         throw Error(LSDD_E_UNSUPPORTED, "element apply: only on level 0 of a hierarchy built from element blocks "
                                         "of at most 128 DOFs");
+    // shapes set by hand are those of the separate launches; the shapes the autotuner found
+    // bring back its choice between these and the fused kernels
+    lv.fuse = std::equal(in, in + 7, lv.tuned) ? lv.tuned_fuse : 0;
     lv.eapply = in[4];
     lv.sup = in[5];
     lv.fact_stash = in[6];
@@ -2991,14 +3218,7 @@ lsdd_status lsdd_set_level_tuning(lsdd_hierarchy* h, int32_t level, const int32_
 lsdd_status lsdd_level_tuning(const lsdd_hierarchy* h, int32_t level, int32_t* out) {
     ABI_BEGIN
     if (!h || !out || level < 0 || level >= (int32_t)h->L.size()) throw Error(LSDD_E_INVAL, "bad argument");
-    const Level& lv = *h->L[level];
-    out[0] = lv.lanes;
-    out[1] = lv.lanes_b;
-    out[2] = lv.chl;
-    out[3] = lv.fl;
-    out[4] = lv.eapply;
-    out[5] = lv.sup;
-    out[6] = lv.fact_stash;
+    level_shapes(*h->L[level], out);
     return LSDD_OK;
     ABI_END
 }

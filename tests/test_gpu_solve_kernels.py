@@ -65,3 +65,67 @@ def test_non_finite_right_hand_side_leaves_the_output(nrhs, bad):
         assert e.value.code == 1 and bool((x == 7.0).all())
         y, infos = h.solve(torch.ones(prob.n, dtype=torch.float64, device="cuda"))   # still usable
         assert infos[0].converged == 1
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("max_iter", [1, 2, 5])
+def test_iterations_stop_at_max_iter(max_iter, graph):
+    """A solve that is cut off returns the iterate its reported residual belongs to (the cycle
+    enqueued behind the last step must not touch it)."""
+    import fegen
+    P = _lsdd()
+    prob, b = fegen.elasticity_small(N=12)
+    A = _dense(prob)
+    with torch.cuda.stream(torch.cuda.Stream()), \
+            P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2, modes_fixed=4, max_iter=max_iter)) as h:
+        h.set_graph(graph)
+        for _ in range(2):
+            x, infos = h.solve(torch.from_numpy(b).cuda(), allow_noconv=True)
+            r = np.linalg.norm(b - A @ x.cpu().numpy()) / np.linalg.norm(b)
+            assert infos[0].iters == max_iter and infos[0].converged == 0
+            assert abs(infos[0].rel_res - r) <= 1e-10
+
+
+def _cycle_problem(kind):
+    import fegen
+    rng = np.random.default_rng(4)
+    if kind.startswith("q1"):      # overlaps of at most 50 DOFs, ragged patches at the edges
+        return fegen.elasticity_q1(int(kind[2:])), dict(max_levels=2, modes_fixed=4)
+    if kind == "p1":               # overlaps of 65 to 128 DOFs, some smaller at the corners
+        return fegen.diffusion_p1_triangles(40), dict(max_levels=3, tau_const=1.0)
+    if kind == "bfs":              # overlaps of several hundred DOFs, few of them
+        return fegen.hyperdiffusion_h2(24, eps=1.0)[0], dict(max_levels=3, tau_const=1.0)
+    return fegen.graddiv_rtcf3(12, kappa=np.exp(rng.standard_normal(144)), beta=1.0), dict(max_levels=3, max_density=1.0)
+
+
+@pytest.mark.parametrize("kind", ["q14", "q117", "p1", "bfs", "rtcf"])
+def test_fused_cycle_matches_separate_launches(kind):
+    """The fused colour, transfer and coarsest kernels against the separate launches (which a set
+    of launch shapes brings back), before and after an update of the operator: the same sums in
+    another order, held to the 1e-10 of the FP64 parity; the FP32 cycle stays as far from the FP64
+    cycle as with separate launches (within 4x)."""
+    P = _lsdd()
+    prob, kw = _cycle_problem(kind)
+    rng = np.random.default_rng(1)
+    r = torch.from_numpy(rng.standard_normal(prob.n)).cuda()
+    blocks = torch.from_numpy(np.ascontiguousarray(prob.blocks)).cuda()
+    theta = torch.ones(prob.n_elem, dtype=torch.float64, device="cuda")
+    with P.Hierarchy.setup_elements_scaled(prob.n, prob.elem_ptr, prob.elem_dofs, blocks, theta, prob.node_of_dof,
+                                           prob.agg_of_dof, P.Params.default(precision=1, **kw)) as h:
+        def cycles():
+            out = []
+            for scale in (1.0, 1.25):
+                h.update_theta(theta * scale)
+                for prec in (0, 1):
+                    h.set_cycle_precision(prec)
+                    out.append(h.vcycle(r))
+            return out
+
+        fused = cycles()
+        for l in range(h.info()["levels"]):
+            h.set_level_tuning(l, h.level_tuning(l))
+        apart = cycles()
+    for i in (0, 2):
+        n = float(apart[i].norm())
+        assert float((fused[i] - apart[i]).norm()) <= 1e-10 * n
+        assert float((fused[i + 1] - fused[i]).norm()) <= 4 * float((apart[i + 1] - apart[i]).norm()) + 1e-12 * n
