@@ -593,107 +593,6 @@ __device__ inline void wg_block_update(double* V, int n, int q0, int qn, int b0,
     }
 }
 
-// The same two steps on the FP64 matrix cores (one 64 x 64 tile of Q^T Y with
-// K = n; then Y -= Q dd tile by tile down the rows).
-__device__ inline void wg_block_dots_mfma(mg::Smem& sm, const double* V, int n, int q0, int qn, int b0, int bn,
-                                          double* dd) {
-    mg::d4 acc[2][2];
-    mg::zero(acc);
-    mg::tile_mma<mg::KMAJ, mg::KMAJ>(sm, V + (long long)q0 * n, n, 0, qn, V + (long long)b0 * n, n, 0, bn, 0, n,
-                                     acc);
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = mg::acc_row(p, v), j = mg::acc_col(q);
-                if (i < qn && j < bn) dd[i + j * qn] = acc[p][q][v];
-            }
-}
-
-__device__ inline void wg_block_update_mfma(mg::Smem& sm, double* V, int n, int q0, int qn, int b0, int bn,
-                                            const double* dd) {
-    if (bn <= 0) return;   // uniform over the workgroup
-    for (int r0 = 0; r0 < n; r0 += mg::T) {
-        mg::d4 acc[2][2];
-        mg::zero(acc);
-        mg::tile_mma<mg::IMAJ, mg::KMAJ>(sm, V + (long long)q0 * n + r0, n, 0, n - r0, dd, qn, 0, bn, 0, qn, acc);
-        double old[2][2][4];   // loaded before use, addresses clamped (no conditional loads)
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int i = min(r0 + mg::acc_row(p, v), n - 1), t = min(mg::acc_col(q), bn - 1);
-                    old[p][q][v] = V[(long long)(b0 + t) * n + i];
-                }
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int i = r0 + mg::acc_row(p, v), t = mg::acc_col(q);
-                    if (i < n && t < bn) V[(long long)(b0 + t) * n + i] = old[p][q][v] - acc[p][q][v];
-                }
-    }
-}
-
-// Orthonormalise the batch Y = V[:, b0 .. b0 + bn) by Cholesky QR: with D the
-// inverse column norms, D Y^T Y D = L L^T and Y <- Y D L^{-T}.  That is the Q of
-// Y = QR, the factor Gram-Schmidt in index order produces, from one product on
-// the matrix cores, a 64 x 64 Cholesky in LDS and one triangular solve per row.
-// Returns false, with Y unchanged, when a pivot of the unit-diagonal Gram matrix
-// falls below 1e-12 (cond(Y D) above about 1e6, where one pass would lose
-// orthogonality); the caller then orthogonalises member by member.  dd: 64 x 64
-// doubles of global scratch.
-__device__ inline bool wg_batch_cholqr(mg::Smem& sm, double* V, int n, int b0, int bn, double* dd) {
-    __shared__ int s_ok;
-    __shared__ double s_d[64];
-    wg_block_dots_mfma(sm, V, n, b0, bn, b0, bn, dd);
-    __syncthreads();
-    double* G = reinterpret_cast<double*>(&sm);                // bn * bn <= 4096 doubles
-    for (int i = tid(); i < bn; i += LSDD_WG) {
-        const double g = dd[i + i * bn];
-        s_d[i] = g > 0.0 ? 1.0 / sqrt(g) : 0.0;
-    }
-    if (tid() == 0) s_ok = 1;
-    __syncthreads();
-    for (int idx = tid(); idx < bn * bn; idx += LSDD_WG) G[idx] = dd[idx] * s_d[idx % bn] * s_d[idx / bn];
-    __syncthreads();
-    for (int j = 0; j < bn; ++j) {
-        const double pjj = G[j + j * bn];
-        if (!(pjj > 1e-12)) {
-            if (tid() == 0) s_ok = 0;
-            break;                                              // same value on every thread
-        }
-        const double ljj = sqrt(pjj);
-        for (int i = j + 1 + tid(); i < bn; i += LSDD_WG) G[i + j * bn] /= ljj;
-        __syncthreads();
-        const int m = bn - 1 - j;                               // trailing (i, k), j < k <= i
-        for (int idx = tid(); idx < m * m; idx += LSDD_WG) {
-            const int i = j + 1 + idx % m, k = j + 1 + idx / m;
-            if (k <= i) G[i + k * bn] -= G[i + j * bn] * G[k + j * bn];
-        }
-        if (tid() == 0) G[j + j * bn] = ljj;
-        __syncthreads();
-    }
-    __syncthreads();
-    const bool ok = s_ok != 0;
-    if (ok) {
-        for (int r = tid(); r < n; r += LSDD_WG)
-            for (int j = 0; j < bn; ++j) {
-                double z = V[(long long)(b0 + j) * n + r] * s_d[j];
-                for (int k = 0; k < j; ++k) z -= V[(long long)(b0 + k) * n + r] * G[j + k * bn];
-                V[(long long)(b0 + j) * n + r] = z / G[j + j * bn];
-            }
-    }
-    __syncthreads();
-    return ok;
-}
-
 // Eigenvectors of the tridiagonal (d, e) for the eigenvalues lam[0..kk) by
 // inverse iteration.  Eigenvalues closer than 1e-4 * tnorm form a cluster.
 // This workgroup handles the single-member clusters with index in [r0, r1)
@@ -703,17 +602,14 @@ __device__ inline bool wg_batch_cholqr(mg::Smem& sm, double* V, int n, int b0, i
 // lane.  The members of a larger cluster are processed in batches of up
 // to 64: each iteration solves every member's shifted system on its own
 // thread, then orthogonalises the batch twice: by block classical Gram-Schmidt
-// against the earlier members of the cluster, then within the batch by Cholesky
-// QR (with sm; wg_batch_cholqr) or, where that is refused or without sm, by
-// Gram-Schmidt in index order, normalising each member.  Every vector is computed the same way
-// whatever the range split.  Output V (n x kk, column-major, ld n); `dd` holds
-// 64 x 64 batch dots.  LDS: cl_start (kk+1 ints), dots (64).
-// sm: LDS staging of the matrix cores for the block Gram-Schmidt steps of
-// clusters (NULL: the same steps as register-blocked vector loops).
+// against the earlier members of the cluster, then within the batch by Gram-Schmidt in
+// index order, normalising each member.  Output V (n x kk, column-major, ld n); `dd` holds
+// 64 x 64 batch dots.  LDS: cl_start (kk+1 ints), dots (64).  (The larger problems have
+// their own multi-workgroup form, k_trd_invit.)
 __device__ inline void wg_inverse_iteration_range(const double* d, const double* e, int n, const double* lam,
                                                   int kk, int r0, int r1, double* V, double* ws, double* dd,
                                                   double tnorm, int* cl_start, double* dots, double* red,
-                                                  int* ncl_sh, mg::Smem* sm = nullptr) {
+                                                  int* ncl_sh) {
     const double eps = 2.220446049250313e-16;
     const double gaptol = 1e-4 * tnorm;
     if (tid() == 0) {
@@ -794,20 +690,12 @@ __device__ inline void wg_inverse_iteration_range(const double* d, const double*
                     // against the earlier members of the cluster (in chunks of 64 members)
                     for (int q0 = c0; q0 < b0; q0 += 64) {
                         const int qn = min(64, b0 - q0);
-                        if (sm) {
-                            wg_block_dots_mfma(*sm, V, n, q0, qn, b0, bn, dd);
-                            __syncthreads();
-                            wg_block_update_mfma(*sm, V, n, q0, qn, b0, bn, dd);
-                        } else {
-                            wg_block_dots(V, n, q0, qn, b0, bn, dd);
-                            __syncthreads();
-                            wg_block_update(V, n, q0, qn, b0, bn, dd);
-                        }
+                        wg_block_dots(V, n, q0, qn, b0, bn, dd);
+                        __syncthreads();
+                        wg_block_update(V, n, q0, qn, b0, bn, dd);
                         __syncthreads();
                     }
-                    // within the batch: Cholesky QR where the batch is well enough
-                    // conditioned, else in index order, each member normalised before use
-                    if (sm && wg_batch_cholqr(*sm, V, n, b0, bn, dd)) continue;
+                    // within the batch in index order, each member normalised before use
                     for (int t = 0; t < bn; ++t) {
                         double* y = V + (long long)(b0 + t) * n;
                         if (t > 0) {

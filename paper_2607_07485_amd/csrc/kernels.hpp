@@ -65,7 +65,7 @@ void launch_local_tridiag_blocked(const LocalArgs& a, const int32_t* d_big, cons
 // Retained eigenvectors of the tridiagonal matrices of the same entries by
 // inverse iteration, ceil(k / 64) workgroups per entry (after the mode-count
 // phase of k_local_eig); iw + iw_off[i] is entry i's scratch of
-// ceil(k_i / 64) * (INVIT_SLOTS n_i + 4096) doubles.
+// ceil(k_i / 64) * (INVIT_BLK_SLOTS n_i + 4096 + 64) doubles.
 void launch_local_invit_blocked(const LocalArgs& a, const int32_t* d_big, const std::vector<int32_t>& sizes,
                                 const std::vector<int32_t>& ks, const int64_t* d_iw_off, double* iw, hipStream_t st);
 // Back-transformation of the retained eigenvectors of the same entries (after

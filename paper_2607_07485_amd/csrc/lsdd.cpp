@@ -1181,7 +1181,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
                 std::vector<int32_t> kall = download(lv.d_k + pos, nb, st);
                 for (size_t t = 0; t < big.size(); ++t) {
                     ks[t] = kall[big[t]];
-                    iw_off[t + 1] = iw_off[t] + (int64_t)((ks[t] + 63) / 64) * ((int64_t)INVIT_SLOTS * bigsz[t] + 4096);
+                    iw_off[t + 1] = iw_off[t] + (int64_t)((ks[t] + 63) / 64) * ((int64_t)INVIT_BLK_SLOTS * bigsz[t] + 4096 + 64);
                 }
                 double* iw = ar.alloc<double>(std::max<int64_t>(iw_off.back(), 1));
                 int64_t* d_iw_off = ar.upload(iw_off, st);
