@@ -17,6 +17,7 @@
 
 #include "batched.hpp"
 #include "mgemm.hpp"
+#include "tile64.hpp"
 
 namespace lsdd {
 
@@ -35,137 +36,85 @@ __device__ inline double wave_min(double v) {
 }
 __device__ inline int ntiles(int n) { return (n + TB - 1) / TB; }
 
-// 64 x 64 tile (rows r0.., cols c0..) into LDS, zero outside the view; if
-// `unit_pad`, padded diagonal entries are 1 (a padded triangular factor).
-__device__ inline void ld_tile64(double (*t)[TB + 1], const double* a, const View& v, int r0, int c0,
-                                 bool unit_pad = false) {
-    for (int idx = t_id(); idx < TB * TB; idx += NT) {
-        int i = idx % TB, j = idx / TB;
-        int r = r0 + i, c = c0 + j;
-        double x = (r < v.rows && c < v.cols) ? a[v.off + r + (int64_t)c * v.ld] : 0.0;
-        if (unit_pad && i == j && !(r < v.rows && c < v.cols)) x = 1.0;
-        t[i][j] = x;
-    }
-}
-
-// ---------------------------------------------------------------- substitution in registers
-//
-// 64 right-hand sides at once: thread t works on vector t / 4 and holds its
-// entries sub, sub + 4, ..., sub + 60 (sub = t % 4) in x[16]; the four lanes
-// of a vector are adjacent, so pivots are passed by lane shuffles.
-
-// L x = b (L lower, LDS), first nb rows
-__device__ inline void fwd_subst(const double (*L)[TB + 1], double (&x)[16], int nb) {
-    const int sub = t_id() & 3, base = (t_id() & 63) & ~3;
+// 64 x 64 tile (rows r0.., cols c0..) of a view into LDS, identity outside it.  All 16 loads of
+// a thread are issued before the first is stored.
+__device__ inline void ld_tile64(double (*t)[t64::LD], const double* a, const View& v, int r0, int c0) {
+    const int i = t_id() & 63, j0 = t_id() >> 6;
+    const int r = min(r0 + i, v.rows - 1);
+    double x[16];
 #pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        if (i < nb) {
-            double xi = x[i >> 2] / L[i][i];
-            xi = __shfl(xi, base | (i & 3), 64);
-            if (sub == (i & 3)) x[i >> 2] = xi;
+    for (int u = 0; u < 16; ++u) x[u] = a[v.off + r + (int64_t)min(c0 + j0 + 4 * u, v.cols - 1) * v.ld];
 #pragma unroll
-            for (int q = 0; q < 16; ++q)
-                if (4 * q + sub > i) x[q] -= L[4 * q + sub][i] * xi;
-        }
-    }
-}
-
-// L^T x = b (L lower, LDS), first nb rows
-__device__ inline void bwd_subst(const double (*L)[TB + 1], double (&x)[16], int nb) {
-    const int sub = t_id() & 3, base = (t_id() & 63) & ~3;
-#pragma unroll
-    for (int i = TB - 1; i >= 0; --i) {
-        if (i < nb) {
-            double xi = x[i >> 2] / L[i][i];
-            xi = __shfl(xi, base | (i & 3), 64);
-            if (sub == (i & 3)) x[i >> 2] = xi;
-#pragma unroll
-            for (int q = 0; q < 16; ++q)
-                if (4 * q + sub < i) x[q] -= L[i][4 * q + sub] * xi;
-        }
+    for (int u = 0; u < 16; ++u) {
+        const int j = j0 + 4 * u;
+        t[i][j] = r0 + i < v.rows && c0 + j < v.cols ? x[u] : (i == j ? 1.0 : 0.0);
     }
 }
 
 // ---------------------------------------------------------------- Cholesky
 
-// unblocked Cholesky of diagonal tile kb by one wave: lane i holds row i of the
-// tile in registers; at column j the pivot is broadcast by a lane shuffle and
-// the new column L[:, j] through LDS.  minpiv[view] tracks the smallest pivot
-// (a non-positive or NaN pivot is replaced by 1 so the factorisation runs to
-// the end; the caller reads minpiv)
-__global__ void __launch_bounds__(64) k_potrf_diag(double* base, const View* views, int kb, double* minpiv) {
-    __shared__ double col[TB];
+// Cholesky factor of diagonal tile kb (tile64.hpp).  minpiv[view] tracks the smallest
+// pivot (a non-positive or NaN pivot is replaced by 1 so the factorisation runs to the end; the
+// caller reads minpiv)
+__global__ void __launch_bounds__(NT) k_potrf_diag(double* base, const View* views, int kb, double* minpiv) {
+    __shared__ t64::Tile sm;
+    __shared__ double piv[TB];
     const View v = views[blockIdx.y];
     const int n = v.rows;
     if (kb * TB >= n) return;
     const int r0 = kb * TB, nb = min(TB, n - r0);
-    const int i = t_id();
-    double x[TB];
-    // every lane loads a full row of the block first (row and column clamped into
-    // the block, so the 64 loads are unconditional and in flight together), then
-    // keeps its lower part (identity rows past the block end)
-    const int ic = min(i, nb - 1);
+    ld_tile64(sm.t, base, v, r0, r0);
+    if (t_id() < TB) piv[t_id()] = 1.0;
+    __syncthreads();
+    t64::cholesky(sm, piv, (nb + 15) >> 4);
+    const int i = t_id() & 63;
 #pragma unroll
-    for (int k = 0; k < TB; ++k) x[k] = base[v.off + (r0 + ic) + (int64_t)(r0 + min(k, nb - 1)) * v.ld];
-#pragma unroll
-    for (int k = 0; k < TB; ++k) x[k] = (i < nb && k <= i) ? x[k] : (k == i ? 1.0 : 0.0);
-    double dmin = INFINITY;
-#pragma unroll
-    for (int j = 0; j < TB; ++j) {
-        if (j < nb) {
-            double dj = 1.0;
-            if (i == j) {
-                const double d = x[j];
-                dmin = (d == d) ? d : -1.0;
-                dj = d > 0.0 ? sqrt(d) : 1.0;
-                x[j] = dj;
-            }
-            dj = __shfl(dj, j, 64);
-            if (i > j) x[j] /= dj;
-            col[i] = i > j ? x[j] : 0.0;
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int k = j + 1; k < TB; ++k)
-                if (i >= k) x[k] -= x[j] * col[k];
-            __builtin_amdgcn_wave_barrier();
-        }
+    for (int u = 0; u < 16; ++u) {
+        const int k = (t_id() >> 6) + 4 * u;
+        if (i < nb && k <= i) base[v.off + r0 + i + (int64_t)(r0 + k) * v.ld] = sm.t[i][k];
     }
-    dmin = wave_min(dmin);
-    if (i < nb) {
-#pragma unroll
-        for (int k = 0; k < TB; ++k)
-            if (k <= i) base[v.off + (r0 + i) + (int64_t)(r0 + k) * v.ld] = x[k];
+    if (t_id() < 64) {
+        double dmin = i < nb ? piv[i] : INFINITY;
+        dmin = wave_min(dmin == dmin ? dmin : -1.0);
+        if (i == 0) minpiv[blockIdx.y] = (kb == 0) ? dmin : fmin(minpiv[blockIdx.y], dmin);
     }
-    if (i == 0) minpiv[blockIdx.y] = (kb == 0) ? dmin : fmin(minpiv[blockIdx.y], dmin);
 }
 
 // L_ib,kb = A_ib,kb L_kk^{-T}, ib = kb + 1 + blockIdx.x: each row solves
 // L_kk x^T = a^T (forward substitution)
 __global__ void __launch_bounds__(NT) k_potrf_panel(double* base, const View* views, int kb) {
-    __shared__ double L[TB][TB + 1];
+    __shared__ t64::Tile sm;
     const View v = views[blockIdx.y];
     const int n = v.rows;
     const int nt = ntiles(n);
     const int ib = kb + 1 + (int)blockIdx.x;
     if (ib >= nt) return;
     const int nb = min(TB, n - kb * TB);
-    ld_tile64(L, base, v, kb * TB, kb * TB, true);
+    // rows of the panel as right-hand sides, 16 per wave; they arrive while the diagonal tile
+    // is staged
+    const int l = t_id() & 63, r = ib * TB + 16 * (t_id() >> 6) + (l & 15);
+    double* A = base + v.off + r + (int64_t)kb * TB * v.ld;
+    const double* Ac = base + v.off + min(r, n - 1) + (int64_t)kb * TB * v.ld;
+    mg::d4 X[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) X[k][q] = Ac[(int64_t)min(16 * k + (l >> 4) + 4 * q, nb - 1) * v.ld];
+    ld_tile64(sm.t, base, v, kb * TB, kb * TB);
     __syncthreads();
-    const int r = ib * TB + t_id() / 4, sub = t_id() & 3;
-    double x[16];
+    t64::prepare(sm);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int c = kb * TB + 4 * q + sub;
-        x[q] = (r < n && 4 * q + sub < nb) ? base[v.off + r + (int64_t)c * v.ld] : 0.0;
-    }
-    fwd_subst(L, x, nb);
-    if (r < n) {
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int c = kb * TB + 4 * q + sub;
-            if (4 * q + sub < nb) base[v.off + r + (int64_t)c * v.ld] = x[q];
+        for (int q = 0; q < 4; ++q) X[k][q] = r < n && 16 * k + (l >> 4) + 4 * q < nb ? X[k][q] : 0.0;
+    t64::forward(sm, X);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int c = 16 * k + (l >> 4) + 4 * q;
+            if (r < n && c < nb) A[(int64_t)c * v.ld] = X[k][q];
         }
-    }
 }
 
 // A_ib,jb -= sum over column tiles k in [kt0, kt1) of L_ib,k L_jb,k^T, for the
@@ -411,7 +360,7 @@ __global__ void __launch_bounds__(NTP) k_pstrf_panel(double* base, const View* v
 // lower triangular (forward only), so column tiles jc > kb are still zero.
 __global__ void __launch_bounds__(NT) k_trsm_diag(const double* lbase, const View* lv, double* bbase, const View* bv,
                                                   int s, int trans, int lower_b) {
-    __shared__ double L[TB][TB + 1];
+    __shared__ t64::Tile sm;
     const View l = lv[blockIdx.y], b = bv[blockIdx.y];
     const int n = l.rows;
     const int nt = ntiles(n);
@@ -420,24 +369,31 @@ __global__ void __launch_bounds__(NT) k_trsm_diag(const double* lbase, const Vie
     const int jc = (int)blockIdx.x;
     if (jc * TB >= b.cols || (lower_b && jc > kb)) return;
     const int nb = min(TB, n - kb * TB);
-    ld_tile64(L, lbase, l, kb * TB, kb * TB, true);
+    // 16 columns of the tile per wave
+    const int t = t_id() & 63, c = jc * TB + 16 * (t_id() >> 6) + (t & 15);
+    double* B = bbase + b.off + kb * TB + (int64_t)c * b.ld;
+    const double* Bc = bbase + b.off + kb * TB + (int64_t)min(c, b.cols - 1) * b.ld;
+    mg::d4 X[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) X[k][q] = Bc[min(16 * k + (t >> 4) + 4 * q, nb - 1)];
+    ld_tile64(sm.t, lbase, l, kb * TB, kb * TB);
     __syncthreads();
-    const int c = jc * TB + t_id() / 4, sub = t_id() & 3;
-    double x[16];
+    t64::prepare(sm);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int r = kb * TB + 4 * q + sub;
-        x[q] = (c < b.cols && 4 * q + sub < nb) ? bbase[b.off + r + (int64_t)c * b.ld] : 0.0;
-    }
-    if (!trans) fwd_subst(L, x, nb);
-    else bwd_subst(L, x, nb);
-    if (c < b.cols) {
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int r = kb * TB + 4 * q + sub;
-            if (4 * q + sub < nb) bbase[b.off + r + (int64_t)c * b.ld] = x[q];
+        for (int q = 0; q < 4; ++q) X[k][q] = c < b.cols && 16 * k + (t >> 4) + 4 * q < nb ? X[k][q] : 0.0;
+    if (!trans) t64::forward(sm, X);
+    else t64::backward(sm, X);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = 16 * k + (t >> 4) + 4 * q;
+            if (c < b.cols && r < nb) B[r] = X[k][q];
         }
-    }
 }
 
 // forward: B_ib -= sum_{k in [kt0, kt1)} L_ib,k X_k for the row tiles ib in
@@ -745,7 +701,7 @@ void Batched::potrf(double* base, const std::vector<View>& a, double* d_minpiv) 
     for (int p0 = 0; p0 < nt; p0 += OB) {
         const int p1 = std::min(p0 + OB, nt);
         for (int kb = p0; kb < p1; ++kb) {
-            hipLaunchKernelGGL(k_potrf_diag, dim3(1, nm), dim3(64), 0, st, base, dv, kb, d_minpiv);
+            hipLaunchKernelGGL(k_potrf_diag, dim3(1, nm), dim3(NT), 0, st, base, dv, kb, d_minpiv);
             const int below = nt - kb - 1;
             if (below <= 0) continue;
             hipLaunchKernelGGL(k_potrf_panel, dim3(below, nm), dim3(NT), 0, st, base, dv, kb);

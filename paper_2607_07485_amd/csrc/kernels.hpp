@@ -59,9 +59,11 @@ struct LocalArgs {
 // Blocked multi-workgroup tridiagonalisation (trd.hip) of the batch entries
 // d_big[0 .. sizes.size()) (sizes = their nw, each > 2 TRD_NB + 1); leaves the
 // same d, e, tau and reflectors as the single-workgroup reduction of k_local_eig.
+// d_mats: TRD_MAT_BYTES of scratch per entry.
 constexpr int TRD_NB = 32;
+constexpr int TRD_MAT_BYTES = 64;
 void launch_local_tridiag_blocked(const LocalArgs& a, const int32_t* d_big, const std::vector<int32_t>& sizes,
-                                  hipStream_t st);
+                                  void* d_mats, hipStream_t st);
 // Retained eigenvectors of the tridiagonal matrices of the same entries by
 // inverse iteration, ceil(k / 64) workgroups per entry (after the mode-count
 // phase of k_local_eig); iw + iw_off[i] is entry i's scratch of

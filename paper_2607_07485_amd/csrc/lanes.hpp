@@ -1,0 +1,87 @@
+// Small device helpers of the serial chains in the dense kernels.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+namespace lsdd {
+
+// 1 / x for normal x whose reciprocal is normal: the hardware's estimate and two Newton
+// steps (each doubles its bits), about half the chain of a division
+__device__ inline double quick_rcp(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// v permuted among 16 lanes by the vector ALU itself (a shuffle goes through LDS, whose one
+// pipe a CU's waves share: 44 ns a double against 20).  Every source lane must be active: not
+// inside a branch or a conditional operand.
+template <int CTRL>
+__device__ inline double quad_perm(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// v of lane s (0 .. 3) of the caller's group of four lanes; s is a constant after unrolling
+__device__ inline double quad_bcast(double v, int s) {
+    switch (s) {
+        case 0: return quad_perm<0x00>(v);
+        case 1: return quad_perm<0x55>(v);
+        case 2: return quad_perm<0xaa>(v);
+        default: return quad_perm<0xff>(v);
+    }
+}
+
+// v of lane s (0 .. 15) of the caller's group of 16 lanes, the same way; s is a constant after
+// unrolling
+__device__ inline double row_bcast(double v, int s) {
+    switch (s) {
+        case 0: return quad_perm<0x150>(v);
+        case 1: return quad_perm<0x151>(v);
+        case 2: return quad_perm<0x152>(v);
+        case 3: return quad_perm<0x153>(v);
+        case 4: return quad_perm<0x154>(v);
+        case 5: return quad_perm<0x155>(v);
+        case 6: return quad_perm<0x156>(v);
+        case 7: return quad_perm<0x157>(v);
+        case 8: return quad_perm<0x158>(v);
+        case 9: return quad_perm<0x159>(v);
+        case 10: return quad_perm<0x15a>(v);
+        case 11: return quad_perm<0x15b>(v);
+        case 12: return quad_perm<0x15c>(v);
+        case 13: return quad_perm<0x15d>(v);
+        case 14: return quad_perm<0x15e>(v);
+        default: return quad_perm<0x15f>(v);
+    }
+}
+
+// Sum of v over the caller's group of L lanes (a power of two), the same in every lane and in
+// a fixed order: inside 16 lanes by the vector ALU's permutations (exchanging halves of 2, 4,
+// 8 and 16 lanes; the last two mirror, which is the same once the smaller groups are equal),
+// across them by shuffles.
+template <int L>
+__device__ inline double sum_lanes(double v) {
+    if constexpr (L >= 2) v += quad_perm<0xb1>(v);         // 1 0 3 2
+    if constexpr (L >= 4) v += quad_perm<0x4e>(v);         // 2 3 0 1
+    if constexpr (L >= 8) v += quad_perm<0x141>(v);        // mirror of 8 lanes
+    if constexpr (L >= 16) v += quad_perm<0x140>(v);       // mirror of 16 lanes
+    if constexpr (L >= 32) v += __shfl_xor(v, 16, 64);
+    if constexpr (L >= 64) v += __shfl_xor(v, 32, 64);
+    return v;
+}
+template <int L>
+__device__ inline float sum_lanes(float v) {
+    auto perm = [](float x, auto c) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(c)::value, 0xf, 0xf, true));
+    };
+    if constexpr (L >= 2) v += perm(v, std::integral_constant<int, 0xb1>{});
+    if constexpr (L >= 4) v += perm(v, std::integral_constant<int, 0x4e>{});
+    if constexpr (L >= 8) v += perm(v, std::integral_constant<int, 0x141>{});
+    if constexpr (L >= 16) v += perm(v, std::integral_constant<int, 0x140>{});
+    if constexpr (L >= 32) v += __shfl_xor(v, 16, 64);
+    if constexpr (L >= 64) v += __shfl_xor(v, 32, 64);
+    return v;
+}
+
+}  // namespace lsdd

@@ -1158,6 +1158,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         launch_views_symmetrize(nb, sb, bt.put(0, vS), st);
         // eigenpairs of C and retained modes
         int32_t* d_big = nullptr;
+        void* d_mats = nullptr;
         {
             int32_t mx = 0;
             std::vector<int32_t> big, bigsz;
@@ -1171,7 +1172,8 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
             }
             if (!big.empty()) {
                 d_big = ar.upload(big, st);
-                launch_local_tridiag_blocked(B, d_big, bigsz, st);
+                d_mats = ar.get(big.size() * TRD_MAT_BYTES);
+                launch_local_tridiag_blocked(B, d_big, bigsz, d_mats, st);
             }
             launch_local_eig(nb, B, mx, 0, 1, st);
             if (!big.empty()) {
@@ -1228,7 +1230,10 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         for (void* p : {(void*)w1, (void*)w2, (void*)sb, (void*)vb, (void*)tb, (void*)d_ws, (void*)d_sq, (void*)d_t,
                         (void*)d_maxd, (void*)d_minp})
             ar.release(p);
-        if (d_big) ar.release(d_big);
+        if (d_big) {
+            ar.release(d_big);
+            ar.release(d_mats);
+        }
         pos = end;
     }
     vlog("level %d: local problems %.3f s", lv.level, now_s() - tl0);

@@ -9,17 +9,24 @@
 // reflectors (V, W) and the matrix-vector product with the trailing block is
 // corrected the same way; after the panel one symmetric rank-2k update
 // C22 -= V W^T + W V^T runs on the FP64 matrix cores.  Per column:
-//   k_trd_col   (one workgroup per matrix): finish the previous W column,
+//   k_trd_col   (one workgroup per matrix): finish the previous W column
+//               (w = tau (C22 v - V (W^T v) - W (V^T v)), then w -= (tau/2) (w . v) v),
 //               correct column j, form reflector v_j (stored in column j, with
-//               an explicit 1 on the subdiagonal), dots W^T v and V^T v;
-//   k_trd_symv  (many workgroups per matrix): w = tau (C22 v - V (W^T v)
-//               - W (V^T v)), one wave per column of C22.
-// Per panel: k_trd_fin (finish the last W column), k_trd_update.
+//               an explicit 1 on the subdiagonal);
+//   k_trd_symv  (many workgroups per matrix): C22 v, four columns of C22 per wave,
+//               and the workgroup's rows' share of the dots W^T v and V^T v.
+// Per panel: k_trd_col once more for the last W column, k_trd_update.
+//
+// The column kernel is one serial chain per column, so what counts is how often it goes to
+// memory: it reads each row of V and W once, for the previous column's finish and this
+// column's correction together, and takes the dots as partial sums from the launch before.
+// 54 matrices of up to 648, then 8 of up to 882 columns: 26.5 -> 15 us a column (column
+// kernel 16.0 -> 7.7, product 10.5 -> 7.0; 256 rows left: 5.8 and 5.2).
 //
 // Storage per matrix: C (n x n, both triangles kept exactly symmetric), the
-// tridiagonal d, e, tau in the T scratch, V and W (n x TRD_NB each,
-// column-major, so row sweeps over one column are coalesced) and the dots in
-// the v_buf slot (n^2 doubles, n > 2 TRD_NB).
+// tridiagonal d, e, tau and the dots' partial sums in the T scratch, V and W (n x
+// TRD_NB each, column-major, so row sweeps over one column are coalesced) in the v_buf
+// slot (n^2 doubles, n > 2 TRD_NB).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,6 +36,7 @@
 #include "dense.hpp"
 #include "kernels.hpp"
 #include "mgemm.hpp"
+#include "tile64.hpp"
 
 namespace lsdd {
 
@@ -39,75 +47,180 @@ constexpr int NB = TRD_NB;
 constexpr int CPW = 4;               // columns per wave in k_trd_symv
 constexpr int CPG = CPW * WG / 64;   // columns per workgroup
 
+// One matrix of the batch; a table of these, so that a launch finds its matrix with one
+// dependent load (k_trd_mats fills it).
 struct Mat {
-    int n;
+    int n, pad;
     double* a;
     double* d;
     double* e;
     double* tau;
     double* V;
     double* W;
-    double* zw;
-    double* zv;
+    double* zp;                      // per k_trd_symv workgroup: its share of W^T v, V^T v (2 NB)
 };
 
-__device__ inline Mat mat_of(const LocalArgs& A, int b) {
+__global__ void k_trd_mats(LocalArgs A, const int32_t* big, int nbig, Mat* out) {
+    const int i = (int)blockIdx.x * 64 + tid();
+    if (i >= nbig) return;
+    const int b = big[i], ag = A.first + b;
     Mat m;
-    const int ag = A.first + b;
     m.n = (int)(A.agg_ptr[ag + 1] - A.agg_ptr[ag]);
+    m.pad = 0;
     m.a = A.s_buf + A.sq_off[b];
     double* T = A.t_buf + A.t_off[b];
     m.d = T;
     m.e = T + m.n;
     m.tau = T + 2 * m.n;
+    m.zp = T + 3 * m.n;              // the inverse iteration's scratch, not in use yet
     m.V = A.v_buf + A.sq_off[b];
     m.W = m.V + (int64_t)NB * m.n;
-    m.zw = m.W + (int64_t)NB * m.n;
-    m.zv = m.zw + NB;
-    return m;
+    out[i] = m;
 }
+static_assert(INVIT_SLOTS * 16 >= 2 * NB, "partial dots fit the scratch: (n / CPG + 1) 2 NB <= INVIT_SLOTS n");
 
-// W(:, q) <- w - (tau_jp / 2) (w . v) v for the raw w of reflector jp
-__device__ inline void finish_w(const Mat& m, int jp, int q, double* red) {
-    double s = 0.0;
-    const double* vq = m.V + (int64_t)q * m.n;
-    double* wq = m.W + (int64_t)q * m.n;
-    for (int i = jp + 1 + tid(); i < m.n; i += WG) s += wq[i] * vq[i];
-    s = wg_sum(s, red);
-    const double K = 0.5 * m.tau[jp] * s;
-    for (int i = jp + 1 + tid(); i < m.n; i += WG) wq[i] -= K * vq[i];
+// sum over the workgroup's TH threads, the same in every thread (red: TH / 64 entries)
+template <int TH>
+__device__ inline double col_sum(double v, double* red) {
+    v = sum_lanes<64>(v);
     __syncthreads();
+    if ((tid() & 63) == 0) red[tid() >> 6] = v;
+    __syncthreads();
+    double s = red[0];
+#pragma unroll
+    for (int q = 1; q < TH / 64; ++q) s += red[q];
+    return s;
 }
 
-__global__ void __launch_bounds__(WG) k_trd_col(LocalArgs A, const int32_t* big, int j, int j0) {
-    __shared__ double red[WG / 64];
-    __shared__ double rowvw[2 * NB];
-    __shared__ double part[WG / 64][2 * NB];
-    const Mat m = mat_of(A, big[blockIdx.x]);
+// Column j of the panel that starts at j0 (fin: only the last W column of that panel).  TH
+// threads, RPT rows each: the factors of a V, W entry come from LDS for every wave that uses
+// them, so up to 1024 rows run on four waves with up to four rows a thread, not on sixteen
+// (10.4 against 7.7 us a column, averaged over n = 648 and 882).
+template <int TH, int RPT>
+__global__ void __launch_bounds__(TH) k_trd_col(const Mat* mats, int j, int j0, int fin) {
+    constexpr int QC = RPT <= 2 ? 8 : 4;               // panel columns in flight
+    constexpr int PW = TH / 64;
+    __shared__ double red[PW];
+    __shared__ double part[PW][2 * NB];
+    __shared__ __align__(16) double fac[NB][4];        // W^T v, V^T v, rows j of V and W
+    __shared__ double s_row[2];
+    const Mat m = mats[blockIdx.x];
     const int n = m.n;
-    if (j + 2 >= n) return;
-    const int p = j - j0;
-    if (p > 0) finish_w(m, j - 1, p - 1, red);
-    // column j (rows j..n-1) with the panel's earlier reflectors applied
-    if (tid() < p) {
-        rowvw[tid()] = m.V[j + (int64_t)tid() * n];
-        rowvw[NB + tid()] = m.W[j + (int64_t)tid() * n];
+    if (fin) {
+        const int pc = min(NB, n - 2 - j0);            // this matrix's columns in the panel
+        if (pc <= 0) return;
+        j = j0 + pc;
+    } else if (j + 2 >= n) {
+        return;
     }
-    __syncthreads();
+    const int p = j - j0, qf = p - 1;                  // the W column to finish: qf
     double* col = m.a + (int64_t)j * n;
-    for (int i = j + tid(); i < n; i += WG) {
-        double s = col[i];
-        for (int q = 0; q < p; ++q) s -= m.V[i + (int64_t)q * n] * rowvw[NB + q] + m.W[i + (int64_t)q * n] * rowvw[q];
-        col[i] = s;
+    double x[RPT];
+    int row[RPT];
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) {
+        row[u] = j + tid() + u * TH;
+        x[u] = fin ? 0.0 : col[min(row[u], n - 1)];
     }
-    __syncthreads();
-    // reflector from x = col[j+1 .. n-1]
-    const int mm = n - j - 1;
-    double* x = col + j + 1;
+    if (p > 0) {
+        // W^T v and V^T v of reflector j - 1 from the partial sums, rows j of V and W
+        const int nblk = (n - j + CPG - 1) / CPG;
+        const int sidx = tid() & 63, g = tid() >> 6;
+        double y[RPT], v[RPT], vv[RPT][QC], ww[RPT][QC];
+        // entries q0 .. q0 + QC - 1 of the rows (columns past qf - 1 have zero factors); the
+        // first ones arrive while the factors are formed
+        auto fetch = [&](int q0) {
+#pragma unroll
+            for (int u = 0; u < RPT; ++u)
+#pragma unroll
+                for (int q = 0; q < QC; ++q) {
+                    const int64_t o = min(row[u], n - 1) + (int64_t)min(q0 + q, max(qf - 1, 0)) * n;
+                    vv[u][q] = m.V[o];
+                    ww[u][q] = m.W[o];
+                }
+        };
+        double z = 0.0;
+        for (int q0 = g; q0 < nblk; q0 += 8 * PW) {
+            double zz[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) zz[u] = m.zp[(int64_t)min(q0 + u * PW, nblk - 1) * 2 * NB + sidx];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) z += q0 + u * PW < nblk ? zz[u] : 0.0;
+        }
+        double rj = 0.0;                               // V(j, q) in lanes 0 .. 31, W(j, q) behind
+        if (g == 0) rj = (sidx < NB ? m.V : m.W)[j + (int64_t)min(sidx & (NB - 1), max(qf - 1, 0)) * n];
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            const int i = min(row[u], n - 1);
+            y[u] = m.W[i + (int64_t)qf * n];
+            v[u] = m.V[i + (int64_t)qf * n];
+        }
+        fetch(0);
+        const double t = m.tau[j - 1];
+        part[g][sidx] = z;
+        __syncthreads();
+        if (g == 0) {
+            double sum = 0.0;
+#pragma unroll
+            for (int q = 0; q < PW; ++q) sum += part[q][sidx];
+            const int q = sidx & (NB - 1);
+            const bool in = q < qf;
+            fac[q][sidx < NB ? 0 : 1] = in ? sum : 0.0;
+            fac[q][sidx < NB ? 3 : 2] = in && !fin ? rj : 0.0;   // V meets W's row and the other way round
+        }
+        __syncthreads();
+        double sv = 0.0, corr[RPT], upd[RPT];
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) corr[u] = upd[u] = 0.0;
+        for (int q0 = 0; q0 < qf; q0 += QC) {
+            double vc[RPT][QC], wc[RPT][QC];
+#pragma unroll
+            for (int u = 0; u < RPT; ++u)
+#pragma unroll
+                for (int q = 0; q < QC; ++q) vc[u][q] = vv[u][q], wc[u][q] = ww[u][q];
+            if (q0 + QC < qf) fetch(q0 + QC);
+#pragma unroll
+            for (int q = 0; q < QC; ++q) {
+                const double2 z2 = *reinterpret_cast<const double2*>(&fac[q0 + q][0]);
+                const double2 r2 = *reinterpret_cast<const double2*>(&fac[q0 + q][2]);
+#pragma unroll
+                for (int u = 0; u < RPT; ++u) {
+                    corr[u] += vc[u][q] * z2.x + wc[u][q] * z2.y;
+                    upd[u] += vc[u][q] * r2.x + wc[u][q] * r2.y;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            y[u] = t * (y[u] - corr[u]);
+            if (row[u] < n) sv += y[u] * v[u];
+        }
+        const double K = 0.5 * t * col_sum<TH>(sv, red);
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+            y[u] -= K * v[u];
+            if (row[u] < n) m.W[row[u] + (int64_t)qf * n] = y[u];
+        }
+        if (fin) return;
+        if (tid() == 0) s_row[0] = y[0], s_row[1] = v[0];      // row j
+        __syncthreads();
+        const double wj = s_row[0], vj = s_row[1];
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) x[u] -= upd[u] + (v[u] * wj + y[u] * vj);
+        __syncthreads();
+    } else if (fin) {
+        return;
+    }
+    // reflector from x(j + 1 .. n - 1)
     double s2 = 0.0;
-    for (int i = 1 + tid(); i < mm; i += WG) s2 += x[i] * x[i];
-    s2 = wg_sum(s2, red);
-    const double alpha = x[0];
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) {
+        if (row[u] == j) col[j] = x[u], m.d[j] = x[u];
+        if (row[u] == j + 1) s_row[0] = x[u];
+        if (row[u] > j + 1 && row[u] < n) s2 += x[u] * x[u];
+    }
+    s2 = col_sum<TH>(s2, red);                         // its barriers publish s_row
+    const double alpha = s_row[0];
     double t = 0.0, beta = alpha, sc = 0.0;
     if (s2 > 0.0) {
         const double nrm = sqrt(alpha * alpha + s2);
@@ -116,73 +229,27 @@ __global__ void __launch_bounds__(WG) k_trd_col(LocalArgs A, const int32_t* big,
         sc = 1.0 / (alpha - beta);
     }
     if (tid() == 0) {
-        m.d[j] = col[j];
         m.e[j] = beta;
         m.tau[j] = t;
     }
-    __syncthreads();
     double* vp = m.V + (int64_t)p * n;
-    for (int i = tid(); i < mm; i += WG) {
-        const double vi = (i == 0) ? 1.0 : (s2 > 0.0 ? x[i] * sc : 0.0);
-        x[i] = vi;
-        vp[j + 1 + i] = vi;
-    }
-    for (int i = j0 + tid(); i <= j; i += WG) {
+#pragma unroll
+    for (int u = 0; u < RPT; ++u)
+        if (row[u] > j && row[u] < n) {
+            const double vi = row[u] == j + 1 ? 1.0 : (s2 > 0.0 ? x[u] * sc : 0.0);
+            col[row[u]] = vi;
+            vp[row[u]] = vi;
+        }
+    for (int i = j0 + tid(); i <= j; i += TH) {
         vp[i] = 0.0;
         m.W[i + (int64_t)p * n] = 0.0;
     }
-    __syncthreads();
-    // zw_q = W(j+1:, q) . v, zv_q = V(j+1:, q) . v for q < p
-    const int w = tid() >> 6, l = tid() & 63;
-    for (int q0 = 0; q0 < p; q0 += 8) {
-        double aw[8], av[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) aw[u] = av[u] = 0.0;
-        for (int i = j + 1 + tid(); i < n; i += WG) {
-            const double vi = x[i - j - 1];
-            // columns past p re-read column p - 1 (the loads stay unconditional and in
-            // flight together) and are not added
-            double ww[8], vv[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t qc = min(q0 + u, p - 1);
-                ww[u] = m.W[i + qc * n];
-                vv[u] = m.V[i + qc * n];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (q0 + u < p) {
-                    aw[u] += ww[u] * vi;
-                    av[u] += vv[u] * vi;
-                }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            aw[u] = wave_sum(aw[u]);
-            av[u] = wave_sum(av[u]);
-        }
-        if (l == 0)
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                part[w][q0 + u] = aw[u];
-                part[w][NB + q0 + u] = av[u];
-            }
-    }
-    __syncthreads();
-    if (tid() < p) {
-        double sw = 0.0, sv = 0.0;
-        for (int r = 0; r < WG / 64; ++r) {
-            sw += part[r][tid()];
-            sv += part[r][NB + tid()];
-        }
-        m.zw[tid()] = sw;
-        m.zv[tid()] = sv;
-    }
 }
 
-__global__ void __launch_bounds__(WG) k_trd_symv(LocalArgs A, const int32_t* big, int j, int j0) {
-    extern __shared__ double s_v[];    // v (n - j - 1), then zw, zv
-    const Mat m = mat_of(A, big[blockIdx.y]);
+// W(:, p) <- C22 v (raw), the partial dots of the workgroup's rows
+__global__ void __launch_bounds__(WG) k_trd_symv(const Mat* mats, int j, int j0) {
+    __shared__ double s_z[WG / 64][2 * NB];
+    const Mat m = mats[blockIdx.y];
     const int n = m.n;
     if (j + 2 >= n) return;
     const int mm = n - j - 1;
@@ -190,50 +257,64 @@ __global__ void __launch_bounds__(WG) k_trd_symv(LocalArgs A, const int32_t* big
     if (c0 >= mm) return;
     const int p = j - j0;
     const double* v = m.a + (int64_t)j * n + j + 1;
-    double* zz = s_v + mm;
-    for (int i = tid(); i < mm; i += WG) s_v[i] = v[i];
-    if (tid() < p) {
-        zz[tid()] = m.zw[tid()];
-        zz[NB + tid()] = m.zv[tid()];
-    }
-    __syncthreads();
-    const double t = m.tau[j];
     const int w = tid() >> 6, l = tid() & 63;
-    for (int cc = 0; cc < CPW; ++cc) {
-        const int c = c0 + w * CPW + cc;
-        if (c >= mm) break;
-        const double* cp = m.a + (int64_t)(j + 1 + c) * n + j + 1;
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-        int i = l;
-        for (; i + 192 < mm; i += 256) {
-            s0 += cp[i] * s_v[i];
-            s1 += cp[i + 64] * s_v[i + 64];
-            s2 += cp[i + 128] * s_v[i + 128];
-            s3 += cp[i + 192] * s_v[i + 192];
-        }
-        for (; i < mm; i += 64) s0 += cp[i] * s_v[i];
-        // the panel's correction V (W^T v) + W (V^T v) of row gi, one term per lane
-        // (p <= NB < 64), folded into the same wave reduction
-        const int gi = j + 1 + c;
-        double corr = 0.0;
-        if (l < p) corr = m.V[gi + (int64_t)l * n] * zz[l] + m.W[gi + (int64_t)l * n] * zz[NB + l];
-        const double s = wave_sum(((s0 + s1) + (s2 + s3)) - corr);
-        if (l == 0) m.W[gi + (int64_t)p * n] = t * s;
+    // this workgroup's rows against column l & 31 of W (l < 32) or V, four rows per wave
+    const int64_t qo = (int64_t)min(l & (NB - 1), max(p - 1, 0)) * n;
+    const double* M = (l < NB ? m.W : m.V) + qo + j + 1;
+    double zr[CPG / (WG / 64)], zx[CPG / (WG / 64)];
+#pragma unroll
+    for (int u = 0; u < CPG / (WG / 64); ++u) {
+        const int i = min(c0 + w * CPW + u, mm - 1);
+        zr[u] = M[i];
+        zx[u] = v[i];
     }
-}
-
-__global__ void __launch_bounds__(WG) k_trd_fin(LocalArgs A, const int32_t* big, int j0) {
-    __shared__ double red[WG / 64];
-    const Mat m = mat_of(A, big[blockIdx.x]);
-    const int pc = min(NB, m.n - 2 - j0);
-    if (pc <= 0) return;
-    finish_w(m, j0 + pc - 1, pc - 1, red);
+    const double* cp[CPW];
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) cp[c] = m.a + (int64_t)(j + 1 + min(c0 + w * CPW + c, mm - 1)) * n + j + 1;
+    double s[CPW] = {0.0, 0.0, 0.0, 0.0};
+    constexpr int U = 4;
+    for (int i0 = l; i0 < mm; i0 += 64 * U) {
+        double x[U], av[CPW][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + 64 * u, mm - 1);
+            x[u] = v[i];
+#pragma unroll
+            for (int c = 0; c < CPW; ++c) av[c][u] = cp[c][i];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double xx = i0 + 64 * u < mm ? x[u] : 0.0;
+#pragma unroll
+            for (int c = 0; c < CPW; ++c) s[c] += av[c][u] * xx;
+        }
+    }
+    double z = 0.0;
+#pragma unroll
+    for (int u = 0; u < CPG / (WG / 64); ++u) z += c0 + w * CPW + u < mm ? zr[u] * zx[u] : 0.0;
+    s_z[w][l] = z;
+    // the four sums over the lanes: lane 16 c ends with column c
+    static_assert(CPW == 4, "fold laid out for 4 columns per wave");
+#pragma unroll
+    for (int h = 2, o = 32; h >= 1; h >>= 1, o >>= 1) {
+        const bool hi = l & o;
+#pragma unroll
+        for (int c = 0; c < h; ++c) {
+            const double send = hi ? s[c] : s[c + h], keep = hi ? s[c + h] : s[c];
+            s[c] = keep + __shfl_xor(send, o, 64);
+        }
+    }
+    const double y = sum_lanes<16>(s[0]);
+    const int c = c0 + w * CPW + (l >> 4);
+    if ((l & 15) == 0 && c < mm) m.W[j + 1 + c + (int64_t)p * n] = y;
+    __syncthreads();
+    if (tid() < 2 * NB) m.zp[(int64_t)blockIdx.x * 2 * NB + tid()] = (s_z[0][tid()] + s_z[1][tid()]) + (s_z[2][tid()] + s_z[3][tid()]);
 }
 
 // C[r0:, r0:] -= V W^T + W V^T over lower tile pairs, stored to both triangles
-__global__ void __launch_bounds__(WG) k_trd_update(LocalArgs A, const int32_t* big, int j0) {
+__global__ void __launch_bounds__(WG) k_trd_update(const Mat* mats, int j0) {
     __shared__ mg::Smem sm;
-    const Mat m = mat_of(A, big[blockIdx.y]);
+    const Mat m = mats[blockIdx.y];
     const int n = m.n;
     const int pc = min(NB, n - 2 - j0);
     if (pc <= 0) return;
@@ -280,8 +361,8 @@ __global__ void __launch_bounds__(WG) k_trd_update(LocalArgs A, const int32_t* b
             }
 }
 
-__global__ void k_trd_tail(LocalArgs A, const int32_t* big) {
-    const Mat m = mat_of(A, big[blockIdx.x]);
+__global__ void k_trd_tail(const Mat* mats) {
+    const Mat m = mats[blockIdx.x];
     const int n = m.n;
     if (tid() == 0 && n >= 3) {
         m.d[n - 2] = m.a[(n - 2) + (int64_t)(n - 2) * n];
@@ -290,17 +371,87 @@ __global__ void k_trd_tail(LocalArgs A, const int32_t* big) {
     }
 }
 
-// All eigenvalues of the large problems' tridiagonal matrices by bisection,
-// WG of them per workgroup (before the mode-count phase of k_local_eig).
+// Eigenvalues of the tridiagonal (d, e) smaller than x (Sturm count; d, and the squares of e
+// from e2[1] on, e2[0] = 0).  One chain of n reciprocals; the estimate with two Newton steps
+// is within an ulp or two of the division, which is what the count's backward error is anyway.
+__device__ inline int sturm_quick(const double* d, const double* e2, int n, double x, double pivmin) {
+    int c = 0;
+    double q = 1.0;
+    constexpr int U = 8;
+    int k = 0;
+    for (; k + U <= n; k += U) {
+        double dk[U], ek[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) dk[u] = d[k + u] - x, ek[u] = e2[k + u];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            q = dk[u] - ek[u] * quick_rcp(q);
+            q = fabs(q) < pivmin ? -pivmin : q;
+            c += q < 0.0;
+        }
+    }
+    for (; k < n; ++k) {
+        q = d[k] - x - e2[k] * quick_rcp(q);
+        q = fabs(q) < pivmin ? -pivmin : q;
+        c += q < 0.0;
+    }
+    return c;
+}
+
+// All eigenvalues of the large problems' tridiagonal matrices by multisection (before the
+// mode-count phase of k_local_eig): BL lanes per eigenvalue cut its interval in BL + 1 parts,
+// so a round gains log2(BL + 1) bits for one count's latency, and the serial rounds drop from
+// about 54 to 18 while the counts go up 2.7 times -- the chip is far from full with one lane
+// per eigenvalue.  d and e^2 lie in LDS.  n = 882: 4.9 -> 1.05 ms.
+constexpr int BL = 7;                // parts - 1; 8 lanes per eigenvalue, the last one idle
+constexpr int BE = WG / 8;           // eigenvalues per workgroup
 __global__ void __launch_bounds__(WG) k_trd_bisect(LocalArgs A, const int32_t* big) {
     __shared__ double red[WG / 64];
+    extern __shared__ double s_t[];                    // d (n), e2 (n)
     const int b = big[blockIdx.y];
     const int ag = A.first + b;
     const int n = (int)(A.agg_ptr[ag + 1] - A.agg_ptr[ag]);
-    const int i0 = (int)blockIdx.x * WG;
+    const int i0 = (int)blockIdx.x * BE;
     if (i0 >= n) return;
-    const double* T = A.t_buf + A.t_off[b];
-    wg_bisect_range(T, T + n, n, A.mu + A.mu_off[ag], i0, min(n, i0 + WG), red);
+    const double* d = A.t_buf + A.t_off[b];
+    const double* e = d + n;
+    double* s_e = s_t + n;
+    double lo = INFINITY, hi = -INFINITY, emax2 = 0.0;
+    for (int i = tid(); i < n; i += WG) {
+        const double el = i > 0 ? e[i - 1] : 0.0, er = i + 1 < n ? e[i] : 0.0, di = d[i];
+        const double r = fabs(el) + fabs(er);
+        lo = fmin(lo, di - r);
+        hi = fmax(hi, di + r);
+        emax2 = fmax(emax2, er * er);
+        s_t[i] = di;
+        s_e[i] = el * el;
+    }
+    lo = -wg_max(-lo, red);
+    hi = wg_max(hi, red);
+    emax2 = wg_max(emax2, red);
+    const double eps = 2.220446049250313e-16;
+    const double tnorm = fmax(fabs(lo), fabs(hi));
+    // smallest pivot: its reciprocal, times e^2, stays finite
+    const double pivmin = fmax(2.2250738585072014e-308 * fmax(emax2, 1.0), 1e-290);
+    const double atol = 2.0 * eps * tnorm + 1e-300;
+    double a = lo - atol, c = hi + atol;
+    const int i = min(i0 + (tid() >> 3), n - 1), l = tid() & 7;
+    for (int it = 0; it < 80; ++it) {
+        const bool done = c - a <= 2.0 * eps * fmax(fabs(a), fabs(c)) + atol;
+        if (__all(done)) break;
+        // lane l counts at the (l + 1)-th of BL inner points; lanes past the last one at c
+        const double x = l < BL ? fmin(fmax(a + (c - a) * ((l + 1) * (1.0 / (BL + 1))), a), c) : c;
+        const bool above = sturm_quick(s_t, s_e, n, x, pivmin) > i;     // the eigenvalue lies below x
+        const unsigned mask = (unsigned)(__ballot(above) >> (tid() & 56)) & ((1u << BL) - 1);
+        const int f = mask ? __ffs(mask) - 1 : BL;                      // first point above it
+        const double xa = __shfl(x, (tid() & 56) + max(f - 1, 0), 64), xc = __shfl(x, (tid() & 56) + min(f, 7), 64);
+        if (!done) {
+            const double na = f > 0 ? xa : a, nc = f < BL ? xc : c;
+            if (na == a && nc == c) a = c = 0.5 * (a + c);              // no representable point between
+            else a = na, c = nc;
+        }
+    }
+    if (l == 0 && i0 + (tid() >> 3) < n) A.mu[A.mu_off[ag] + i] = 0.5 * (a + c);
 }
 
 // ---------------------------------------------------------------- inverse iteration
@@ -324,14 +475,6 @@ __device__ inline TriLane tri_lane(double* ws, int n, int t) {
     L.f = L.y + (int64_t)64 * n;
     L.sw = reinterpret_cast<uint32_t*>(ws + (int64_t)5 * 64 * n) + t;
     return L;
-}
-
-// 1 / x for normal x whose reciprocal is normal: the hardware's estimate and two Newton
-// steps (each doubles its bits), about half the chain of a division
-__device__ inline double quick_rcp(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
 }
 
 // Rows go in blocks of 8: a full block has no branch, so that the compiler knows how many
@@ -466,23 +609,27 @@ __device__ inline double tri_back(int n, const TriLane& L) {
     return nr;
 }
 
+// LDS of the inverse iteration: the matrix cores' staging buffers, then the 64 x 64 tile.
+union InvSmem {
+    mg::Smem mm;
+    t64::Tile tile;
+    double s[64 * 65];
+};
+
 // Members of one cluster (cl[t] equal) are made orthonormal, members of different ones only
 // normalised: with D the inverse column norms and the cross-cluster entries of the Gram
 // matrix left out, D Y^T Y D = L L^T and Y <- Y D L^{-T}, the Q that Gram-Schmidt in index
-// order gives per cluster (Y: n x bn, row-major, ld 64).  The Gram matrix and the product with the 64 x 64 inverse run on the matrix cores
-// (row-wise substitution, 2016 dependent loads a row, took about 1 ms a pass at n = 882),
-// the Cholesky factor and its inverse in LDS.  False, with Y unchanged, when a pivot falls
-// below 1e-12, where one pass would lose orthogonality.  M: 64 x 64 doubles of scratch.
-__device__ inline bool batch_cholqr(mg::Smem& sm, double* Y, int n, int bn, const int* cl, double* M) {
-    __shared__ double s_d[64], s_col[2][64], s_piv[64];
-    __shared__ int s_ok;
-    constexpr int LD = 65;
-    double* G = reinterpret_cast<double*>(&sm);                // bn x bn, leading dimension 65
-    static_assert(sizeof(mg::Smem) >= 64 * LD * sizeof(double), "Gram matrix in the staging buffers");
+// order gives per cluster (Y: n x bn, row-major, ld 64).  The Gram matrix runs on the matrix
+// cores, its factor and the row-wise substitution through tile64.hpp (as 2016 dependent
+// loads a row the substitution took about 1 ms a pass at n = 882).  False, with Y unchanged,
+// when a pivot falls below 1e-12, where one pass would lose orthogonality.
+__device__ inline bool batch_cholqr(InvSmem& sm, double* Y, int n, int bn, const int* cl) {
+    __shared__ double s_d[64], s_piv[64];
     mg::d4 acc[2][2];
     mg::zero(acc);
-    mg::tile_mma<mg::IMAJ, mg::IMAJ>(sm, Y, 64, 0, bn, Y, 64, 0, bn, 0, n, acc);
+    mg::tile_mma<mg::IMAJ, mg::IMAJ>(sm.mm, Y, 64, 0, bn, Y, 64, 0, bn, 0, n, acc);
     __syncthreads();
+    t64::Tile& T = sm.tile;
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -490,83 +637,45 @@ __device__ inline bool batch_cholqr(mg::Smem& sm, double* Y, int n, int bn, cons
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int i = mg::acc_row(p, v), j = mg::acc_col(q);
-                G[i + j * LD] = i < bn && j < bn ? (cl[i] == cl[j] ? acc[p][q][v] : 0.0) : (i == j ? 1.0 : 0.0);
+                T.t[i][j] = i < bn && j < bn ? (cl[i] == cl[j] ? acc[p][q][v] : 0.0) : (i == j ? 1.0 : 0.0);
             }
-    if (tid() == 0) s_ok = 1;
     __syncthreads();
     if (tid() < 64) {
-        const double g = G[tid() * (LD + 1)];
+        const double g = T.t[tid()][tid()];
         s_d[tid()] = g > 0.0 ? 1.0 / sqrt(g) : 0.0;
+        s_piv[tid()] = 1.0;
     }
     __syncthreads();
-    // thread (row i, columns k = g mod 4) of the scaled matrix; column j is final when its
-    // step begins, one barrier a step (two column buffers)
-    const int i = tid() & 63, g = tid() >> 6;
-    double x[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) x[u] = G[i + (4 * u + g) * LD] * s_d[i] * s_d[4 * u + g];
-#pragma unroll
-    for (int j = 0; j < 64; ++j) {
-        if (j >= bn) break;                                    // the rest is the identity
-        if (g == (j & 3)) s_col[j & 1][i] = x[j >> 2];
-        __syncthreads();
-        const double* c = s_col[j & 1];
-        const double pj = c[j];
-        if (!(pj > 1e-12) && j < bn && tid() == 0) s_ok = 0;
-        const double r = pj > 1e-12 ? quick_rcp(pj) : 0.0, li = c[i] * r;
-#pragma unroll
-        for (int u = j >> 2; u < 16; ++u)
-            if (4 * u + g > j) x[u] -= li * c[4 * u + g];
-        if (tid() == j) s_piv[j] = pj;
+    for (int u = 0; u < 16; ++u) {
+        const int i = tid() & 63, j = (tid() >> 6) + 4 * u;
+        T.t[i][j] *= s_d[i] * s_d[j];
     }
     __syncthreads();
-    const bool ok = s_ok != 0;
-    if (!ok) {
-        __syncthreads();
-        return false;
-    }
-    if (tid() < 64) s_piv[tid()] = tid() < bn ? 1.0 / sqrt(s_piv[tid()]) : 1.0;   // 1 / L(j, j)
-    __syncthreads();
-    // M = D L^{-T}: thread c solves L z = e_c (z = column c of L^{-1}), four threads a column,
-    // rows r = 4 u + s; M(k, j) = s_d[k] (L^{-1})(j, k)
+    t64::cholesky(T, s_piv, (bn + 15) >> 4);
+    const int l = tid() & 63;
+    const bool ok = __all(s_piv[l] > 1e-12);            // the same in every wave
+    if (ok) {
+        t64::prepare(T);
+        // 16 rows of Y per wave as right-hand sides: L z = D y
+        for (int r0 = 16 * (tid() >> 6); r0 < n; r0 += 64) {
+            const int r = r0 + (l & 15);
+            double* y = Y + (int64_t)min(r, n - 1) * 64 + (l >> 4);
+            mg::d4 X[4];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) G[i + (4 * u + g) * LD] = x[u] * s_piv[4 * u + g];   // (rows above: unused)
-    __syncthreads();
-    {
-        const int c = tid() >> 2, s = tid() & 3;
-        double z[16];
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int u = 0; u < 16; ++u) z[u] = 4 * u + s == c ? 1.0 : 0.0;
+                for (int q = 0; q < 4; ++q) X[k][q] = y[16 * k + 4 * q] * s_d[16 * k + 4 * q + (l >> 4)];
+            t64::forward(T, X);
+            if (r < n)
 #pragma unroll
-        for (int j = 0; j < 64; ++j) {
-            if (j >= bn) break;
-            double zj = z[j >> 2] * s_piv[j];
-            zj = __shfl(zj, (tid() & 60) + (j & 3), 64);
-            if (s == (j & 3)) z[j >> 2] = zj;
+                for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int u = j >> 2; u < 16; ++u)
-                if (4 * u + s > j) z[u] -= G[4 * u + s + j * LD] * zj;
+                    for (int q = 0; q < 4; ++q) y[16 * k + 4 * q] = X[k][q];
         }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) M[c + (4 * u + s) * 64] = s_d[c] * z[u];
     }
     __syncthreads();
-    for (int r0 = 0; r0 < n; r0 += mg::T) {
-        mg::zero(acc);
-        // the rows of this tile are in LDS before the product ends: updated in place
-        mg::tile_mma<mg::KMAJ, mg::KMAJ>(sm, Y, 64, r0, n, M, 64, 0, bn, 0, bn, acc);
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int r = r0 + mg::acc_row(p, v), t = mg::acc_col(q);
-                    if (r < n && t < bn) Y[(int64_t)r * 64 + t] = acc[p][q][v];
-                }
-    }
-    __syncthreads();
-    return true;
+    return ok;
 }
 
 // Retained eigenvectors of the large problems' tridiagonal matrices by inverse iteration.
@@ -587,14 +696,16 @@ __device__ inline bool batch_cholqr(mg::Smem& sm, double* Y, int n, int bn, cons
 // the iteration stops when every member is there (at most 4 solves).
 //
 // Bound by the serial chains of the solves and of the 64-column factorisations, not by
-// bytes.  FIGURES
+// bytes: at n = 882 a factoring solve takes 187 us, a later one 104, an orthonormalisation
+// 100.  Eight matrices of up to 882 with 179 vectors each: 15.4 -> 4.6 ms; 64 of up to 285
+// with 40 each: 0.91 -> 0.31 ms.
 __global__ void __launch_bounds__(WG) k_trd_invit(LocalArgs A, const int32_t* big, const int64_t* iw_off,
                                                   double* iw) {
     __shared__ double red[WG / 64];
     __shared__ double s_dot[64];
     __shared__ int s_cl[64];
     __shared__ int s_conv;
-    __shared__ mg::Smem sm;
+    __shared__ InvSmem sm;
     extern __shared__ double s_dyn[];
     unsigned char* first = reinterpret_cast<unsigned char*>(s_dyn);   // kk + 1: a cluster starts here
     const int b = big[blockIdx.y];
@@ -655,7 +766,7 @@ __global__ void __launch_bounds__(WG) k_trd_invit(LocalArgs A, const int32_t* bi
                     const int qn = min(64, b0 - q0);
                     mg::d4 acc[2][2];
                     mg::zero(acc);
-                    mg::tile_mma<mg::KMAJ, mg::IMAJ>(sm, Q, n, 0, qn, Y, 64, 0, bn, 0, n, acc);
+                    mg::tile_mma<mg::KMAJ, mg::IMAJ>(sm.mm, Q, n, 0, qn, Y, 64, 0, bn, 0, n, acc);
 #pragma unroll
                     for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -668,7 +779,7 @@ __global__ void __launch_bounds__(WG) k_trd_invit(LocalArgs A, const int32_t* bi
                     __syncthreads();
                     for (int t0 = 0; t0 < n; t0 += mg::T) {
                         mg::zero(acc);
-                        mg::tile_mma<mg::IMAJ, mg::KMAJ>(sm, Q + t0, n, 0, n - t0, dd, qn, 0, bn, 0, qn, acc);
+                        mg::tile_mma<mg::IMAJ, mg::KMAJ>(sm.mm, Q + t0, n, 0, n - t0, dd, qn, 0, bn, 0, qn, acc);
 #pragma unroll
                         for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -681,7 +792,7 @@ __global__ void __launch_bounds__(WG) k_trd_invit(LocalArgs A, const int32_t* bi
                     }
                     __syncthreads();
                 }
-                if (batch_cholqr(sm, Y, n, bn, s_cl, dd)) continue;
+                if (batch_cholqr(sm, Y, n, bn, s_cl)) continue;
                 // member by member, each normalised before its use
                 for (int t = 0; t < bn; ++t) {
                     const int w = tid() >> 6, l = tid() & 63, t0 = max(0, s_cl[t] - b0);
@@ -709,7 +820,7 @@ __global__ void __launch_bounds__(WG) k_trd_invit(LocalArgs A, const int32_t* bi
             if (last) break;
         }
         // to V, column-major, through LDS tiles: rows contiguous on both sides
-        double* s = reinterpret_cast<double*>(&sm);    // 64 x 65
+        double* s = sm.s;
         for (int k0 = 0; k0 < n; k0 += 64) {
             __syncthreads();
             for (int q = tid(); q < 64 * 64; q += WG)
@@ -732,13 +843,10 @@ __global__ void __launch_bounds__(WG) k_trd_invit(LocalArgs A, const int32_t* bi
             if (ce - b0 > 64) break;
             end = ce;
         }
-        if (end > b0) {
-            batch(b0, end - b0, b0);
-            b0 = end;
-        } else {
-            for (int m = b0; m < ce; m += 64) batch(m, min(64, ce - m), b0);
-            b0 = ce;
-        }
+        const bool large = end == b0;                  // more than 64 members: 64 at a time
+        const int stop = large ? ce : end;
+        for (int m = b0; m < stop; m += 64) batch(m, min(64, stop - m), large ? b0 : m);
+        b0 = stop;
     }
 }
 
@@ -833,8 +941,10 @@ void launch_local_invit_blocked(const LocalArgs& a, const int32_t* d_big, const 
     hipLaunchKernelGGL(k_trd_invit, dim3(max_g, nbig), dim3(WG), lds, st, a, d_big, d_iw_off, iw);
 }
 
+static_assert(sizeof(Mat) <= TRD_MAT_BYTES, "matrix table");
+
 void launch_local_tridiag_blocked(const LocalArgs& a, const int32_t* d_big, const std::vector<int32_t>& sizes,
-                                  hipStream_t st) {
+                                  void* d_mats, hipStream_t st) {
     const int nbig = (int)sizes.size();
     if (nbig == 0) return;
     int max_n = 0;
@@ -842,15 +952,26 @@ void launch_local_tridiag_blocked(const LocalArgs& a, const int32_t* d_big, cons
         if (s <= 2 * NB + 1) throw std::runtime_error("blocked tridiagonalisation needs n > 2 * TRD_NB + 1");
         max_n = std::max(max_n, (int)s);
     }
-    const size_t lds = (size_t)(max_n + 2 * NB) * sizeof(double);
+    Mat* mats = static_cast<Mat*>(d_mats);
+    hipLaunchKernelGGL(k_trd_mats, dim3((nbig + 63) / 64), dim3(64), 0, st, a, d_big, nbig, mats);
+    auto column = [&](int j, int j0, int fin) {
+        auto go = [&](auto kern, int th) { hipLaunchKernelGGL(kern, dim3(nbig), dim3(th), 0, st, mats, j, j0, fin); };
+        const int rows = max_n - (fin ? j0 : j);       // at most these are left
+        if (rows <= 256) go(k_trd_col<256, 1>, 256);
+        else if (rows <= 512) go(k_trd_col<256, 2>, 256);
+        else if (rows <= 1024) go(k_trd_col<256, 4>, 256);
+        else if (rows <= 2048) go(k_trd_col<1024, 2>, 1024);
+        else go(k_trd_col<1024, 4>, 1024);
+    };
+    if (max_n > 4096) throw std::runtime_error("blocked tridiagonalisation: more than 4096 DOFs");
     for (int j0 = 0; j0 < max_n - 2; j0 += NB) {
         const int j1 = std::min(j0 + NB, max_n - 2);
         for (int j = j0; j < j1; ++j) {
-            hipLaunchKernelGGL(k_trd_col, dim3(nbig), dim3(WG), 0, st, a, d_big, j, j0);
+            column(j, j0, 0);
             const int mm = max_n - j - 1;
-            hipLaunchKernelGGL(k_trd_symv, dim3((mm + CPG - 1) / CPG, nbig), dim3(WG), lds, st, a, d_big, j, j0);
+            hipLaunchKernelGGL(k_trd_symv, dim3((mm + CPG - 1) / CPG, nbig), dim3(WG), 0, st, mats, j, j0);
         }
-        hipLaunchKernelGGL(k_trd_fin, dim3(nbig), dim3(WG), 0, st, a, d_big, j0);
+        column(0, j0, 1);
         int64_t jobs = 0;
         for (int32_t n : sizes) {
             const int pc = std::min(NB, (int)n - 2 - j0);
@@ -858,10 +979,14 @@ void launch_local_tridiag_blocked(const LocalArgs& a, const int32_t* d_big, cons
             const int64_t mt = (n - j0 - pc + mg::T - 1) / mg::T;
             jobs = std::max(jobs, mt * (mt + 1) / 2);
         }
-        if (jobs > 0) hipLaunchKernelGGL(k_trd_update, dim3((unsigned)jobs, nbig), dim3(WG), 0, st, a, d_big, j0);
+        if (jobs > 0) hipLaunchKernelGGL(k_trd_update, dim3((unsigned)jobs, nbig), dim3(WG), 0, st, mats, j0);
     }
-    hipLaunchKernelGGL(k_trd_tail, dim3(nbig), dim3(64), 0, st, a, d_big);
-    hipLaunchKernelGGL(k_trd_bisect, dim3((max_n + WG - 1) / WG, nbig), dim3(WG), 0, st, a, d_big);
+    hipLaunchKernelGGL(k_trd_tail, dim3(nbig), dim3(64), 0, st, mats);
+    const size_t lds = 2 * (size_t)max_n * sizeof(double);
+    if (lds > 60 * 1024)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_trd_bisect),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k_trd_bisect, dim3((max_n + BE - 1) / BE, nbig), dim3(WG), lds, st, a, d_big);
 }
 
 }  // namespace lsdd

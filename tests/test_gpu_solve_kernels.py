@@ -129,3 +129,38 @@ def test_fused_cycle_matches_separate_launches(kind):
         n = float(apart[i].norm())
         assert float((fused[i] - apart[i]).norm()) <= 1e-10 * n
         assert float((fused[i + 1] - fused[i]).norm()) <= 4 * float((apart[i + 1] - apart[i]).norm()) + 1e-12 * n
+
+
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 63, 64, 65, 129, 200])
+def test_direct_solve_tile_edges(n):
+    """A one-level hierarchy is a dense Cholesky factorisation and its inverse: tiles of 64 in
+    blocks of 16.  An explicit inverse in FP64 is within a few n cond eps of the solution."""
+    P = _lsdd()
+    prob = _chain(n)
+    r = np.random.default_rng(n).standard_normal(n)
+    ref = np.linalg.solve(_dense(prob), r)
+    with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=1)) as h:
+        z = h.vcycle(torch.from_numpy(r).cuda()).cpu().numpy()
+    assert np.linalg.norm(z - ref) <= 4 * n * COND * 2.3e-16 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("width", [1, 4, 8, 16])
+def test_blocked_eigensolver_sizes(width):
+    """Local spectral problems of 66 width DOFs (the smallest the blocked reduction takes, then one,
+    two and four rows per thread and more threads), whose spectra hold clusters of more than 64
+    members, against the reduction in one workgroup: eigenvalues to 1e-10, the V-cycle, which does
+    not depend on the basis, to 1e-10."""
+    import fegen
+    P = _lsdd()
+    prob = fegen.elasticity_q1(32, nu=0.3)
+    prob.agg_of_dof = (np.arange(prob.n) // (66 * width)).astype(np.int32)
+    r = torch.from_numpy(np.random.default_rng(width).standard_normal(prob.n)).cuda()
+    out = []
+    for blocked in (-1, 66):
+        with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2, blocked_eig_min=blocked)) as h:
+            ex = h.export_level(0)
+            out.append((ex["k"], ex["mu"], h.vcycle(r)))
+    (k0, mu0, z0), (k1, mu1, z1) = out
+    assert np.array_equal(k0, k1) and k0.max() > 64
+    assert np.abs(mu0 - mu1).max() <= 1e-10
+    assert float((z0 - z1).norm()) <= 1e-10 * float(z0.norm())
