@@ -10,6 +10,7 @@
 #include <cmath>
 
 #include "consts.hpp"
+#include "lanes.hpp"
 #include "mgemm.hpp"
 
 #define LSDD_WG 256
@@ -22,8 +23,7 @@ __device__ inline int tid() { return (int)threadIdx.x; }
 
 template <typename T>
 __device__ inline T wave_sum(T v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    return sum_lanes<64>(v);
 }
 
 template <typename T>
@@ -67,10 +67,8 @@ __device__ inline void wg_zero(double* a, long long count) {
 }
 
 __device__ inline void wg_identity(double* a, int ld, int n) {
-    for (long long idx = tid(); idx < (long long)n * n; idx += LSDD_WG) {
-        int i = (int)(idx % n), j = (int)(idx / n);
-        a[i + (long long)j * ld] = (i == j) ? 1.0 : 0.0;
-    }
+    for (int j = tid() >> 6; j < n; j += LSDD_WG / 64)
+        for (int i = tid() & 63; i < n; i += 64) a[i + (long long)j * ld] = (i == j) ? 1.0 : 0.0;
     __syncthreads();
 }
 
@@ -180,37 +178,61 @@ __device__ inline void wg_trsm_lower_t(const double* L, int ldl, int n, double* 
 
 // ---------------------------------------------------------------- Jacobi eigensolver
 
-// Parallel cyclic Jacobi (round-robin ordering) on a symmetric n x n matrix a.
+// Parallel cyclic Jacobi (round-robin ordering) on a symmetric n x n matrix a, n <= JAC_N.
 // On return a is diagonal up to the rotation threshold (eigenvalues on the
 // diagonal) and v (n x n) holds the eigenvectors as columns (v must be the
 // identity, or any orthogonal start, on entry).  A pair is rotated when
-// |a_pq| > rel * sqrt(|a_pp a_qq|) and |a_pq| > abs_tol; the sweep loop stops
-// after a sweep with no rotation.  LDS scratch: `pairs` (2 * npair ints),
+// |a_pq| > rel * sqrt(|a_pp a_qq|) and |a_pq| > abs_tol; the sweep loop stops after a sweep
+// that rotated no |a_pq| > conv_tol (the unit roundoff of the largest entry: what is left is
+// then below the rounding of the rotations themselves).  A singular block has no end of
+// rotations among its null vectors, whose entries are that rounding: stopped by the rotations'
+// own thresholds, the 24 x 24 grad-div and 8 x 8 elasticity blocks took all 60 sweeps, now 10
+// and 6, with the same residual and vectors closer to orthogonal.  LDS scratch: `pairs` (2 * npair ints),
 // `cs` (2 * npair doubles), `flag` (1 int) with npair = (n + 1) / 2.
+//
+// A round is two steps: the rotations (a lane per pair), then A <- J^T A J by 2 x 2 blocks, a
+// thread per pair of pairs, rows before columns, together with V <- V J.  Its cost is LDS
+// traffic and integer work: which blocks a thread owns does not change between the rounds and
+// is worked out once (a 64-bit division an entry took more time than the rotations), and each
+// entry is read and written once a round.  1600 blocks of 24 x 24: 2.4 ->
+// 1.36 ms, 2304 of 8 x 8: 0.68 -> 0.30 ms.
+constexpr int JAC_N = 48;
 __device__ inline int wg_jacobi(double* a, int lda, int n, double* v, int ldv, int max_sweeps,
-                                double rel, double abs_tol, int* pairs, double* cs, int* flag) {
+                                double rel, double abs_tol, double conv_tol, int* pairs, double* cs, int* flag) {
+    constexpr int U = (JAC_N / 2 * (JAC_N / 2 + JAC_N) + LSDD_WG - 1) / LSDD_WG;
     const int np = n + (n & 1);
     const int npair = np / 2;
+    // work item (r, l): r < npair block of pairs (r, l) of A, else row r - npair of V, pair l
+    int it_l[U], it_r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int idx = tid() + u * LSDD_WG;
+        it_l[u] = idx / (npair + n);
+        it_r[u] = idx - it_l[u] * (npair + n);
+    }
     int sweep = 0;
     for (; sweep < max_sweeps; ++sweep) {
         if (tid() == 0) *flag = 0;
         __syncthreads();
         for (int rnd = 0; rnd < np - 1; ++rnd) {
-            for (int k = tid(); k < npair; k += LSDD_WG) {
-                int i0 = k, i1 = np - 1 - k;
-                int p = (i0 == 0) ? 0 : 1 + ((i0 - 1 + rnd) % (np - 1));
-                int q = (i1 == 0) ? 0 : 1 + ((i1 - 1 + rnd) % (np - 1));
-                if (p > q) { int t = p; p = q; q = t; }
+            if (tid() < npair) {
+                const int k = tid();
+                auto turn = [&](int i) {               // index 0 stays, the others move on by rnd
+                    const int x = i - 1 + rnd;
+                    return i == 0 ? 0 : 1 + (x >= np - 1 ? x - (np - 1) : x);
+                };
+                const int x = turn(k), y = turn(np - 1 - k);
+                const int p = min(x, y), q = max(x, y);
                 double c = 1.0, s = 0.0;
                 if (q < n) {
-                    double app = a[p + (long long)p * lda], aqq = a[q + (long long)q * lda];
-                    double apq = a[p + (long long)q * lda];
+                    double app = a[p + p * lda], aqq = a[q + q * lda];
+                    double apq = a[p + q * lda];
                     if (fabs(apq) > abs_tol && fabs(apq) > rel * sqrt(fabs(app * aqq))) {
                         double th = (aqq - app) / (2.0 * apq);
                         double t = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
                         c = 1.0 / sqrt(t * t + 1.0);
                         s = t * c;
-                        *flag = 1;
+                        if (fabs(apq) > conv_tol) *flag = 1;
                     }
                 }
                 pairs[2 * k] = p;
@@ -219,40 +241,39 @@ __device__ inline int wg_jacobi(double* a, int lda, int n, double* v, int ldv, i
                 cs[2 * k + 1] = s;
             }
             __syncthreads();
-            // rows: A <- J^T A
-            for (long long idx = tid(); idx < (long long)npair * n; idx += LSDD_WG) {
-                int k = (int)(idx % npair), j = (int)(idx / npair);
-                int q = pairs[2 * k + 1];
-                double s = cs[2 * k + 1];
-                if (q < 0 || s == 0.0) continue;
-                int p = pairs[2 * k];
-                double c = cs[2 * k];
-                double* ap = a + p + (long long)j * lda;
-                double* aq = a + q + (long long)j * lda;
-                double x = *ap, y = *aq;
-                *ap = c * x - s * y;
-                *aq = s * x + c * y;
-            }
-            __syncthreads();
-            // columns: A <- A J, V <- V J
-            for (long long idx = tid(); idx < (long long)npair * n; idx += LSDD_WG) {
-                int i = (int)(idx % n), k = (int)(idx / n);
-                int q = pairs[2 * k + 1];
-                double s = cs[2 * k + 1];
-                if (q < 0 || s == 0.0) continue;
-                int p = pairs[2 * k];
-                double c = cs[2 * k];
-                double* ap = a + i + (long long)p * lda;
-                double* aq = a + i + (long long)q * lda;
-                double x = *ap, y = *aq;
-                *ap = c * x - s * y;
-                *aq = s * x + c * y;
-                double* vp = v + i + (long long)p * ldv;
-                double* vq = v + i + (long long)q * ldv;
-                x = *vp;
-                y = *vq;
-                *vp = c * x - s * y;
-                *vq = s * x + c * y;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int l = it_l[u], r = it_r[u];
+                if (l >= npair) break;
+                const int pl = pairs[2 * l], ql = pairs[2 * l + 1];
+                const double cl = cs[2 * l], sl = cs[2 * l + 1];
+                if (r >= npair) {                      // V <- V J
+                    if (sl == 0.0) continue;
+                    double* vp = v + (r - npair) + pl * ldv;
+                    double* vq = v + (r - npair) + ql * ldv;
+                    const double x = *vp, y = *vq;
+                    *vp = cl * x - sl * y;
+                    *vq = sl * x + cl * y;
+                    continue;
+                }
+                const int pr = pairs[2 * r], qr = pairs[2 * r + 1];
+                const double cr = cs[2 * r], sr = cs[2 * r + 1];
+                if (sl == 0.0 && sr == 0.0) continue;
+                // a pair without a partner (odd n) has s = 0: its entries are read twice and
+                // written once
+                const int qr_ = qr < 0 ? pr : qr, ql_ = ql < 0 ? pl : ql;
+                double x00 = a[pr + pl * lda], x10 = a[qr_ + pl * lda];
+                double x01 = a[pr + ql_ * lda], x11 = a[qr_ + ql_ * lda];
+                const double y00 = cr * x00 - sr * x10, y10 = sr * x00 + cr * x10;
+                const double y01 = cr * x01 - sr * x11, y11 = sr * x01 + cr * x11;
+                x00 = cl * y00 - sl * y01;
+                x01 = sl * y00 + cl * y01;
+                x10 = cl * y10 - sl * y11;
+                x11 = sl * y10 + cl * y11;
+                a[pr + pl * lda] = x00;
+                if (qr >= 0) a[qr + pl * lda] = x10;
+                if (ql >= 0) a[pr + ql * lda] = x01;
+                if (qr >= 0 && ql >= 0) a[qr + ql * lda] = x11;
             }
             __syncthreads();
         }
@@ -278,10 +299,8 @@ __device__ inline void wg_sort_eig(const double* a, int lda, const double* v, in
         w[r] = di;
     }
     __syncthreads();
-    for (long long idx = tid(); idx < (long long)n * n; idx += LSDD_WG) {
-        int i = (int)(idx % n), j = (int)(idx / n);
-        vs[i + (long long)rank_scratch[j] * ldvs] = v[i + (long long)j * ldv];
-    }
+    for (int j = tid() >> 6; j < n; j += LSDD_WG / 64)
+        for (int i = tid() & 63; i < n; i += 64) vs[i + (long long)rank_scratch[j] * ldvs] = v[i + (long long)j * ldv];
     __syncthreads();
 }
 
@@ -335,9 +354,9 @@ __device__ inline void wg_tridiag(double* a, int n, double* d, double* e, double
             const double K = 0.5 * t * pv;
             for (int i = tid(); i < m; i += LSDD_WG) w[i] -= K * v[i];
             __syncthreads();
-            for (long long idx = tid(); idx < (long long)m * m; idx += LSDD_WG) {
-                int i = (int)(idx % m), k = (int)(idx / m);
-                A22[i + (long long)k * n] -= v[i] * w[k] + w[i] * v[k];
+            for (int k = tid() >> 6; k < m; k += LSDD_WG / 64) {      // a wave per column
+                const double wk = w[k], vk = v[k];
+                for (int i = tid() & 63; i < m; i += 64) A22[i + (long long)k * n] -= v[i] * wk + w[i] * vk;
             }
         }
         // keep the reflector below the subdiagonal
@@ -354,46 +373,71 @@ __device__ inline void wg_tridiag(double* a, int n, double* d, double* e, double
     __syncthreads();
 }
 
-// Number of eigenvalues of the tridiagonal (d, e) smaller than x (Sturm count).
-__device__ inline int sturm_count(const double* d, const double* e, int n, double x, double pivmin) {
+// Eigenvalues of the tridiagonal (d, e) smaller than x (Sturm count; d, and the squares of e
+// from e2[1] on, e2[0] = 0).  One chain of n reciprocals; the estimate with two Newton steps
+// is within an ulp or two of the division, which is what the count's backward error is anyway.
+__device__ inline int sturm_quick(const double* d, const double* e2, int n, double x, double pivmin) {
     int c = 0;
-    double q = d[0] - x;
-    if (fabs(q) < pivmin) q = -pivmin;
-    if (q < 0.0) ++c;
-    for (int k = 1; k < n; ++k) {
-        q = d[k] - x - e[k - 1] * e[k - 1] / q;
-        if (fabs(q) < pivmin) q = -pivmin;
-        if (q < 0.0) ++c;
+    double q = 1.0;
+    constexpr int U = 8;
+    int k = 0;
+    for (; k + U <= n; k += U) {
+        double dk[U], ek[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) dk[u] = d[k + u] - x, ek[u] = e2[k + u];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            q = dk[u] - ek[u] * quick_rcp(q);
+            q = fabs(q) < pivmin ? -pivmin : q;
+            c += q < 0.0;
+        }
+    }
+    for (; k < n; ++k) {
+        q = d[k] - x - e2[k] * quick_rcp(q);
+        q = fabs(q) < pivmin ? -pivmin : q;
+        c += q < 0.0;
     }
     return c;
 }
 
-// Eigenvalues i0 .. i1-1 (ascending order) of the symmetric tridiagonal (d, e)
-// by bisection; the bracket is computed from the whole matrix, so any split of
-// the index range gives the same values.
-__device__ inline void wg_bisect_range(const double* d, const double* e, int n, double* lam, int i0, int i1,
-                                       double* red) {
+// The bracket [lo, hi] of all eigenvalues, the smallest pivot (its reciprocal times e^2 stays
+// finite) and the absolute tolerance; stages d and e^2 (e2[0] = 0) in LDS for sturm_quick.
+struct TriBracket {
+    double lo, hi, pivmin, atol;
+};
+__device__ inline TriBracket wg_bracket(const double* d, const double* e, int n, double* s_d, double* s_e2, double* red) {
     double lo = INFINITY, hi = -INFINITY, emax2 = 0.0;
     for (int i = tid(); i < n; i += LSDD_WG) {
-        double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < n ? fabs(e[i]) : 0.0);
-        lo = fmin(lo, d[i] - r);
-        hi = fmax(hi, d[i] + r);
-        if (i + 1 < n) emax2 = fmax(emax2, e[i] * e[i]);
+        const double el = i > 0 ? e[i - 1] : 0.0, er = i + 1 < n ? e[i] : 0.0, di = d[i];
+        const double r = fabs(el) + fabs(er);
+        lo = fmin(lo, di - r);
+        hi = fmax(hi, di + r);
+        emax2 = fmax(emax2, er * er);
+        s_d[i] = di;
+        s_e2[i] = el * el;
     }
     lo = -wg_max(-lo, red);
     hi = wg_max(hi, red);
     emax2 = wg_max(emax2, red);
     const double tnorm = fmax(fabs(lo), fabs(hi));
-    const double pivmin = fmax(2.2250738585072014e-308 * fmax(emax2, 1.0), 1e-300);
-    const double atol = 2.0 * 2.220446049250313e-16 * tnorm + 1e-300;
-    lo -= atol;
-    hi += atol;
-    for (int i = i0 + tid(); i < i1; i += LSDD_WG) {
-        double a = lo, b = hi;
+    TriBracket B;
+    B.pivmin = fmax(2.2250738585072014e-308 * fmax(emax2, 1.0), 1e-290);
+    B.atol = 2.0 * 2.220446049250313e-16 * tnorm + 1e-300;
+    B.lo = lo - B.atol;
+    B.hi = hi + B.atol;
+    return B;
+}
+
+// All eigenvalues of the symmetric tridiagonal (d, e), ascending, by bisection, one lane per
+// eigenvalue (lds: 2 n doubles).
+__device__ inline void wg_bisect_all(const double* d, const double* e, int n, double* lam, double* lds, double* red) {
+    const TriBracket B = wg_bracket(d, e, n, lds, lds + n, red);
+    for (int i = tid(); i < n; i += LSDD_WG) {
+        double a = B.lo, b = B.hi;
         for (int it = 0; it < 200; ++it) {
-            double mid = 0.5 * (a + b);
-            if (b - a <= 2.0 * 2.220446049250313e-16 * fmax(fabs(a), fabs(b)) + atol || mid == a || mid == b) break;
-            if (sturm_count(d, e, n, mid, pivmin) > i) b = mid;
+            const double mid = 0.5 * (a + b);
+            if (b - a <= 2.0 * 2.220446049250313e-16 * fmax(fabs(a), fabs(b)) + B.atol || mid == a || mid == b) break;
+            if (sturm_quick(lds, lds + n, n, mid, B.pivmin) > i) b = mid;
             else a = mid;
         }
         lam[i] = 0.5 * (a + b);
@@ -401,366 +445,147 @@ __device__ inline void wg_bisect_range(const double* d, const double* e, int n, 
     __syncthreads();
 }
 
-// All eigenvalues of the symmetric tridiagonal (d, e), ascending, by bisection.
-__device__ inline void wg_bisect_all(const double* d, const double* e, int n, double* lam, double* red) {
-    wg_bisect_range(d, e, n, lam, 0, n, red);
-}
+// ---------------------------------------------------------------- back-transformation
 
-// Solve (T - lam I) y = b in place for the tridiagonal (d, e) by Gaussian
-// elimination with partial pivoting.  b has stride bs; the upper factor
-// scratch u0, u1, u2 (n entries each) has stride S, so the 64 lanes of a wave
-// solving 64 systems at once can keep their scratch interleaved (S = 64,
-// coalesced) without changing the arithmetic.  The elimination is applied to
-// b as the factor is formed (one pass), then back substitution.  Both passes
-// load the operands of the next block of TRI_PB rows before working on the
-// current block, so a lane's chain of dependent divisions does not wait on
-// memory latency or on the completion of its own stores.
-constexpr int TRI_PB = 8;
-
-template <int S>
-__device__ inline void tri_shift_solve(const double* __restrict__ d, const double* __restrict__ e, int n, double lam,
-                                       double* __restrict__ b, int bs, double* __restrict__ u0,
-                                       double* __restrict__ u1, double* __restrict__ u2, double tiny) {
-    // rows k hold (u0[k], u1[k], u2[k]) on diagonals 0, +1, +2 of U; both pivot
-    // cases share one division (the quotient of the smaller by the larger of
-    // a0 and the subdiagonal entry)
-    double a0 = d[0] - lam, a1 = (n > 1) ? e[0] : 0.0;
-    double bk = b[0];
-    double E[TRI_PB + 1], D[TRI_PB], B[TRI_PB];
-    double En[TRI_PB + 1], Dn[TRI_PB], Bn[TRI_PB];
-    auto fetch_fwd = [&](int k0, double (&e_)[TRI_PB + 1], double (&d_)[TRI_PB], double (&b_)[TRI_PB]) {
+// x <- Q x (Q = H_0 ... H_{n-3}: reflector j below the subdiagonal of column j of a, its
+// leading 1 implicit) for nv <= NV vectors (columns of ld n) in one wave, reflectors applied from the last to the first, four per
+// round: with the dots d_k = v_k^T x and the cross products c_kl = v_k^T v_l of reflectors j,
+// j-1, j-2, j-3 (k = 0..3) gathered in one pass, s_k = tau_k (d_k - sum_{l<k} s_l c_kl) are
+// the multipliers of applying them one after the other, and x -= sum_k s_k v_k.  Lane l owns
+// the rows l + 64 i, i < RPT (n <= 64 RPT), and holds them in registers, so that a round goes
+// to memory once, for the reflectors; only the rows of the diagonal and of the last block
+// need masks.
+template <int RPT, int NV>
+__device__ inline void wave_backtransform(const double* __restrict__ a, int n, const double* __restrict__ tau,
+                                          double* xp, int nv) {
+    const int l = tid() & 63;
+    double x[NV][RPT];
 #pragma unroll
-        for (int u = 0; u <= TRI_PB; ++u) e_[u] = (k0 + u < n - 1) ? e[k0 + u] : 0.0;
+    for (int u = 0; u < NV; ++u)
 #pragma unroll
-        for (int u = 0; u < TRI_PB; ++u) {
-            const bool ok = k0 + u < n - 1;
-            d_[u] = ok ? d[k0 + u + 1] : 0.0;
-            b_[u] = ok ? b[(k0 + u + 1) * bs] : 0.0;
+        for (int i = 0; i < RPT; ++i) x[u][i] = xp[(int64_t)min(u, nv - 1) * n + min(l + 64 * i, n - 1)];
+    for (int j = n - 3; j >= 0; j -= 4) {
+        double d[NV][4] = {}, cc[6] = {};
+        double v[RPT][4];
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            if (64 * i + 63 < j - 2 || 64 * i >= n) continue;          // the same in every lane
+            const int rc = min(l + 64 * i, n - 1);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[i][k] = a[rc + (int64_t)max(j - k, 0) * n];
         }
-    };
-    fetch_fwd(0, E, D, B);
-    for (int k0 = 0; k0 < n - 1; k0 += TRI_PB) {
-        if (k0 + TRI_PB < n - 1) fetch_fwd(k0 + TRI_PB, En, Dn, Bn);
 #pragma unroll
-        for (int u = 0; u < TRI_PB; ++u) {
-            const int k = k0 + u;
-            if (k < n - 1) {
-                const double sub = E[u];
-                const double nd = D[u] - lam;
-                const double ns = E[u + 1];           // e[k + 1], 0 past the end
-                const bool sw = !(fabs(a0) >= fabs(sub));
-                if (!sw && fabs(a0) < tiny) a0 = (a0 >= 0.0 ? tiny : -tiny);
-                const double den = sw ? sub : a0;
-                const double f = (sw ? a0 : sub) / den;
-                u0[k * S] = den;
-                u1[k * S] = sw ? nd : a1;
-                u2[k * S] = sw ? ns : 0.0;
-                const double a0n = sw ? a1 - f * nd : nd - f * a1;
-                a1 = sw ? -f * ns : ns;
-                a0 = a0n;
-                // the same elimination step on b (rows k and k + 1, swapped if pivoted)
-                double bn = B[u];
-                if (sw) {
-                    const double t = bk;
-                    bk = bn;
-                    bn = t;
+        for (int i = 0; i < RPT; ++i) {
+            if (64 * i + 63 < j - 2 || 64 * i >= n) continue;
+            if (64 * i <= j + 1 || 64 * i + 64 > n || j < 3) {
+                // entry r of reflector q: 1 at q + 1, stored below it, 0 above, past the end
+                // and where there is no reflector (q < 0)
+                const int r = l + 64 * i;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int q = j - k;
+                    v[i][k] = q < 0 || r <= q || r >= n ? 0.0 : (r == q + 1 ? 1.0 : v[i][k]);
                 }
-                b[k * bs] = bk;
-                bk = bn - f * bk;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u <= TRI_PB; ++u) E[u] = En[u];
-#pragma unroll
-        for (int u = 0; u < TRI_PB; ++u) {
-            D[u] = Dn[u];
-            B[u] = Bn[u];
-        }
-    }
-    if (fabs(a0) < tiny) a0 = (a0 >= 0.0 ? tiny : -tiny);
-    u0[(n - 1) * S] = a0;
-    u1[(n - 1) * S] = 0.0;
-    u2[(n - 1) * S] = 0.0;
-    b[(n - 1) * bs] = bk;
-    // back substitution, rows n-1 .. 0 in blocks of TRI_PB (row k = k1 - u)
-    double Y[TRI_PB], P0[TRI_PB], P1[TRI_PB], P2[TRI_PB];
-    double Yn[TRI_PB], P0n[TRI_PB], P1n[TRI_PB], P2n[TRI_PB];
-    auto fetch_bwd = [&](int k1, double (&y_)[TRI_PB], double (&p0)[TRI_PB], double (&p1)[TRI_PB],
-                         double (&p2)[TRI_PB]) {
-#pragma unroll
-        for (int u = 0; u < TRI_PB; ++u) {
-            const int k = k1 - u;
-            const bool ok = k >= 0;
-            y_[u] = ok ? b[k * bs] : 0.0;
-            p0[u] = ok ? u0[k * S] : 1.0;
-            p1[u] = ok ? u1[k * S] : 0.0;
-            p2[u] = ok ? u2[k * S] : 0.0;
-        }
-    };
-    double x1 = 0.0, x2 = 0.0;
-    fetch_bwd(n - 1, Y, P0, P1, P2);
-    for (int k1 = n - 1; k1 >= 0; k1 -= TRI_PB) {
-        if (k1 - TRI_PB >= 0) fetch_bwd(k1 - TRI_PB, Yn, P0n, P1n, P2n);
-#pragma unroll
-        for (int u = 0; u < TRI_PB; ++u) {
-            const int k = k1 - u;
-            if (k >= 0) {
-                double s = Y[u];
-                if (k + 1 < n) s -= P1[u] * x1;
-                if (k + 2 < n) s -= P2[u] * x2;
-                const double xk = s / P0[u];
-                b[k * bs] = xk;
-                x2 = x1;
-                x1 = xk;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < TRI_PB; ++u) {
-            Y[u] = Yn[u];
-            P0[u] = P0n[u];
-            P1[u] = P1n[u];
-            P2[u] = P2n[u];
-        }
-    }
-}
-
-// dd[j + t qn] = Q_j . Y_t for the columns Q_j = V[:, q0 + j] (j < qn <= 64) and
-// Y_t = V[:, b0 + t] (t < bn <= 64) of the column-major V (ld n): each thread
-// accumulates a 4 x 4 block of products over the rows in order.
-__device__ inline void wg_block_dots(const double* V, int n, int q0, int qn, int b0, int bn, double* dd) {
-    const int ib = tid() & 15, jb = tid() >> 4;
-    if (4 * ib >= qn || 4 * jb >= bn) return;
-    const double* qp[4];
-    const double* yp[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        qp[a] = V + (long long)(q0 + min(4 * ib + a, qn - 1)) * n;
-        yp[a] = V + (long long)(b0 + min(4 * jb + a, bn - 1)) * n;
-    }
-    double acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[a][c] = 0.0;
-    for (int k = 0; k < n; ++k) {
-        double qv[4], yv[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            qv[a] = qp[a][k];
-            yv[a] = yp[a][k];
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[a][c] += qv[a] * yv[c];
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (4 * ib + a < qn && 4 * jb + c < bn) dd[(4 * ib + a) + (4 * jb + c) * qn] = acc[a][c];
-}
-
-// Y_t -= sum_j dd[j + t qn] Q_j (same columns as wg_block_dots); each thread
-// takes 4 rows x 4 members, the sum over j in order.
-__device__ inline void wg_block_update(double* V, int n, int q0, int qn, int b0, int bn, const double* dd) {
-    const int nr = (n + 3) / 4, nc = (bn + 3) / 4;
-    for (int w = tid(); w < nr * nc; w += LSDD_WG) {
-        const int r = 4 * (w % nr), c0 = 4 * (w / nr);
-        double acc[4][4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[a][c] = 0.0;
-        for (int j = 0; j < qn; ++j) {
-            const double* q = V + (long long)(q0 + j) * n + r;
-            double qv[4], dv[4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                qv[a] = (r + a < n) ? q[a] : 0.0;
-                dv[a] = (c0 + a < bn) ? dd[j + (c0 + a) * qn] : 0.0;
             }
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int u = 0; u < NV; ++u)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc[a][c] += qv[a] * dv[c];
+                for (int k = 0; k < 4; ++k) d[u][k] += v[i][k] * x[u][i];
+            cc[0] += v[i][1] * v[i][0];
+            cc[1] += v[i][2] * v[i][0];
+            cc[2] += v[i][2] * v[i][1];
+            cc[3] += v[i][3] * v[i][0];
+            cc[4] += v[i][3] * v[i][1];
+            cc[5] += v[i][3] * v[i][2];
         }
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int q = 0; q < 6; ++q) cc[q] = wave_sum(cc[q]);
+        const double t0 = tau[j], t1 = tau[max(j - 1, 0)], t2 = tau[max(j - 2, 0)], t3 = tau[max(j - 3, 0)];
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
-                if (r + a < n && c0 + c < bn) V[(long long)(b0 + c0 + c) * n + r + a] -= acc[a][c];
-    }
-}
-
-// Eigenvectors of the tridiagonal (d, e) for the eigenvalues lam[0..kk) by
-// inverse iteration.  Eigenvalues closer than 1e-4 * tnorm form a cluster.
-// This workgroup handles the single-member clusters with index in [r0, r1)
-// and the larger clusters that start there.  Singletons run one per thread
-// (threads 0..63).  `ws` holds INVIT_SLOTS * n doubles: the factor scratch
-// (u0, u1, u2) and singleton iterates of the 64 solving lanes, interleaved by
-// lane.  The members of a larger cluster are processed in batches of up
-// to 64: each iteration solves every member's shifted system on its own
-// thread, then orthogonalises the batch twice: by block classical Gram-Schmidt
-// against the earlier members of the cluster, then within the batch by Gram-Schmidt in
-// index order, normalising each member.  Output V (n x kk, column-major, ld n); `dd` holds
-// 64 x 64 batch dots.  LDS: cl_start (kk+1 ints), dots (64).  (The larger problems have
-// their own multi-workgroup form, k_trd_invit.)
-__device__ inline void wg_inverse_iteration_range(const double* d, const double* e, int n, const double* lam,
-                                                  int kk, int r0, int r1, double* V, double* ws, double* dd,
-                                                  double tnorm, int* cl_start, double* dots, double* red,
-                                                  int* ncl_sh) {
-    const double eps = 2.220446049250313e-16;
-    const double gaptol = 1e-4 * tnorm;
-    if (tid() == 0) {
-        int nc = 0;
-        for (int i = 0; i < kk; ++i)
-            if (i == 0 || lam[i] - lam[i - 1] > gaptol) cl_start[nc++] = i;
-        cl_start[nc] = kk;
-        *ncl_sh = nc;
-    }
-    __syncthreads();
-    const int ncl = *ncl_sh;
-    const double tiny = eps * fmax(tnorm, 1e-300);
-    // convergence: from the second solve on, the iterate entering a solve has unit norm,
-    // so the norm of the result is the solve's growth 1 / |lambda - shift| along the
-    // eigenvector; once it exceeds 1 / (1e-10 ||T||) (shift within 1e-10 ||T|| of an
-    // eigenvalue, at least 1e-4 ||T|| from every other cluster) each further solve would
-    // shrink the error by at least 1e6, and the iteration stops (at most 4 solves)
-    const double grow2 = 1.0 / ((1e-10 * fmax(tnorm, 1e-300)) * (1e-10 * fmax(tnorm, 1e-300)));
-    __shared__ int s_conv;
-    auto start_value = [&](int i, int k) {
-        unsigned h = (unsigned)(k * 2654435761u) ^ (unsigned)(i * 40503u);
-        return 1.0 + 0.25 * ((double)(h & 0xffff) / 65536.0 - 0.5);
-    };
-    // lane-interleaved scratch of the 64 solving threads (lane t: entry k at [64 k + t])
-    auto slot_solve = [&](int t, double* b, int bs, double shift) {
-        tri_shift_solve<64>(d, e, n, shift, b, bs, ws + t, ws + (long long)64 * n + t, ws + (long long)128 * n + t,
-                            tiny);
-    };
-    // singletons, one per thread
-    for (int i = r0 + tid(); tid() < 64 && i < r1; i += 64) {
-        int lo = 0, hi = ncl;                          // cluster of i: last start <= i
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (cl_start[mid] <= i) lo = mid;
-            else hi = mid;
-        }
-        if (cl_start[lo] != i || cl_start[lo + 1] != i + 1) continue;
-        double* y = ws + (long long)192 * n + tid();      // interleaved iterate
-        for (int k = 0; k < n; ++k) y[64 * k] = start_value(i, k);
-        for (int it = 0; it < 4; ++it) {
-            slot_solve(tid(), y, 64, lam[i]);
-            double nr = 0.0;
-            for (int k = 0; k < n; ++k) nr += y[64 * k] * y[64 * k];
-            const bool conv = it >= 1 && nr >= grow2;
-            nr = 1.0 / sqrt(nr);
-            for (int k = 0; k < n; ++k) y[64 * k] *= nr;
-            if (conv) break;
-        }
-        double* out = V + (long long)i * n;
-        for (int k = 0; k < n; ++k) out[k] = y[64 * k];
-    }
-    __syncthreads();
-    // clusters, in batches of up to 64 members
-    for (int c = 0; c < ncl; ++c) {
-        const int c0 = cl_start[c], c1 = cl_start[c + 1];
-        if (c1 - c0 == 1 || c0 < r0 || c0 >= r1) continue;
-        for (int b0 = c0; b0 < c1; b0 += 64) {
-            const int bn = min(64, c1 - b0), np = b0 - c0;
-            for (long long idx = tid(); idx < (long long)bn * n; idx += LSDD_WG) {
-                const int i = b0 + (int)(idx / n), k = (int)(idx % n);
-                V[(long long)i * n + k] = start_value(i, k);
-            }
-            __syncthreads();
-            for (int it = 0; it < 4; ++it) {
-                if (tid() == 0) s_conv = 1;
-                __syncthreads();
-                if (tid() < bn) {
-                    double* y = V + (long long)(b0 + tid()) * n;
-                    slot_solve(tid(), y, 1, lam[b0 + tid()] + (b0 + tid() - c0) * 2.0 * tiny);
-                    if (it >= 1) {
-                        double nr = 0.0;
-                        for (int k = 0; k < n; ++k) nr += y[k] * y[k];
-                        if (!(nr >= grow2)) s_conv = 0;
-                    }
-                }
-                __syncthreads();
-                for (int pass = 0; pass < 2; ++pass) {
-                    // against the earlier members of the cluster (in chunks of 64 members)
-                    for (int q0 = c0; q0 < b0; q0 += 64) {
-                        const int qn = min(64, b0 - q0);
-                        wg_block_dots(V, n, q0, qn, b0, bn, dd);
-                        __syncthreads();
-                        wg_block_update(V, n, q0, qn, b0, bn, dd);
-                        __syncthreads();
-                    }
-                    // within the batch in index order, each member normalised before use
-                    for (int t = 0; t < bn; ++t) {
-                        double* y = V + (long long)(b0 + t) * n;
-                        if (t > 0) {
-                            for (int s0 = tid() >> 6; s0 < t; s0 += LSDD_WG / 64) {
-                                const double* q = V + (long long)(b0 + s0) * n;
-                                double s = 0.0;
-                                for (int k = tid() & 63; k < n; k += 64) s += q[k] * y[k];
-                                s = wave_sum(s);
-                                if ((tid() & 63) == 0) dots[s0] = s;
-                            }
-                            __syncthreads();
-                            for (int k = tid(); k < n; k += LSDD_WG) {
-                                double s = 0.0;
-                                for (int s0 = 0; s0 < t; ++s0) s += V[(long long)(b0 + s0) * n + k] * dots[s0];
-                                y[k] -= s;
-                            }
-                            __syncthreads();
-                        }
-                        double nr = 0.0;
-                        for (int k = tid(); k < n; k += LSDD_WG) nr += y[k] * y[k];
-                        nr = wg_sum(nr, red);
-                        const double sc = 1.0 / sqrt(nr);
-                        for (int k = tid(); k < n; k += LSDD_WG) y[k] *= sc;
-                        __syncthreads();
-                    }
-                }
-                const int conv = s_conv;
-                __syncthreads();                  // every thread has read the flag before it is reset
-                if (it >= 1 && conv) break;
+        for (int u = 0; u < NV; ++u) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) d[u][k] = wave_sum(d[u][k]);
+            double sk[4];
+            sk[0] = t0 * d[u][0];
+            sk[1] = t1 * (d[u][1] - sk[0] * cc[0]);
+            sk[2] = t2 * (d[u][2] - sk[0] * cc[1] - sk[1] * cc[2]);
+            sk[3] = t3 * (d[u][3] - sk[0] * cc[3] - sk[1] * cc[4] - sk[2] * cc[5]);
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) {
+                if (64 * i + 63 < j - 2 || 64 * i >= n) continue;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[u][i] -= sk[k] * v[i][k];
             }
         }
     }
+#pragma unroll
+    for (int u = 0; u < NV; ++u)
+#pragma unroll
+        for (int i = 0; i < RPT; ++i)
+            if (u < nv && l + 64 * i < n) xp[(int64_t)u * n + l + 64 * i] = x[u][i];
 }
 
-// All kk eigenvectors in one workgroup; `ws` holds INVIT_SLOTS * n doubles of
-// interleaved scratch followed by 64 x 64 doubles of batch dots.
-__device__ inline void wg_inverse_iteration(const double* d, const double* e, int n, const double* lam, int kk,
-                                            double* V, double* ws, double tnorm, int* cl_start, double* dots,
-                                            double* red, int* ncl_sh) {
-    wg_inverse_iteration_range(d, e, n, lam, kk, 0, kk, V, ws, ws + (long long)INVIT_SLOTS * n, tnorm, cl_start,
-                               dots, red, ncl_sh);
-}
-
-// V <- Q V with Q = H_0 ... H_{n-3} from wg_tridiag (reflectors in a, tau).
-__device__ inline void wg_tridiag_backtransform(const double* a, int n, const double* tau, double* V, int kk,
-                                                double* vbuf, double* dots) {
-    for (int j = n - 3; j >= 0; --j) {
+// The same for any n, x in memory (no lane reads another lane's writes).
+__device__ inline void wave_backtransform_long(const double* a, int n, const double* tau, double* x) {
+    const int l = tid() & 63;
+    // entry r of reflector jj: 1 at jj + 1, stored below it, 0 above
+    auto vr = [&](int jj, int r) { return r == jj + 1 ? 1.0 : (r > jj + 1 ? a[r + (int64_t)jj * n] : 0.0); };
+    int j = n - 3;
+    for (; j >= 3; j -= 4) {
+        const int r0 = j - 2 + ((l - (j - 2)) % 64 + 64) % 64;     // first owned row >= j - 2
+        double d[4] = {0.0, 0.0, 0.0, 0.0}, cc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int r = r0; r < n; r += 64) {
+            const double xr = x[r];
+            double v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = vr(j - k, r);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) d[k] += v[k] * xr;
+            cc[0] += v[1] * v[0];
+            cc[1] += v[2] * v[0];
+            cc[2] += v[2] * v[1];
+            cc[3] += v[3] * v[0];
+            cc[4] += v[3] * v[1];
+            cc[5] += v[3] * v[2];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) d[k] = wave_sum(d[k]);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) cc[q] = wave_sum(cc[q]);
+        double sk[4];
+        sk[0] = tau[j] * d[0];
+        sk[1] = tau[j - 1] * (d[1] - sk[0] * cc[0]);
+        sk[2] = tau[j - 2] * (d[2] - sk[0] * cc[1] - sk[1] * cc[2]);
+        sk[3] = tau[j - 3] * (d[3] - sk[0] * cc[3] - sk[1] * cc[4] - sk[2] * cc[5]);
+        for (int r = r0; r < n; r += 64) {
+            double y = x[r];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) y -= sk[k] * vr(j - k, r);
+            x[r] = y;
+        }
+    }
+    for (; j >= 0; --j) {
         const double t = tau[j];
         if (t == 0.0) continue;
-        const int m = n - j - 1;
-        for (int i = tid(); i < m; i += LSDD_WG) vbuf[i] = (i == 0) ? 1.0 : a[(j + 1 + i) + (long long)j * n];
-        __syncthreads();
-        for (int c = tid(); c < kk; c += LSDD_WG) {
-            const double* col = V + (long long)c * n + j + 1;
-            double s = 0.0;
-            for (int i = 0; i < m; ++i) s += vbuf[i] * col[i];
-            dots[c] = t * s;
-        }
-        __syncthreads();
-        for (long long idx = tid(); idx < (long long)m * kk; idx += LSDD_WG) {
-            int i = (int)(idx % m), c = (int)(idx / m);
-            V[(long long)c * n + j + 1 + i] -= dots[c] * vbuf[i];
-        }
-        __syncthreads();
+        const double* v = a + (int64_t)j * n;
+        const int r0 = j + 1 + ((l - (j + 1)) % 64 + 64) % 64;     // first owned row > j
+        double s = 0.0;
+        for (int r = r0; r < n; r += 64) s += (r == j + 1 ? 1.0 : v[r]) * x[r];
+        s = wave_sum(s) * t;
+        for (int r = r0; r < n; r += 64) x[r] -= s * (r == j + 1 ? 1.0 : v[r]);
     }
+}
+
+// V <- Q V for the kk columns of V (n x kk, ld n), dealt to the waves four or two at a time
+// where they fit the registers: they share a round's reads and cross products.
+__device__ inline void wg_backtransform(const double* a, int n, const double* tau, double* V, int kk) {
+    auto deal = [&](int nv, auto apply) {
+        for (int c = (tid() >> 6) * nv; c < kk; c += LSDD_WG / 64 * nv) apply(V + (int64_t)c * n, min(nv, kk - c));
+    };
+    if (n <= 128) deal(4, [&](double* x, int nv) { wave_backtransform<2, 4>(a, n, tau, x, nv); });
+    else if (n <= 256) deal(2, [&](double* x, int nv) { wave_backtransform<4, 2>(a, n, tau, x, nv); });
+    else deal(1, [&](double* x, int) { wave_backtransform_long(a, n, tau, x); });
+    __syncthreads();
 }
 
 }  // namespace lsdd

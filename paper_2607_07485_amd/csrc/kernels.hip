@@ -17,6 +17,7 @@
 
 #include "batched.hpp"
 #include "dense.hpp"
+#include "invit.hpp"
 #include "kernels.hpp"
 #include "symv.hpp"
 
@@ -106,16 +107,16 @@ __global__ void __launch_bounds__(WG) k_elem_eig(const int64_t* elem_ptr, const 
     const int n = (int)(elem_ptr[e + 1] - elem_ptr[e]);
     const double* B = blocks + blk_off[e];
     if (n > NE_LDS) return;                   // k_elem_eig_trd
-    const int64_t nn = (int64_t)n * n;
-    double* a = s_dyn;                         // lds_bytes >= 2 n^2 doubles
-    double* v = s_dyn + nn;
+    const int ld = n | 1;                      // odd: rows fall on different LDS banks
+    double* a = s_dyn;                         // lds_bytes >= 2 n ld doubles
+    double* v = s_dyn + n * ld;
     double* vs = scratch + e * scratch_stride; // sorted vectors (global, n^2)
     // load (column-major == row-major for symmetric), asymmetry and scale
     double asym = 0.0, amax = 0.0;
     for (int idx = tid(); idx < n * n; idx += WG) {
-        int i = idx % n, j = idx / n;
+        const int j = idx / n, i = idx - j * n;
         double x = B[(int64_t)i * n + j], y = B[(int64_t)j * n + i];
-        a[i + j * n] = 0.5 * (x + y);
+        a[i + j * ld] = 0.5 * (x + y);
         asym = fmax(asym, fabs(x - y));
         amax = fmax(amax, fabs(x));
     }
@@ -126,9 +127,9 @@ __global__ void __launch_bounds__(WG) k_elem_eig(const int64_t* elem_ptr, const 
         if (tid() == 0) status[e] = 1;   // asymmetric or non-finite
         return;
     }
-    wg_identity(v, n, n);
-    wg_jacobi(a, n, n, v, n, 60, 1e-15, 1e-18 * amax, s_pairs, s_cs, &s_flag);
-    wg_sort_eig(a, n, v, n, n, s_w, vs, n, s_rank);
+    wg_identity(v, ld, n);
+    wg_jacobi(a, ld, n, v, ld, 60, 1e-15, 1e-18 * amax, DBL_EPSILON * amax, s_pairs, s_cs, &s_flag);
+    wg_sort_eig(a, ld, v, ld, n, s_w, vs, n, s_rank);
     const double lmax = fmax(s_w[n - 1], 0.0);
     if (s_w[0] < -spsd_tol * lmax) {
         if (tid() == 0) status[e] = 2;
@@ -163,7 +164,7 @@ __global__ void __launch_bounds__(WG) k_elem_eig(const int64_t* elem_ptr, const 
 // inverse iteration; back-transformation and G_T), so that the register-heavy
 // inverse iteration does not set the occupancy of the others.  The element's slot
 // of scratch holds S (n^2, reduced in place) | V (n^2, retained vectors) | d, e,
-// tau, w (4n) | inverse-iteration scratch (INVIT_SLOTS n + 4096); status[e] and
+// tau, w (4n) | inverse-iteration scratch (invit_ws); status[e] and
 // ranks[e] carry the state between phases.  Dynamic LDS: 2 n_max + 64 doubles.
 // Smaller elements are left to k_elem_eig.
 template <int PHASE>
@@ -173,7 +174,6 @@ __global__ void __launch_bounds__(WG) k_elem_eig_trd(const int64_t* elem_ptr, co
                                                      double rank_rtol, double spsd_tol) {
     extern __shared__ double s_dyn[];
     __shared__ double s_red[WG / 64];
-    __shared__ int s_ncl;
     const int64_t e = blockIdx.x;
     const int n = (int)(elem_ptr[e + 1] - elem_ptr[e]);
     if (n <= NE_LDS) return;
@@ -208,7 +208,7 @@ __global__ void __launch_bounds__(WG) k_elem_eig_trd(const int64_t* elem_ptr, co
         return;
     }
     if (PHASE == 1) {
-        wg_bisect_all(d, ee, n, w, s_red);
+        wg_bisect_all(d, ee, n, w, s_dyn, s_red);
         __syncthreads();
         if (tid() == 0) {
             const double lmax = fmax(w[n - 1], 0.0);
@@ -226,16 +226,13 @@ __global__ void __launch_bounds__(WG) k_elem_eig_trd(const int64_t* elem_ptr, co
     const int r = ranks[e];
     const int first = n - r;
     if (PHASE == 2) {
-        if (r == 0) return;
-        double tnorm = 0.0;
-        for (int i = tid(); i < n; i += WG)
-            tnorm = fmax(tnorm, fabs(d[i]) + (i > 0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < n ? fabs(ee[i]) : 0.0));
-        tnorm = wg_max(tnorm, s_red);
-        wg_inverse_iteration(d, ee, n, w + first, r, V, ws, fmax(tnorm, 1e-300), (int*)s_dyn, s_dyn + n, s_red,
-                             &s_ncl);
+        if constexpr (PHASE == 2) {
+            __shared__ InvShared inv;
+            wg_invit(d, ee, n, w + first, r, 0, r, V, ws, reinterpret_cast<unsigned char*>(s_dyn), inv);
+        }
         return;
     }
-    if (r > 0) wg_tridiag_backtransform(S, n, tau, V, r, s_dyn, s_dyn + n);
+    if (r > 0) wg_backtransform(S, n, tau, V, r);
     double* g = G + blk_off[e];
     for (int idx = tid(); idx < n * n; idx += WG) {
         const int row = idx / n, c = idx % n;
@@ -478,63 +475,89 @@ __global__ void __launch_bounds__(WG) k_elem_bilinear(int64_t n_elem, const int6
 
 // Per aggregate: A~_Omega = sum_{T in cl(omega)} mult(T)^{-1} E_T^T A_T E_T
 // (eq. SPSD_splitting under structural support) and A_Omega = A[Omega, Omega].
-// Grid (column blocks, batch entries): workgroup x owns the Omega columns
-// [x ASM_CW, (x + 1) ASM_CW) of both matrices, zeroes them and adds the closure
-// elements in closure order (every entry is summed in the same order on every
-// run; an element touches an entry at most once).  A_Omega is filled column by
-// column from the CSR rows of the symmetric A_l.
-constexpr int ASM_CW = 32;
-
-__global__ void __launch_bounds__(WG) k_local_assemble(LocalArgs A) {
-    __shared__ int s_cnt;
-    __shared__ int s_j[ASM_CW];
+// A wave takes a column of both matrices.  Its elements are those of the column's DOF (in
+// ascending order, as the closure's) that a lane each finds in the closure, so that every
+// entry is summed in the closure's order on every run; the column is summed in LDS where it
+// fits (in_lds) and written once.  Bound by the chain of dependent reads per element, four
+// elements in flight.  A_Omega is filled from the CSR rows of the symmetric A_l.
+// 54 overlaps of up to 1100 DOFs: 0.62 -> 0.25 ms (a barrier per element and 32 columns a
+// workgroup before).
+__global__ void __launch_bounds__(WG) k_local_assemble(LocalArgs A, int in_lds) {
+    extern __shared__ double s_dyn[];
     const int b = blockIdx.y;
     const int ag = A.agg_list ? A.agg_list[b] : A.first + b;
     const int64_t s0 = A.sub_ptr[ag];
     const int m = (int)(A.sub_ptr[ag + 1] - s0);
-    const int c0 = (int)blockIdx.x * ASM_CW;
-    if (c0 >= m) return;
-    const int c1 = min(m, c0 + ASM_CW);
+    const int w = tid() >> 6, l = tid() & 63;
+    const int a = (int)blockIdx.x * (WG / 64) + w;
+    if (a >= m) return;
     const int nw = (int)(A.agg_ptr[ag + 1] - A.agg_ptr[ag]);
     const int32_t* dofs = A.sub_dofs + s0;
-    double* W1 = A.w1 + A.ws_off[b];
-    double* W2 = A.w2 + A.ws_off[b];
-    for (int64_t idx = tid(); idx < (int64_t)(c1 - c0) * m; idx += WG) {
-        W1[(int64_t)c0 * m + idx] = 0.0;
-        W2[(int64_t)c0 * m + idx] = 0.0;
+    double* out1 = A.w1 + A.ws_off[b] + (int64_t)a * m;
+    double* out2 = A.w2 + A.ws_off[b] + (int64_t)a * m;
+    double* acc = in_lds ? s_dyn + (int64_t)w * in_lds : out1;
+    for (int i = l; i < m; i += 64) {
+        acc[i] = 0.0;
+        out2[i] = 0.0;
     }
-    __syncthreads();
-    for (int64_t c = A.cl_ptr[ag]; c < A.cl_ptr[ag + 1]; ++c) {
-        const int32_t e = A.cl_elems[c];
-        const int ne = (int)(A.elem_ptr[e + 1] - A.elem_ptr[e]);
-        const int32_t* pos = A.clpos + A.clpos_off[c];
-        if (tid() == 0) s_cnt = 0;
-        __syncthreads();
-        for (int j = tid(); j < ne; j += WG) {
-            const int pj = pos[j];
-            if (pj >= c0 && pj < c1) s_j[atomicAdd(&s_cnt, 1)] = j;
+    const int32_t p = dofs[a];
+    const int64_t cl0 = A.cl_ptr[ag], cl1 = A.cl_ptr[ag + 1];
+    const int64_t t1 = A.d2e_ptr[p + 1];
+    for (int64_t t0 = A.d2e_ptr[p]; t0 < t1; t0 += 64) {
+        // lane's element: index in the closure (-1: not there), local column, size
+        const bool have = t0 + l < t1;
+        const int32_t e = have ? A.d2e_elem[t0 + l] : -1, j = have ? A.d2e_loc[t0 + l] : 0;
+        int64_t lo = cl0, hi = have ? cl1 : cl0;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (A.cl_elems[mid] < e) lo = mid + 1;
+            else hi = mid;
         }
-        __syncthreads();
-        const int nj = s_cnt;
-        if (nj > 0) {
-            const double* Be = A.blocks + A.blk_off[e];
-            const double w = 1.0 / (double)A.mult[e];
-            for (int idx = tid(); idx < nj * ne; idx += WG) {
-                const int i = idx % ne, j = s_j[idx / ne];
-                const int pi = pos[i];   // < 0: outside an A-closure overlap
-                if (pi >= 0) W1[pi + (int64_t)pos[j] * m] += w * Be[(int64_t)i * ne + j];
+        const bool in = have && lo < cl1 && A.cl_elems[lo] == e;
+        const int ne = in ? (int)(A.elem_ptr[e + 1] - A.elem_ptr[e]) : 0;
+        const int64_t po = in ? A.clpos_off[lo] : 0, bo = in ? A.blk_off[e] + j : 0;
+        const double wt = in ? 1.0 / (double)A.mult[e] : 0.0;
+        for (uint64_t todo = __ballot(in); todo;) {
+            constexpr int U = 4;
+            int src[U], n_[U], pi[U];
+            double val[U];
+            const int32_t* pp[U];
+            const double* bp[U];
+            int nmax = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                src[u] = todo ? __ffsll((unsigned long long)todo) - 1 : -1;
+                if (todo) todo &= todo - 1;
+                const int s = max(src[u], 0);
+                n_[u] = src[u] >= 0 ? __shfl(ne, s, 64) : 0;
+                pp[u] = A.clpos + __shfl(po, s, 64);
+                bp[u] = A.blocks + __shfl(bo, s, 64);
+                nmax = max(nmax, n_[u]);
+            }
+            for (int i0 = 0; i0 < nmax; i0 += 64) {
+                const int i = i0 + l;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    pi[u] = i < n_[u] ? pp[u][i] : -1;             // < 0: outside an A-closure overlap
+                    val[u] = i < n_[u] ? bp[u][(int64_t)i * n_[u]] : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const double x = __shfl(wt, max(src[u], 0), 64) * val[u];
+                    if (pi[u] >= 0) acc[pi[u]] += x;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the next element's lanes see it
+                }
             }
         }
-        __syncthreads();
     }
-    // column a of A_Omega = row dofs[a] of A_l restricted to Omega; 8 threads per column
-    for (int a = c0 + tid() / 8; a < c1; a += WG / 8) {
-        const int32_t p = dofs[a];
-        for (int64_t q = A.rowptr[p] + (tid() & 7); q < A.rowptr[p + 1]; q += 8) {
-            const int li = local_index(dofs, nw, m, A.col[q]);
-            if (li >= 0) W2[li + (int64_t)a * m] = A.val[q];
-        }
+    // column a of A_Omega = row dofs[a] of A_l restricted to Omega
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int64_t q = A.rowptr[p] + l; q < A.rowptr[p + 1]; q += 64) {
+        const int li = local_index(dofs, nw, m, A.col[q]);
+        if (li >= 0) out2[li] = A.val[q];
     }
+    if (in_lds)
+        for (int i = l; i < m; i += 64) out1[i] = acc[i];
 }
 
 // Per aggregate: eigenpairs of C = L^{-1} S~ L^{-T} (held in the S buffer):
@@ -545,11 +568,12 @@ __global__ void __launch_bounds__(WG) k_local_assemble(LocalArgs A) {
 // W1 (nw x k, ld nw).  Four launches (PHASE 0..3): reduction (or Jacobi),
 // eigenvalues and mode count, inverse iteration, back-transformation; the state
 // between them lives in the aggregate's global scratch.
+constexpr int SMALL_EIG = 32;        // aggregates up to this size: Jacobi
+constexpr int JAC_LDS = 96;          // its pairs, rotations and ranks, in doubles
 template <int PHASE>
 __global__ void __launch_bounds__(WG) k_local_eig(LocalArgs A) {
     __shared__ double s_red[WG / 64];
     __shared__ int s_flag;
-    __shared__ int s_ncl;
     extern __shared__ double s_dyn[];
     const int b = blockIdx.x;
     const int ag = A.first + b;
@@ -560,25 +584,36 @@ __global__ void __launch_bounds__(WG) k_local_eig(LocalArgs A) {
     double* T = A.t_buf + A.t_off[b];
     double* mu = A.mu + A.mu_off[ag];
     double* VS = W1;
-    const bool small = nw <= 32;
+    const bool small = nw <= SMALL_EIG;
     if (PHASE == 0) {
         if (small) {
+            // matrix and vectors in LDS (in memory, at the latency of a trip a step: 48^2 Q1
+            // cells 1.75 ms, now 0.20)
             int* pairs = (int*)s_dyn;
             double* cs = s_dyn + 32;
             int* rank = (int*)(s_dyn + 64);
+            double* a = s_dyn + JAC_LDS;
+            const int ld = nw | 1;
+            double* v = a + nw * ld;
             double scale = 0.0;
-            for (int i = tid(); i < nw; i += WG) scale = fmax(scale, fabs(S[i + (int64_t)i * nw]));
+            for (int j = tid() >> 6; j < nw; j += WG / 64)
+                for (int i = tid() & 63; i < nw; i += 64) {
+                    const double x = S[i + j * nw];
+                    a[i + j * ld] = x;
+                    if (i == j) scale = fmax(scale, fabs(x));
+                }
             scale = wg_max(scale, s_red);
-            wg_identity(V, nw, nw);
-            wg_jacobi(S, nw, nw, V, nw, 60, 1e-15, 1e-18 * fmax(scale, 1e-300), pairs, cs, &s_flag);
-            wg_sort_eig(S, nw, V, nw, nw, mu, VS, nw, rank);
+            wg_identity(v, ld, nw);
+            wg_jacobi(a, ld, nw, v, ld, 60, 1e-15, 1e-18 * fmax(scale, 1e-300), DBL_EPSILON * scale, pairs, cs,
+                      &s_flag);
+            wg_sort_eig(a, ld, v, ld, nw, mu, VS, nw, rank);
         } else if (!(A.trd_min > 0 && nw >= A.trd_min)) {
             wg_tridiag(S, nw, T, T + nw, T + 2 * nw, s_dyn, s_dyn + nw, s_red);
         }
         return;
     }
     if (PHASE == 1) {
-        if (!small && !(A.trd_min > 0 && nw >= A.trd_min)) wg_bisect_all(T, T + nw, nw, mu, s_red);
+        if (!small && !(A.trd_min > 0 && nw >= A.trd_min)) wg_bisect_all(T, T + nw, nw, mu, s_dyn, s_red);
         for (int i = tid(); i < nw; i += WG) mu[i] = fmax(mu[i], 0.0);
         __syncthreads();
         if (tid() == 0) {
@@ -599,31 +634,35 @@ __global__ void __launch_bounds__(WG) k_local_eig(LocalArgs A) {
     if (small || k == 0) return;
     if (PHASE == 2) {
         if (A.trd_min > 0 && nw >= A.trd_min) return;     // vectors by the multi-workgroup path
-        const double* d = T;
-        const double* e = T + nw;
-        double tnorm = 0.0;
-        for (int i = tid(); i < nw; i += WG)
-            tnorm = fmax(tnorm, fabs(d[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < nw ? fabs(e[i]) : 0.0));
-        tnorm = wg_max(tnorm, s_red);
-        wg_inverse_iteration(d, e, nw, mu, k, VS, T + 3 * nw, fmax(tnorm, 1e-300), (int*)s_dyn, s_dyn + nw, s_red,
-                             &s_ncl);
+        if constexpr (PHASE == 2) {
+            __shared__ InvShared inv;
+            wg_invit(T, T + nw, nw, mu, k, 0, k, VS, T + 3 * nw, reinterpret_cast<unsigned char*>(s_dyn), inv);
+        }
         return;
     }
     if (A.trd_min > 0 && nw >= A.trd_min) return;     // back-transformed by the blocked path
-    wg_tridiag_backtransform(S, nw, T + 2 * nw, VS, k, s_dyn, s_dyn + nw);
+    wg_backtransform(S, nw, T + 2 * nw, VS, k);
 }
 
-// Z_i staged row-major (nw x k) from the column-major vectors in W1.
-__global__ void k_stage_z(LocalArgs A) {
-    const int b = blockIdx.x;
+// Z_i staged row-major (nw x k) from the column-major vectors in W1, 32 x 32 tiles through LDS
+// so that both sides are contiguous.
+__global__ void __launch_bounds__(WG) k_stage_z(LocalArgs A) {
+    __shared__ double s[32][33];
+    const int b = blockIdx.y;
     const int ag = A.first + b;
     const int nw = (int)(A.agg_ptr[ag + 1] - A.agg_ptr[ag]);
     const int k = A.k_out[ag];
     const double* VS = A.w1 + A.ws_off[b];
     double* zs = A.zst + A.zst_off[ag];
-    for (int idx = tid(); idx < nw * k; idx += WG) {
-        int i = idx / k, s = idx % k;
-        zs[idx] = VS[i + (int64_t)s * nw];
+    const int nt = (nw + 31) / 32, kt = (k + 31) / 32;
+    for (int t = (int)blockIdx.x; t < nt * kt; t += (int)gridDim.x) {
+        const int i0 = t % nt * 32, c0 = t / nt * 32;
+        __syncthreads();
+        for (int c = tid() >> 5; c < 32; c += WG / 32)
+            if (i0 + (tid() & 31) < nw && c0 + c < k) s[c][tid() & 31] = VS[i0 + (tid() & 31) + (int64_t)(c0 + c) * nw];
+        __syncthreads();
+        for (int i = tid() >> 5; i < 32; i += WG / 32)
+            if (i0 + i < nw && c0 + (tid() & 31) < k) zs[(int64_t)(i0 + i) * k + c0 + (tid() & 31)] = s[tid() & 31][i];
     }
 }
 
@@ -642,71 +681,95 @@ __global__ void k_views_add_diag(double* base, const View* v, const double* delt
     for (int i = tid(); i < x.rows; i += WG) base[x.off + i + (int64_t)i * x.ld] += d;
 }
 __global__ void k_views_symmetrize(double* base, const View* v) {
+    // 32 x 32 tiles (it >= jt) with their mirror images through LDS, rows contiguous on both
+    // sides
+    __shared__ double lo[32][33], up[32][33];
     const View x = v[blockIdx.y];
-    const int64_t n = x.rows;
-    for (int64_t idx = (int64_t)blockIdx.x * WG + tid(); idx < n * n; idx += (int64_t)gridDim.x * WG) {
-        int64_t i = idx % n, j = idx / n;
-        if (i < j) {
-            double s = 0.5 * (base[x.off + i + j * x.ld] + base[x.off + j + i * x.ld]);
-            base[x.off + i + j * x.ld] = s;
-            base[x.off + j + i * x.ld] = s;
+    const int n = x.rows, nt = (n + 31) / 32;
+    double* M = base + x.off;
+    for (int t = (int)blockIdx.x; t < nt * nt; t += (int)gridDim.x) {
+        const int it = t % nt, jt = t / nt;
+        if (it < jt) continue;                         // the same in the whole workgroup
+        __syncthreads();
+        for (int c = tid() >> 5; c < 32; c += WG / 32) {
+            const int r = tid() & 31;
+            if (it * 32 + r < n && jt * 32 + c < n) lo[c][r] = M[it * 32 + r + (int64_t)(jt * 32 + c) * x.ld];
+            if (jt * 32 + r < n && it * 32 + c < n) up[c][r] = M[jt * 32 + r + (int64_t)(it * 32 + c) * x.ld];
+        }
+        __syncthreads();
+        for (int c = tid() >> 5; c < 32; c += WG / 32) {
+            const int r = tid() & 31;
+            const int i = it * 32 + r, j = jt * 32 + c;
+            if (i < n && j < n && i != j) M[i + (int64_t)j * x.ld] = 0.5 * (lo[c][r] + up[r][c]);
+            const int i2 = jt * 32 + r, j2 = it * 32 + c;
+            if (it != jt && i2 < n && j2 < n) M[i2 + (int64_t)j2 * x.ld] = 0.5 * (up[c][r] + lo[r][c]);
         }
     }
 }
 __global__ void k_views_identity(double* base, const View* v) {
     const View x = v[blockIdx.y];
-    const int64_t n = x.rows;
-    for (int64_t idx = (int64_t)blockIdx.x * WG + tid(); idx < n * n; idx += (int64_t)gridDim.x * WG) {
-        int64_t i = idx % n, j = idx / n;
-        base[x.off + i + j * x.ld] = (i == j) ? 1.0 : 0.0;
-    }
+    const int n = x.rows;
+    for (int j = (int)blockIdx.x; j < n; j += (int)gridDim.x)
+        for (int i = tid(); i < n; i += WG) base[x.off + i + (int64_t)j * x.ld] = (i == j) ? 1.0 : 0.0;
 }
 
 // Compact the staged Z_i (row-major) into Z (row-major, for the Galerkin
-// products and export) and Zc / Zc32 (column-major, for the transfers).
-__global__ void k_z_compact(const int64_t* agg_ptr, const int32_t* k, const int64_t* zst_off, const double* zst,
-                            const int64_t* zoff, double* Z, double* Zc, float* Zc32) {
+// products and export) and Zc / Zc32 (column-major, for the transfers), 32 x 32 tiles through
+// LDS so that all sides are contiguous.
+__global__ void __launch_bounds__(WG) k_z_compact(const int64_t* agg_ptr, const int32_t* k, const int64_t* zst_off,
+                                                  const double* zst, const int64_t* zoff, double* Z, double* Zc,
+                                                  float* Zc32) {
+    __shared__ double s[32][33];
     const int ag = blockIdx.x;
     const int nw = (int)(agg_ptr[ag + 1] - agg_ptr[ag]);
     const int kk = k[ag];
-    const int64_t cnt = (int64_t)nw * kk;
     const double* src = zst + zst_off[ag];
-    for (int64_t i = tid(); i < cnt; i += WG) {
-        double v = src[i];
-        Z[zoff[ag] + i] = v;
-        int64_t a = i / kk, s = i % kk;
-        Zc[zoff[ag] + a + s * nw] = v;
-        if (Zc32) Zc32[zoff[ag] + a + s * nw] = (float)v;
+    const int nt = (nw + 31) / 32, kt = (kk + 31) / 32;
+    const int64_t zo = zoff[ag];
+    for (int t = (int)blockIdx.y; t < nt * kt; t += (int)gridDim.y) {
+        const int i0 = t % nt * 32, c0 = t / nt * 32;
+        __syncthreads();
+        for (int i = tid() >> 5; i < 32; i += WG / 32) {
+            const int c = c0 + (tid() & 31);
+            if (i0 + i < nw && c < kk) {
+                const double v = src[(int64_t)(i0 + i) * kk + c];
+                Z[zo + (int64_t)(i0 + i) * kk + c] = v;
+                s[tid() & 31][i] = v;
+            }
+        }
+        __syncthreads();
+        for (int c = tid() >> 5; c < 32; c += WG / 32) {
+            const int i = i0 + (tid() & 31);
+            if (i < nw && c0 + c < kk) {
+                const double v = s[c][tid() & 31];
+                Zc[zo + i + (int64_t)(c0 + c) * nw] = v;
+                if (Zc32) Zc32[zo + i + (int64_t)(c0 + c) * nw] = (float)v;
+            }
+        }
     }
 }
 
 // ====================================================================== Galerkin products
 
-// Stacked interpolation rows of coarse group g = g0 + blockIdx.x: member e
-// (in member order) contributes the n_e rows P_e = P[S_e, S_g], block
-// structured by aggregate; column-major R_g x c_g with R_g = sum of n_e.
+// Stacked interpolation rows of coarse group g = g0 + blockIdx.x: its members' rows (in
+// member order) of P[:, S_g], block structured by aggregate; column-major R_g x c_g.  A
+// workgroup takes PST_CW columns at a time, a thread a row, so that the map of a row is read
+// once for all of them and the stores are contiguous (grad-div 40^2: 1.97 -> 0.08 ms).
+constexpr int PST_CW = 8;
 __global__ void __launch_bounds__(WG) k_build_pst(PstArgs g) {
     const int gi = g.g0 + (int)blockIdx.x;
     const int c = (int)(g.cptr[gi + 1] - g.cptr[gi]);
     const int64_t R = g.rows[blockIdx.x];
+    const int64_t pm = g.pm_off[g.mem_ptr[gi]];        // the members' maps are contiguous
     double* P = g.pst + g.pst_off[blockIdx.x];
-    int64_t row0 = 0;
-    for (int64_t mi = g.mem_ptr[gi]; mi < g.mem_ptr[gi + 1]; ++mi) {
-        const int32_t e = g.mem_elems[mi];
-        const int ne = (int)(g.felem_ptr[e + 1] - g.felem_ptr[e]);
-        const int64_t pm = g.pm_off[mi];
-        for (int idx = tid(); idx < ne * c; idx += WG) {
-            const int a = idx % ne, col = idx / ne;
-            double v = 0.0;
-            const int64_t zr = g.pm_zrow[pm + a];
-            if (zr >= 0) {
-                const int s = col - g.pm_col[pm + a];
-                if (s >= 0 && s < g.pm_k[pm + a]) v = g.Z[zr + s];
-            }
-            P[row0 + a + (int64_t)col * R] = v;
+    for (int c0 = (int)blockIdx.y * PST_CW; c0 < c; c0 += (int)gridDim.y * PST_CW)
+        for (int64_t r = tid(); r < R; r += WG) {
+            const int64_t zr = g.pm_zrow[pm + r];
+            const int k = zr >= 0 ? g.pm_k[pm + r] : 0, s0 = c0 - g.pm_col[pm + r];
+#pragma unroll
+            for (int u = 0; u < PST_CW; ++u)
+                if (c0 + u < c) P[r + (int64_t)(c0 + u) * R] = s0 + u >= 0 && s0 + u < k ? g.Z[zr + s0 + u] : 0.0;
         }
-        row0 += ne;
-    }
 }
 
 // ====================================================================== coarsest level
@@ -1318,25 +1381,36 @@ __global__ void __launch_bounds__(WG) k_sub_finalize_tab(int64_t r0, int64_t r1,
 
 // Pack full m x m symmetric inverses (aggregate order, column-major) into the
 // tiled lower storage of k_sub_symv (FP64 and, optionally, FP32).
-__global__ void k_pack_tiles(const int64_t* sub_ptr, const int64_t* inv_off, const double* inv, const int64_t* tp_off,
+__global__ void __launch_bounds__(WG) k_pack_tiles(const int64_t* sub_ptr, const int64_t* inv_off, const double* inv, const int64_t* tp_off,
                              double* tiles, float* tiles32) {
     const int ag = blockIdx.y;
     if (tp_off[ag] < 0) return;                   // stored in the small (packed) format
     const int m = (int)(sub_ptr[ag + 1] - sub_ptr[ag]);
     const int nt = (m + 63) / 64;
-    const int64_t ntile = (int64_t)nt * (nt + 1) / 2;
+    const int ntile = nt * (nt + 1) / 2;
     const double* M = inv + inv_off[ag];
-    for (int64_t idx = (int64_t)blockIdx.x * WG + tid(); idx < ntile * 4096; idx += (int64_t)gridDim.x * WG) {
-        int64_t t = idx >> 12;
-        int e = (int)(idx & 4095);
+    // a tile at a time through LDS, halves of 32 columns, so that both sides are contiguous
+    __shared__ double s[32][65];
+    for (int t = (int)blockIdx.x; t < ntile; t += (int)gridDim.x) {
         int I = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-        while ((int64_t)I * (I + 1) / 2 > t) --I;
-        while ((int64_t)(I + 1) * (I + 2) / 2 <= t) ++I;
-        int J = (int)(t - (int64_t)I * (I + 1) / 2);
-        int r = I * 64 + (e >> 6), c = J * 64 + (e & 63);
-        double v = (r < m && c < m) ? M[r + (int64_t)c * m] : 0.0;
-        if (tiles) tiles[tp_off[ag] + idx] = v;
-        if (tiles32) tiles32[tp_off[ag] + idx] = (float)v;
+        while (I * (I + 1) / 2 > t) --I;
+        while ((I + 1) * (I + 2) / 2 <= t) ++I;
+        const int J = t - I * (I + 1) / 2;
+        const int64_t o = tp_off[ag] + (int64_t)t * 4096;
+        for (int h = 0; h < 64; h += 32) {
+            __syncthreads();
+            for (int c = tid() >> 6; c < 32; c += WG / 64) {
+                const int row = I * 64 + (tid() & 63), col = J * 64 + h + c;
+                s[c][tid() & 63] = row < m && col < m ? M[row + (int64_t)col * m] : 0.0;
+            }
+            __syncthreads();
+            for (int r = tid() >> 5; r < 64; r += WG / 32) {
+                const int c = tid() & 31;
+                const double v = s[c][r];
+                if (tiles) tiles[o + r * 64 + h + c] = v;
+                if (tiles32) tiles32[o + r * 64 + h + c] = (float)v;
+            }
+        }
     }
 }
 
@@ -1490,7 +1564,7 @@ void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk
     // blocks up to NE_LDS: Jacobi with matrix and vectors in LDS; larger blocks: the
     // tridiagonal route (k_elem_eig_trd; 81 x 81 Q2 blocks: Jacobi took 0.67 s)
     const int64_t nl = std::min<int64_t>(n_max, NE_LDS);
-    const int64_t lds = 2 * nl * nl * 8;
+    const int64_t lds = 2 * nl * (nl | 1) * 8;
     hipLaunchKernelGGL(k_elem_eig, dim3((unsigned)n_elem), dim3(WG), (size_t)lds, st, elem_ptr, blk_off, blocks, G,
                        ranks, status, scratch, scratch_stride, rank_rtol, spsd_tol, lds);
     if (n_max > NE_LDS) {
@@ -1500,7 +1574,7 @@ void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk
                            scratch, scratch_stride, rank_rtol, spsd_tol);
         hipLaunchKernelGGL(k_elem_eig_trd<1>, g, dim3(WG), ld, st, elem_ptr, blk_off, blocks, G, ranks, status,
                            scratch, scratch_stride, rank_rtol, spsd_tol);
-        hipLaunchKernelGGL(k_elem_eig_trd<2>, g, dim3(WG), ld, st, elem_ptr, blk_off, blocks, G, ranks, status,
+        hipLaunchKernelGGL(k_elem_eig_trd<2>, g, dim3(WG), (size_t)n_max + 8, st, elem_ptr, blk_off, blocks, G, ranks, status,
                            scratch, scratch_stride, rank_rtol, spsd_tol);
         hipLaunchKernelGGL(k_elem_eig_trd<3>, g, dim3(WG), ld, st, elem_ptr, blk_off, blocks, G, ranks, status,
                            scratch, scratch_stride, rank_rtol, spsd_tol);
@@ -1509,7 +1583,7 @@ void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk
 
 int64_t elem_eig_scratch_stride(int64_t n_max) {
     const int64_t jac = 3 * n_max * n_max;
-    const int64_t trd = n_max > NE_LDS ? 2 * n_max * n_max + 4 * n_max + (int64_t)INVIT_SLOTS * n_max + 4096 : 0;
+    const int64_t trd = n_max > NE_LDS ? 2 * n_max * n_max + 4 * n_max + invit_ws(n_max) : 0;
     return std::max(jac, trd);
 }
 
@@ -1640,23 +1714,31 @@ void launch_block_offsets(int64_t n_elem, const int64_t* elem_ptr, int64_t* blk_
 
 void launch_local_assemble(int32_t nbatch, const LocalArgs& a, int32_t max_m, hipStream_t st) {
     if (nbatch <= 0 || max_m <= 0) return;
-    hipLaunchKernelGGL(k_local_assemble, dim3((max_m + ASM_CW - 1) / ASM_CW, nbatch), dim3(WG), 0, st, a);
+    // a column per wave in LDS up to 1920 rows (60 KB a workgroup), in memory above
+    const int in_lds = max_m <= 640 ? max_m : 0;
+    hipLaunchKernelGGL(k_local_assemble, dim3((max_m + WG / 64 - 1) / (WG / 64), nbatch), dim3(WG),
+                       (size_t)in_lds * (WG / 64) * sizeof(double), st, a, in_lds);
 }
 
 void launch_local_eig(int32_t nbatch, const LocalArgs& a, int32_t max_nw, int first_phase, int last_phase,
                       hipStream_t st) {
     if (nbatch <= 0) return;
-    // dynamic LDS: tridiagonal work vectors, cluster starts and dots, 2 |omega| doubles
-    const size_t lds = (size_t)std::max(2 * max_nw, 4096) * sizeof(double);
-    if (first_phase <= 0 && last_phase >= 0) hipLaunchKernelGGL(k_local_eig<0>, dim3(nbatch), dim3(WG), lds, st, a);
-    if (first_phase <= 1 && last_phase >= 1) hipLaunchKernelGGL(k_local_eig<1>, dim3(nbatch), dim3(WG), lds, st, a);
-    if (first_phase <= 2 && last_phase >= 2) hipLaunchKernelGGL(k_local_eig<2>, dim3(nbatch), dim3(WG), lds, st, a);
-    if (first_phase <= 3 && last_phase >= 3) hipLaunchKernelGGL(k_local_eig<3>, dim3(nbatch), dim3(WG), lds, st, a);
+    // dynamic LDS: the reduction's and the bisection's two vectors, or the Jacobi sweeps'
+    // scratch and two matrices; in the inverse iteration the cluster starts, a byte each
+    const int nj = std::min(max_nw, SMALL_EIG);
+    const size_t lds = (size_t)std::max(2 * max_nw, JAC_LDS + 2 * nj * (nj | 1)) * sizeof(double);
+    auto phase = [&](auto kern, int p, size_t bytes) {
+        if (first_phase <= p && last_phase >= p) hipLaunchKernelGGL(kern, dim3(nbatch), dim3(WG), bytes, st, a);
+    };
+    phase(k_local_eig<0>, 0, lds);
+    phase(k_local_eig<1>, 1, (size_t)(2 * max_nw) * sizeof(double));
+    phase(k_local_eig<2>, 2, (size_t)max_nw + 8);
+    phase(k_local_eig<3>, 3, 0);
 }
 
 void launch_stage_z(int32_t nbatch, const LocalArgs& a, hipStream_t st) {
     if (nbatch <= 0) return;
-    hipLaunchKernelGGL(k_stage_z, dim3(nbatch), dim3(WG), 0, st, a);
+    hipLaunchKernelGGL(k_stage_z, dim3(16, nbatch), dim3(WG), 0, st, a);
 }
 
 void launch_views_max_diag(int32_t nv, const double* base, const View* v, double* out, hipStream_t st) {
@@ -1675,12 +1757,13 @@ void launch_views_identity(int32_t nv, double* base, const View* v, hipStream_t 
 void launch_z_compact(int32_t n_agg, const int64_t* agg_ptr, const int32_t* k, const int64_t* zst_off, const double* zst,
                       const int64_t* zoff, double* Z, double* Zc, float* Zc32, hipStream_t st) {
     if (n_agg <= 0) return;
-    hipLaunchKernelGGL(k_z_compact, dim3(n_agg), dim3(WG), 0, st, agg_ptr, k, zst_off, zst, zoff, Z, Zc, Zc32);
+    hipLaunchKernelGGL(k_z_compact, dim3(n_agg, 16), dim3(WG), 0, st, agg_ptr, k, zst_off, zst, zoff, Z, Zc, Zc32);
 }
 
-void launch_build_pst(const PstArgs& g, hipStream_t st) {
+void launch_build_pst(const PstArgs& g, int32_t max_c, hipStream_t st) {
     if (g.n_groups <= 0) return;
-    hipLaunchKernelGGL(k_build_pst, dim3(g.n_groups), dim3(WG), 0, st, g);
+    hipLaunchKernelGGL(k_build_pst, dim3(g.n_groups, std::clamp((max_c + PST_CW - 1) / PST_CW, 1, 64)), dim3(WG), 0,
+                       st, g);
 }
 
 void launch_dense_from_csr(int64_t off, int64_t n, const int64_t* rowptr, const int32_t* col, const double* val, double* D,

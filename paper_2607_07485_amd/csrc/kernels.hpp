@@ -23,6 +23,9 @@ struct LocalArgs {
     const int32_t* cl_elems;
     const int64_t* clpos_off;      // per cl entry: offset of its n_e local positions
     const int32_t* clpos;
+    const int64_t* d2e_ptr;        // DOF -> (element ascending, local index)
+    const int32_t* d2e_elem;
+    const int32_t* d2e_loc;
     const int32_t* mult;           // per element
     const int64_t* elem_ptr;       // element supports (for n_e)
     const int64_t* blk_off;        // element block offsets (n_e^2 each, row-major)
@@ -67,7 +70,7 @@ void launch_local_tridiag_blocked(const LocalArgs& a, const int32_t* d_big, cons
 // Retained eigenvectors of the tridiagonal matrices of the same entries by
 // inverse iteration, ceil(k / 64) workgroups per entry (after the mode-count
 // phase of k_local_eig); iw + iw_off[i] is entry i's scratch of
-// ceil(k_i / 64) * (INVIT_BLK_SLOTS n_i + 4096 + 64) doubles.
+// ceil(k_i / 64) * invit_ws(n_i) doubles.
 void launch_local_invit_blocked(const LocalArgs& a, const int32_t* d_big, const std::vector<int32_t>& sizes,
                                 const std::vector<int32_t>& ks, const int64_t* d_iw_off, double* iw, hipStream_t st);
 // Back-transformation of the retained eigenvectors of the same entries (after
@@ -153,8 +156,6 @@ struct PstArgs {
     int32_t g0, n_groups;          // groups g0 .. g0 + n_groups - 1
     const int64_t* cptr;           // coarse group supports (sizes c_g)
     const int64_t* mem_ptr;        // members of group g
-    const int32_t* mem_elems;
-    const int64_t* felem_ptr;      // fine element supports (n_e)
     const int64_t* pm_off;         // per member entry: offset of its n_e map entries
     const int64_t* pm_zrow;        // per (member, local dof): Z row offset (-1: no mode)
     const int32_t* pm_k;           //   modes of its aggregate
@@ -164,7 +165,8 @@ struct PstArgs {
     const int64_t* rows;           //   R_g
     double* pst;
 };
-void launch_build_pst(const PstArgs& g, hipStream_t st);
+// max_c: the largest c_g of the launch
+void launch_build_pst(const PstArgs& g, int32_t max_c, hipStream_t st);
 
 // D = A[off:off+n, off:off+n] (column-major n x n; D must be zeroed first)
 void launch_dense_from_csr(int64_t off, int64_t n, const int64_t* rowptr, const int32_t* col, const double* val,

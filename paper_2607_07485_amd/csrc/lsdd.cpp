@@ -161,7 +161,7 @@ struct Level {
     int64_t* d_rowptr = nullptr;
     int32_t* d_col = nullptr;
     double* d_val = nullptr;
-    int64_t* d_d2e_ptr = nullptr;     // level 0: DOF -> (element, local index), kept for re-assembly
+    int64_t* d_d2e_ptr = nullptr;     // DOF -> (element, local index); level 0 keeps it for re-assembly
     int32_t* d_d2e_elem = nullptr;
     int32_t* d_d2e_loc = nullptr;
     // level 0: element-batch operator apply from the packed lower triangles of the
@@ -471,15 +471,9 @@ void assemble_operator(lsdd_hierarchy* h, Level& lv) {
         launch_assemble_rows(lv.n, d_dptr, d_de, d_dl, lv.d_elem_ptr, lv.d_elem_dofs, lv.d_blk_off, lv.d_blocks,
                              nullptr, lv.d_rowptr, lv.d_col, lv.d_val, h->st, max_ne > 48);
         HIPCHK(hipStreamSynchronize(h->st));
-        if (lv.level == 0) {
-            lv.d_d2e_ptr = d_dptr;
-            lv.d_d2e_elem = d_de;
-            lv.d_d2e_loc = d_dl;
-        } else {
-            h->arena.release(d_dptr);
-            h->arena.release(d_de);
-            h->arena.release(d_dl);
-        }
+        lv.d_d2e_ptr = d_dptr;
+        lv.d_d2e_elem = d_de;
+        lv.d_d2e_loc = d_dl;
     }
     if (h->prm.precision >= 1) {
         lv.d_val32 = h->arena.alloc<float>(lv.nnz);
@@ -652,12 +646,21 @@ void append_symv_items(const std::vector<int64_t>& sub_off, const std::vector<in
 // chain of the tiled product cost (2171 DOFs: 10 us against 24 us with its conversions).
 constexpr int64_t DENSE_MAX = 3000;
 
+// the element tables of a coarse level, used by its local problems only
+void drop_d2e(lsdd_hierarchy* h, Level& lv) {
+    if (lv.level == 0 || !lv.d_d2e_ptr) return;
+    for (void* p : {(void*)lv.d_d2e_ptr, (void*)lv.d_d2e_elem, (void*)lv.d_d2e_loc}) h->arena.release(p);
+    lv.d_d2e_ptr = nullptr;
+    lv.d_d2e_elem = lv.d_d2e_loc = nullptr;
+}
+
 // Terminal blocks of a level: the dense Cholesky factorisation and explicit
 // inverse of the instance blocks of A_l listed in `term` (on the coarsest level:
 // every instance present, i.e. the whole level for a single problem), packed into
 // lower 64 x 64 tiles and applied by the symmetric subdomain kernel with one
 // "subdomain" per block.
 void make_terminal(lsdd_hierarchy* h, Level& lv, const std::vector<int32_t>& term, bool coarsest) {
+    if (coarsest) drop_d2e(h, lv);
     Arena& ar = h->arena;
     const int32_t nb = (int32_t)term.size();
     lv.term = term;
@@ -989,6 +992,9 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
     A.cl_elems = d_cl_elems;
     A.clpos_off = d_clpos_off;
     A.clpos = d_clpos;
+    A.d2e_ptr = lv.d_d2e_ptr;
+    A.d2e_elem = lv.d_d2e_elem;
+    A.d2e_loc = lv.d_d2e_loc;
     A.mult = d_mult;
     A.elem_ptr = lv.d_elem_ptr;
     A.blk_off = lv.d_blk_off;
@@ -1038,7 +1044,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         int64_t bytes = 0;
         while (end < n_agg && (end - pos) < 32768) {
             int64_t m = C.sub_ptr[end + 1] - C.sub_ptr[end], nw = C.agg_ptr[end + 1] - C.agg_ptr[end];
-            int64_t tl = 3 * nw + (int64_t)INVIT_SLOTS * nw + 4096;
+            int64_t tl = 3 * nw + invit_ws(nw);
             int64_t need = (2 * m * m + 2 * nw * nw + tl) * 8;
             if (end > pos && bytes + need > budget) break;
             bytes += need;
@@ -1183,7 +1189,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
                 std::vector<int32_t> kall = download(lv.d_k + pos, nb, st);
                 for (size_t t = 0; t < big.size(); ++t) {
                     ks[t] = kall[big[t]];
-                    iw_off[t + 1] = iw_off[t] + (int64_t)((ks[t] + 63) / 64) * ((int64_t)INVIT_BLK_SLOTS * bigsz[t] + 4096 + 64);
+                    iw_off[t + 1] = iw_off[t] + (int64_t)((ks[t] + 63) / 64) * invit_ws(bigsz[t]);
                 }
                 double* iw = ar.alloc<double>(std::max<int64_t>(iw_off.back(), 1));
                 int64_t* d_iw_off = ar.upload(iw_off, st);
@@ -1462,6 +1468,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
                     (void*)d_clpos, (void*)d_mult, (void*)d_inv_off, (void*)d_zst_off, (void*)d_status})
         ar.release(p);
     if (d_thr) ar.release(d_thr);
+    drop_d2e(h, lv);
     const int64_t nc = lv.coff[n_agg];
     // coarse DOF ranges of the instances; an instance without retained modes
     // would end its hierarchy here while the others continue
@@ -1547,8 +1554,6 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         PstArgs pa{};
         pa.cptr = cv->d_elem_ptr;
         pa.mem_ptr = ar.upload(G.mem_ptr, st);
-        pa.mem_elems = ar.upload(G.mem_elems, st);
-        pa.felem_ptr = lv.d_elem_ptr;
         pa.pm_off = ar.upload(pm_off, st);
         pa.pm_zrow = ar.upload(pm_zrow, st);
         pa.pm_k = ar.upload(pm_k, st);
@@ -1580,7 +1585,9 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
             pa.pst_off = ar.upload(off, st);
             pa.rows = ar.upload(rows, st);
             pa.pst = pst;
-            launch_build_pst(pa, st);
+            int64_t max_c = 0;
+            for (int64_t g = g0; g < g1; ++g) max_c = std::max(max_c, cv->el.ptr[g + 1] - cv->el.ptr[g]);
+            launch_build_pst(pa, (int32_t)max_c, st);
             std::vector<View> va, vb;
             auto flush_members = [&]() {
                 if (va.empty()) return;
@@ -1622,7 +1629,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
             g0 = g1;
         }
         bt.free_all();
-        for (const void* p : {(const void*)pa.mem_ptr, (const void*)pa.mem_elems, (const void*)pa.pm_off,
+        for (const void* p : {(const void*)pa.mem_ptr, (const void*)pa.pm_off,
                               (const void*)pa.pm_zrow, (const void*)pa.pm_k, (const void*)pa.pm_col})
             ar.release(const_cast<void*>(p));
     }

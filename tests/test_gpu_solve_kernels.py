@@ -7,7 +7,7 @@ most 82 rho (2-norm condition number).
 import numpy as np
 import pytest
 
-from fegen.common import uniform_problem
+from fegen.common import Problem, uniform_problem
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -164,3 +164,49 @@ def test_blocked_eigensolver_sizes(width):
     assert np.array_equal(k0, k1) and k0.max() > 64
     assert np.abs(mu0 - mu1).max() <= 1e-10
     assert float((z0 - z1).norm()) <= 1e-10 * float(z0.norm())
+
+
+def test_element_factors_at_block_sizes():
+    """G^T G = A of singular element blocks with a cluster of equal eigenvalues, at the sizes where
+    the eigensolver changes (Jacobi up to 48; pairs without a partner; a wave's rows, 64 and 128).
+    The Jacobi route is backward stable (50 n eps); in the other, vectors of different clusters are
+    orthogonal to eps over the clusters' distance, 1e-4 (1e-11)."""
+    P = _lsdd()
+    rng = np.random.default_rng(3)
+    sizes = [1, 2, 3, 8, 24, 47, 48, 49, 64, 65, 127, 128]
+    blocks = []
+    for n in sizes:
+        w = np.concatenate([np.zeros(n // 3), np.ones(n // 3), rng.uniform(0.1, 10.0, n - 2 * (n // 3))])
+        Q = np.linalg.qr(rng.standard_normal((n, n)))[0]
+        B = Q @ np.diag(w) @ Q.T
+        blocks.append(0.5 * (B + B.T))
+    N = sum(sizes)
+    ptr = np.concatenate([np.cumsum([0] + sizes), N + np.arange(1, N + 1)])
+    prob = Problem(n=N, elem_ptr=ptr.astype(np.int64), elem_dofs=np.tile(np.arange(N, dtype=np.int32), 2),
+                   blocks=np.concatenate([b.ravel() for b in blocks] + [np.full(N, 0.1)]),
+                   node_of_dof=np.arange(N, dtype=np.int32))
+    with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=1)) as h:
+        ranks, G = h.export_gram(ptr)
+    off = 0
+    for n, r, B in zip(sizes, ranks, blocks):
+        g = G[off:off + n * n].reshape(n, n)
+        off += n * n
+        assert r == n - n // 3 and not g[r:].any()
+        assert np.abs(g.T @ g - B).max() <= (50 * n * np.finfo(float).eps if n <= 48 else 1e-11) * 10.0
+
+
+def test_local_assembly_in_lds_and_memory():
+    """Aggregates of 300 DOFs, assembled in LDS, and the same ones in a batch with one of 700 DOFs,
+    which is assembled in memory: the same arithmetic, so equal eigenvalues."""
+    P = _lsdd()
+    a, b = _chain(600), _chain(700)
+    both = uniform_problem(1300, np.concatenate([a.elem_dofs.reshape(-1, 2), 600 + b.elem_dofs.reshape(-1, 2)]),
+                           np.concatenate([a.blocks, b.blocks]).reshape(-1, 2, 2), np.arange(1300))
+    a.agg_of_dof = (np.arange(600) // 300).astype(np.int32)
+    both.agg_of_dof = np.minimum(np.arange(1300) // 300, 2).astype(np.int32)
+    out = []
+    for prob in (a, both):
+        with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2)) as h:
+            ex = h.export_level(0)
+            out.append((ex["k"][:2], ex["mu"][:600]))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
