@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <cfloat>
 #include <cmath>
 #include <stdexcept>
@@ -671,8 +672,11 @@ View* Batched::put(int slot, const std::vector<View>& v) {
         slot_cap = std::max<size_t>(v.size(), 64);
         for (View*& p : d_slot) p = (View*)alloc(ctx, slot_cap * sizeof(View));
     }
-    chk(hipMemcpyAsync(d_slot[slot], v.data(), v.size() * sizeof(View), hipMemcpyHostToDevice, st), "view upload");
-    chk(hipStreamSynchronize(st), "view upload sync");
+    const size_t bytes = v.size() * sizeof(View);
+    void* pin = stage && bytes ? stage(ctx, bytes, st) : nullptr;   // no wait: the views are the caller's
+    if (pin) std::memcpy(pin, v.data(), bytes);
+    chk(hipMemcpyAsync(d_slot[slot], pin ? pin : v.data(), bytes, hipMemcpyHostToDevice, st), "view upload");
+    if (!pin) chk(hipStreamSynchronize(st), "view upload sync");
     return d_slot[slot];
 }
 

@@ -26,6 +26,7 @@ struct Batched {
     size_t slot_cap = 0;
     void* (*alloc)(void* ctx, size_t bytes) = nullptr;
     void (*release)(void* ctx, void* p) = nullptr;
+    void* (*stage)(void* ctx, size_t bytes, hipStream_t st) = nullptr;   // pinned room or nullptr
     void* ctx = nullptr;
 
     // copy views into device slot 0, 1 or 2 (grown on demand) and return it

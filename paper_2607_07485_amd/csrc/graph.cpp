@@ -11,21 +11,6 @@ namespace lsdd {
 
 namespace {
 
-// Build a CSR from (row, col) pairs, deduplicated and sorted per row.
-Csr pairs_to_csr(int64_t nrows, std::vector<std::pair<int32_t, int32_t>>& pr) {
-    std::sort(pr.begin(), pr.end());
-    pr.erase(std::unique(pr.begin(), pr.end()), pr.end());
-    Csr c;
-    c.ptr.assign(nrows + 1, 0);
-    c.idx.resize(pr.size());
-    for (size_t t = 0; t < pr.size(); ++t) {
-        c.ptr[pr[t].first + 1]++;
-        c.idx[t] = pr[t].second;
-    }
-    for (int64_t r = 0; r < nrows; ++r) c.ptr[r + 1] += c.ptr[r];
-    return c;
-}
-
 // Transpose of an incidence list: for each target, the sources listing it.
 Csr transpose(int64_t n_targets, const std::vector<int64_t>& ptr, const std::vector<int32_t>& idx) {
     Csr t;
@@ -124,15 +109,31 @@ std::vector<int32_t> aggregate(const Csr& g0, int passes, int32_t* n_agg) {
         int32_t nn = 0;
         std::vector<int32_t> a = standard_aggregation(g, &nn);
         for (int64_t i = 0; i < n; ++i) agg[i] = a[agg[i]];
-        // quotient graph on the new aggregates
-        std::vector<std::pair<int32_t, int32_t>> pr;
-        for (int64_t u = 0; u < g.rows(); ++u)
-            for (int64_t q = g.ptr[u]; q < g.ptr[u + 1]; ++q) {
-                int32_t au = a[u], av = a[g.idx[q]];
-                if (au != av) pr.emplace_back(au, av);
-            }
-        g = pairs_to_csr(nn, pr);
         na = nn;
+        if (p + 1 == passes) break;
+        // quotient graph on the new aggregates, a mark per neighbour (sorting all pairs of
+        // aggregates took 3 ms on Q2 hexes 8^3)
+        std::vector<int64_t> one(a.size() + 1);
+        for (size_t u = 0; u <= a.size(); ++u) one[u] = (int64_t)u;
+        const Csr nodes = transpose(nn, one, a);
+        Csr q;
+        q.ptr.assign(nn + 1, 0);
+        std::vector<int32_t> mark(nn, -1);
+        for (int32_t i = 0; i < nn; ++i) {
+            mark[i] = i;
+            const size_t start = q.idx.size();
+            for (int64_t t = nodes.ptr[i]; t < nodes.ptr[i + 1]; ++t)
+                for (int64_t r = g.ptr[nodes.idx[t]]; r < g.ptr[nodes.idx[t] + 1]; ++r) {
+                    const int32_t j = a[g.idx[r]];
+                    if (mark[j] != i) {
+                        mark[j] = i;
+                        q.idx.push_back(j);
+                    }
+                }
+            std::sort(q.idx.begin() + start, q.idx.end());
+            q.ptr[i + 1] = (int64_t)q.idx.size();
+        }
+        g = std::move(q);
     }
     *n_agg = na;
     return agg;
@@ -242,14 +243,19 @@ std::vector<int32_t> color_subdomains(int64_t n, const Closure& c, const ElemLis
     Csr es;
     es.ptr.assign(el.count() + 1, 0);
     std::vector<int32_t> subs;
+    std::vector<int64_t> met(na, -1);
     for (int64_t e = 0; e < el.count(); ++e) {
         subs.clear();
         for (int64_t q = el.ptr[e]; q < el.ptr[e + 1]; ++q) {
             int32_t d = el.dofs[q];
-            for (int64_t r = d2s.ptr[d]; r < d2s.ptr[d + 1]; ++r) subs.push_back(d2s.idx[r]);
+            for (int64_t r = d2s.ptr[d]; r < d2s.ptr[d + 1]; ++r) {
+                const int32_t s = d2s.idx[r];
+                if (met[s] == e) continue;
+                met[s] = e;
+                subs.push_back(s);
+            }
         }
         std::sort(subs.begin(), subs.end());
-        subs.erase(std::unique(subs.begin(), subs.end()), subs.end());
         es.idx.insert(es.idx.end(), subs.begin(), subs.end());
         es.ptr[e + 1] = (int64_t)es.idx.size();
     }

@@ -12,10 +12,12 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <memory>
 #include <stdexcept>
 #include <string>
 #include <type_traits>
+#include <unordered_map>
 #include <vector>
 
 #include "graph.hpp"
@@ -81,44 +83,194 @@ void vlog(const char* fmt, ...) {
 
 namespace lsdd {
 
-// Device memory owned by one hierarchy; released in one go.
+// Device memory of one hierarchy; what is left is released in one go.
+//
+// hipMalloc and hipFree cost 10 and 20 us from 2 MB on and 100 and 330 us above 64 MB, whatever
+// the size, and a set-up asked for some 100 blocks (grad-div 40^2: 13 of 87 ms, Q2 hexes 8^3: 8
+// of 60 ms; now 1.5 and 1.8).  Requests of up to POOL_MAX are ranges of a few chunks, each as large as what the
+// hierarchy holds already (8 to 512 MB); larger ones, whose cost is nothing beside the work on them, are allocations
+// of their own and go back at once.  All work of the set-up runs on one stream, so a range
+// released there may be handed out again behind the kernels that still use it; when the set-up
+// is over (seal), chunks without a live range go back, and later releases wait for the device
+// first, as hipFree does, because calls after it may use several streams.  A caller's allocator
+// (lsdd_set_allocator) gets every request as it is.
 struct Arena {
-    std::vector<void*> ptrs;
+    static constexpr size_t POOL_MAX = size_t(512) << 20;
+    static constexpr size_t CHUNK_MIN = size_t(8) << 20, CHUNK_MAX = size_t(512) << 20;
+    static constexpr size_t STAGE = size_t(1) << 20;
+    struct Live {
+        size_t bytes;
+        bool pooled;
+    };
+    std::unordered_map<void*, Live> live;
+    std::map<char*, size_t> chunks;         // base, size
+    std::map<char*, size_t> room;           // free ranges; neighbours in a chunk are one range
+    size_t held = 0;                        // bytes of the chunks
+    bool sealed = false;
+    char* pin = nullptr;                    // pinned buffer of the small uploads
+    size_t pin_pos = 0;
+    hipStream_t pin_st = nullptr;
+
+    Arena() = default;
+    Arena(const Arena&) = delete;
+    Arena& operator=(const Arena&) = delete;
+    ~Arena() {
+        if (live.empty() && chunks.empty() && !pin) return;
+        (void)hipDeviceSynchronize();       // a set-up that failed: its kernels may still run
+        clear();
+    }
     void* get(size_t bytes) {
         if (bytes == 0) bytes = 8;
         bytes = (bytes + 255) & ~size_t(255);
         void* p = nullptr;
+        bool pooled = false;
         if (g_alloc) {
             p = g_alloc(bytes, g_alloc_ctx);
             if (!p) throw Error(LSDD_E_NOMEM, "allocator hook returned NULL for " + std::to_string(bytes) + " bytes");
+        } else if (bytes > POOL_MAX) {
+            p = device(bytes);
         } else {
-            hipError_t e = hipMalloc(&p, bytes);
-            if (e != hipSuccess) throw Error(LSDD_E_NOMEM, "hipMalloc(" + std::to_string(bytes) + "): " + hipGetErrorString(e));
+            pooled = true;
+            p = carve(bytes);
+            if (!p) {
+                grow(bytes);
+                p = carve(bytes);
+            }
         }
-        ptrs.push_back(p);
+        live.emplace(p, Live{bytes, pooled});
         return p;
     }
     template <typename T>
     T* alloc(size_t count) { return static_cast<T*>(get(count * sizeof(T))); }
+    // A pageable source costs the host 0.4 us per KB up to 256 KB; through the pinned buffer it
+    // is a copy and a launch, and the source may go at once.
     template <typename T>
     T* upload(const std::vector<T>& v, hipStream_t st) {
         T* p = alloc<T>(v.size());
-        if (!v.empty()) HIPCHK(hipMemcpyAsync(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, st));
+        const size_t bytes = v.size() * sizeof(T);
+        const void* src = v.data();
+        if (void* s = bytes ? stage(bytes, st) : nullptr) src = std::memcpy(s, src, bytes);
+        if (bytes) HIPCHK(hipMemcpyAsync(p, src, bytes, hipMemcpyHostToDevice, st));
+        return p;
+    }
+    // pinned room for one upload on st; nullptr: too large for it, or none to be had
+    void* stage(size_t bytes, hipStream_t st) {
+        if (bytes > STAGE / 4) return nullptr;
+        if (!pin) {
+            if (hipHostMalloc((void**)&pin, STAGE, hipHostMallocDefault) != hipSuccess) {
+                (void)hipGetLastError();
+                pin = nullptr;
+                return nullptr;
+            }
+            pin_st = st;
+            pin_pos = 0;
+        }
+        if (st != pin_st) {                 // the copies on the stream before, which may be gone
+            HIPCHK(hipDeviceSynchronize());
+            pin_st = st;
+            pin_pos = 0;
+        }
+        if (pin_pos + bytes > STAGE) {
+            HIPCHK(hipStreamSynchronize(st));
+            pin_pos = 0;
+        }
+        void* p = pin + pin_pos;
+        pin_pos += (bytes + 63) & ~size_t(63);
         return p;
     }
     void release(void* p) {
-        auto it = std::find(ptrs.begin(), ptrs.end(), p);
-        if (it == ptrs.end()) return;
-        if (g_free) g_free(p, g_alloc_ctx);
-        else (void)hipFree(p);
-        ptrs.erase(it);
+        auto it = live.find(p);
+        if (it == live.end()) return;
+        const Live b = it->second;
+        live.erase(it);
+        if (!b.pooled) {
+            give_back(p);
+            return;
+        }
+        if (sealed) (void)hipDeviceSynchronize();
+        char* lo = static_cast<char*>(p);
+        char* hi = lo + b.bytes;
+        auto next = room.lower_bound(lo);
+        if (next != room.end() && next->first == hi && !chunks.count(hi)) {
+            hi += next->second;
+            next = room.erase(next);
+        }
+        if (next != room.begin() && !chunks.count(lo)) {
+            auto prev = std::prev(next);
+            if (prev->first + prev->second == lo) lo = prev->first;
+        }
+        room[lo] = (size_t)(hi - lo);
+    }
+    // the set-up's stream is synchronized
+    void seal() {
+        trim();
+        sealed = true;
     }
     void clear() {
-        for (void* p : ptrs) {
-            if (g_free) g_free(p, g_alloc_ctx);
-            else (void)hipFree(p);
+        for (auto& q : live)
+            if (!q.second.pooled) give_back(q.first);
+        for (auto& c : chunks) (void)hipFree(c.first);
+        live.clear();
+        chunks.clear();
+        room.clear();
+        held = 0;
+        if (pin) (void)hipHostFree(pin);
+        pin = nullptr;
+    }
+
+private:
+    static void give_back(void* p) {
+        if (g_free) g_free(p, g_alloc_ctx);
+        else (void)hipFree(p);
+    }
+    // smallest range that holds it
+    void* carve(size_t bytes) {
+        auto best = room.end();
+        for (auto it = room.begin(); it != room.end(); ++it)
+            if (it->second >= bytes && (best == room.end() || it->second < best->second)) best = it;
+        if (best == room.end()) return nullptr;
+        char* p = best->first;
+        const size_t left = best->second - bytes;
+        room.erase(best);
+        if (left) room[p + bytes] = left;
+        return p;
+    }
+    void grow(size_t bytes) {
+        size_t want = std::max(bytes, std::clamp(held, CHUNK_MIN, CHUNK_MAX));
+        void* p = nullptr;
+        if (hipMalloc(&p, want) != hipSuccess) {
+            (void)hipGetLastError();
+            want = bytes;
+            p = device(bytes);
         }
-        ptrs.clear();
+        chunks[static_cast<char*>(p)] = want;
+        room[static_cast<char*>(p)] = want;
+        held += want;
+    }
+    void* device(size_t bytes) {
+        void* p = nullptr;
+        hipError_t e = hipMalloc(&p, bytes);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            trim();
+            e = hipMalloc(&p, bytes);
+        }
+        if (e != hipSuccess) throw Error(LSDD_E_NOMEM, "hipMalloc(" + std::to_string(bytes) + "): " + hipGetErrorString(e));
+        return p;
+    }
+    // chunks without a live range (hipFree waits for the device)
+    void trim() {
+        for (auto it = chunks.begin(); it != chunks.end();) {
+            auto r = room.find(it->first);
+            if (r != room.end() && r->second == it->second) {
+                (void)hipFree(it->first);
+                held -= it->second;
+                room.erase(r);
+                it = chunks.erase(it);
+            } else {
+                ++it;
+            }
+        }
     }
 };
 
@@ -705,6 +857,7 @@ void make_terminal(lsdd_hierarchy* h, Level& lv, const std::vector<int32_t>& ter
     bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
     bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
     bt.ctx = &ar;
+    bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
     bt.potrf(W, vq, d_minp);
     launch_views_identity(nb, X, bt.put(0, vq), h->st);
     bt.trsm(W, vq, X, vq, false, true);
@@ -1036,6 +1189,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
     bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
     bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
     bt.ctx = &ar;
+    bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
     std::vector<int32_t> status(n_agg, 0);
     int32_t pos = 0;
     while (pos < n_agg) {
@@ -1564,6 +1718,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
         bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
         bt.ctx = &ar;
+        bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
         const int64_t budget = int64_t(2) << 30;    // bytes of P and Y per launch batch
         constexpr size_t MAXV = 65535;              // views per launch
         int64_t g0 = 0;
@@ -2607,6 +2762,7 @@ lsdd_hierarchy* build(ElemList el0, const double* blocks, bool blocks_on_device,
     init_segments(h.get(), h->L[0]->inst_off);
     alloc_pcg(h.get(), 0);
     sync(h->st);
+    h->arena.seal();
     h->setup_s = now_s() - t0;
     vlog("setup %.3f s", h->setup_s);
     h->cycle_prec = P.precision;
@@ -3374,6 +3530,7 @@ void coarse_gram(lsdd_hierarchy* h, Level& lv) {
     bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
     bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
     bt.ctx = &ar;
+    bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
     std::vector<int32_t> ranks(ne, 0);
     for (int64_t e0 = 0; e0 < ne; e0 += CH) {
         const int64_t cnt = std::min(CH, ne - e0);

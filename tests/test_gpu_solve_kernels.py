@@ -210,3 +210,41 @@ def test_local_assembly_in_lds_and_memory():
             ex = h.export_level(0)
             out.append((ex["k"][:2], ex["mu"][:600]))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("hook", [False, True])
+def test_setup_memory(hook):
+    """Set-ups that share nothing, one that fails, calls on other streams that allocate after the
+    set-up, and everything given back at the end (up to the 64 MB the runtime may keep)."""
+    import fegen
+    P = _lsdd()
+    prob = fegen.elasticity_q1(24, nu=0.3)
+    B = torch.from_numpy(np.random.default_rng(0).standard_normal((3, prob.n))).cuda()
+    bad = uniform_problem(4, np.array([[0, 1], [2, 3]]), np.stack([np.eye(2), -np.eye(2)]), np.arange(4))
+    P.set_torch_allocator(hook)
+    try:
+        P.Hierarchy.setup_problem(prob, P.Params.default()).close()
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        free = torch.cuda.mem_get_info()[0]
+        hs = [P.Hierarchy.setup_problem(prob, P.Params.default(rtol=1e-10)) for _ in range(3)]
+        with pytest.raises(P.LsddError):
+            P.Hierarchy.setup_problem(bad, P.Params.default())
+        hs.pop(1).close()
+        X = hs[0].solve(B)[0]
+        with torch.cuda.stream(torch.cuda.Stream()):
+            torch.cuda.current_stream().wait_stream(torch.cuda.default_stream())
+            Y = hs[1].solve(B)[0]
+            G1 = hs[1].export_gram_level(1)
+            Y2 = hs[1].solve(B)[0]
+            torch.cuda.current_stream().synchronize()
+        G0 = hs[0].export_gram_level(1)
+        assert torch.equal(X, Y) and torch.equal(Y, Y2)
+        assert np.array_equal(G0["ranks"], G1["ranks"]) and np.array_equal(G0["G"], G1["G"])
+        for h in hs:
+            h.close()
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        assert torch.cuda.mem_get_info()[0] >= free - (64 << 20)
+    finally:
+        P.set_torch_allocator(False)
