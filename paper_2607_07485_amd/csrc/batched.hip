@@ -705,10 +705,12 @@ void Batched::potrf(double* base, const std::vector<View>& a, double* d_minpiv) 
     for (int p0 = 0; p0 < nt; p0 += OB) {
         const int p1 = std::min(p0 + OB, nt);
         for (int kb = p0; kb < p1; ++kb) {
-            hipLaunchKernelGGL(k_potrf_diag, dim3(1, nm), dim3(NT), 0, st, base, dv, kb, d_minpiv);
+            if (fixed_order) fixed::launch_potrf_diag(nm, base, dv, kb, d_minpiv, st);
+            else hipLaunchKernelGGL(k_potrf_diag, dim3(1, nm), dim3(NT), 0, st, base, dv, kb, d_minpiv);
             const int below = nt - kb - 1;
             if (below <= 0) continue;
-            hipLaunchKernelGGL(k_potrf_panel, dim3(below, nm), dim3(NT), 0, st, base, dv, kb);
+            if (fixed_order) fixed::launch_potrf_panel(below, nm, base, dv, kb, st);
+            else hipLaunchKernelGGL(k_potrf_panel, dim3(below, nm), dim3(NT), 0, st, base, dv, kb);
             int64_t jobs = 0;
             for (int jb = kb + 1; jb < p1; ++jb) jobs += nt - jb;
             if (jobs > 0)
@@ -787,10 +789,14 @@ void Batched::trsm(const double* lbase, const std::vector<View>& l, double* bbas
     const int nt = max_tiles(l, true);
     const int nct = max_tiles(b, false);
     if (nct == 0) return;
+    auto diag = [&](int s, int tr, int lb) {
+        if (fixed_order) fixed::launch_trsm_diag(nct, nm, lbase, d1, bbase, d2, s, tr, lb, st);
+        else hipLaunchKernelGGL(k_trsm_diag, dim3(nct, nm), dim3(NT), 0, st, lbase, d1, bbase, d2, s, tr, lb);
+    };
     if (trans) {
         // backward solves (few right-hand sides here): one tile step at a time
         for (int s = 0; s < nt; ++s) {
-            hipLaunchKernelGGL(k_trsm_diag, dim3(nct, nm), dim3(NT), 0, st, lbase, d1, bbase, d2, s, 1, 0);
+            diag(s, 1, 0);
             const int jobs = (nt - 1 - s) * nct;
             if (jobs > 0)
                 hipLaunchKernelGGL(k_trsm_update, dim3(jobs, nm), dim3(NT), 0, st, lbase, d1, bbase, d2, 0, 0, 0, 0,
@@ -802,8 +808,7 @@ void Batched::trsm(const double* lbase, const std::vector<View>& l, double* bbas
         for (int p0 = 0; p0 < nt; p0 += OB) {
             const int p1 = std::min(p0 + OB, nt);
             for (int kb = p0; kb < p1; ++kb) {
-                hipLaunchKernelGGL(k_trsm_diag, dim3(nct, nm), dim3(NT), 0, st, lbase, d1, bbase, d2, kb, 0,
-                                   lower_b ? 1 : 0);
+                diag(kb, 0, lower_b ? 1 : 0);
                 const int cols = lower_b ? std::min(nct, kb + 1) : nct;
                 const int jobs = (p1 - kb - 1) * cols;
                 if (jobs > 0)

@@ -28,6 +28,7 @@ struct Batched {
     void (*release)(void* ctx, void* p) = nullptr;
     void* (*stage)(void* ctx, size_t bytes, hipStream_t st) = nullptr;   // pinned room or nullptr
     void* ctx = nullptr;
+    bool fixed_order = false;             // diagonal-tile steps of fixed.hip
 
     // copy views into device slot 0, 1 or 2 (grown on demand) and return it
     View* put(int slot, const std::vector<View>& v);
@@ -69,5 +70,13 @@ struct Batched {
     // In-place transpose of square views.
     void transpose(double* base, const std::vector<View>& a);
 };
+
+// The diagonal-tile steps with the order of operations of fixed.hpp (one call per tile column).
+namespace fixed {
+void launch_potrf_diag(unsigned nm, double* base, const View* views, int kb, double* minpiv, hipStream_t st);
+void launch_potrf_panel(unsigned below, unsigned nm, double* base, const View* views, int kb, hipStream_t st);
+void launch_trsm_diag(unsigned nct, unsigned nm, const double* lbase, const View* lv, double* bbase, const View* bv,
+                      int s, int trans, int lower_b, hipStream_t st);
+}  // namespace fixed
 
 }  // namespace lsdd

@@ -95,7 +95,8 @@ __device__ inline int local_index(const int32_t* dofs, int nw, int m, int32_t q)
 __global__ void __launch_bounds__(WG) k_elem_eig(const int64_t* elem_ptr, const int64_t* blk_off,
                                                  const double* blocks, double* G, int32_t* ranks,
                                                  int32_t* status, double* scratch, int64_t scratch_stride,
-                                                 double rank_rtol, double spsd_tol, int64_t lds_bytes) {
+                                                 double rank_rtol, double spsd_tol, int64_t lds_bytes,
+                                                 const int32_t* fixed_order) {
     extern __shared__ double s_dyn[];
     __shared__ double s_w[128];
     __shared__ int s_rank[128];
@@ -128,7 +129,7 @@ __global__ void __launch_bounds__(WG) k_elem_eig(const int64_t* elem_ptr, const 
         return;
     }
     wg_identity(v, ld, n);
-    wg_jacobi(a, ld, n, v, ld, 60, 1e-15, 1e-18 * amax, DBL_EPSILON * amax, s_pairs, s_cs, &s_flag);
+    wg_jacobi(a, ld, n, v, ld, 60, 1e-15, 1e-18 * amax, *fixed_order ? 0.0 : DBL_EPSILON * amax, s_pairs, s_cs, &s_flag);
     wg_sort_eig(a, ld, v, ld, n, s_w, vs, n, s_rank);
     const double lmax = fmax(s_w[n - 1], 0.0);
     if (s_w[0] < -spsd_tol * lmax) {
@@ -153,6 +154,25 @@ __global__ void __launch_bounds__(WG) k_elem_eig(const int64_t* elem_ptr, const 
         ranks[e] = r;
         status[e] = 0;
     }
+}
+
+// A thread per element: flags a block whose positive diagonal entries span more than
+// FIXED_SPREAD.
+__global__ void k_diag_spread(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
+                              int32_t* flag) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= n_elem) return;
+    const int64_t n = elem_ptr[e + 1] - elem_ptr[e];
+    const double* B = blocks + blk_off[e];
+    double lo = DBL_MAX, hi = 0.0;
+    for (int64_t i = 0; i < n; ++i) {
+        const double d = B[i * (n + 1)];
+        if (d > 0.0) {
+            lo = fmin(lo, d);
+            hi = fmax(hi, d);
+        }
+    }
+    if (hi > 0.0 && hi > FIXED_SPREAD * lo) atomicOr(flag, 1);
 }
 
 // Element blocks larger than NE_LDS, one workgroup per element: the same outputs
@@ -523,7 +543,6 @@ __global__ void __launch_bounds__(WG) k_local_assemble(LocalArgs A, int in_lds) 
             double val[U];
             const int32_t* pp[U];
             const double* bp[U];
-            int nmax = 0;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 src[u] = todo ? __ffsll((unsigned long long)todo) - 1 : -1;
@@ -532,21 +551,19 @@ __global__ void __launch_bounds__(WG) k_local_assemble(LocalArgs A, int in_lds) 
                 n_[u] = src[u] >= 0 ? __shfl(ne, s, 64) : 0;
                 pp[u] = A.clpos + __shfl(po, s, 64);
                 bp[u] = A.blocks + __shfl(bo, s, 64);
-                nmax = max(nmax, n_[u]);
+                pi[u] = l < n_[u] ? pp[u][l] : -1;                 // < 0: outside an A-closure overlap
+                val[u] = l < n_[u] ? bp[u][(int64_t)l * n_[u]] : 0.0;
             }
-            for (int i0 = 0; i0 < nmax; i0 += 64) {
-                const int i = i0 + l;
+            // element after element, also where one has more than 64 rows
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    pi[u] = i < n_[u] ? pp[u][i] : -1;             // < 0: outside an A-closure overlap
-                    val[u] = i < n_[u] ? bp[u][(int64_t)i * n_[u]] : 0.0;
+            for (int u = 0; u < U; ++u) {
+                const double w_ = __shfl(wt, max(src[u], 0), 64);
+                if (pi[u] >= 0) acc[pi[u]] = fma(w_, val[u], acc[pi[u]]);
+                for (int i = 64 + l; i < n_[u]; i += 64) {
+                    const int q = pp[u][i];
+                    if (q >= 0) acc[q] = fma(w_, bp[u][(int64_t)i * n_[u]], acc[q]);
                 }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const double x = __shfl(wt, max(src[u], 0), 64) * val[u];
-                    if (pi[u] >= 0) acc[pi[u]] += x;
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the next element's lanes see it
-                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the next element's lanes see it
             }
         }
     }
@@ -604,16 +621,17 @@ __global__ void __launch_bounds__(WG) k_local_eig(LocalArgs A) {
                 }
             scale = wg_max(scale, s_red);
             wg_identity(v, ld, nw);
-            wg_jacobi(a, ld, nw, v, ld, 60, 1e-15, 1e-18 * fmax(scale, 1e-300), DBL_EPSILON * scale, pairs, cs,
-                      &s_flag);
+            wg_jacobi(a, ld, nw, v, ld, 60, 1e-15, 1e-18 * fmax(scale, 1e-300),
+                      A.fixed_order ? 0.0 : DBL_EPSILON * scale, pairs, cs, &s_flag);
             wg_sort_eig(a, ld, v, ld, nw, mu, VS, nw, rank);
-        } else if (!(A.trd_min > 0 && nw >= A.trd_min)) {
+        } else if (!A.fixed_order && !(A.trd_min > 0 && nw >= A.trd_min)) {
             wg_tridiag(S, nw, T, T + nw, T + 2 * nw, s_dyn, s_dyn + nw, s_red);
         }
         return;
     }
     if (PHASE == 1) {
-        if (!small && !(A.trd_min > 0 && nw >= A.trd_min)) wg_bisect_all(T, T + nw, nw, mu, s_dyn, s_red);
+        if (!small && !A.fixed_order && !(A.trd_min > 0 && nw >= A.trd_min))
+            wg_bisect_all(T, T + nw, nw, mu, s_dyn, s_red);
         for (int i = tid(); i < nw; i += WG) mu[i] = fmax(mu[i], 0.0);
         __syncthreads();
         if (tid() == 0) {
@@ -1559,14 +1577,14 @@ __global__ void k_check_finite(int64_t n, const double* a, int32_t* flag) {
 
 void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks, double* G,
                      int32_t* ranks, int32_t* status, double* scratch, int64_t scratch_stride, double rank_rtol,
-                     double spsd_tol, int64_t n_max, hipStream_t st) {
+                     double spsd_tol, int64_t n_max, const int32_t* fixed_order, hipStream_t st) {
     if (n_elem <= 0) return;
     // blocks up to NE_LDS: Jacobi with matrix and vectors in LDS; larger blocks: the
     // tridiagonal route (k_elem_eig_trd; 81 x 81 Q2 blocks: Jacobi took 0.67 s)
     const int64_t nl = std::min<int64_t>(n_max, NE_LDS);
     const int64_t lds = 2 * nl * (nl | 1) * 8;
     hipLaunchKernelGGL(k_elem_eig, dim3((unsigned)n_elem), dim3(WG), (size_t)lds, st, elem_ptr, blk_off, blocks, G,
-                       ranks, status, scratch, scratch_stride, rank_rtol, spsd_tol, lds);
+                       ranks, status, scratch, scratch_stride, rank_rtol, spsd_tol, lds, fixed_order);
     if (n_max > NE_LDS) {
         const size_t ld = (size_t)(2 * n_max + 64) * 8;
         const dim3 g((unsigned)n_elem);
@@ -1579,6 +1597,14 @@ void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk
         hipLaunchKernelGGL(k_elem_eig_trd<3>, g, dim3(WG), ld, st, elem_ptr, blk_off, blocks, G, ranks, status,
                            scratch, scratch_stride, rank_rtol, spsd_tol);
     }
+}
+
+void launch_diag_spread(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
+                        int32_t* flag, hipStream_t st) {
+    hipLaunchKernelGGL(k_zero<int32_t>, dim3(1), dim3(WG), 0, st, (int64_t)1, flag);
+    if (n_elem > 0)
+        hipLaunchKernelGGL(k_diag_spread, dim3((unsigned)((n_elem + 63) / 64)), dim3(64), 0, st, n_elem, elem_ptr,
+                           blk_off, blocks, flag);
 }
 
 int64_t elem_eig_scratch_stride(int64_t n_max) {
@@ -1714,7 +1740,8 @@ void launch_block_offsets(int64_t n_elem, const int64_t* elem_ptr, int64_t* blk_
 
 void launch_local_assemble(int32_t nbatch, const LocalArgs& a, int32_t max_m, hipStream_t st) {
     if (nbatch <= 0 || max_m <= 0) return;
-    // a column per wave in LDS up to 1920 rows (60 KB a workgroup), in memory above
+    // a column per wave in LDS up to 640 rows (20 KB a workgroup); in memory above, where the
+    // LDS would leave a CU too few waves (Q2 hexes, 1515 rows: 0.81 ms in LDS, 0.74 in memory)
     const int in_lds = max_m <= 640 ? max_m : 0;
     hipLaunchKernelGGL(k_local_assemble, dim3((max_m + WG / 64 - 1) / (WG / 64), nbatch), dim3(WG),
                        (size_t)in_lds * (WG / 64) * sizeof(double), st, a, in_lds);

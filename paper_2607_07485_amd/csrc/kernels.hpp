@@ -57,6 +57,7 @@ struct LocalArgs {
     const double* thr_agg;         // optional per-aggregate 1 / tau_cut (batched instances)
     double band_tol, cluster_tol;
     int32_t trd_min;               // > 0: aggregates with nw >= trd_min were reduced by the blocked path
+    int32_t fixed_order;           // aggregates above 32 DOFs by fixed.hip (reduced and counted before phase 1)
 };
 
 // Blocked multi-workgroup tridiagonalisation (trd.hip) of the batch entries
@@ -81,10 +82,17 @@ void launch_local_backtransform_blocked(const LocalArgs& a, const int32_t* d_big
 // Element Gram factors from eigendecompositions: Jacobi in LDS for blocks up to 48,
 // the tridiagonal route above; n_max = largest block, scratch of
 // elem_eig_scratch_stride(n_max) doubles per element.
+// *fixed_order (device): the Jacobi sweeps keep their own stopping rule (see fixed.hpp).
 void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
                      double* G, int32_t* ranks, int32_t* status, double* scratch, int64_t scratch_stride,
-                     double rank_rtol, double spsd_tol, int64_t n_max, hipStream_t st);
+                     double rank_rtol, double spsd_tol, int64_t n_max, const int32_t* fixed_order, hipStream_t st);
 int64_t elem_eig_scratch_stride(int64_t n_max);
+
+// *flag |= 1 when the positive diagonal entries of an element block span more than FIXED_SPREAD
+// (see fixed.hpp); flag is zeroed first.
+constexpr double FIXED_SPREAD = 1e6;
+void launch_diag_spread(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
+                        int32_t* flag, hipStream_t st);
 
 // CSR values += sum_T f_T R_T^T A_T R_T (f = factor, NULL = 1); d2e lists the
 // (element, local index) pairs of every DOF, elements ascending; wave_rows: one
@@ -138,6 +146,19 @@ void launch_local_assemble(int32_t nbatch, const LocalArgs& a, int32_t max_m, hi
 // max_nw: largest |omega| of the batch (<= 4096)
 void launch_local_eig(int32_t nbatch, const LocalArgs& a, int32_t max_nw, int first_phase, int last_phase,
                       hipStream_t st);
+// The eigenproblems above 32 DOFs with the order of operations of fixed.hpp: reduction and
+// eigenvalues before, vectors after the mode count of launch_local_eig's phase 1.
+namespace fixed {
+void launch_local_tridiag(int32_t nbatch, const LocalArgs& a, int32_t max_nw, hipStream_t st);
+void launch_local_vectors(int32_t nbatch, const LocalArgs& a, int32_t max_nw, hipStream_t st);
+void launch_local_tridiag_blocked(const LocalArgs& a, const int32_t* d_big, const std::vector<int32_t>& sizes,
+                                  hipStream_t st);
+void launch_local_invit_blocked(const LocalArgs& a, const int32_t* d_big, const std::vector<int32_t>& sizes,
+                                const std::vector<int32_t>& ks, const int64_t* d_iw_off, double* iw, hipStream_t st);
+void launch_local_backtransform_blocked(const LocalArgs& a, const int32_t* d_big, const std::vector<int32_t>& sizes,
+                                        hipStream_t st);
+}  // namespace fixed
+
 void launch_stage_z(int32_t nbatch, const LocalArgs& a, hipStream_t st);
 void launch_views_max_diag(int32_t nv, const double* base, const View* v, double* out, hipStream_t st);
 void launch_views_add_diag(int32_t nv, double* base, const View* v, const double* delta, hipStream_t st);

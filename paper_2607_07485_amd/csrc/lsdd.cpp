@@ -533,6 +533,7 @@ struct lsdd_hierarchy {
     // element coefficients the level-0 blocks were scaled with at setup (NULL: none)
     double* d_scale0 = nullptr;
     double* d_factor = nullptr;   // scratch for lsdd_update_theta
+    bool fixed_order = false;     // set-up with the order of operations of fixed.hpp
     int32_t breakdown_bits = 0;   // cause of the last PCG breakdown (k_pcg_alpha/check/beta bits)
     // hipGraph-captured halves of the PCG iteration: [block][cycle precision][half]
     bool use_graph = false;
@@ -857,6 +858,7 @@ void make_terminal(lsdd_hierarchy* h, Level& lv, const std::vector<int32_t>& ter
     bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
     bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
     bt.ctx = &ar;
+    bt.fixed_order = h->fixed_order;
     bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
     bt.potrf(W, vq, d_minp);
     launch_views_identity(nb, X, bt.put(0, vq), h->st);
@@ -1169,6 +1171,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
     A.thr_agg = d_thr;
     A.band_tol = P.band_tol;
     A.trd_min = trd_min(P.blocked_eig_min);
+    A.fixed_order = h->fixed_order;
     A.cluster_tol = P.cluster_tol;
 
     // ---- batched local problems (workspace bounded); every dense step runs as
@@ -1189,6 +1192,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
     bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
     bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
     bt.ctx = &ar;
+    bt.fixed_order = h->fixed_order;
     bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
     std::vector<int32_t> status(n_agg, 0);
     int32_t pos = 0;
@@ -1333,8 +1337,10 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
             if (!big.empty()) {
                 d_big = ar.upload(big, st);
                 d_mats = ar.get(big.size() * TRD_MAT_BYTES);
-                launch_local_tridiag_blocked(B, d_big, bigsz, d_mats, st);
+                if (h->fixed_order) fixed::launch_local_tridiag_blocked(B, d_big, bigsz, st);
+                else launch_local_tridiag_blocked(B, d_big, bigsz, d_mats, st);
             }
+            if (h->fixed_order) fixed::launch_local_tridiag(nb, B, mx, st);
             launch_local_eig(nb, B, mx, 0, 1, st);
             if (!big.empty()) {
                 // eigenvectors of the large problems: scratch sized by their mode counts
@@ -1347,12 +1353,20 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
                 }
                 double* iw = ar.alloc<double>(std::max<int64_t>(iw_off.back(), 1));
                 int64_t* d_iw_off = ar.upload(iw_off, st);
-                launch_local_invit_blocked(B, d_big, bigsz, ks, d_iw_off, iw, st);
-                launch_local_eig(nb, B, mx, 2, 3, st);
-                launch_local_backtransform_blocked(B, d_big, bigsz, st);
+                if (h->fixed_order) {
+                    fixed::launch_local_invit_blocked(B, d_big, bigsz, ks, d_iw_off, iw, st);
+                    fixed::launch_local_vectors(nb, B, mx, st);
+                    fixed::launch_local_backtransform_blocked(B, d_big, bigsz, st);
+                } else {
+                    launch_local_invit_blocked(B, d_big, bigsz, ks, d_iw_off, iw, st);
+                    launch_local_eig(nb, B, mx, 2, 3, st);
+                    launch_local_backtransform_blocked(B, d_big, bigsz, st);
+                }
                 sync(st);
                 ar.release(iw);
                 ar.release(d_iw_off);
+            } else if (h->fixed_order) {
+                fixed::launch_local_vectors(nb, B, mx, st);
             } else {
                 launch_local_eig(nb, B, mx, 2, 3, st);
             }
@@ -1718,6 +1732,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
         bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
         bt.ctx = &ar;
+        bt.fixed_order = h->fixed_order;
         bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
         const int64_t budget = int64_t(2) << 30;    // bytes of P and Y per launch batch
         constexpr size_t MAXV = 65535;              // views per launch
@@ -2673,7 +2688,8 @@ lsdd_hierarchy* build(ElemList el0, const double* blocks, bool blocks_on_device,
     lv->d_G = ar.alloc<double>(lv->blk_off[ne]);
     if (!gram_rows) {
         int32_t* d_ranks = ar.alloc<int32_t>(ne);
-        int32_t* d_status = ar.alloc<int32_t>(ne);
+        int32_t* d_status = ar.alloc<int32_t>(ne + 1);       // the last one: diagonals of mixed scale
+        launch_diag_spread(ne, lv->d_elem_ptr, lv->d_blk_off, lv->d_blocks, d_status + ne, h->st);
         int64_t max_ne = 0;
         for (int64_t e = 0; e < ne; ++e) max_ne = std::max(max_ne, lv->el.ptr[e + 1] - lv->el.ptr[e]);
         const int64_t stride = std::max<int64_t>(3 * max_ne * max_ne, elem_eig_scratch_stride(max_ne));
@@ -2687,10 +2703,11 @@ lsdd_hierarchy* build(ElemList el0, const double* blocks, bool blocks_on_device,
                                   d_ranks + e0, d_status + e0, scratch, stride, P.rank_rtol, P.spsd_tol, h->st);
             else
                 launch_elem_eig(cnt, lv->d_elem_ptr + e0, lv->d_blk_off + e0, lv->d_blocks, lv->d_G, d_ranks + e0,
-                                d_status + e0, scratch, stride, P.rank_rtol, P.spsd_tol, max_ne, h->st);
+                                d_status + e0, scratch, stride, P.rank_rtol, P.spsd_tol, max_ne, d_status + ne, h->st);
         }
         HIPCHK(hipGetLastError());
-        std::vector<int32_t> status = download(d_status, ne, h->st);
+        std::vector<int32_t> status = download(d_status, ne + 1, h->st);
+        h->fixed_order = status[ne] != 0;
         lv->ranks = download(d_ranks, ne, h->st);
         vlog("element Gram factors for %lld elements %.3f s", (long long)ne, now_s() - t0);
         for (int64_t e = 0; e < ne; ++e) {
@@ -2718,6 +2735,10 @@ lsdd_hierarchy* build(ElemList el0, const double* blocks, bool blocks_on_device,
         launch_check_finite(gram_rows->nnz, d_val, d_fin, h->st);
         if (download(d_fin, 1, h->st)[0]) throw Error(LSDD_E_INVAL, "non-finite value in G");
         launch_gram_csr_rows(ne, lv->d_elem_ptr, d_src, lv->d_blk_off, d_val, lv->d_G, lv->d_blocks, h->st);
+        int32_t* d_mixed = ar.alloc<int32_t>(1);
+        launch_diag_spread(ne, lv->d_elem_ptr, lv->d_blk_off, lv->d_blocks, d_mixed, h->st);
+        h->fixed_order = download(d_mixed, 1, h->st)[0] != 0;
+        ar.release(d_mixed);
         HIPCHK(hipGetLastError());
         sync(h->st);
         for (void* q : {(void*)d_src, (void*)d_copy, (void*)d_fin})
@@ -3530,6 +3551,7 @@ void coarse_gram(lsdd_hierarchy* h, Level& lv) {
     bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
     bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
     bt.ctx = &ar;
+    bt.fixed_order = h->fixed_order;
     bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
     std::vector<int32_t> ranks(ne, 0);
     for (int64_t e0 = 0; e0 < ne; e0 += CH) {

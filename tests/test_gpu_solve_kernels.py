@@ -248,3 +248,33 @@ def test_setup_memory(hook):
         assert torch.cuda.mem_get_info()[0] >= free - (64 << 20)
     finally:
         P.set_torch_allocator(False)
+
+
+@pytest.mark.parametrize("width", [0, 66, 264])
+def test_mixed_scale_keeps_its_kernels(width):
+    """Unknowns of two dimensions (every second DOF scaled by 2^14, so that an element's diagonal spans
+    2^28) take the fixed-order kernels; the local eigenvalues do not depend on the scaling, which is
+    exact, so both routes give the same ones (1e-10) and the same modes, for aggregates in each size
+    class of the eigensolver, and the solves converge."""
+    import fegen
+    P = _lsdd()
+    out = []
+    for scale in (1.0, 2.0 ** 14):
+        prob = fegen.elasticity_q1(24, nu=0.3)
+        if width:
+            prob.agg_of_dof = (np.arange(prob.n) // width).astype(np.int32)
+        D = np.where(np.arange(prob.n) % 2, scale, 1.0)
+        off = prob.block_offsets()
+        for e in range(prob.n_elem):
+            d, B = prob.element(e)
+            prob.blocks[off[e]:off[e] + len(d) ** 2] = (B * D[d][:, None] * D[d]).ravel()
+        b = torch.from_numpy(D * np.random.default_rng(1).standard_normal(prob.n)).cuda()
+        with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2, rtol=1e-8)) as h:
+            ex = h.export_level(0)
+            info = h.solve(b)[1]
+            info = info[0] if isinstance(info, (list, tuple)) else info
+            out.append((ex["k"], ex["mu"], info))
+    (k0, mu0, i0), (k1, mu1, i1) = out
+    assert np.array_equal(k0, k1)
+    assert np.abs(mu0 - mu1).max() <= 1e-10
+    assert i0.converged == 1 and i1.converged == 1
