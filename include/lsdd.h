@@ -195,8 +195,8 @@ lsdd_status lsdd_update_theta(lsdd_hierarchy* h, const double* theta, void* hip_
  *              float64, the n_e x n_e blocks row-major, concatenated
  *   u, v       device float64[nrhs * ld]: vector k at offset k * ld
  *   nrhs >= 1, ld >= 1; out device float64[n_elem] (overwritten)
- * Allocates two small device arrays per call (elem_ptr and the block offsets);
- * blocks until the result is written. */
+ * Elements of different sizes: allocates a small device array per call (elem_ptr and
+ * the block offsets).  Blocks until the result is written. */
 lsdd_status lsdd_elem_bilinear(int64_t n_elem, const int64_t* elem_ptr, const int32_t* elem_dofs,
                                const double* blocks, const double* u, const double* v, int32_t nrhs,
                                int64_t ld, double scale, double* out, void* hip_stream);

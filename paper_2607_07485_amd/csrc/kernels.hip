@@ -463,32 +463,80 @@ __global__ void k_gram_csr_rows(int64_t n_elem, const int64_t* elem_ptr, const i
     }
 }
 
-// out[e] = u_e^T B_e v_e (B_e row-major n_e x n_e at blk_off[e]); one wave per
-// element: lane j sums u_i B_ij v_j over the rows i (coalesced row reads), then
-// a fixed-order wave reduction.
-__global__ void __launch_bounds__(WG) k_elem_bilinear(int64_t n_elem, const int64_t* elem_ptr,
-                                                      const int32_t* elem_dofs, const int64_t* blk_off,
-                                                      const double* blocks, const double* u, const double* v,
-                                                      int32_t nrhs, int64_t ld, double scale, double* out) {
-    const int lane = tid() & 63;
-    const int64_t e = (int64_t)blockIdx.x * (WG / 64) + (tid() >> 6);
-    if (e >= n_elem) return;
-    const int64_t base = elem_ptr[e];
-    const int ne = (int)(elem_ptr[e + 1] - base);
-    const double* B = blocks + blk_off[e];
+// Element bilinear forms out[e] = scale * sum_k u_k,e^T B_e v_k,e, P threads per element (a
+// workgroup, or a wave where all elements have at most 32 DOFs), KB vector pairs at a time.  A
+// group of n_e threads takes a row of B, the P / n_e groups every P / n_e-th one, so that a step
+// reads P consecutive entries whatever n_e is; a thread sums u_i B_ij over its rows, times v_j at
+// the end, then a fixed-order reduction.  u_e waits in LDS (u_cap entries a pair; 0: read where it
+// lies).  Elements of one size need no tables (elem_ptr NULL).  Bound by reading the blocks once:
+// 8000 blocks of 81 x 81 163 -> 90 us (a column per lane of a wave before: 17 of 64 lanes in
+// the second pass, and a chain of two dependent loads of u per row).
+template <int P, int KB>
+__global__ void __launch_bounds__(WG) k_elem_bilinear(int64_t n_elem, int32_t n_uni, const int64_t* __restrict__ elem_ptr,
+                                                      const int32_t* __restrict__ elem_dofs,
+                                                      const int64_t* __restrict__ blk_off,
+                                                      const double* __restrict__ blocks, const double* __restrict__ u,
+                                                      const double* __restrict__ v, int32_t nrhs, int64_t ld,
+                                                      double scale, int32_t u_cap, double* __restrict__ out) {
+    extern __shared__ double s_dyn[];
+    __shared__ double red[WG / 64];
+    const int t = tid() & (P - 1), slot = tid() / P;
+    const int64_t e = (int64_t)blockIdx.x * (WG / P) + slot;
+    if (e >= n_elem) return;                           // P = 64: whole waves; P = WG: never
+    const int64_t base = elem_ptr ? elem_ptr[e] : e * n_uni;
+    const int ne = elem_ptr ? (int)(elem_ptr[e + 1] - base) : n_uni;
+    const double* B = blocks + (elem_ptr ? blk_off[e] : e * n_uni * n_uni);
+    const int32_t* dofs = elem_dofs + base;
+    auto sync = [] {
+        if constexpr (P == WG) __syncthreads();
+        else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    double* su = s_dyn + (int64_t)slot * KB * u_cap;
+    const int w = min(ne, P), G = P / w, g = t / w, j = t - g * w;
     double acc = 0.0;
-    for (int32_t k = 0; k < nrhs; ++k) {
-        const double* uk = u + (int64_t)k * ld;
-        const double* vk = v + (int64_t)k * ld;
-        for (int j = lane; j < ne; j += 64) {
-            const double vj = vk[elem_dofs[base + j]];
-            double t = 0.0;
-            for (int i = 0; i < ne; ++i) t += uk[elem_dofs[base + i]] * B[(int64_t)i * ne + j];
-            acc += t * vj;
+    for (int32_t k0 = 0; k0 < nrhs; k0 += KB) {
+        if (u_cap) {
+            if (k0) sync();
+            for (int i = t; i < ne; i += P) {
+                const int32_t d = dofs[i];
+#pragma unroll
+                for (int q = 0; q < KB; ++q) su[q * u_cap + i] = k0 + q < nrhs ? u[(k0 + q) * ld + d] : 0.0;
+            }
+            sync();
         }
+        if (g < G)
+            for (int c = j; c < ne; c += w) {          // once, unless n_e > P
+                double s[KB] = {};
+                auto row = [&](int i, double b) {
+#pragma unroll
+                    for (int q = 0; q < KB; ++q) {
+                        const double x = u_cap ? su[q * u_cap + i] : (k0 + q < nrhs ? u[(k0 + q) * ld + dofs[i]] : 0.0);
+                        s[q] += x * b;
+                    }
+                };
+                constexpr int U = 8;
+                int i = g;
+                for (; i + (U - 1) * G < ne; i += U * G) {
+                    double b[U];
+#pragma unroll
+                    for (int r = 0; r < U; ++r) b[r] = B[(int64_t)(i + r * G) * ne + c];
+#pragma unroll
+                    for (int r = 0; r < U; ++r) row(i + r * G, b[r]);
+                }
+                for (; i < ne; i += G) row(i, B[(int64_t)i * ne + c]);
+                const int32_t d = dofs[c];
+#pragma unroll
+                for (int q = 0; q < KB; ++q)
+                    if (k0 + q < nrhs) acc += s[q] * v[(k0 + q) * ld + d];
+            }
     }
     acc = wave_sum(acc);
-    if (lane == 0) out[e] = scale * acc;
+    if constexpr (P == WG) {
+        if ((t & 63) == 0) red[t >> 6] = acc;
+        __syncthreads();
+        acc = (red[0] + red[1]) + (red[2] + red[3]);
+    }
+    if (t == 0) out[e] = scale * acc;
 }
 
 // ====================================================================== local problems
@@ -1696,12 +1744,21 @@ void launch_pack_elem_tri(int64_t n_elem, const int64_t* elem_ptr, const int64_t
                        n_elem, elem_ptr, blk_off, blocks, factor, tri_off, tri, tri32);
 }
 
-void launch_elem_bilinear(int64_t n_elem, const int64_t* elem_ptr, const int32_t* elem_dofs, const int64_t* blk_off,
-                          const double* blocks, const double* u, const double* v, int32_t nrhs, int64_t ld,
-                          double scale, double* out, hipStream_t st) {
+void launch_elem_bilinear(int64_t n_elem, int32_t n_uni, int32_t n_max, const int64_t* elem_ptr,
+                          const int32_t* elem_dofs, const int64_t* blk_off, const double* blocks, const double* u,
+                          const double* v, int32_t nrhs, int64_t ld, double scale, double* out, hipStream_t st) {
     if (n_elem <= 0) return;
-    hipLaunchKernelGGL(k_elem_bilinear, dim3(grid_for(n_elem * 64)), dim3(WG), 0, st, n_elem, elem_ptr, elem_dofs,
-                       blk_off, blocks, u, v, nrhs, ld, scale, out);
+    const int32_t cap = n_max <= 512 ? n_max : 0;
+    auto go = [&](auto kern, int per, int kb) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((n_elem + per - 1) / per)), dim3(WG),
+                           (size_t)per * kb * cap * sizeof(double), st, n_elem, n_uni, elem_ptr, elem_dofs, blk_off,
+                           blocks, u, v, nrhs, ld, scale, cap, out);
+    };
+    // a wave holds a 32 x 32 block in 16 steps; a workgroup there would have half its rows idle
+    if (n_max <= 32 && nrhs == 1) go(k_elem_bilinear<64, 1>, WG / 64, 1);
+    else if (n_max <= 32) go(k_elem_bilinear<64, 4>, WG / 64, 4);
+    else if (nrhs == 1) go(k_elem_bilinear<WG, 1>, 1, 1);
+    else go(k_elem_bilinear<WG, 4>, 1, 4);
 }
 
 // blk_off[e] = sum_{f < e} n_f^2 for n_f = elem_ptr[f + 1] - elem_ptr[f], e = 0 .. n_elem:

@@ -129,10 +129,11 @@ void launch_gram_rows(int64_t n_elem, const int64_t* perm_off, const int64_t* bl
                       const int32_t* perm, const int32_t* rank, double* G, hipStream_t st);
 // blocks of element e *= scale[e]
 void launch_scale_blocks(int64_t n_elem, const int64_t* blk_off, const double* scale, double* blocks, hipStream_t st);
-// out[e] = scale * sum_k u_{k,e}^T B_e v_{k,e} over nrhs vectors at stride ld
-void launch_elem_bilinear(int64_t n_elem, const int64_t* elem_ptr, const int32_t* elem_dofs, const int64_t* blk_off,
-                          const double* blocks, const double* u, const double* v, int32_t nrhs, int64_t ld,
-                          double scale, double* out, hipStream_t st);
+// out[e] = scale * sum_k u_{k,e}^T B_e v_{k,e} over nrhs vectors at stride ld; n_max: the largest
+// element; elem_ptr and blk_off NULL: every element has n_uni DOFs
+void launch_elem_bilinear(int64_t n_elem, int32_t n_uni, int32_t n_max, const int64_t* elem_ptr,
+                          const int32_t* elem_dofs, const int64_t* blk_off, const double* blocks, const double* u,
+                          const double* v, int32_t nrhs, int64_t ld, double scale, double* out, hipStream_t st);
 // blk_off[0 .. n_elem] = prefix sums of the squared element sizes (device elem_ptr)
 void launch_block_offsets(int64_t n_elem, const int64_t* elem_ptr, int64_t* blk_off, hipStream_t st);
 

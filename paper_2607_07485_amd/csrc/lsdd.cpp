@@ -107,11 +107,13 @@ struct Arena {
     std::map<char*, size_t> room;           // free ranges; neighbours in a chunk are one range
     size_t held = 0;                        // bytes of the chunks
     bool sealed = false;
+    const bool pool;
     char* pin = nullptr;                    // pinned buffer of the small uploads
     size_t pin_pos = 0;
     hipStream_t pin_st = nullptr;
 
-    Arena() = default;
+    // pool = false: every request an allocation of its own, uploads from where they lie
+    explicit Arena(bool pool_ = true) : pool(pool_) {}
     Arena(const Arena&) = delete;
     Arena& operator=(const Arena&) = delete;
     ~Arena() {
@@ -127,7 +129,7 @@ struct Arena {
         if (g_alloc) {
             p = g_alloc(bytes, g_alloc_ctx);
             if (!p) throw Error(LSDD_E_NOMEM, "allocator hook returned NULL for " + std::to_string(bytes) + " bytes");
-        } else if (bytes > POOL_MAX) {
+        } else if (!pool || bytes > POOL_MAX) {
             p = device(bytes);
         } else {
             pooled = true;
@@ -155,7 +157,7 @@ struct Arena {
     }
     // pinned room for one upload on st; nullptr: too large for it, or none to be had
     void* stage(size_t bytes, hipStream_t st) {
-        if (bytes > STAGE / 4) return nullptr;
+        if (!pool || bytes > STAGE / 4) return nullptr;
         if (!pin) {
             if (hipHostMalloc((void**)&pin, STAGE, hipHostMallocDefault) != hipSuccess) {
                 (void)hipGetLastError();
@@ -2797,6 +2799,26 @@ using namespace lsdd;
 
 // ====================================================================== C-ABI
 
+namespace {
+
+// sizes of a caller's elements (checked): the largest, and whether all are of that size
+struct ElemSizes {
+    int32_t n_max = 0;
+    bool uniform = true;
+};
+ElemSizes elem_sizes(int64_t n_elem, const int64_t* elem_ptr) {
+    ElemSizes z;
+    for (int64_t e = 0; e < n_elem; ++e) {
+        const int64_t s = elem_ptr[e + 1] - elem_ptr[e];
+        if (s < 1 || s > 4096) throw Error(LSDD_E_INVAL, "bad element size");
+        z.uniform = z.uniform && (e == 0 || s == z.n_max);
+        z.n_max = std::max(z.n_max, (int32_t)s);
+    }
+    return z;
+}
+
+}  // namespace
+
 extern "C" {
 
 void lsdd_params_default(lsdd_params* p) {
@@ -2930,21 +2952,23 @@ lsdd_status lsdd_elem_bilinear(int64_t n_elem, const int64_t* elem_ptr, const in
     if (n_elem < 1 || !elem_ptr || !elem_dofs || !blocks || !u || !v || !out || nrhs < 1 || ld < 1)
         throw Error(LSDD_E_INVAL, "bad argument");
     if (elem_ptr[0] != 0) throw Error(LSDD_E_INVAL, "elem_ptr[0] must be 0");
-    std::vector<int64_t> boff(n_elem + 1, 0);
-    for (int64_t e = 0; e < n_elem; ++e) {
-        const int64_t s = elem_ptr[e + 1] - elem_ptr[e];
-        if (s < 1 || s > 4096) throw Error(LSDD_E_INVAL, "bad element size");
-        boff[e + 1] = boff[e] + s * s;
-    }
+    const ElemSizes z = elem_sizes(n_elem, elem_ptr);
     hipStream_t st = (hipStream_t)hip_stream;
-    struct Scoped {
-        Arena a;
-        ~Scoped() { a.clear(); }
-    } sc;
-    const std::vector<int64_t> ptr(elem_ptr, elem_ptr + n_elem + 1);
-    int64_t* d_ptr = sc.a.upload(ptr, st);
-    int64_t* d_boff = sc.a.upload(boff, st);
-    launch_elem_bilinear(n_elem, d_ptr, elem_dofs, d_boff, blocks, u, v, nrhs, ld, scale, out, st);
+    Arena a(false);
+    if (z.uniform) {
+        launch_elem_bilinear(n_elem, z.n_max, z.n_max, nullptr, elem_dofs, nullptr, blocks, u, v, nrhs, ld, scale, out,
+                             st);
+    } else {
+        std::vector<int64_t> tab(elem_ptr, elem_ptr + n_elem + 1);
+        tab.resize(2 * (n_elem + 1), 0);
+        int64_t* boff = tab.data() + n_elem + 1;
+        for (int64_t e = 0; e < n_elem; ++e) {
+            const int64_t s = elem_ptr[e + 1] - elem_ptr[e];
+            boff[e + 1] = boff[e] + s * s;
+        }
+        const int64_t* d = a.upload(tab, st);
+        launch_elem_bilinear(n_elem, 0, z.n_max, d, elem_dofs, d + n_elem + 1, blocks, u, v, nrhs, ld, scale, out, st);
+    }
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     return LSDD_OK;
@@ -3106,18 +3130,20 @@ lsdd_status lsdd_elem_bilinear_noalloc(int64_t n_elem, const int64_t* elem_ptr, 
     if (n_elem > NOALLOC_MAX_ELEM)
         throw Error(LSDD_E_UNSUPPORTED, "lsdd_elem_bilinear_noalloc: more than 1048576 elements");
     if (elem_ptr[0] != 0) throw Error(LSDD_E_INVAL, "elem_ptr[0] must be 0");
-    for (int64_t e = 0; e < n_elem; ++e) {
-        const int64_t m = elem_ptr[e + 1] - elem_ptr[e];
-        if (m < 1 || m > 4096) throw Error(LSDD_E_INVAL, "bad element size");
-    }
-    int64_t* scr = nullptr;
-    HIPCHK(noalloc_scratch(&scr));
+    const ElemSizes z = elem_sizes(n_elem, elem_ptr);
     hipStream_t st = (hipStream_t)hip_stream;
-    int64_t* d_ptr = scr;
-    int64_t* d_boff = scr + (n_elem + 1);
-    HIPCHK(hipMemcpyAsync(d_ptr, elem_ptr, (size_t)(n_elem + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    launch_block_offsets(n_elem, d_ptr, d_boff, st);
-    launch_elem_bilinear(n_elem, d_ptr, elem_dofs, d_boff, blocks, u, v, nrhs, ld, scale, out, st);
+    if (z.uniform) {
+        launch_elem_bilinear(n_elem, z.n_max, z.n_max, nullptr, elem_dofs, nullptr, blocks, u, v, nrhs, ld, scale, out,
+                             st);
+    } else {
+        int64_t* scr = nullptr;
+        HIPCHK(noalloc_scratch(&scr));
+        int64_t* d_ptr = scr;
+        int64_t* d_boff = scr + (n_elem + 1);
+        HIPCHK(hipMemcpyAsync(d_ptr, elem_ptr, (size_t)(n_elem + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
+        launch_block_offsets(n_elem, d_ptr, d_boff, st);
+        launch_elem_bilinear(n_elem, 0, z.n_max, d_ptr, elem_dofs, d_boff, blocks, u, v, nrhs, ld, scale, out, st);
+    }
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     return LSDD_OK;

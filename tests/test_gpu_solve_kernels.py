@@ -278,3 +278,25 @@ def test_mixed_scale_keeps_its_kernels(width):
     assert np.array_equal(k0, k1)
     assert np.abs(mu0 - mu1).max() <= 1e-10
     assert i0.converged == 1 and i1.converged == 1
+
+
+@pytest.mark.parametrize("nrhs", [1, 3, 5])
+@pytest.mark.parametrize("sizes", [[1], [8] * 70, [32] * 5, [33] * 5, [81] * 9, [256] * 3, [257] * 2, [513] * 2,
+                                   [2, 31, 1, 32, 7], [300, 1, 257, 64, 600, 33]])
+def test_element_contraction_sizes(sizes, nrhs):
+    """Waves and workgroups per element, several elements and partial groups of them, rows in LDS and
+    in memory, equal and mixed sizes; a sum of n^2 nrhs terms in any order is within 2 n eps of
+    the sum of their magnitudes (n + n partial sums deep at most)."""
+    P = _lsdd()
+    rng = np.random.default_rng(len(sizes) + nrhs)
+    ptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    dofs = rng.integers(0, 700, ptr[-1]).astype(np.int32)
+    blocks = [rng.standard_normal((n, n)) for n in sizes]
+    u, v = rng.standard_normal((2, nrhs, 700))
+    out = P.elem_bilinear(ptr, torch.from_numpy(dofs).cuda(), torch.from_numpy(np.concatenate([b.ravel() for b in blocks])).cuda(),
+                          torch.from_numpy(u).cuda(), torch.from_numpy(v).cuda(), scale=-2.0).cpu().numpy()
+    for e, (n, B) in enumerate(zip(sizes, blocks)):
+        d = dofs[ptr[e]:ptr[e + 1]]
+        want = -2.0 * sum(u[k, d] @ B @ v[k, d] for k in range(nrhs))
+        size = 2.0 * sum(np.abs(u[k, d]) @ np.abs(B) @ np.abs(v[k, d]) for k in range(nrhs))
+        assert abs(out[e] - want) <= 2 * (n + nrhs) * np.finfo(float).eps * size
