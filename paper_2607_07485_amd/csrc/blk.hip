@@ -577,6 +577,79 @@ __global__ void __launch_bounds__(64) k_small_sub(int32_t s0, int32_t n_sub, con
     }
 }
 
+// The same for NB right-hand sides in FP32 on the matrix cores, y^T = x^T A with A from the packed
+// triangle: 16 rows of A, four columns at a time, against four rows of x (8 of the 16 rows of x^T
+// carry right-hand sides).  With a lane per row a step took an entry of A and two 16-byte rows of
+// x from LDS, whose one pipe the CU's waves share, for 8 products a lane; here it takes an entry
+// of each for 16 x 16 x 4.  The transposed product leaves a row's right-hand sides in a lane, four
+// at a time, as they lie in x.  The data go to LDS without registers in between, so that a CU
+// holds the wave of every subdomain at once (with the next one's loads waiting in registers 12
+// waves, 3530 subdomains on 3072 of them: nearly two full rounds).  3500 overlaps of up to 50
+// DOFs: 12.9 -> 9.7 us.
+// cnt consecutive values from memory to LDS without passing through registers
+__device__ inline void wave_to_lds(const float* src, float* dst, int cnt) {
+    for (int g = 0; g < cnt; g += 64)
+        if (g + tid() < cnt)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + g + tid()),
+                                             (__attribute__((address_space(3))) void*)(dst + g), 4, 0, 0);
+}
+
+__global__ void __launch_bounds__(64) k_small_sub_mm(int32_t s0, const int64_t* sub_off, const int32_t* sub_dofs,
+                                                     const int64_t* pk_off, const float* pk, const float* rloc, float* x,
+                                                     int max_m) {
+    using Acc = float __attribute__((ext_vector_type(4)));
+    static_assert(NB == 8, "a lane of the first two groups of 16 holds four right-hand sides of a row");
+    constexpr int RT = (SMALL_M + 15) / 16;
+    extern __shared__ __align__(16) unsigned char s_small[];
+    float* s_a = reinterpret_cast<float*>(s_small);
+    float* s_x = s_a + max_m * (max_m + 1) / 2;        // rows up to a multiple of four, zero past m
+    const int lane = tid(), c = lane & 15, q = lane >> 4;
+    const int64_t sb = s0 + (int64_t)blockIdx.x;
+    const int64_t o = sub_off[sb];
+    const int m = (int)(sub_off[sb + 1] - o);
+    if (m < 1) return;
+    const int m4 = (m + 3) & ~3;
+    if (lane < (m4 - m) * NB) s_x[m * NB + lane] = 0;  // before the copies, which a later store would wait for
+    // DOFs of the rows this lane writes; rows >= m read a valid entry and store nothing
+    int32_t d[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) d[t] = sub_dofs[o + min(16 * t + c, m - 1)];
+    wave_to_lds(rloc + o * NB, s_x, m * NB);
+    wave_to_lds(pk + pk_off[sb], s_a, m * (m + 1) / 2);
+    // and their current x (a masked entry reads x[0])
+    float4 xo[RT];
+    const bool writes = q < 2;
+    if (writes)
+#pragma unroll
+        for (int t = 0; t < RT; ++t) xo[t] = *reinterpret_cast<const float4*>(x + (int64_t)max(d[t], 0) * NB + 4 * q);
+    Acc y[RT];
+    int ri[RT], ti[RT];                                // this lane's row of A in every row tile
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        y[t] = Acc{0, 0, 0, 0};
+        ri[t] = min(16 * t + c, m - 1);
+        ti[t] = ri[t] * (ri[t] + 1) / 2;
+    }
+    __builtin_amdgcn_s_waitcnt(0);                     // the copies to LDS are done
+    __syncthreads();
+#pragma unroll 2
+    for (int k = 0; k < m4; k += 4) {
+        const int j = min(k + q, m - 1), tj = j * (j + 1) / 2;
+        const float b = s_x[(k + q) * NB + (c & (NB - 1))];
+        float a[RT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) a[t] = s_a[j <= ri[t] ? ti[t] + j : tj + ri[t]];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) y[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(b, a[t], y[t], 0, 0, 0);
+    }
+    if (writes)
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+            if (16 * t + c < m && d[t] >= 0)
+                *reinterpret_cast<float4*>(x + (int64_t)d[t] * NB + 4 * q) =
+                    make_float4(xo[t].x + y[t][0], xo[t].y + y[t][1], xo[t].z + y[t][2], xo[t].w + y[t][3]);
+}
+
 // Transfers for aggregates with |omega| <= SMALL_M, one thread per coarse DOF for
 // the restriction and per aggregate entry for the prolongation, each for all NR
 // right-hand sides (the index and the Z entry are loaded once for the NR products;
@@ -1329,9 +1402,21 @@ void launch_small_sub(int64_t s0, int64_t n_sub, const int64_t* sub_off, const i
     if (n_sub <= 0) return;
     if (max_m < 1 || max_m > SMALL_M) throw std::runtime_error("launch_small_sub: max_m outside 1 .. SMALL_M");
     if (n_sub > INT32_MAX) throw std::runtime_error("launch_small_sub: more than 2^31 - 1 subdomains");
-    const size_t lds = ((size_t)max_m * (max_m + 1) / 2 + (fact ? 2 : 1) * (size_t)max_m * NR) * sizeof(T);
+    const int max_x = NR == NB ? (max_m + 3) & ~3 : max_m;
+    const size_t lds = ((size_t)max_m * (max_m + 1) / 2 + (fact ? 2 : 1) * (size_t)max_x * NR) * sizeof(T);
     // persistent waves: as many as fit on the device at once (LDS or registers bound)
-    auto kern = fact ? &k_small_sub<T, NR, true> : &k_small_sub<T, NR, false>;
+    // FP32 blocks on the matrix cores; in FP64, where a step of theirs takes twice the time for
+    // half the data, the row form is faster (3500 overlaps 24.3 against 26.4 us, 24 of them 8.6
+    // against 9.7)
+    if constexpr (NR == NB && sizeof(T) == 4)
+        if (!fact) {
+            hipLaunchKernelGGL(k_small_sub_mm, dim3((unsigned)n_sub), dim3(64), lds, st, (int32_t)s0, sub_off,
+                               sub_dofs, pk_off, pk, rloc, x, max_m);
+            return;
+        }
+    auto kern = &k_small_sub<T, NR, true>;
+    if constexpr (NR != NB || sizeof(T) != 4)
+        if (!fact) kern = &k_small_sub<T, NR, false>;
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern), 64, lds) !=
             hipSuccess ||

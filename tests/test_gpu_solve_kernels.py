@@ -300,3 +300,22 @@ def test_element_contraction_sizes(sizes, nrhs):
         want = -2.0 * sum(u[k, d] @ B @ v[k, d] for k in range(nrhs))
         size = 2.0 * sum(np.abs(u[k, d]) @ np.abs(B) @ np.abs(v[k, d]) for k in range(nrhs))
         assert abs(out[e] - want) <= 2 * (n + nrhs) * np.finfo(float).eps * size
+
+
+@pytest.mark.parametrize("width", [1, 2, 3, 13, 14, 15, 29, 30, 31, 45, 46, 47, 61, 62])
+def test_small_overlaps_fp32_blocks(width):
+    """Overlaps of width + 2 DOFs (one less at the ends) around the 4- and 16-wide steps, FP32 cycle, 8
+    right-hand sides: the preconditioner is the FP64 one's up to FP32 rounding, so PCG to 1e-6 takes
+    as many iterations, give or take one."""
+    P = _lsdd()
+    prob = _chain(5 * width + max(1, width // 2))
+    prob.agg_of_dof = (np.arange(prob.n) // width).astype(np.int32)
+    B = torch.from_numpy(np.random.default_rng(width).standard_normal((8, prob.n))).cuda()
+    its = []
+    for precision in (0, 1):
+        with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2, min_coarse=1, max_density=1.0, rtol=1e-6,
+                                                              precision=precision)) as h:
+            assert h.info()["levels"] == 2
+            its.append([f.iters for f in h.solve(B)[1]])
+            assert all(f.converged == 1 for f in h.solve(B)[1])
+    assert max(abs(a - b) for a, b in zip(*its)) <= 1
