@@ -4,11 +4,12 @@
 // (values with first and mixed derivatives).  Their coarse interface blocks have spectra that
 // decay down to the rounding, so that from the third level on the retained modes, and with
 // them the V-cycle, are determined by the rounding of the set-up: on Hermite bicubics (spread
-// 5e9 and more) any other order of the same sums, even in the 64-wide tile steps alone, moves a
-// V-cycle by 1e-6 to 1e-4, on elements with a spread of up to 4e2 by 1e-10 at most 20 sizes
-// out of 22 and 2e-9 at most.  Such hierarchies keep these kernels, bit for bit, and the
-// vectors and numbers they always gave; all others take the faster ones (trd.hip, invit.hpp,
-// tile64.hpp; set-up and solve of grad-div 40^2 126 ms here, 74 there).
+// 5e9 and more) any other order of the same sums, even in the diagonal-tile steps alone, moves a
+// V-cycle by 1e-6 to 1e-4; on elements with a spread of up to 4e2 by 1e-13 to 1.3e-10, at one
+// of 28 sizes by 1e-9.  Such hierarchies keep these kernels, bit for bit, and the vectors and
+// numbers they always gave; all others take the faster ones of trd.hip, invit.hpp and tile64.hpp
+// (inverse iteration for 8 matrices of up to 882 with 179 vectors 15.4 ms here, 4.6 there;
+// eigenvalues 4.9 and 1.05; a diagonal tile 48 and 17.5 us).
 #pragma once
 #include <hip/hip_runtime.h>
 

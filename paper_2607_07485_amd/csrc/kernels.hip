@@ -645,7 +645,6 @@ __global__ void __launch_bounds__(WG) k_local_eig(LocalArgs A) {
     const int nw = (int)(A.agg_ptr[ag + 1] - A.agg_ptr[ag]);
     double* W1 = A.w1 + A.ws_off[b];
     double* S = A.s_buf + A.sq_off[b];
-    double* V = A.v_buf + A.sq_off[b];
     double* T = A.t_buf + A.t_off[b];
     double* mu = A.mu + A.mu_off[ag];
     double* VS = W1;

@@ -39,7 +39,7 @@ struct LocalArgs {
     double* w2;                    // A_Omega, then its Cholesky factor
     const int64_t* sq_off;         // per batch entry: offset of its nw x nw slots
     double* s_buf;                 // S~, then C
-    double* v_buf;                 // Jacobi eigenvectors
+    double* v_buf;                 // V and W panels of the blocked reduction
     const int64_t* t_off;          // per batch entry: tridiagonal data + inverse-iteration scratch
     double* t_buf;
     // outputs
