@@ -632,7 +632,6 @@ __global__ void __launch_bounds__(64) k_small_sub_mm(int32_t s0, const int64_t* 
     }
     __builtin_amdgcn_s_waitcnt(0);                     // the copies to LDS are done
     __syncthreads();
-#pragma unroll 2
     for (int k = 0; k < m4; k += 4) {
         const int j = min(k + q, m - 1), tj = j * (j + 1) / 2;
         const float b = s_x[(k + q) * NB + (c & (NB - 1))];
