@@ -5,8 +5,9 @@
 // the tails of its launches: residual rows, local product and partial sums took 3 to 10 us
 // each, three launches a colour.  Here one workgroup carries a subdomain (an aggregate)
 // from its residual rows through LDS to its update, so that a colour, a restriction and a
-// prolongation are one launch each.  Subdomains of one colour share no element, so none of
-// them reads an x that another one of the launch writes.
+// prolongation are one launch each.  The colour kernel is for classes whose subdomains share
+// no element (a colouring of the overlaps), so that none of them reads an x that another one
+// of the launch writes; block Jacobi's one class of aggregates is none.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

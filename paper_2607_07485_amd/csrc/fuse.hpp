@@ -38,8 +38,8 @@ struct AggItem {
 void launch_row_table(int64_t n_sub, const int64_t* off, const int32_t* dofs, const int64_t* rowptr,
                       const int64_t* scoff, int pad, int4* tab, hipStream_t st);
 
-// x[Omega] += A_Omega^{-1} (r - A x)[Omega] for n_sub subdomains of one colour; rows: their
-// row tables (pad a multiple of 64, <= FUSE_M), row_len: average entries per row of A;
+// x[Omega] += A_Omega^{-1} (r - A x)[Omega] for n_sub subdomains no two of which share an
+// element (x is read and written in one launch); rows: their row tables (pad a multiple of 64, <= FUSE_M), row_len: average entries per row of A;
 // x_zero: x is zero
 template <typename T>
 void launch_colour_step(int64_t n_sub, const SubItem* items, const int4* rows, const int32_t* col, const T* val,

@@ -933,7 +933,9 @@ bool build_fused(lsdd_hierarchy* h, Level& lv, const std::vector<int64_t>& sw_tp
     const int64_t rows = lv.sw_sub_off[n_sub];
     const double full_max = *std::max_element(full.begin(), full.end());
     if (lv.nnz > INT32_MAX || rows > INT32_MAX || lv.coff[n_sub] > INT32_MAX) return false;
-    lv.fuse_has[1] = lv.spad <= FUSE_M;
+    // one launch per colour reads neighbours' x while others write theirs: only where the
+    // classes are a colouring (block Jacobi has one class of aggregates that share elements)
+    lv.fuse_has[1] = lv.smoother == 0 && lv.spad <= FUSE_M;
     lv.fuse_has[2] = full_max <= FULL_MAX_COLOUR;
     if (!lv.fuse_has[1] && !lv.fuse_has[2]) return false;
     lv.row_len = (int32_t)(lv.nnz / std::max<int64_t>(lv.n, 1));
