@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <map>
 #include <memory>
 #include <stdexcept>
@@ -2803,6 +2804,17 @@ using namespace lsdd;
 
 namespace {
 
+// A call that fails with work of its own queued waits for it: the caller may go on with the
+// hierarchy on another stream, or destroy it.
+struct IdleOnError {
+    hipStream_t st;
+    const int before = std::uncaught_exceptions();
+    explicit IdleOnError(hipStream_t s) : st(s) {}
+    ~IdleOnError() {
+        if (std::uncaught_exceptions() > before) (void)hipStreamSynchronize(st);
+    }
+};
+
 // sizes of a caller's elements (checked): the largest, and whether all are of that size
 struct ElemSizes {
     int32_t n_max = 0;
@@ -3169,6 +3181,7 @@ lsdd_status lsdd_solve(lsdd_hierarchy* h, const double* b, double* x, int32_t nr
     if (nrhs > 1 && h->cycle_prec == 2) throw Error(LSDD_E_UNSUPPORTED, "the mixed cycle runs single right-hand sides only");
     h->st = (hipStream_t)hip_stream;
     hipStream_t st = h->st;
+    const IdleOnError idle(st);           // a refused right-hand side is found with the next cycle queued
     const int64_t n = h->L[0]->n;
     const int32_t nseg = h->seg[0].n_seg;
     const double t0 = now_s();

@@ -44,3 +44,32 @@ def test_smoothers_without_a_colouring(smoother, tuned):
         assert abs(float(s @ z - r @ zs)) <= 1e-10 * float(s.norm() * z.norm())
         _separate(h)
         assert float((h.vcycle(r) - z).norm()) <= 1e-10 * float(z.norm())
+
+
+@pytest.mark.parametrize("nrhs", [1, 8])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_refused_solve_leaves_its_stream_idle(nrhs, precision):
+    """A right-hand side with a NaN is found after the next cycle is queued; the call returns when that
+    has ended, so that a solve on another stream has the hierarchy's vectors to itself."""
+    P = _lsdd()
+    prob = fegen.elasticity_q1(96, nu=0.3)
+    rng = np.random.default_rng(3)
+    shape = (prob.n,) if nrhs == 1 else (nrhs, prob.n)
+    good = torch.from_numpy(rng.standard_normal(shape)).cuda()
+    bad = good.clone()
+    bad.view(-1)[-1] = float("nan")
+    prm = P.Params.default(max_levels=3, tau_const=0.75, precision=precision)
+    with P.Hierarchy.setup_problem(prob, prm) as h:
+        ref = h.solve(good)[0]
+    sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with P.Hierarchy.setup_problem(prob, prm) as h:
+        for _ in range(3):
+            with torch.cuda.stream(sa):
+                with pytest.raises(P.LsddError):
+                    h.solve(bad)
+                assert sa.query()
+            with torch.cuda.stream(sb):
+                x = h.solve(good)[0]
+            sb.synchronize()
+            assert torch.equal(x, ref)
