@@ -43,7 +43,6 @@ bool take_launch_events(hipEvent_t* start, hipEvent_t* stop) {
 namespace {
 
 constexpr int WG = LSDD_WG;
-constexpr int NE_LDS = 48;          // element blocks up to this size stay in LDS
 
 inline unsigned grid_for(int64_t n, int per_block = WG) {
     int64_t g = (n + per_block - 1) / per_block;
@@ -96,7 +95,7 @@ __global__ void __launch_bounds__(WG) k_elem_eig(const int64_t* elem_ptr, const 
                                                  const double* blocks, double* G, int32_t* ranks,
                                                  int32_t* status, double* scratch, int64_t scratch_stride,
                                                  double rank_rtol, double spsd_tol, int64_t lds_bytes,
-                                                 const int32_t* fixed_order) {
+                                                 ElemFixed fixed_order) {
     extern __shared__ double s_dyn[];
     __shared__ double s_w[128];
     __shared__ int s_rank[128];
@@ -129,7 +128,7 @@ __global__ void __launch_bounds__(WG) k_elem_eig(const int64_t* elem_ptr, const 
         return;
     }
     wg_identity(v, ld, n);
-    wg_jacobi(a, ld, n, v, ld, 60, 1e-15, 1e-18 * amax, *fixed_order ? 0.0 : DBL_EPSILON * amax, s_pairs, s_cs, &s_flag);
+    wg_jacobi(a, ld, n, v, ld, 60, 1e-15, 1e-18 * amax, fixed_order(e) ? 0.0 : DBL_EPSILON * amax, s_pairs, s_cs, &s_flag);
     wg_sort_eig(a, ld, v, ld, n, s_w, vs, n, s_rank);
     const double lmax = fmax(s_w[n - 1], 0.0);
     if (s_w[0] < -spsd_tol * lmax) {
@@ -156,10 +155,10 @@ __global__ void __launch_bounds__(WG) k_elem_eig(const int64_t* elem_ptr, const 
     }
 }
 
-// A thread per element: flags a block whose positive diagonal entries span more than
-// FIXED_SPREAD.
+// A thread per element: flags the instance of a block whose positive diagonal entries span more
+// than FIXED_SPREAD.
 __global__ void k_diag_spread(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
-                              int32_t* flag) {
+                              const int32_t* elem_inst, int32_t* flag) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n_elem) return;
     const int64_t n = elem_ptr[e + 1] - elem_ptr[e];
@@ -172,7 +171,7 @@ __global__ void k_diag_spread(int64_t n_elem, const int64_t* elem_ptr, const int
             hi = fmax(hi, d);
         }
     }
-    if (hi > 0.0 && hi > FIXED_SPREAD * lo) atomicOr(flag, 1);
+    if (hi > 0.0 && hi > FIXED_SPREAD * lo) atomicOr(flag + (elem_inst ? elem_inst[e] : 0), 1);
 }
 
 // Element blocks larger than NE_LDS, one workgroup per element: the same outputs
@@ -1624,7 +1623,7 @@ __global__ void k_check_finite(int64_t n, const double* a, int32_t* flag) {
 
 void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks, double* G,
                      int32_t* ranks, int32_t* status, double* scratch, int64_t scratch_stride, double rank_rtol,
-                     double spsd_tol, int64_t n_max, const int32_t* fixed_order, hipStream_t st) {
+                     double spsd_tol, int64_t n_max, ElemFixed fixed_order, hipStream_t st) {
     if (n_elem <= 0) return;
     // blocks up to NE_LDS: Jacobi with matrix and vectors in LDS; larger blocks: the
     // tridiagonal route (k_elem_eig_trd; 81 x 81 Q2 blocks: Jacobi took 0.67 s)
@@ -1647,11 +1646,11 @@ void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk
 }
 
 void launch_diag_spread(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
-                        int32_t* flag, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero<int32_t>, dim3(1), dim3(WG), 0, st, (int64_t)1, flag);
+                        const int32_t* elem_inst, int32_t n_inst, int32_t* flag, hipStream_t st) {
+    hipLaunchKernelGGL(k_zero<int32_t>, dim3(grid_for(n_inst)), dim3(WG), 0, st, (int64_t)n_inst, flag);
     if (n_elem > 0)
         hipLaunchKernelGGL(k_diag_spread, dim3((unsigned)((n_elem + 63) / 64)), dim3(64), 0, st, n_elem, elem_ptr,
-                           blk_off, blocks, flag);
+                           blk_off, blocks, elem_inst, flag);
 }
 
 int64_t elem_eig_scratch_stride(int64_t n_max) {

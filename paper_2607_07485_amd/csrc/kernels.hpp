@@ -57,7 +57,7 @@ struct LocalArgs {
     const double* thr_agg;         // optional per-aggregate 1 / tau_cut (batched instances)
     double band_tol, cluster_tol;
     int32_t trd_min;               // > 0: aggregates with nw >= trd_min were reduced by the blocked path
-    int32_t fixed_order;           // aggregates above 32 DOFs by fixed.hip (reduced and counted before phase 1)
+    int32_t fixed_order;           // the batch's aggregates by fixed.hip (above 32 DOFs reduced and counted before phase 1)
 };
 
 // Blocked multi-workgroup tridiagonalisation (trd.hip) of the batch entries
@@ -79,20 +79,28 @@ void launch_local_invit_blocked(const LocalArgs& a, const int32_t* d_big, const 
 void launch_local_backtransform_blocked(const LocalArgs& a, const int32_t* d_big, const std::vector<int32_t>& sizes,
                                         hipStream_t st);
 
-// Element Gram factors from eigendecompositions: Jacobi in LDS for blocks up to 48,
+constexpr int NE_LDS = 48;          // element blocks up to this size stay in LDS
+
+// Element Gram factors from eigendecompositions: Jacobi in LDS for blocks up to NE_LDS,
 // the tridiagonal route above; n_max = largest block, scratch of
 // elem_eig_scratch_stride(n_max) doubles per element.
-// *fixed_order (device): the Jacobi sweeps keep their own stopping rule (see fixed.hpp).
+// fixed_order: instances whose elements keep the order of operations of fixed.hpp (blocks up to
+// NE_LDS).
+struct ElemFixed {
+    const int32_t* flag;           // per instance
+    const int32_t* inst;           // instance of an element, NULL: all in the first
+    __host__ __device__ bool operator()(int64_t e) const { return flag[inst ? inst[e] : 0] != 0; }
+};
 void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
                      double* G, int32_t* ranks, int32_t* status, double* scratch, int64_t scratch_stride,
-                     double rank_rtol, double spsd_tol, int64_t n_max, const int32_t* fixed_order, hipStream_t st);
+                     double rank_rtol, double spsd_tol, int64_t n_max, ElemFixed fixed_order, hipStream_t st);
 int64_t elem_eig_scratch_stride(int64_t n_max);
 
-// *flag |= 1 when the positive diagonal entries of an element block span more than FIXED_SPREAD
-// (see fixed.hpp); flag is zeroed first.
+// flag[i] = 1 when the positive diagonal entries of an element block of instance i span more than
+// FIXED_SPREAD (see fixed.hpp), else 0; elem_inst: instance of an element, NULL: one instance.
 constexpr double FIXED_SPREAD = 1e6;
 void launch_diag_spread(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
-                        int32_t* flag, hipStream_t st);
+                        const int32_t* elem_inst, int32_t n_inst, int32_t* flag, hipStream_t st);
 
 // CSR values += sum_T f_T R_T^T A_T R_T (f = factor, NULL = 1); d2e lists the
 // (element, local index) pairs of every DOF, elements ascending; wave_rows: one

@@ -536,7 +536,7 @@ struct lsdd_hierarchy {
     // element coefficients the level-0 blocks were scaled with at setup (NULL: none)
     double* d_scale0 = nullptr;
     double* d_factor = nullptr;   // scratch for lsdd_update_theta
-    bool fixed_order = false;     // set-up with the order of operations of fixed.hpp
+    std::vector<char> fixed_inst; // instances set up with the order of operations of fixed.hpp
     int32_t breakdown_bits = 0;   // cause of the last PCG breakdown (k_pcg_alpha/check/beta bits)
     // hipGraph-captured halves of the PCG iteration: [block][cycle precision][half]
     bool use_graph = false;
@@ -861,13 +861,25 @@ void make_terminal(lsdd_hierarchy* h, Level& lv, const std::vector<int32_t>& ter
     bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
     bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
     bt.ctx = &ar;
-    bt.fixed_order = h->fixed_order;
     bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
-    bt.potrf(W, vq, d_minp);
-    launch_views_identity(nb, X, bt.put(0, vq), h->st);
-    bt.trsm(W, vq, X, vq, false, true);
-    bt.gemm_tn(X, vq, X, vq, nullptr, vq, 0.0, W, vq, -1.0, true, true);
-    std::vector<double> minp = download(d_minp, nb, h->st);
+    std::vector<double> minp(nb);
+    for (const bool fixed : {false, true}) {
+        std::vector<View> v;
+        std::vector<int32_t> of;
+        for (int32_t q = 0; q < nb; ++q)
+            if ((bool)h->fixed_inst[term[q]] == fixed) {
+                v.push_back(vq[q]);
+                of.push_back(q);
+            }
+        if (v.empty()) continue;
+        bt.fixed_order = fixed;
+        bt.potrf(W, v, d_minp);
+        launch_views_identity((int32_t)v.size(), X, bt.put(0, v), h->st);
+        bt.trsm(W, v, X, v, false, true);
+        bt.gemm_tn(X, v, X, v, nullptr, v, 0.0, W, v, -1.0, true, true);
+        const std::vector<double> mp = download(d_minp, v.size(), h->st);
+        for (size_t t = 0; t < of.size(); ++t) minp[of[t]] = mp[t];
+    }
     bt.free_all();
     vlog("level %d: %d terminal block(s), %lld DOFs, dense Cholesky + inverse %.3f s", lv.level, nb,
          (long long)lv.term_len, now_s() - t0);
@@ -1176,7 +1188,6 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
     A.thr_agg = d_thr;
     A.band_tol = P.band_tol;
     A.trd_min = trd_min(P.blocked_eig_min);
-    A.fixed_order = h->fixed_order;
     A.cluster_tol = P.cluster_tol;
 
     // ---- batched local problems (workspace bounded); every dense step runs as
@@ -1197,7 +1208,6 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
     bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
     bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
     bt.ctx = &ar;
-    bt.fixed_order = h->fixed_order;
     bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
     std::vector<int32_t> status(n_agg, 0);
     int32_t pos = 0;
@@ -1205,7 +1215,9 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         std::vector<int64_t> ws_off(1, 0), sq_off(1, 0), t_off(1, 0);
         int32_t end = pos;
         int64_t bytes = 0;
-        while (end < n_agg && (end - pos) < 32768) {
+        // instances in the order of operations of fixed.hpp have batches of their own
+        const bool fixed = h->fixed_inst[inst_of_agg[pos]];
+        while (end < n_agg && (end - pos) < 32768 && (bool)h->fixed_inst[inst_of_agg[end]] == fixed) {
             int64_t m = C.sub_ptr[end + 1] - C.sub_ptr[end], nw = C.agg_ptr[end + 1] - C.agg_ptr[end];
             int64_t tl = 3 * nw + invit_ws(nw);
             int64_t need = (2 * m * m + 2 * nw * nw + tl) * 8;
@@ -1217,6 +1229,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
             ++end;
         }
         const int32_t nb = end - pos;
+        bt.fixed_order = fixed;
         double* w1 = ar.alloc<double>(ws_off.back());
         double* w2 = ar.alloc<double>(ws_off.back());
         double* sb = ar.alloc<double>(sq_off.back());
@@ -1232,6 +1245,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         double* d_minp = ar.alloc<double>(nb);
         LocalArgs B = A;
         B.first = pos;
+        B.fixed_order = fixed;
         B.agg_list = nullptr;
         B.ws_off = d_ws;
         B.w1 = w1;
@@ -1342,10 +1356,10 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
             if (!big.empty()) {
                 d_big = ar.upload(big, st);
                 d_mats = ar.get(big.size() * TRD_MAT_BYTES);
-                if (h->fixed_order) fixed::launch_local_tridiag_blocked(B, d_big, bigsz, st);
+                if (fixed) fixed::launch_local_tridiag_blocked(B, d_big, bigsz, st);
                 else launch_local_tridiag_blocked(B, d_big, bigsz, d_mats, st);
             }
-            if (h->fixed_order) fixed::launch_local_tridiag(nb, B, mx, st);
+            if (fixed) fixed::launch_local_tridiag(nb, B, mx, st);
             launch_local_eig(nb, B, mx, 0, 1, st);
             if (!big.empty()) {
                 // eigenvectors of the large problems: scratch sized by their mode counts
@@ -1358,7 +1372,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
                 }
                 double* iw = ar.alloc<double>(std::max<int64_t>(iw_off.back(), 1));
                 int64_t* d_iw_off = ar.upload(iw_off, st);
-                if (h->fixed_order) {
+                if (fixed) {
                     fixed::launch_local_invit_blocked(B, d_big, bigsz, ks, d_iw_off, iw, st);
                     fixed::launch_local_vectors(nb, B, mx, st);
                     fixed::launch_local_backtransform_blocked(B, d_big, bigsz, st);
@@ -1370,7 +1384,7 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
                 sync(st);
                 ar.release(iw);
                 ar.release(d_iw_off);
-            } else if (h->fixed_order) {
+            } else if (fixed) {
                 fixed::launch_local_vectors(nb, B, mx, st);
             } else {
                 launch_local_eig(nb, B, mx, 2, 3, st);
@@ -1737,7 +1751,6 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
         bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
         bt.ctx = &ar;
-        bt.fixed_order = h->fixed_order;
         bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
         const int64_t budget = int64_t(2) << 30;    // bytes of P and Y per launch batch
         constexpr size_t MAXV = 65535;              // views per launch
@@ -2691,10 +2704,28 @@ lsdd_hierarchy* build(ElemList el0, const double* blocks, bool blocks_on_device,
     }
     // element Gram factors (Sec. 5.2)
     lv->d_G = ar.alloc<double>(lv->blk_off[ne]);
+    // instances with element diagonals of mixed scale: one's numbers do not depend on the others
+    const int32_t n_inst0 = (int32_t)lv->inst_off.size() - 1;
+    ElemFixed fixed{nullptr, nullptr};
+    int32_t *d_fixed = ar.alloc<int32_t>(n_inst0), *d_elem_inst = nullptr;
+    if (n_inst0 > 1) {
+        std::vector<int32_t> ei(ne);
+        for (int64_t e = 0; e < ne; ++e)
+            if (lv->el.ptr[e + 1] > lv->el.ptr[e])
+                ei[e] = (int32_t)(std::upper_bound(lv->inst_off.begin(), lv->inst_off.end(),
+                                                   (int64_t)lv->el.dofs[lv->el.ptr[e]]) - lv->inst_off.begin()) - 1;
+        d_elem_inst = ar.upload(ei, h->st);
+        sync(h->st);
+    }
+    fixed.flag = d_fixed;
+    auto read_fixed = [&] {
+        const std::vector<int32_t> f = download(d_fixed, n_inst0, h->st);
+        h->fixed_inst.assign(f.begin(), f.end());
+    };
     if (!gram_rows) {
         int32_t* d_ranks = ar.alloc<int32_t>(ne);
-        int32_t* d_status = ar.alloc<int32_t>(ne + 1);       // the last one: diagonals of mixed scale
-        launch_diag_spread(ne, lv->d_elem_ptr, lv->d_blk_off, lv->d_blocks, d_status + ne, h->st);
+        int32_t* d_status = ar.alloc<int32_t>(ne);
+        launch_diag_spread(ne, lv->d_elem_ptr, lv->d_blk_off, lv->d_blocks, d_elem_inst, n_inst0, d_fixed, h->st);
         int64_t max_ne = 0;
         for (int64_t e = 0; e < ne; ++e) max_ne = std::max(max_ne, lv->el.ptr[e + 1] - lv->el.ptr[e]);
         const int64_t stride = std::max<int64_t>(3 * max_ne * max_ne, elem_eig_scratch_stride(max_ne));
@@ -2706,13 +2737,16 @@ lsdd_hierarchy* build(ElemList el0, const double* blocks, bool blocks_on_device,
             if (P.elem_factor == 1)
                 launch_elem_pchol(cnt, lv->d_elem_ptr + e0, lv->d_blk_off + e0, lv->d_blocks, lv->d_G,
                                   d_ranks + e0, d_status + e0, scratch, stride, P.rank_rtol, P.spsd_tol, h->st);
-            else
+            else {
+                fixed.inst = d_elem_inst ? d_elem_inst + e0 : nullptr;
                 launch_elem_eig(cnt, lv->d_elem_ptr + e0, lv->d_blk_off + e0, lv->d_blocks, lv->d_G, d_ranks + e0,
-                                d_status + e0, scratch, stride, P.rank_rtol, P.spsd_tol, max_ne, d_status + ne, h->st);
+                                d_status + e0, scratch, stride, P.rank_rtol, P.spsd_tol, max_ne, fixed,
+                                h->st);
+            }
         }
         HIPCHK(hipGetLastError());
-        std::vector<int32_t> status = download(d_status, ne + 1, h->st);
-        h->fixed_order = status[ne] != 0;
+        std::vector<int32_t> status = download(d_status, ne, h->st);
+        read_fixed();
         lv->ranks = download(d_ranks, ne, h->st);
         vlog("element Gram factors for %lld elements %.3f s", (long long)ne, now_s() - t0);
         for (int64_t e = 0; e < ne; ++e) {
@@ -2740,15 +2774,15 @@ lsdd_hierarchy* build(ElemList el0, const double* blocks, bool blocks_on_device,
         launch_check_finite(gram_rows->nnz, d_val, d_fin, h->st);
         if (download(d_fin, 1, h->st)[0]) throw Error(LSDD_E_INVAL, "non-finite value in G");
         launch_gram_csr_rows(ne, lv->d_elem_ptr, d_src, lv->d_blk_off, d_val, lv->d_G, lv->d_blocks, h->st);
-        int32_t* d_mixed = ar.alloc<int32_t>(1);
-        launch_diag_spread(ne, lv->d_elem_ptr, lv->d_blk_off, lv->d_blocks, d_mixed, h->st);
-        h->fixed_order = download(d_mixed, 1, h->st)[0] != 0;
-        ar.release(d_mixed);
+        launch_diag_spread(ne, lv->d_elem_ptr, lv->d_blk_off, lv->d_blocks, d_elem_inst, n_inst0, d_fixed, h->st);
+        read_fixed();
         HIPCHK(hipGetLastError());
         sync(h->st);
         for (void* q : {(void*)d_src, (void*)d_copy, (void*)d_fin})
             if (q) ar.release(q);
     }
+    ar.release(d_fixed);
+    if (d_elem_inst) ar.release(d_elem_inst);
     const double tas = now_s();
     assemble_operator(h.get(), *lv);
     HIPCHK(hipGetLastError());
@@ -3592,7 +3626,6 @@ void coarse_gram(lsdd_hierarchy* h, Level& lv) {
     bt.alloc = [](void* c, size_t b) { return static_cast<Arena*>(c)->get(b); };
     bt.release = [](void* c, void* p) { static_cast<Arena*>(c)->release(p); };
     bt.ctx = &ar;
-    bt.fixed_order = h->fixed_order;
     bt.stage = [](void* c, size_t b, hipStream_t st) { return static_cast<Arena*>(c)->stage(b, st); };
     std::vector<int32_t> ranks(ne, 0);
     for (int64_t e0 = 0; e0 < ne; e0 += CH) {

@@ -73,3 +73,49 @@ def test_refused_solve_leaves_its_stream_idle(nrhs, precision):
                 x = h.solve(good)[0]
             sb.synchronize()
             assert torch.equal(x, ref)
+
+
+def _scale_second_dofs(prob, factor):
+    D = np.where(np.arange(prob.n) % 2, factor, 1.0)
+    off = prob.block_offsets()
+    for e in range(prob.n_elem):
+        d, B = prob.element(e)
+        prob.blocks[off[e]:off[e] + len(d) ** 2] = (B * D[d][:, None] * D[d]).ravel()
+    return prob
+
+
+@pytest.mark.parametrize("kind", ["q1", "q2"])
+@pytest.mark.parametrize("first", [True, False])
+def test_instances_do_not_depend_on_their_batch(kind, first):
+    """An instance's element factors, modes, coarse operators and V-cycle are the same bits beside an
+    instance like itself and beside one whose element diagonals span 2^28 (which the set-up treats in
+    another order of operations), with element blocks of either eigensolver."""
+    P = _lsdd()
+
+    def make(factor):
+        prob = fegen.elasticity_q1(16, nu=0.3) if kind == "q1" else fegen.elasticity_q2hex(3, nu=0.3)
+        return _scale_second_dofs(prob, factor)
+
+    kw = dict(max_levels=2, modes_fixed=4) if kind == "q1" else dict(max_levels=3, agg_passes=1, tau_const=0.75)
+    r = np.random.default_rng(5).standard_normal(make(1.0).n)
+    out = []
+    for own in (1.0, 2.0 ** 14):
+        for mate in (1.0, 2.0 ** 14):
+            probs = [make(own), make(mate)] if first else [make(mate), make(own)]
+            with P.Hierarchy.setup_batched(probs, P.Params.default(**kw)) as h:
+                part = []
+                i = 0 if first else 1
+                ptr = np.concatenate([probs[0].elem_ptr, probs[0].elem_ptr[-1] + probs[1].elem_ptr[1:]])
+                ranks, G = h.export_gram(ptr)
+                ne, nb = probs[0].n_elem, len(probs[0].blocks)
+                part += [ranks[i * ne:(i + 1) * ne], G[i * nb:(i + 1) * nb]]
+                for l in range(h.info()["levels"] - 1):
+                    off = h.level_segments(l)[0]
+                    ex = h.export_level(l)
+                    part.append(ex["mu"][off[i]:off[i + 1]])
+                rr = np.zeros(2 * len(r))
+                rr[i * len(r):(i + 1) * len(r)] = r
+                part.append(h.vcycle(torch.from_numpy(rr).cuda()).cpu().numpy()[i * len(r):(i + 1) * len(r)])
+                out.append(part)
+    for a, b in ((out[0], out[1]), (out[2], out[3])):
+        assert len(a) == len(b) and all(np.array_equal(x, y) for x, y in zip(a, b))
