@@ -6,8 +6,8 @@
 // them the V-cycle, are determined by the rounding of the set-up: on Hermite bicubics (spread
 // 5e9 and more) any other order of the same sums, even in the diagonal-tile steps alone, moves a
 // V-cycle by 1e-6 to 1e-4; on elements with a spread of up to 4e2 by 1e-13 to 1.3e-10, at one
-// of 28 sizes by 1e-9.  Such problems keep these kernels, bit for bit, for their local problems and
-// dense tiles; the instances of a batch are told apart.  All others take the faster ones of trd.hip, invit.hpp and tile64.hpp
+// of 28 sizes by 1e-9.  Such problems keep these kernels in their set-up, element factors
+// included, bit for bit; the instances of a batch are told apart.  All others take the faster ones of trd.hip, invit.hpp and tile64.hpp
 // (inverse iteration for 8 matrices of up to 882 with 179 vectors 15.4 ms here, 4.6 there;
 // eigenvalues 4.9 and 1.05; a diagonal tile 48 and 17.5 us).
 #pragma once

@@ -17,6 +17,7 @@
 
 #include "batched.hpp"
 #include "dense.hpp"
+#include "fixed.hpp"
 #include "invit.hpp"
 #include "kernels.hpp"
 #include "symv.hpp"
@@ -185,17 +186,18 @@ __global__ void k_diag_spread(int64_t n_elem, const int64_t* elem_ptr, const int
 // of scratch holds S (n^2, reduced in place) | V (n^2, retained vectors) | d, e,
 // tau, w (4n) | inverse-iteration scratch (invit_ws); status[e] and
 // ranks[e] carry the state between phases.  Dynamic LDS: 2 n_max + 64 doubles.
-// Smaller elements are left to k_elem_eig.
-template <int PHASE>
+// Smaller elements are left to k_elem_eig.  FIXED: the elements of the flagged instances, by the
+// routines of fixed.hpp; else the others.
+template <int PHASE, bool FIXED>
 __global__ void __launch_bounds__(WG) k_elem_eig_trd(const int64_t* elem_ptr, const int64_t* blk_off,
                                                      const double* blocks, double* G, int32_t* ranks,
                                                      int32_t* status, double* scratch, int64_t scratch_stride,
-                                                     double rank_rtol, double spsd_tol) {
+                                                     double rank_rtol, double spsd_tol, ElemFixed fixed_order) {
     extern __shared__ double s_dyn[];
     __shared__ double s_red[WG / 64];
     const int64_t e = blockIdx.x;
     const int n = (int)(elem_ptr[e + 1] - elem_ptr[e]);
-    if (n <= NE_LDS) return;
+    if (n <= NE_LDS || fixed_order(e) != FIXED) return;
     if (PHASE > 0 && status[e] != 0) return;
     const int64_t nn = (int64_t)n * n;
     double* S = scratch + e * scratch_stride;
@@ -222,12 +224,14 @@ __global__ void __launch_bounds__(WG) k_elem_eig_trd(const int64_t* elem_ptr, co
             if (tid() == 0) status[e] = 1;   // asymmetric or non-finite
             return;
         }
-        wg_tridiag(S, n, d, ee, tau, s_dyn, s_dyn + n, s_red);
+        if constexpr (FIXED) fixed::wg_tridiag(S, n, d, ee, tau, s_dyn, s_dyn + n, s_red);
+        else wg_tridiag(S, n, d, ee, tau, s_dyn, s_dyn + n, s_red);
         if (tid() == 0) status[e] = 0;
         return;
     }
     if (PHASE == 1) {
-        wg_bisect_all(d, ee, n, w, s_dyn, s_red);
+        if constexpr (FIXED) fixed::wg_bisect_all(d, ee, n, w, s_red);
+        else wg_bisect_all(d, ee, n, w, s_dyn, s_red);
         __syncthreads();
         if (tid() == 0) {
             const double lmax = fmax(w[n - 1], 0.0);
@@ -245,13 +249,25 @@ __global__ void __launch_bounds__(WG) k_elem_eig_trd(const int64_t* elem_ptr, co
     const int r = ranks[e];
     const int first = n - r;
     if (PHASE == 2) {
-        if constexpr (PHASE == 2) {
+        if constexpr (PHASE == 2 && FIXED) {
+            __shared__ int s_ncl;
+            if (r == 0) return;
+            double tnorm = 0.0;
+            for (int i = tid(); i < n; i += WG)
+                tnorm = fmax(tnorm, fabs(d[i]) + (i > 0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < n ? fabs(ee[i]) : 0.0));
+            tnorm = wg_max(tnorm, s_red);
+            fixed::wg_inverse_iteration(d, ee, n, w + first, r, V, ws, fmax(tnorm, 1e-300), (int*)s_dyn, s_dyn + n,
+                                        s_red, &s_ncl);
+        } else if constexpr (PHASE == 2) {
             __shared__ InvShared inv;
             wg_invit(d, ee, n, w + first, r, 0, r, V, ws, reinterpret_cast<unsigned char*>(s_dyn), inv);
         }
         return;
     }
-    if (r > 0) wg_backtransform(S, n, tau, V, r);
+    if (r > 0) {
+        if constexpr (FIXED) fixed::wg_tridiag_backtransform(S, n, tau, V, r, s_dyn, s_dyn + n);
+        else wg_backtransform(S, n, tau, V, r);
+    }
     double* g = G + blk_off[e];
     for (int idx = tid(); idx < n * n; idx += WG) {
         const int row = idx / n, c = idx % n;
@@ -1623,7 +1639,7 @@ __global__ void k_check_finite(int64_t n, const double* a, int32_t* flag) {
 
 void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks, double* G,
                      int32_t* ranks, int32_t* status, double* scratch, int64_t scratch_stride, double rank_rtol,
-                     double spsd_tol, int64_t n_max, ElemFixed fixed_order, hipStream_t st) {
+                     double spsd_tol, int64_t n_max, ElemFixed fixed_order, int fixed_any, hipStream_t st) {
     if (n_elem <= 0) return;
     // blocks up to NE_LDS: Jacobi with matrix and vectors in LDS; larger blocks: the
     // tridiagonal route (k_elem_eig_trd; 81 x 81 Q2 blocks: Jacobi took 0.67 s)
@@ -1633,15 +1649,22 @@ void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk
                        ranks, status, scratch, scratch_stride, rank_rtol, spsd_tol, lds, fixed_order);
     if (n_max > NE_LDS) {
         const size_t ld = (size_t)(2 * n_max + 64) * 8;
-        const dim3 g((unsigned)n_elem);
-        hipLaunchKernelGGL(k_elem_eig_trd<0>, g, dim3(WG), ld, st, elem_ptr, blk_off, blocks, G, ranks, status,
-                           scratch, scratch_stride, rank_rtol, spsd_tol);
-        hipLaunchKernelGGL(k_elem_eig_trd<1>, g, dim3(WG), ld, st, elem_ptr, blk_off, blocks, G, ranks, status,
-                           scratch, scratch_stride, rank_rtol, spsd_tol);
-        hipLaunchKernelGGL(k_elem_eig_trd<2>, g, dim3(WG), (size_t)n_max + 8, st, elem_ptr, blk_off, blocks, G, ranks, status,
-                           scratch, scratch_stride, rank_rtol, spsd_tol);
-        hipLaunchKernelGGL(k_elem_eig_trd<3>, g, dim3(WG), ld, st, elem_ptr, blk_off, blocks, G, ranks, status,
-                           scratch, scratch_stride, rank_rtol, spsd_tol);
+        auto go = [&](auto kern, size_t lds_p) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)n_elem), dim3(WG), lds_p, st, elem_ptr, blk_off, blocks, G, ranks,
+                               status, scratch, scratch_stride, rank_rtol, spsd_tol, fixed_order);
+        };
+        if (fixed_any != 2) {
+            go(k_elem_eig_trd<0, false>, ld);
+            go(k_elem_eig_trd<1, false>, ld);
+            go(k_elem_eig_trd<2, false>, (size_t)n_max + 8);
+            go(k_elem_eig_trd<3, false>, ld);
+        }
+        if (fixed_any != 0) {
+            go(k_elem_eig_trd<0, true>, ld);
+            go(k_elem_eig_trd<1, true>, ld);
+            go(k_elem_eig_trd<2, true>, ld);
+            go(k_elem_eig_trd<3, true>, ld);
+        }
     }
 }
 

@@ -84,8 +84,8 @@ constexpr int NE_LDS = 48;          // element blocks up to this size stay in LD
 // Element Gram factors from eigendecompositions: Jacobi in LDS for blocks up to NE_LDS,
 // the tridiagonal route above; n_max = largest block, scratch of
 // elem_eig_scratch_stride(n_max) doubles per element.
-// fixed_order: instances whose elements keep the order of operations of fixed.hpp (blocks up to
-// NE_LDS).
+// fixed_order: instances whose elements keep the order of operations of fixed.hpp; fixed_any: 0 none
+// of the instances, 1 some, 2 all (a block above NE_LDS takes one of two sets of kernels).
 struct ElemFixed {
     const int32_t* flag;           // per instance
     const int32_t* inst;           // instance of an element, NULL: all in the first
@@ -93,7 +93,7 @@ struct ElemFixed {
 };
 void launch_elem_eig(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
                      double* G, int32_t* ranks, int32_t* status, double* scratch, int64_t scratch_stride,
-                     double rank_rtol, double spsd_tol, int64_t n_max, ElemFixed fixed_order, hipStream_t st);
+                     double rank_rtol, double spsd_tol, int64_t n_max, ElemFixed fixed_order, int fixed_any, hipStream_t st);
 int64_t elem_eig_scratch_stride(int64_t n_max);
 
 // flag[i] = 1 when the positive diagonal entries of an element block of instance i span more than

@@ -2728,6 +2728,12 @@ lsdd_hierarchy* build(ElemList el0, const double* blocks, bool blocks_on_device,
         launch_diag_spread(ne, lv->d_elem_ptr, lv->d_blk_off, lv->d_blocks, d_elem_inst, n_inst0, d_fixed, h->st);
         int64_t max_ne = 0;
         for (int64_t e = 0; e < ne; ++e) max_ne = std::max(max_ne, lv->el.ptr[e + 1] - lv->el.ptr[e]);
+        int fixed_any = 0;
+        if (max_ne > NE_LDS) {                          // below, one kernel serves both
+            read_fixed();
+            const auto n_fixed = std::count(h->fixed_inst.begin(), h->fixed_inst.end(), 1);
+            fixed_any = n_fixed == 0 ? 0 : n_fixed < n_inst0 ? 1 : 2;
+        }
         const int64_t stride = std::max<int64_t>(3 * max_ne * max_ne, elem_eig_scratch_stride(max_ne));
         // process elements in chunks so the eigen scratch stays bounded
         const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(ne, (int64_t(1) << 30) / (stride * 8)));
@@ -2740,7 +2746,7 @@ lsdd_hierarchy* build(ElemList el0, const double* blocks, bool blocks_on_device,
             else {
                 fixed.inst = d_elem_inst ? d_elem_inst + e0 : nullptr;
                 launch_elem_eig(cnt, lv->d_elem_ptr + e0, lv->d_blk_off + e0, lv->d_blocks, lv->d_G, d_ranks + e0,
-                                d_status + e0, scratch, stride, P.rank_rtol, P.spsd_tol, max_ne, fixed,
+                                d_status + e0, scratch, stride, P.rank_rtol, P.spsd_tol, max_ne, fixed, fixed_any,
                                 h->st);
             }
         }
