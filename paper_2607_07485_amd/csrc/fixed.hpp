@@ -3,11 +3,14 @@
 // Element blocks whose diagonal spans more than FIXED_SPREAD mix DOFs of different dimension
 // (values with first and mixed derivatives).  Their coarse interface blocks have spectra that
 // decay down to the rounding, so that from the third level on the retained modes, and with
-// them the V-cycle, are determined by the rounding of the set-up: on Hermite bicubics (spread
-// 5e9 and more) any other order of the same sums, even in the diagonal-tile steps alone, moves a
-// V-cycle by 1e-6 to 1e-4; on elements with a spread of up to 4e2 by 1e-13 to 1.3e-10, at one
-// of 28 sizes by 1e-9.  Such problems keep these kernels in their set-up, element factors
-// included, bit for bit; the instances of a batch are told apart.  All others take the faster ones of trd.hip, invit.hpp and tile64.hpp
+// them the V-cycle, are determined by the rounding of the set-up: on Hermite bicubics one unit
+// in the last place of the element entries moves a V-cycle by 4e-6 to 5e-5, and so does any
+// other order of the same sums, even in the diagonal-tile steps alone; on the other elements
+// another order moves it by 1e-13 to 1.3e-10, at one size of 17 by 1e-9.  The diagonals of the
+// Hermites span 5e9 to 1e12 on meshes of 24^2 to 96^2 cells, 5.3e3 with the derivatives scaled by
+// the mesh size; those of the others at most 4.3e2, and the line is drawn halfway (in decades).
+// Such problems keep these kernels in their set-up, element factors included, bit for bit; the
+// instances of a batch are told apart.  All others take the faster ones of trd.hip, invit.hpp and tile64.hpp
 // (inverse iteration for 8 matrices of up to 882 with 179 vectors 15.4 ms here, 4.6 there;
 // eigenvalues 4.9 and 1.05; a diagonal tile 48 and 17.5 us).
 #pragma once

@@ -98,7 +98,7 @@ int64_t elem_eig_scratch_stride(int64_t n_max);
 
 // flag[i] = 1 when the positive diagonal entries of an element block of instance i span more than
 // FIXED_SPREAD (see fixed.hpp), else 0; elem_inst: instance of an element, NULL: one instance.
-constexpr double FIXED_SPREAD = 1e6;
+constexpr double FIXED_SPREAD = 1.5e3;
 void launch_diag_spread(int64_t n_elem, const int64_t* elem_ptr, const int64_t* blk_off, const double* blocks,
                         const int32_t* elem_inst, int32_t n_inst, int32_t* flag, hipStream_t st);
 

@@ -1,4 +1,6 @@
 """Which kernels a cycle runs, for every smoother, precision and tuning."""
+import os
+
 import numpy as np
 import pytest
 
@@ -124,11 +126,28 @@ def test_instances_do_not_depend_on_their_batch(kind, first):
 def test_mixed_scale_keeps_its_vcycle_with_large_elements():
     """Element blocks above 48 DOFs of mixed scale: the V-cycle, which the rounding of the set-up moves by
     1e-7 there, is the recorded one (of the library before it had a second eigensolver)."""
-    import os
     P = _lsdd()
     prob = _scale_second_dofs(fegen.elasticity_q2hex(3, nu=0.3), 2.0 ** 14)
     ref = np.load(os.path.join(os.path.dirname(__file__), "golden", "mixed_scale_q2hex3_vcycle.npz"))["z"]
     r = np.random.default_rng(0).standard_normal(prob.n)
     with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=3, tau_const=0.75, agg_passes=1)) as h:
         z = h.vcycle(torch.from_numpy(r).cuda()).cpu().numpy()
+    assert np.linalg.norm(z - ref) <= 1e-10 * np.linalg.norm(ref)
+
+
+def test_scaled_hermites_keep_their_vcycle():
+    """Hermite bicubics in unknowns scaled by the mesh size (element diagonals span 5e3 instead of 9e10):
+    still a V-cycle that the rounding of the set-up moves by 1e-5, so it is the recorded one (every
+    16th entry, of the library before it had a second eigensolver)."""
+    P = _lsdd()
+    prob, _ = fegen.hyperdiffusion_h2(48, eps=1e-4)
+    D = np.tile([1.0, 64.0, 64.0, 4096.0], prob.n // 4)
+    off = prob.block_offsets()
+    for e in range(prob.n_elem):
+        d, B = prob.element(e)
+        prob.blocks[off[e]:off[e] + len(d) ** 2] = (B * D[d][:, None] * D[d]).ravel()
+    ref = np.load(os.path.join(os.path.dirname(__file__), "golden", "scaled_hermite48_vcycle.npz"))["z"]
+    r = np.random.default_rng(0).standard_normal(prob.n)
+    with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=4, tau_const=1.0)) as h:
+        z = h.vcycle(torch.from_numpy(r).cuda()).cpu().numpy()[::16]
     assert np.linalg.norm(z - ref) <= 1e-10 * np.linalg.norm(ref)
