@@ -95,9 +95,11 @@ __device__ inline double col_sum(double v, double* red) {
 // Column j of the panel that starts at j0 (fin: only the last W column of that panel).  TH
 // threads, RPT rows each: the factors of a V, W entry come from LDS for every wave that uses
 // them, so up to 1024 rows run on four waves with up to four rows a thread, not on sixteen
-// (10.4 against 7.7 us a column, averaged over n = 648 and 882).
+// (10.4 against 7.7 us a column, averaged over n = 648 and 882).  The order of the sums depends
+// on TH, so a matrix takes the TH of its own remaining rows whatever else is in the batch: a
+// launch is for matrices with more than `above` rows left and at most TH RPT.
 template <int TH, int RPT>
-__global__ void __launch_bounds__(TH) k_trd_col(const Mat* mats, int j, int j0, int fin) {
+__global__ void __launch_bounds__(TH) k_trd_col(const Mat* mats, int j, int j0, int fin, int above) {
     constexpr int QC = RPT <= 2 ? 8 : 4;               // panel columns in flight
     constexpr int PW = TH / 64;
     __shared__ double red[PW];
@@ -106,6 +108,8 @@ __global__ void __launch_bounds__(TH) k_trd_col(const Mat* mats, int j, int j0, 
     __shared__ double s_row[2];
     const Mat m = mats[blockIdx.x];
     const int n = m.n;
+    const int left = n - (fin ? j0 : j);
+    if (left <= above || left > TH * RPT) return;
     if (fin) {
         const int pc = min(NB, n - 2 - j0);            // this matrix's columns in the panel
         if (pc <= 0) return;
@@ -429,7 +433,7 @@ __global__ void __launch_bounds__(WG) k_trd_invit(LocalArgs A, const int32_t* bi
 }
 
 // Retained eigenvectors for the large problems, a wave each (VS = W1, n x k, ld n; RPT: rows
-// per lane, 0 for any n); bound by the reads of the reflectors and the ten sums over the wave
+// per lane, 0 for more than 1024, which sum in another order and so have a launch of their own); bound by the reads of the reflectors and the ten sums over the wave
 // a round takes.  Eight matrices of up to 882 with 179 vectors each: 1.94 -> 1.04
 // ms.
 template <int RPT>
@@ -438,7 +442,7 @@ __global__ void __launch_bounds__(WG) k_trd_backtransform(LocalArgs A, const int
     const int ag = A.first + b;
     const int n = (int)(A.agg_ptr[ag + 1] - A.agg_ptr[ag]);
     const int c = (int)blockIdx.x * (WG / 64) + (tid() >> 6);
-    if (c >= A.k_out[ag]) return;
+    if (c >= A.k_out[ag] || (n > 1024) != (RPT == 0)) return;
     const double* a = A.s_buf + A.sq_off[b];
     const double* tau = A.t_buf + A.t_off[b] + 2 * n;
     double* x = A.w1 + A.ws_off[b] + (int64_t)c * n;
@@ -452,15 +456,18 @@ void launch_local_backtransform_blocked(const LocalArgs& a, const int32_t* d_big
                                         hipStream_t st) {
     const int nbig = (int)sizes.size();
     if (nbig == 0) return;
-    int max_n = 0;
-    for (int32_t s : sizes) max_n = std::max(max_n, (int)s);
+    int max_n = 0, min_n = INT32_MAX;
+    for (int32_t s : sizes) {
+        max_n = std::max(max_n, (int)s);
+        min_n = std::min(min_n, (int)s);
+    }
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3((max_n + WG / 64 - 1) / (WG / 64), nbig), dim3(WG), 0, st, a, d_big);
     };
     if (max_n <= 256) go(k_trd_backtransform<4>);
     else if (max_n <= 512) go(k_trd_backtransform<8>);
-    else if (max_n <= 1024) go(k_trd_backtransform<16>);
-    else go(k_trd_backtransform<0>);
+    else if (min_n <= 1024) go(k_trd_backtransform<16>);
+    if (max_n > 1024) go(k_trd_backtransform<0>);
 }
 
 void launch_local_invit_blocked(const LocalArgs& a, const int32_t* d_big, const std::vector<int32_t>& sizes,
@@ -490,13 +497,17 @@ void launch_local_tridiag_blocked(const LocalArgs& a, const int32_t* d_big, cons
     Mat* mats = static_cast<Mat*>(d_mats);
     hipLaunchKernelGGL(k_trd_mats, dim3((nbig + 63) / 64), dim3(64), 0, st, a, d_big, nbig, mats);
     auto column = [&](int j, int j0, int fin) {
-        auto go = [&](auto kern, int th) { hipLaunchKernelGGL(kern, dim3(nbig), dim3(th), 0, st, mats, j, j0, fin); };
-        const int rows = max_n - (fin ? j0 : j);       // at most these are left
-        if (rows <= 256) go(k_trd_col<256, 1>, 256);
-        else if (rows <= 512) go(k_trd_col<256, 2>, 256);
-        else if (rows <= 1024) go(k_trd_col<256, 4>, 256);
-        else if (rows <= 2048) go(k_trd_col<1024, 2>, 1024);
-        else go(k_trd_col<1024, 4>, 1024);
+        auto go = [&](auto kern, int th, int above) {
+            hipLaunchKernelGGL(kern, dim3(nbig), dim3(th), 0, st, mats, j, j0, fin, above);
+        };
+        const int base = fin ? j0 : j, rows = max_n - base;       // at most these are left
+        const bool short_ones = std::any_of(sizes.begin(), sizes.end(),
+                                            [&](int32_t n) { return n - base > 2 && n - base <= 1024; });
+        if (rows <= 256) go(k_trd_col<256, 1>, 256, 0);
+        else if (rows <= 512) go(k_trd_col<256, 2>, 256, 0);
+        else if (short_ones) go(k_trd_col<256, 4>, 256, 0);
+        if (rows > 2048) go(k_trd_col<1024, 4>, 1024, 1024);
+        else if (rows > 1024) go(k_trd_col<1024, 2>, 1024, 1024);
     };
     if (max_n > 4096) throw std::runtime_error("blocked tridiagonalisation: more than 4096 DOFs");
     for (int j0 = 0; j0 < max_n - 2; j0 += NB) {

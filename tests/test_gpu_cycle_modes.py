@@ -151,3 +151,24 @@ def test_scaled_hermites_keep_their_vcycle():
     with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=4, tau_const=1.0)) as h:
         z = h.vcycle(torch.from_numpy(r).cuda()).cpu().numpy()[::16]
     assert np.linalg.norm(z - ref) <= 1e-10 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("mate", [1100, 2200])
+def test_eigenpairs_do_not_depend_on_larger_aggregates_in_the_batch(mate):
+    """Aggregates of 400 and 900 DOFs beside ones like themselves and beside one of 1,100 or 2,200, for
+    which the reduction has other workgroups: the same eigenvalues and modes, bit for bit."""
+    P = _lsdd()
+
+    def make(*cuts):
+        prob = fegen.elasticity_q1(40, nu=0.3)
+        prob.agg_of_dof = np.searchsorted(np.array(cuts), np.arange(prob.n), side="right").astype(np.int32)
+        return prob
+
+    out = []
+    for other in (make(400, 1300, 2200, 2700), make(400, 400 + mate)):
+        own = make(400, 1300, 2200, 2700)
+        with P.Hierarchy.setup_batched([own, other], P.Params.default(max_levels=2, tau_const=0.75)) as h:
+            ex = h.export_level(0)
+            nz = sum(int(k) * w for k, w in zip(ex["k"][:5], (400, 900, 900, 500, own.n - 2700)))
+            out.append((ex["k"][:5], ex["mu"][:own.n], np.asarray(ex["Z"]).ravel()[:nz]))
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
