@@ -869,8 +869,7 @@ __global__ void __launch_bounds__(PCG_WG) k_pcg_begin(const int64_t* blk_lo, con
     if (tid() < NR) part_bad[(int64_t)blk * NR + tid()] = bad;
 }
 
-// One workgroup; a wave per segment adds the partials of its NR pairs: lanes =
-// (block lane, right-hand side).
+// A wave adds the partials of a segment's NR pairs: lanes = (block lane, right-hand side).
 template <int NR>
 __device__ inline double wave_seg_total(const double* part, int b0, int b1) {
     const int lane = tid() & 63, k = lane % NR;
@@ -884,26 +883,53 @@ __device__ inline double wave_seg_total(const double* part, int b0, int b1) {
 
 constexpr int PCG_CHECK_WG = 1024;
 
+// Sums of two sets of partials (p1 NULL: one) for every pair, a wave per segment: for tables of so
+// many segments that one workgroup, a wave per segment, takes longer than a launch.
+template <int NR>
+__global__ void __launch_bounds__(PCG_WG) k_seg_totals(int n_seg, const int32_t* seg_blk, const double* p0,
+                                                       const double* p1, double* tot0, double* tot1) {
+    const int s = (int)blockIdx.x * (PCG_WG / 64) + (tid() >> 6), lane = tid() & 63;
+    if (s >= n_seg) return;
+    const double u = wave_seg_total<NR>(p0, seg_blk[s], seg_blk[s + 1]);
+    const double v = p1 ? wave_seg_total<NR>(p1, seg_blk[s], seg_blk[s + 1]) : 0.0;
+    if (lane < NR) {
+        tot0[s * NR + lane] = u;
+        if (p1) tot1[s * NR + lane] = v;
+    }
+}
+
+// f(pair, first sum, second sum) for every pair, from one workgroup: the sums as given (tot), else a
+// wave per segment adds the partials
+template <int NR, class F>
+__device__ inline void each_pair(int n_seg, const int32_t* seg_blk, const double* p0, const double* p1,
+                                 const double* tot0, const double* tot1, F&& f) {
+    if (tot0) {
+        for (int i = tid(); i < n_seg * NR; i += PCG_CHECK_WG) f(i, tot0[i], p1 ? tot1[i] : 0.0);
+        return;
+    }
+    const int lane = tid() & 63;
+    for (int s = tid() >> 6; s < n_seg; s += PCG_CHECK_WG / 64) {
+        const double u = wave_seg_total<NR>(p0, seg_blk[s], seg_blk[s + 1]);
+        const double v = p1 ? wave_seg_total<NR>(p1, seg_blk[s], seg_blk[s + 1]) : 0.0;
+        if (lane < NR) f(s * NR + lane, u, v);
+    }
+}
+
 template <int NR>
 __global__ void __launch_bounds__(PCG_CHECK_WG) k_pcg_init(int n_seg, const int32_t* seg_blk, const double* part_bb,
-                                                           const double* part_bad, double* bb, int32_t* act,
+                                                           const double* part_bad, const double* tot_bb,
+                                                           const double* tot_bad, double* bb, int32_t* act,
                                                            int32_t* iters, double* relres, int32_t* st) {
     __shared__ int s_bad;
     if (tid() == 0) s_bad = 0;
     __syncthreads();
-    const int lane = tid() & 63;
-    for (int s = tid() >> 6; s < n_seg; s += PCG_CHECK_WG / 64) {
-        const double v = wave_seg_total<NR>(part_bb, seg_blk[s], seg_blk[s + 1]);
-        const double bad = wave_seg_total<NR>(part_bad, seg_blk[s], seg_blk[s + 1]);
-        if (lane < NR) {
-            const int i = s * NR + lane;
-            bb[i] = v;
-            act[i] = v > 0.0 ? 1 : 0;
-            iters[i] = 0;
-            relres[i] = v > 0.0 ? 1.0 : 0.0;
-            if (bad > 0.0) s_bad = 1;
-        }
-    }
+    each_pair<NR>(n_seg, seg_blk, part_bb, part_bad, tot_bb, tot_bad, [&](int i, double v, double bad) {
+        bb[i] = v;
+        act[i] = v > 0.0 ? 1 : 0;
+        iters[i] = 0;
+        relres[i] = v > 0.0 ? 1.0 : 0.0;
+        if (bad > 0.0) s_bad = 1;
+    });
     __syncthreads();
     if (tid() == 0) {
         st[PCG_ST_COUNT] = 0;
@@ -983,38 +1009,41 @@ __global__ void __launch_bounds__(PCG_WG) k_pcg_update_xr(int n_seg, const int32
     if (tid() < NR) part_rr[(int64_t)b * NR + tid()] = u;
 }
 
-// State transitions and the active count, one workgroup: a wave per segment adds the
-// partials of <r, r>; the status goes to the device and to the host's pinned mirror, which
-// the host reads after the launch has ended (no copy launch); behind them the largest
-// |r|^2 / (tol^2 |b|^2) of the pairs still active.
+// State transitions and the active count, one workgroup; the status goes to the device and to
+// the host's pinned mirror, which the host reads after the launch has ended (no copy launch);
+// behind them the largest |r|^2 / (tol^2 |b|^2) of the pairs still active.
 template <int NR>
 __global__ void __launch_bounds__(PCG_CHECK_WG) k_pcg_check(int n_seg, const int32_t* seg_blk, const double* part_rr,
-                                                            double tol2, const double* bb, int32_t* act,
-                                                            int32_t* iters, double* relres, int32_t* st,
+                                                            const double* tot_rr, double tol2, const double* bb,
+                                                            int32_t* act, int32_t* iters, double* relres, int32_t* st,
                                                             int32_t* host_st) {
     __shared__ int s_count, s_flag;
     __shared__ unsigned long long s_excess;             // non-negative doubles order like their bits
     if (tid() == 0) s_count = s_flag = 0, s_excess = 0;
     __syncthreads();
     const int it = st[PCG_ST_IT] + 1;
-    const int lane = tid() & 63;
-    for (int s = tid() >> 6; s < n_seg; s += PCG_CHECK_WG / 64) {
-        const double v = wave_seg_total<NR>(part_rr, seg_blk[s], seg_blk[s + 1]);
-        const int i = s * NR + lane;
-        if (lane < NR && act[i]) {
-            if (!isfinite(v)) {
-                atomicOr(&s_flag, 4);          // residual norm not finite
-            } else {
-                relres[i] = sqrt(v / bb[i]);
-                iters[i] = it;
-                if (v <= tol2 * bb[i]) act[i] = 0;
-                else {
-                    atomicAdd(&s_count, 1);
-                    atomicMax(&s_excess, __double_as_longlong(v / (tol2 * bb[i])));
-                }
-            }
+    int count = 0, flag = 0;
+    unsigned long long excess = 0;
+    each_pair<NR>(n_seg, seg_blk, part_rr, nullptr, tot_rr, nullptr, [&](int i, double v, double) {
+        if (!act[i]) return;
+        if (!isfinite(v)) {
+            flag = 4;                                   // residual norm not finite
+            return;
         }
+        relres[i] = sqrt(v / bb[i]);
+        iters[i] = it;
+        if (v <= tol2 * bb[i]) {
+            act[i] = 0;
+        } else {
+            ++count;
+            excess = max(excess, (unsigned long long)__double_as_longlong(v / (tol2 * bb[i])));
+        }
+    });
+    if (count) {
+        atomicAdd(&s_count, count);
+        atomicMax(&s_excess, excess);
     }
+    if (flag) atomicOr(&s_flag, flag);
     __syncthreads();
     if (tid() == 0) {
         const int flag = st[PCG_ST_FLAG] | s_flag;
@@ -1339,6 +1368,19 @@ void seg_dot_parts(const SegTable& t, const double* a0, const Z* b0, const doubl
 
 }  // namespace
 
+namespace {
+
+// Segments up to which k_pcg_init and k_pcg_check add the partials themselves.
+constexpr int SEG_DIRECT = 64;
+
+template <int NR>
+void seg_totals(const SegTable& t, const double* p0, const double* p1, double* tot0, double* tot1, hipStream_t st) {
+    hipLaunchKernelGGL(k_seg_totals<NR>, dim3((unsigned)((t.n_seg + PCG_WG / 64 - 1) / (PCG_WG / 64))), dim3(PCG_WG), 0,
+                       st, t.n_seg, t.seg_blk, p0, p1, tot0, tot1);
+}
+
+}  // namespace
+
 void launch_seg_dot(const SegTable& t, int nr, const double* a, const double* b, double* part, double* out,
                     double* host, hipStream_t st) {
     with_nr(nr, [&](auto c) {
@@ -1355,8 +1397,14 @@ void launch_pcg_begin(const PcgArgs<Z>& a, int nrhs, const double* b, int64_t ld
         const SegTable& t = a.seg;
         hipLaunchKernelGGL((k_pcg_begin<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.blk_lo, t.blk_hi, nrhs,
                            b, ldb, a.r, a.x, a.r32, a.z, a.part_rr, a.part_pq);
+        double *tot = nullptr, *tot2 = nullptr;
+        if (t.n_seg > SEG_DIRECT) {
+            tot = a.tot;
+            tot2 = tot + (size_t)t.n_seg * NR;
+            seg_totals<NR>(t, a.part_rr, a.part_pq, tot, tot2, st);
+        }
         hipLaunchKernelGGL(k_pcg_init<NR>, dim3(1), dim3(PCG_CHECK_WG), 0, st, t.n_seg, t.seg_blk, a.part_rr, a.part_pq,
-                           a.bb, a.act, a.iters, a.relres, a.st);
+                           tot, tot2, a.bb, a.act, a.iters, a.relres, a.st);
     });
 }
 
@@ -1369,7 +1417,9 @@ void launch_pcg_step(const PcgArgs<Z>& a, double tol2, int32_t* host_st, hipStre
         hipLaunchKernelGGL((k_pcg_update_xr<NR, Z>), dim3((unsigned)t.n_blk), dim3(PCG_WG), 0, st, t.n_seg, t.blk_seg, t.blk_lo,
                            t.blk_hi, t.seg_blk, a.act, a.rz2, a.nsm, a.part_pq, a.p, a.q, a.x, a.r, a.rold, a.r32, a.z,
                            a.part_rr, a.st);
-        hipLaunchKernelGGL(k_pcg_check<NR>, dim3(1), dim3(PCG_CHECK_WG), 0, st, t.n_seg, t.seg_blk, a.part_rr, tol2,
+        double* tot = t.n_seg > SEG_DIRECT ? a.tot : nullptr;
+        if (tot) seg_totals<NR>(t, a.part_rr, nullptr, tot, nullptr, st);
+        hipLaunchKernelGGL(k_pcg_check<NR>, dim3(1), dim3(PCG_CHECK_WG), 0, st, t.n_seg, t.seg_blk, a.part_rr, tot, tol2,
                            a.bb, a.act, a.iters, a.relres, a.st, host_st);
     });
 }

@@ -107,6 +107,7 @@ struct PcgArgs {
     double *bb, *rz2, *relres;    // rz2: two slots of nsm
     int32_t *act, *iters, *st;
     double *part_pq, *part_rr;    // n_blk * nr partials each
+    double* tot;                  // 2 * n_seg * nr sums (tables of many segments)
 };
 
 // out[i] = <a, b>_i (and, for the first segment, host[k]); part holds n_blk * nr doubles

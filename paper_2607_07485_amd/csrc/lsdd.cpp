@@ -530,6 +530,7 @@ struct lsdd_hierarchy {
     int32_t* ic = nullptr;        // status words of the solve
     double* part = nullptr;       // reduction partials, two sets
     size_t part_len = 0;          // doubles per set
+    double* tot = nullptr;        // two sums per pair
     int32_t* h_ic = nullptr;      // pinned: mirror of the status words, then a residual norm (double)
     hipEvent_t ev_step = nullptr; // after the step of a PCG iteration
     void* h_res = nullptr;        // pinned: relres, act, iters of a finished solve
@@ -2295,6 +2296,7 @@ void init_segments(lsdd_hierarchy* h, const std::vector<int64_t>& seg_off) {
     h->sc = a.alloc<double>((size_t)5 * h->nsm);
     h->ic = a.alloc<int32_t>(PCG_ST_WORDS);
     h->part = a.alloc<double>(2 * h->part_len);
+    h->tot = a.alloc<double>(2 * (size_t)h->nsm);
     if (!h->h_ic)
         HIPCHK(hipHostMalloc((void**)&h->h_ic, PCG_ST_WORDS * sizeof(int32_t) + sizeof(double), hipHostMallocDefault));
     if (!h->ev_step) HIPCHK(hipEventCreateWithFlags(&h->ev_step, hipEventDisableTiming));
@@ -2343,6 +2345,7 @@ bool pcg_run(lsdd_hierarchy* h, const double* rhs, int32_t nrhs, int64_t ldb) {
     A.st = h->ic;
     A.part_pq = h->part;
     A.part_rr = h->part + h->part_len;
+    A.tot = h->tot;
     const double tol2 = h->prm.rtol * h->prm.rtol;
     // z = 0 and, for an FP32 cycle, its residual are written by the PCG kernels
     auto cycle = [&] {

@@ -172,3 +172,31 @@ def test_eigenpairs_do_not_depend_on_larger_aggregates_in_the_batch(mate):
             nz = sum(int(k) * w for k, w in zip(ex["k"][:5], (400, 900, 900, 500, own.n - 2700)))
             out.append((ex["k"][:5], ex["mu"][:own.n], np.asarray(ex["Z"]).ravel()[:nz]))
     assert all(np.array_equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("nrhs", [1, 3])
+@pytest.mark.parametrize("count", [64, 65, 1200])
+def test_many_instances(count, nrhs):
+    """Instances beyond what one workgroup adds up by itself (64), and more of them than it has threads:
+    each converges in the iterations it takes in a batch of two, to the same residual."""
+    P = _lsdd()
+    kinds = [fegen.elasticity_q1(4, nu=nu) for nu in (0.3, 0.45)]
+    n = kinds[0].n
+    rng = np.random.default_rng(8)
+    rhs = rng.standard_normal((nrhs, 2, n))
+    rhs[0, 1] = 0.0                                     # a pair that never starts
+    prm = P.Params.default(max_levels=2, modes_fixed=2, min_coarse=1, max_density=1.0, rtol=1e-10)
+
+    def solve(reps):
+        b = np.concatenate([rhs.reshape(nrhs, -1)] * reps, axis=1)
+        with P.Hierarchy.setup_batched([kinds[i % 2] for i in range(2 * reps)], prm) as h:
+            x, infos = h.solve(torch.from_numpy(b if nrhs > 1 else b[0]).cuda())
+        return (x.cpu().numpy().reshape(nrhs, reps, 2 * n),
+                [[(f.iters, f.rel_res, f.converged) for f in infos[k * 2 * reps:(k + 1) * 2 * reps]] for k in range(nrhs)])
+
+    x2, i2 = solve(1)
+    x, infos = solve((count + 1) // 2)
+    assert all(i[2] == 1 for row in i2 for i in row) and i2[0][1][0] == 0
+    for k in range(nrhs):
+        assert infos[k] == i2[k] * ((count + 1) // 2)
+        assert np.array_equal(x[k], np.broadcast_to(x2[k], x[k].shape))
