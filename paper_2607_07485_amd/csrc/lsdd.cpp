@@ -296,6 +296,8 @@ struct VecSet {
     T* scr = nullptr;
 };
 
+constexpr int XFER_DOWN = 1, XFER_UP = 2;
+
 struct Level {
     int32_t level = 0;
     int64_t n = 0;
@@ -368,11 +370,12 @@ struct Level {
     int32_t* d_pitems = nullptr;  // prolongation work items
     int64_t n_ritems = 0, n_pitems = 0;
     double* d_mu = nullptr;
-    // Single-vector cycle kernels of levels bound by launches (fuse.hip).  fuse: 0 separate
-    // launches (residual rows, tiled product, partial sums), 1 one launch per colour, 2
-    // residual rows and whole rows of the unpacked inverses; with 1 and 2 the transfers run
-    // fused with the level's residual.  fuse_has: the modes whose tables are there
-    int fuse = 0;
+    // Single-vector cycle kernels of levels bound by launches (fuse.hip), for the FP64 and the
+    // FP32 cycle.  fuse: sweeps by 0 separate launches (residual rows, tiled product, partial
+    // sums), 1 one launch per colour, 2 residual rows and whole rows of the unpacked inverses.
+    // xfer: XFER_DOWN residual and restriction in one launch, XFER_UP prolongation by
+    // aggregates.  fuse_has: the sweep modes whose tables are there
+    int fuse[2] = {0, 0}, xfer[2] = {0, 0};
     bool fuse_has[3] = {true, false, false};
     SubItem* d_sitems = nullptr;      // subdomains in sweep order
     int4* d_srows = nullptr;          // their row tables, spad entries each
@@ -383,9 +386,8 @@ struct Level {
     double* d_full = nullptr;         // unpacked inverses
     float* d_full32 = nullptr;
     int32_t spad = 0, apad = 0, max_k = 0, row_len = 0;
-    bool fuse_rr = false;             // an aggregate's rows are few enough for one workgroup
-    int tuned_fuse = 0;               // the autotuner's choice and the launch shapes it made it with
-    int32_t tuned[7] = {};
+    int tuned_fuse[2] = {0, 0}, tuned_xfer[2] = {0, 0};   // the autotuner's choice
+    int32_t tuned[2][7] = {};         // and the launch shapes it made it with
     double* d_cfull = nullptr;        // coarsest level of at most DENSE_MAX DOFs: its inverse, unpacked
     // smoother, sweep order (colour-major, aggregate index within a colour)
     std::vector<int32_t> sweep;
@@ -989,21 +991,40 @@ bool build_fused(lsdd_hierarchy* h, Level& lv, const std::vector<int64_t>& sw_tp
     }
     HIPCHK(hipGetLastError());
     sync(st);
-    // Until the autotuner has timed the modes: one launch per colour up to |Omega| = 128 (ms
-    // per sweep, one launch against two against three: |Omega| <= 50 0.019 / 0.028 / 0.040,
-    // <= 123 0.041 / 0.053 / 0.081), two above (<= 141 0.036 / 0.029 / 0.072, <= 161 0.060 /
-    // 0.030 / 0.063, <= 552 0.094 / 0.046 / 0.062), where a workgroup per subdomain leaves
-    // most CUs idle.  Past some 24 MB per colour the matrix entries set the time of all three
-    // and the packed ones are the fewest.
+    // Until the autotuner has timed them (us per pair of sweeps in modes 0 / 1 / 2, FP64):
+    // * overlaps up to 64: one launch per colour (121 of 50: 75 / 35 / 52; 4,489 a colour 284 /
+    //   219), separate launches from 5,000 a colour (6,750 a colour: 241 / 259 / 383) and where
+    //   the classes are no colouring (block Jacobi, 1,936 of 18: 22 / - / 29);
+    // * up to 128: one launch (841 of 123: 159 / 75 / 99) up to 24 MB per colour;
+    // * else rows of the unpacked inverses (121 of 552: 171 / 302 / 125; 64 of 1515: 934 / - / 811;
+    //   2,025 of 100, 40 MB a colour: 274 / 156 / 165).
+    // The way down in one launch where a workgroup has not too many rows' entries (16 aggregates
+    // of 441 x 376: 77 us against 16 in two launches) and small aggregates are not too many
+    // (1,849 of 18 DOFs: 7.3 against 10.8, 10,201: 32 against 21).  The way up by aggregates where
+    // their blocks of Z are not too large (841 of 81 x 7: 4.8 against 7.3; 54 of 648 x 113: 13.3
+    // against 10.4; in FP32 16 of 441 x 149: 9.4 against 9.3, and a solve 1.5 % faster) and, for
+    // small ones, which are one launch either way, where they have more modes than a thread
+    // should add up (100 of 63 x 23: 3.5 against 4.4; 1,849 of 18 x 4: 5.9 against 3.7).
     double bytes = 0.0;
-    for (int32_t c = 0; c < lv.n_colors; ++c)
+    int32_t per_colour = 0;
+    for (int32_t c = 0; c < lv.n_colors; ++c) {
         bytes = std::max(bytes, 8.0 * (lv.color_m2[c] + lv.color_pk[c]) + 12.0 * lv.color_nnz[c]);
-    lv.fuse = lv.fuse_has[1] && max_sub <= 128 && bytes <= 24e6 ? 1 : lv.fuse_has[2] ? 2 : 0;
-    // 16 aggregates of 441 rows x 376 entries: 52 us in one workgroup each, 10.7 us as a
-    // product and a restriction; 100 of 80 x 46 entries: 6.4 against 14 us
-    lv.fuse_rr = (double)max_nw * lv.row_len <= 16384.0;
-    vlog("level %d: single-vector mode %d (%.1f MB per colour, overlaps up to %d, %d entries per row)", lv.level,
-         lv.fuse, bytes * 1e-6, max_sub, lv.row_len);
+        per_colour = std::max(per_colour, lv.color_sub0[c + 1] - lv.color_sub0[c]);
+    }
+    int mode = lv.fuse_has[2] ? 2 : 0;
+    if (max_sub <= SMALL_M) mode = lv.fuse_has[1] && per_colour < 5000 ? 1 : 0;
+    else if (max_sub <= 128 && lv.fuse_has[1] && bytes <= 24e6) mode = 1;
+    const bool small = max_nw <= SMALL_M;
+    const int down = (double)max_nw * lv.row_len <= 16384.0 && (!small || n_sub <= 2500) ? XFER_DOWN : 0;
+    auto up = [&](double w) {
+        return (small ? lv.max_k >= 12 && n_sub <= 500 : max_nw * w * lv.max_k <= 288e3) ? XFER_UP : 0;
+    };
+    for (int p = 0; p < 2; ++p) {
+        lv.fuse[p] = mode;
+        lv.xfer[p] = down | up(p ? 4.0 : 8.0);
+    }
+    vlog("level %d: single-vector mode %d, transfers %d (%.1f MB per colour, %d aggregates of up to %d DOFs and %d modes, overlaps up to %d, %d entries per row)",
+         lv.level, mode, lv.xfer[0], bytes * 1e-6, n_sub, max_nw, lv.max_k, max_sub, lv.row_len);
     return lv.fuse_has[2];
 }
 
@@ -2063,12 +2084,12 @@ void sweep(lsdd_hierarchy* h, Level& lv, const T* r, T* x, bool forward, bool x_
         }
     }
     if constexpr (NR == 1) {
-        if (lv.fuse) {
+        if (const int mode = lv.fuse[std::is_same<T, float>::value]) {
             for (int32_t cc = 0; cc < lv.n_colors; ++cc) {
                 const int32_t c = forward ? cc : lv.n_colors - 1 - cc;
                 const bool xz = x_zero_first && cc == 0;
                 const double ab = xz ? 0.0 : lv.color_nnz[c] * ((lv.d_scoff ? lv.sup_ib : 4.0) + w);
-                if (lv.fuse == 2) {
+                if (mode == 2) {
                     traced(h, "csr_resid_rows", lv.color_m[c] * (4 + 8 + 3 * w) + ab, [&] {
                         C::template resid_colour<T>(lv, c, O::val(lv), x, r, v.rloc, xz, h->st);
                     });
@@ -2142,61 +2163,22 @@ void terminal_solve(lsdd_hierarchy* h, Level& lv, const double* r, double* x) {
                  h->st);
 }
 
-// x_zero: the caller has zeroed x
+// r_c = Z^T (r - A x) on the next level; fused: in one launch, which also zeroes x_c
 template <typename T, int NR>
-void vcycle(lsdd_hierarchy* h, size_t l, const T* r, T* x, bool x_zero = false) {
+void descend(lsdd_hierarchy* h, Level& lv, Level& nx, const T* r, const T* x, bool fused) {
     using O = LvOps<T>;
     using C = Cyc<T, NR>;
     constexpr int b = NR > 1 ? 1 : 0;
-    Level& lv = *h->L[l];
-    const double w = (double)sizeof(T), wv = w * NR;
-    // terminal blocks (all of the coarsest level) in FP64
-    auto terminal = [&] {
-        if constexpr (NR == 1) {
-            if (lv.coarsest && lv.d_cfull) {
-                traced(h, "coarse_dense", (double)lv.n * lv.n * 8.0 + 2.0 * lv.n * w,
-                       [&] { launch_dense_apply<T>(lv.n, lv.d_cfull, r, x, h->st); });
-                return;
-            }
-        }
-        if constexpr (std::is_same<T, double>::value) {
-            terminal_solve<NR>(h, lv, r, x);
-        } else {
-            launch_to_f64(lv.n * NR, r, lv.cr64[b], h->st);
-            if (!lv.coarsest) launch_zero<double>(lv.n * NR, lv.cx64[b], h->st);
-            terminal_solve<NR>(h, lv, lv.cr64[b], lv.cx64[b]);
-            launch_to_f32(lv.n * NR, lv.cx64[b], x, h->st);
-        }
-    };
-    if (lv.coarsest) {
-        terminal();
-        return;
-    }
-    Level& nx = *h->L[l + 1];
     VecSet<T>& v = O::v(lv, b);
     VecSet<T>& vn = O::v(nx, b);
-    if (!x_zero) launch_zero<T>(lv.n * NR, x, h->st);
-    if (!lv.term.empty()) terminal();     // instances whose hierarchy ends on this level
-    sweep<T, NR>(h, lv, r, x, true, true);
+    const double w = (double)sizeof(T), wv = w * NR;
     if constexpr (NR == 1) {
-        if (lv.fuse && h->cycle_prec != 2) {
+        if (fused) {
             const double tb = (double)lv.zoff.back() * w + (double)lv.n * 16 + (double)nx.n * w;
-            if (lv.fuse_rr) {
-                traced(h, "resid_restrict", tb + full_apply_bytes(lv, w, w, true), [&] {
-                    launch_resid_restrict<T>(lv.cl.n_agg, lv.d_aitems, lv.d_arows, lv.d_scoff ? lv.d_scol : lv.d_col,
-                                             O::val(lv), O::Z(lv), r, x, vn.r, vn.x, lv.apad, lv.row_len, h->st);
-                });
-            } else {
-                traced(h, "csr_spmv", full_apply_bytes(lv, w, w, true),
-                       [&] { C::spmv(lv, O::val(lv), x, v.t, r, h->st); });
-                traced(h, "restrict", tb, [&] { C::restrict_(lv, O::Z(lv), v.t, vn.r, h->st); });
-            }
-            vcycle<T, NR>(h, l + 1, vn.r, vn.x, lv.fuse_rr);
-            traced(h, "prolong_agg", tb + (double)lv.n * w, [&] {
-                launch_prolong_agg<T>(lv.cl.n_agg, lv.d_aitems, lv.d_arows, O::Z(lv), vn.x, x, lv.apad, lv.max_k,
-                                      h->st);
+            traced(h, "resid_restrict", tb + full_apply_bytes(lv, w, w, true), [&] {
+                launch_resid_restrict<T>(lv.cl.n_agg, lv.d_aitems, lv.d_arows, lv.d_scoff ? lv.d_scol : lv.d_col,
+                                         O::val(lv), O::Z(lv), r, x, vn.r, vn.x, lv.apad, lv.row_len, h->st);
             });
-            sweep<T, NR>(h, lv, r, x, false, false);
             return;
         }
     }
@@ -2220,10 +2202,66 @@ void vcycle(lsdd_hierarchy* h, size_t l, const T* r, T* x, bool x_zero = false) 
                NR == 1 ? full_apply_bytes(lv, w, wv, true)
                        : (double)lv.nnz * ((lv.sup ? lv.sup_ib : 4.0) + w) + (double)lv.n * (8 + 3 * wv),
                [&] { C::spmv(lv, O::val(lv), x, v.t, r, h->st); });
-    const double zb = (double)lv.zoff.back() * w + (double)lv.n * (4 + wv) + (double)nx.n * wv;
-    traced(h, "restrict", zb, [&] { C::restrict_(lv, O::Z(lv), v.t, vn.r, h->st); });
-    vcycle<T, NR>(h, l + 1, vn.r, vn.x);
-    traced(h, "prolong", zb + (double)lv.n * wv, [&] { C::prolong(lv, O::Z(lv), vn.x, x, h->st); });
+    traced(h, "restrict", (double)lv.zoff.back() * w + (double)lv.n * (4 + wv) + (double)nx.n * wv,
+           [&] { C::restrict_(lv, O::Z(lv), v.t, vn.r, h->st); });
+}
+
+// x += Z x_c; fused: a workgroup per aggregate
+template <typename T, int NR>
+void ascend(lsdd_hierarchy* h, Level& lv, Level& nx, T* x, bool fused) {
+    using O = LvOps<T>;
+    const T* xc = O::v(nx, NR > 1 ? 1 : 0).x;
+    const double w = (double)sizeof(T), wv = w * NR;
+    if constexpr (NR == 1) {
+        if (fused) {
+            traced(h, "prolong_agg", (double)lv.zoff.back() * w + (double)lv.n * (16 + w) + (double)nx.n * w, [&] {
+                launch_prolong_agg<T>(lv.cl.n_agg, lv.d_aitems, lv.d_arows, O::Z(lv), xc, x, lv.apad, lv.max_k, h->st);
+            });
+            return;
+        }
+    }
+    traced(h, "prolong", (double)lv.zoff.back() * w + (double)lv.n * (4 + 2 * wv) + (double)nx.n * wv,
+           [&] { Cyc<T, NR>::prolong(lv, O::Z(lv), xc, x, h->st); });
+}
+
+// x_zero: the caller has zeroed x
+template <typename T, int NR>
+void vcycle(lsdd_hierarchy* h, size_t l, const T* r, T* x, bool x_zero = false) {
+    using O = LvOps<T>;
+    constexpr int b = NR > 1 ? 1 : 0;
+    Level& lv = *h->L[l];
+    const double w = (double)sizeof(T);
+    // terminal blocks (all of the coarsest level) in FP64
+    auto terminal = [&] {
+        if constexpr (NR == 1) {
+            if (lv.coarsest && lv.d_cfull) {
+                traced(h, "coarse_dense", (double)lv.n * lv.n * 8.0 + 2.0 * lv.n * w,
+                       [&] { launch_dense_apply<T>(lv.n, lv.d_cfull, r, x, h->st); });
+                return;
+            }
+        }
+        if constexpr (std::is_same<T, double>::value) {
+            terminal_solve<NR>(h, lv, r, x);
+        } else {
+            launch_to_f64(lv.n * NR, r, lv.cr64[b], h->st);
+            if (!lv.coarsest) launch_zero<double>(lv.n * NR, lv.cx64[b], h->st);
+            terminal_solve<NR>(h, lv, lv.cr64[b], lv.cx64[b]);
+            launch_to_f32(lv.n * NR, lv.cx64[b], x, h->st);
+        }
+    };
+    if (lv.coarsest) {
+        terminal();
+        return;
+    }
+    Level& nx = *h->L[l + 1];
+    VecSet<T>& vn = O::v(nx, b);
+    if (!x_zero) launch_zero<T>(lv.n * NR, x, h->st);
+    if (!lv.term.empty()) terminal();     // instances whose hierarchy ends on this level
+    sweep<T, NR>(h, lv, r, x, true, true);
+    const int xfer = NR == 1 && h->cycle_prec != 2 ? lv.xfer[std::is_same<T, float>::value] : 0;
+    descend<T, NR>(h, lv, nx, r, x, xfer & XFER_DOWN);
+    vcycle<T, NR>(h, l + 1, vn.r, vn.x, xfer & XFER_DOWN);
+    ascend<T, NR>(h, lv, nx, x, xfer & XFER_UP);
     sweep<T, NR>(h, lv, r, x, false, false);
 }
 
@@ -2460,9 +2498,10 @@ void set_chunk(lsdd_hierarchy* h, Level& lv, int chl) {
 }
 
 template <class F>
-double time_ms(lsdd_hierarchy* h, F&& fn, int reps = 5) {
-    // fastest of `reps` separately timed runs after a warm-up: the minimum is the
-    // least noisy estimate of a candidate's own cost
+double time_ms(lsdd_hierarchy* h, F&& fn, int reps = 5, int runs = 1) {
+    // fastest of `reps` separately timed samples (`runs` runs each, so that the events' own
+    // 4 us do not hide a short one) after a warm-up: the minimum is the least noisy
+    // estimate of a candidate's own cost
     fn();
     hipEvent_t a, b;
     HIPCHK(hipEventCreate(&a));
@@ -2470,12 +2509,12 @@ double time_ms(lsdd_hierarchy* h, F&& fn, int reps = 5) {
     float best = 3.0e38f;
     for (int r = 0; r < reps; ++r) {
         HIPCHK(hipEventRecord(a, h->st));
-        fn();
+        for (int i = 0; i < runs; ++i) fn();
         HIPCHK(hipEventRecord(b, h->st));
         HIPCHK(hipEventSynchronize(b));
         float ms = 0.0f;
         HIPCHK(hipEventElapsedTime(&ms, a, b));
-        best = std::min(best, ms);
+        best = std::min(best, ms / (float)runs);
     }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
@@ -2542,7 +2581,10 @@ void autotune_levels(lsdd_hierarchy* h) {
                     break;
                 }
                 vlog("autotune level %d: CSR lanes %d%s: %.3f ms", lv.level, L, sp ? ", shared column lists" : "", ms);
-                if (ms < best) best = ms, pick = L, pick_sup = sp;
+                // the lists are fewer bytes, which these runs, one after another, find in the
+                // caches and a cycle does not (residual rows of BFS 96^2: a tie here, 3 % there)
+                const double cost = sp && NR == 1 ? 0.97 * ms : ms;
+                if (cost < best) best = cost, pick = L, pick_sup = sp;
                 if (ms < best_row) best_row = ms, pick_row = L;
             }
         }
@@ -2562,22 +2604,51 @@ void autotune_levels(lsdd_hierarchy* h) {
             }
             lv.eapply = pick_e;
         }
-        // last: the fused kernels against the launches chosen above, a cycle's sweep each
+        // last: the fused kernels against the launches chosen above -- both sweeps of a cycle, the
+        // way down and the way up, each by itself
         auto pick_fused = [&] {
             if constexpr (NR == 1) {
-                lv.tuned_fuse = 0;
-                if (h->cycle_prec == 2) return;
-                double low = 1e300;
-                int pick_f = 0;
-                for (int f : {0, 1, 2}) {
-                    if (!lv.fuse_has[f]) continue;
-                    lv.fuse = f;
-                    const double ms = time_ms(h, [&] { sweep<T, NR>(h, lv, v.r, v.x, true, false); });
-                    vlog("autotune level %d: sweep in mode %d: %.3f ms", lv.level, f, ms);
-                    if (ms < low) low = ms, pick_f = f;
+                if (h->cycle_prec == 2 || lv.smoother == 1) return;
+                constexpr int p = std::is_same<T, float>::value;
+                Level& nx = *h->L[lv.level + 1];
+                VecSet<T>& vn = O::v(nx, b);
+                launch_zero<T>(nx.n, vn.r, h->st);
+                launch_zero<T>(nx.n, vn.x, h->st);
+                // the fastest candidate, or the one at hand if none is faster by 5 %: runs of one
+                // kernel after another find its operands in the caches, a cycle does not (the way
+                // up of 16 aggregates in FP32, 9.2 us apart against 9.4: the cycle is 3 us longer)
+                auto pick = [&](const char* what, int now, int runs, std::initializer_list<int> cand, auto&& run) {
+                    double low = 1e300;
+                    int best_c = now;
+                    for (int c : cand) {
+                        double ms = time_ms(h, [&] { run(c); }, 5, runs);
+                        vlog("autotune level %d: %s %d: %.4f ms", lv.level, what, c, ms);
+                        if (c == now) ms *= 0.95;
+                        if (ms < low) low = ms, best_c = c;
+                    }
+                    return best_c;
+                };
+                auto sweeps = [&](int f) {
+                    lv.fuse[p] = lv.fuse_has[f] ? f : 0;
+                    sweep<T, NR>(h, lv, v.r, v.x, true, true);
+                    sweep<T, NR>(h, lv, v.r, v.x, false, false);
+                };
+                const int now = lv.fuse[p];
+                if (lv.fuse_has[1] && lv.fuse_has[2]) lv.tuned_fuse[p] = pick("sweeps, mode", now, 1, {0, 1, 2}, sweeps);
+                else if (lv.fuse_has[1]) lv.tuned_fuse[p] = pick("sweeps, mode", now, 1, {0, 1}, sweeps);
+                else if (lv.fuse_has[2]) lv.tuned_fuse[p] = pick("sweeps, mode", now, 1, {0, 2}, sweeps);
+                lv.fuse[p] = lv.tuned_fuse[p];
+                lv.tuned_xfer[p] = 0;
+                if (lv.d_arows) {
+                    lv.tuned_xfer[p] = pick("way down, fused", lv.xfer[p] & XFER_DOWN, 8, {0, XFER_DOWN}, [&](int c) {
+                        if (!c) launch_zero<T>(nx.n, vn.x, h->st);
+                        descend<T, NR>(h, lv, nx, v.r, v.x, c);
+                    });
+                    lv.tuned_xfer[p] |= pick("way up, fused", lv.xfer[p] & XFER_UP, 8, {0, XFER_UP},
+                                             [&](int c) { ascend<T, NR>(h, lv, nx, v.x, c); });
                 }
-                lv.fuse = lv.tuned_fuse = pick_f;
-                level_shapes(lv, lv.tuned);
+                lv.xfer[p] = lv.tuned_xfer[p];
+                level_shapes(lv, lv.tuned[p]);
             }
         };
         if (lv.color_item0.back() == 0) {           // no large overlap on this level
@@ -3472,7 +3543,11 @@ lsdd_status lsdd_set_level_tuning(lsdd_hierarchy* h, int32_t level, const int32_
                                         "of at most 128 DOFs");
     // shapes set by hand are those of the separate launches; the shapes the autotuner found
     // bring back its choice between these and the fused kernels
-    lv.fuse = std::equal(in, in + 7, lv.tuned) ? lv.tuned_fuse : 0;
+    for (int p = 0; p < 2; ++p) {
+        const bool t = std::equal(in, in + 7, lv.tuned[p]);
+        lv.fuse[p] = t ? lv.tuned_fuse[p] : 0;
+        lv.xfer[p] = t ? lv.tuned_xfer[p] : 0;
+    }
     lv.eapply = in[4];
     lv.sup = in[5];
     lv.fact_stash = in[6];

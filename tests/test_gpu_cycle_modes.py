@@ -178,7 +178,8 @@ def test_eigenpairs_do_not_depend_on_larger_aggregates_in_the_batch(mate):
 @pytest.mark.parametrize("count", [64, 65, 1200])
 def test_many_instances(count, nrhs):
     """Instances beyond what one workgroup adds up by itself (64), and more of them than it has threads:
-    each converges in the iterations it takes in a batch of two, to the same residual."""
+    each converges in the iterations it takes in a batch of two, to the same residual (cycles in
+    separate launches, which do not depend on the size of the batch)."""
     P = _lsdd()
     kinds = [fegen.elasticity_q1(4, nu=nu) for nu in (0.3, 0.45)]
     n = kinds[0].n
@@ -190,6 +191,7 @@ def test_many_instances(count, nrhs):
     def solve(reps):
         b = np.concatenate([rhs.reshape(nrhs, -1)] * reps, axis=1)
         with P.Hierarchy.setup_batched([kinds[i % 2] for i in range(2 * reps)], prm) as h:
+            _separate(h)
             x, infos = h.solve(torch.from_numpy(b if nrhs > 1 else b[0]).cuda())
         return (x.cpu().numpy().reshape(nrhs, reps, 2 * n),
                 [[(f.iters, f.rel_res, f.converged) for f in infos[k * 2 * reps:(k + 1) * 2 * reps]] for k in range(nrhs)])
