@@ -358,11 +358,29 @@ lsdd_status lsdd_level_tuning(const lsdd_hierarchy* h, int32_t level, int32_t* o
  * DOFs, or shared column lists (row blocks) on a level without them ->
  * LSDD_E_UNSUPPORTED (the
  * triangles are built on first use).  Captured PCG graphs are
- * dropped and recaptured on the next solve.  The shapes are those of a cycle in separate
- * launches: a level that runs single vectors through the fused kernels goes back to
- * separate launches, except with the shapes lsdd_autotune chose along with them.  Like
- * lsdd_autotune, it changes only the summation order of the sums involved. */
+ * dropped and recaptured on the next solve.  The kernels of the single-vector cycle
+ * (lsdd_level_kernels) follow: shapes that lsdd_autotune chose for the current cycle
+ * precision bring back what it chose with them, the shapes in effect and those it chose
+ * for another precision or for blocks change nothing, and any others put the level into
+ * separate launches for every precision.  Like lsdd_autotune, it changes only the
+ * summation order of the sums involved. */
 lsdd_status lsdd_set_level_tuning(lsdd_hierarchy* h, int32_t level, const int32_t* in);
+
+/* Kernels of the single-vector cycle on level l for the current cycle precision (host
+ * int32[3]): the sweeps in separate launches (0), in one launch per colour (1) or by rows of
+ * the unpacked subdomain inverses (2); the transfers, a sum of 1 (residual and restriction
+ * in one launch) and 2 (prolongation by aggregates); and whether lsdd_autotune or
+ * lsdd_set_level_kernels chose them (1) or the library's rule or lsdd_set_level_tuning
+ * did (0).  The mixed cycle and the restricted additive Schwarz smoother run in separate
+ * launches. */
+lsdd_status lsdd_level_kernels(const lsdd_hierarchy* h, int32_t level, int32_t* out);
+
+/* Set them (host int32[2], the first two values of lsdd_level_kernels), e.g. to restore on
+ * one hierarchy what lsdd_autotune chose on another.  Values outside these -> LSDD_E_INVAL;
+ * kernels the level does not have -> LSDD_E_UNSUPPORTED (sweeps: one launch per colour
+ * needs a colouring and overlaps of at most 640 DOFs, rows of the unpacked inverses need
+ * room for these).  Drops captured PCG graphs; changes only the order of sums. */
+lsdd_status lsdd_set_level_kernels(lsdd_hierarchy* h, int32_t level, const int32_t* in);
 
 /* Per-kernel timing: on != 0 clears the counters and records a pair of HIP
  * events on the solve stream around every launch of the traced kernel classes

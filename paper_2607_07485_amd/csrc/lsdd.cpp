@@ -386,8 +386,9 @@ struct Level {
     double* d_full = nullptr;         // unpacked inverses
     float* d_full32 = nullptr;
     int32_t spad = 0, apad = 0, max_k = 0, row_len = 0;
+    bool chosen[2] = {false, false};  // by the autotuner or the caller, not by the rule
     int tuned_fuse[2] = {0, 0}, tuned_xfer[2] = {0, 0};   // the autotuner's choice
-    int32_t tuned[2][7] = {};         // and the launch shapes it made it with
+    int32_t tuned[4][7] = {};         // and its launch shapes: FP64, FP32, mixed cycle, blocks
     double* d_cfull = nullptr;        // coarsest level of at most DENSE_MAX DOFs: its inverse, unpacked
     // smoother, sweep order (colour-major, aggregate index within a colour)
     std::vector<int32_t> sweep;
@@ -2648,7 +2649,7 @@ void autotune_levels(lsdd_hierarchy* h) {
                                              [&](int c) { ascend<T, NR>(h, lv, nx, v.x, c); });
                 }
                 lv.xfer[p] = lv.tuned_xfer[p];
-                level_shapes(lv, lv.tuned[p]);
+                lv.chosen[p] = true;
             }
         };
         if (lv.color_item0.back() == 0) {           // no large overlap on this level
@@ -2708,6 +2709,7 @@ void autotune_levels(lsdd_hierarchy* h) {
         }
         pick_fused();
     }
+    for (auto& lp : h->L) level_shapes(*lp, lp->tuned[NR > 1 ? 3 : h->cycle_prec]);
     sync(h->st);
 }
 
@@ -3541,12 +3543,22 @@ lsdd_status lsdd_set_level_tuning(lsdd_hierarchy* h, int32_t level, const int32_
     if (in[4] && !build_elem_apply(h, lv))
         throw Error(LSDD_E_UNSUPPORTED, "element apply: only on level 0 of a hierarchy built from element blocks "
                                         "of at most 128 DOFs");
-    // shapes set by hand are those of the separate launches; the shapes the autotuner found
-    // bring back its choice between these and the fused kernels
-    for (int p = 0; p < 2; ++p) {
-        const bool t = std::equal(in, in + 7, lv.tuned[p]);
-        lv.fuse[p] = t ? lv.tuned_fuse[p] : 0;
-        lv.xfer[p] = t ? lv.tuned_xfer[p] : 0;
+    // the shapes the autotuner found for this precision bring back the kernels it chose with
+    // them; other shapes than its own and those in effect are meant for separate launches
+    int32_t cur[7];
+    level_shapes(lv, cur);
+    const int p = h->cycle_prec;
+    bool own = std::equal(in, in + 7, cur);
+    for (auto& t : lv.tuned) own = own || std::equal(in, in + 7, t);
+    if (p < 2 && std::equal(in, in + 7, lv.tuned[p])) {
+        lv.fuse[p] = lv.tuned_fuse[p];
+        lv.xfer[p] = lv.tuned_xfer[p];
+        lv.chosen[p] = true;
+    } else if (!own) {
+        for (int q = 0; q < 2; ++q) {
+            lv.fuse[q] = lv.xfer[q] = 0;
+            lv.chosen[q] = false;
+        }
     }
     lv.eapply = in[4];
     lv.sup = in[5];
@@ -3558,6 +3570,38 @@ lsdd_status lsdd_set_level_tuning(lsdd_hierarchy* h, int32_t level, const int32_
         set_chunk(h, lv, in[2]);
         sync(h->st);
     }
+    reset_graphs(h);
+    return LSDD_OK;
+    ABI_END
+}
+
+lsdd_status lsdd_level_kernels(const lsdd_hierarchy* h, int32_t level, int32_t* out) {
+    ABI_BEGIN
+    if (!h || !out || level < 0 || level >= (int32_t)h->L.size()) throw Error(LSDD_E_INVAL, "bad argument");
+    const Level& lv = *h->L[level];
+    const int p = h->cycle_prec;
+    out[0] = p < 2 ? lv.fuse[p] : 0;
+    out[1] = p < 2 ? lv.xfer[p] : 0;
+    out[2] = p < 2 && lv.chosen[p];
+    return LSDD_OK;
+    ABI_END
+}
+
+lsdd_status lsdd_set_level_kernels(lsdd_hierarchy* h, int32_t level, const int32_t* in) {
+    ABI_BEGIN
+    if (!h || !in || level < 0 || level >= (int32_t)h->L.size() || in[0] < 0 || in[0] > 2 || in[1] < 0 ||
+        in[1] > (XFER_DOWN | XFER_UP))
+        throw Error(LSDD_E_INVAL, "bad argument");
+    Level& lv = *h->L[level];
+    const int p = h->cycle_prec;
+    if (p == 2 && (in[0] || in[1]))
+        throw Error(LSDD_E_UNSUPPORTED, "the mixed cycle runs in separate launches");
+    if (p == 2) return LSDD_OK;
+    if (!lv.fuse_has[in[0]] || (in[1] && !lv.d_arows))
+        throw Error(LSDD_E_UNSUPPORTED, "the level does not have these kernels of the single-vector cycle");
+    lv.fuse[p] = in[0];
+    lv.xfer[p] = in[1];
+    lv.chosen[p] = true;
     reset_graphs(h);
     return LSDD_OK;
     ABI_END

@@ -101,6 +101,8 @@ def lib():
                                          C.POINTER(Info)]
         L.lsdd_level_tuning.argtypes = [_P, C.c_int32, i32p]
         L.lsdd_set_level_tuning.argtypes = [_P, C.c_int32, i32p]
+        L.lsdd_level_kernels.argtypes = [_P, C.c_int32, i32p]
+        L.lsdd_set_level_kernels.argtypes = [_P, C.c_int32, i32p]
         L.lsdd_set_allocator.restype = None
         for name in ("lsdd_setup_elements", "lsdd_setup_gram_csr", "lsdd_solve", "lsdd_solve_stationary",
                      "lsdd_vcycle", "lsdd_apply",
@@ -109,7 +111,8 @@ def lib():
                      "lsdd_set_solve_params", "lsdd_set_graph", "lsdd_segments", "lsdd_setup_batched",
                      "lsdd_level_segments", "lsdd_autotune", "lsdd_level_tuning", "lsdd_setup_elements_scaled",
                      "lsdd_update_theta", "lsdd_elem_bilinear", "lsdd_elem_bilinear_noalloc",
-                     "lsdd_solve_batched", "lsdd_export_gram_level", "lsdd_set_level_tuning"):
+                     "lsdd_solve_batched", "lsdd_export_gram_level", "lsdd_set_level_tuning",
+                     "lsdd_level_kernels", "lsdd_set_level_kernels"):
             getattr(L, name).restype = C.c_int
         _LIB = L
     return _LIB
@@ -337,17 +340,37 @@ class Hierarchy:
         _check(lib().lsdd_autotune(self._h, 1 if block else 0, _stream()))
         return [self.level_tuning(l) for l in range(self.info()["levels"])]
 
+    def level_kernels(self, level: int):
+        """lsdd_level_kernels: (sweeps, transfers, chosen) of the current cycle precision."""
+        out = np.zeros(3, dtype=np.int32)
+        _check(lib().lsdd_level_kernels(self._h, int(level), out.ctypes.data_as(C.POINTER(C.c_int32))))
+        return tuple(out.tolist())
+
+    def set_level_kernels(self, level: int, sweeps: int, transfers: int):
+        """lsdd_set_level_kernels, for the current cycle precision."""
+        a = np.array([sweeps, transfers], dtype=np.int32)
+        _check(lib().lsdd_set_level_kernels(self._h, int(level), a.ctypes.data_as(C.POINTER(C.c_int32))))
+
     def level_tuning(self, level: int):
+        """lsdd_level_tuning as a dict; with "sweeps" and "transfers" of lsdd_level_kernels where they
+        were chosen for the current cycle precision."""
         out = np.zeros(7, dtype=np.int32)
         _check(lib().lsdd_level_tuning(self._h, int(level), out.ctypes.data_as(C.POINTER(C.c_int32))))
-        return dict(lanes=int(out[0]), lanes_block=int(out[1]), tiles_per_item=int(out[2]), finalize_threads=int(out[3]),
-                    elem_apply=int(out[4]), shared_cols=int(out[5]), fact_stash=int(out[6]))
+        t = dict(lanes=int(out[0]), lanes_block=int(out[1]), tiles_per_item=int(out[2]), finalize_threads=int(out[3]),
+                 elem_apply=int(out[4]), shared_cols=int(out[5]), fact_stash=int(out[6]))
+        sweeps, transfers, chosen = self.level_kernels(level)
+        return dict(t, sweeps=sweeps, transfers=transfers) if chosen else t
 
     def set_level_tuning(self, level: int, t: dict):
-        """lsdd_set_level_tuning with a dict as returned by level_tuning."""
+        """lsdd_set_level_tuning with a dict as returned by level_tuning, and lsdd_set_level_kernels
+        with its "sweeps" and "transfers" if it has them."""
         a = np.array([t["lanes"], t["lanes_block"], t["tiles_per_item"], t["finalize_threads"],
                       t.get("elem_apply", 0), t.get("shared_cols", 0), t.get("fact_stash", 1)], dtype=np.int32)
+        if "sweeps" in t:                      # refused before anything changes
+            self.set_level_kernels(level, t["sweeps"], t["transfers"])
         _check(lib().lsdd_set_level_tuning(self._h, int(level), a.ctypes.data_as(C.POINTER(C.c_int32))))
+        if "sweeps" in t:
+            self.set_level_kernels(level, t["sweeps"], t["transfers"])
 
     def set_tuning(self, tuning):
         """Apply a list of per-level shapes (the return value of autotune)."""

@@ -202,3 +202,111 @@ def test_many_instances(count, nrhs):
     for k in range(nrhs):
         assert infos[k] == i2[k] * ((count + 1) // 2)
         assert np.array_equal(x[k], np.broadcast_to(x2[k], x[k].shape))
+
+
+def _kernels(h):
+    return [h.level_kernels(l) for l in range(h.info()["levels"] - 1)]
+
+
+def _launched(h, r):
+    """Names and counts of the traced launches of one V-cycle."""
+    h.trace(True)
+    h.vcycle(r)
+    h.trace(False)
+    return {k: v["launches"] for k, v in h.trace_read().items() if v["launches"]}
+
+
+def test_tuning_describes_the_tuned_state():
+    """Reading the shapes and setting them back changes nothing, tuned or not; the tuning of every
+    precision brings its kernels back after the others were tuned, on this hierarchy, on a new one and
+    through the seven shapes alone; shapes set by hand run in separate launches."""
+    P = _lsdd()
+    prob = fegen.elasticity_q1(64, nu=0.3)
+    r = torch.from_numpy(np.random.default_rng(9).standard_normal(prob.n)).cuda()
+    prm = P.Params.default(max_levels=3, tau_const=0.75, precision=2)
+    shapes = ("lanes", "lanes_block", "tiles_per_item", "finalize_threads", "elem_apply", "shared_cols", "fact_stash")
+    with P.Hierarchy.setup_problem(prob, prm) as h, P.Hierarchy.setup_problem(prob, prm) as other:
+        levels = range(h.info()["levels"])
+        h.set_cycle_precision(0)
+        rule, ran = _kernels(h), _launched(h, r)
+        assert any(k[0] for k in rule) and not any(k[2] for k in rule) and "colour_step" in ran
+        h.set_tuning([h.level_tuning(l) for l in levels])
+        assert _kernels(h) == rule and _launched(h, r) == ran
+        tuned, state, names = {}, {}, {}
+        for p in (0, 1, 2):
+            h.set_cycle_precision(p)
+            tuned[p] = h.autotune()
+            state[p], names[p] = _kernels(h), _launched(h, r)
+        assert "colour_step" not in names[2] and "sub_rows" not in names[2]
+        for p in (0, 2, 1, 0, 1, 2, 0):
+            h.set_cycle_precision(p)
+            h.set_tuning(tuned[p])
+            assert _kernels(h) == state[p] and _launched(h, r) == names[p]
+            other.set_cycle_precision(p)
+            other.set_tuning(tuned[p])
+            assert _kernels(other) == state[p] and _launched(other, r) == names[p]
+        h.set_cycle_precision(1)
+        h.autotune(block=True)                              # other shapes, the same kernels
+        assert [k[:2] for k in _kernels(h)] == [k[:2] for k in state[1]]
+        for p in (0, 1):                                    # by the shapes alone
+            h.set_cycle_precision(p)
+            h.set_tuning([{k: t[k] for k in shapes} for t in tuned[p]])
+            assert _kernels(h) == state[p]
+        _separate(h)
+        for p in (0, 1):
+            h.set_cycle_precision(p)
+            assert _kernels(h) == [(0, 0, 0)] * (len(levels) - 1)
+            assert not {"colour_step", "sub_rows", "resid_restrict", "prolong_agg"} & set(_launched(h, r))
+        h.set_cycle_precision(0)
+        for bad in ((3, 0), (-1, 0), (0, 4)):
+            with pytest.raises(P.LsddError) as e:
+                h.set_level_kernels(0, *bad)
+            assert e.value.code == 1
+        h.set_cycle_precision(2)
+        with pytest.raises(P.LsddError) as e:
+            h.set_level_kernels(0, 1, 0)
+        assert e.value.code == 7
+    with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2, modes_fixed=4, smoother=2)) as h:
+        with pytest.raises(P.LsddError) as e:               # its one class is no colouring
+            h.set_level_kernels(0, 1, 0)
+        assert e.value.code == 7
+
+
+@pytest.mark.parametrize("kind", ["q14", "q117", "p1", "bfs", "rtcf"])
+def test_every_kernel_of_the_cycle_matches_separate_launches(kind):
+    """All combinations of sweeps and transfers a hierarchy has against separate launches, FP64 and FP32,
+    before and after an update of the operator (the same sums in another order: 1e-10; the FP32 cycle
+    within 4x of the distance separate launches have from the FP64 cycle)."""
+    from test_gpu_solve_kernels import _cycle_problem
+    P = _lsdd()
+    prob, kw = _cycle_problem(kind)
+    r = torch.from_numpy(np.random.default_rng(1).standard_normal(prob.n)).cuda()
+    theta = torch.ones(prob.n_elem, dtype=torch.float64, device="cuda")
+    blocks = torch.from_numpy(np.ascontiguousarray(prob.blocks)).cuda()
+    with P.Hierarchy.setup_elements_scaled(prob.n, prob.elem_ptr, prob.elem_dofs, blocks, theta, prob.node_of_dof,
+                                           prob.agg_of_dof, P.Params.default(precision=1, **kw)) as h:
+        def cycles(sweeps, transfers):
+            out = []
+            for scale in (1.0, 1.25):
+                h.update_theta(theta * scale)
+                for prec in (0, 1):
+                    h.set_cycle_precision(prec)
+                    for l in range(h.info()["levels"] - 1):
+                        h.set_level_kernels(l, sweeps, transfers)
+                    out.append(h.vcycle(r))
+            return out
+
+        apart, tried = cycles(0, 0), 0
+        for sweeps in (0, 1, 2):
+            for transfers in (0, 1, 2, 3):
+                try:
+                    z = cycles(sweeps, transfers)
+                except P.LsddError as e:
+                    assert e.code == 7 and (sweeps == 1 or transfers)
+                    continue
+                tried += 1
+                for i in (0, 2):
+                    n = float(apart[i].norm())
+                    assert float((z[i] - apart[i]).norm()) <= 1e-10 * n
+                    assert float((z[i + 1] - z[i]).norm()) <= 4 * float((apart[i + 1] - apart[i]).norm()) + 1e-12 * n
+        assert tried >= 5
