@@ -247,6 +247,38 @@ __global__ void __launch_bounds__(NW * 64) k_colour_step(const SubItem* __restri
     }
 }
 
+// Unpacked inverses from the packed ones, a 64 x 64 tile of the lower triangle at a time through
+// LDS, so that the rows of the tile and of its mirror image are contiguous on both sides.
+template <typename T>
+__global__ void __launch_bounds__(256) k_unpack(const int64_t* __restrict__ sub_off, const int64_t* __restrict__ tp_off,
+                                                const int64_t* __restrict__ pk_off, const T* __restrict__ tiles,
+                                                const T* __restrict__ pk, const int64_t* __restrict__ full_off,
+                                                T* __restrict__ full) {
+    __shared__ T s[64][65];
+    const int sb = blockIdx.x;
+    const int m = (int)(sub_off[sb + 1] - sub_off[sb]);
+    const int nt = (m + 63) >> 6;
+    T* F = full + full_off[sb];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int t = (int)blockIdx.y; t < nt * (nt + 1) / 2; t += (int)gridDim.y) {
+        int I = 0, J = t;
+        while (J > I) J -= ++I;
+        __syncthreads();
+        for (int r = w; r < 64; r += 4) {
+            const int i = I * 64 + r, j = J * 64 + lane;
+            if (m > SMALL_M) s[r][lane] = tiles[tp_off[sb] + (int64_t)t * 4096 + r * 64 + lane];
+            else if (i < m && j <= i) s[r][lane] = s[lane][r] = pk[pk_off[sb] + i * (i + 1) / 2 + j];
+        }
+        __syncthreads();
+        for (int r = w; r < 64; r += 4) {
+            const int i = I * 64 + r, j = J * 64 + lane;
+            if (i < m && j < m) F[(int64_t)i * m + j] = s[r][lane];
+            const int i2 = J * 64 + r, j2 = I * 64 + lane;
+            if (I != J && i2 < m && j2 < m) F[(int64_t)i2 * m + j2] = s[lane][r];
+        }
+    }
+}
+
 // x[Omega] += A_Omega^{-1} rloc by rows of the unpacked inverse, for subdomains too large
 // for one workgroup: a wave per 4 rows (rloc loaded once for the four), 16 rows per
 // workgroup, every row complete in its wave -- no partial sums to add in a second launch.
@@ -469,6 +501,15 @@ void launch_row_table(int64_t n_sub, const int64_t* off, const int32_t* dofs, co
 }
 
 template <typename T>
+void launch_unpack(int64_t n_sub, int max_sub, const int64_t* sub_off, const int64_t* tp_off, const int64_t* pk_off,
+                   const T* tiles, const T* pk, const int64_t* full_off, T* full, hipStream_t st) {
+    if (n_sub <= 0) return;
+    const int nt = (max_sub + 63) / 64;
+    hipLaunchKernelGGL(k_unpack<T>, dim3((unsigned)n_sub, (unsigned)std::min(nt * (nt + 1) / 2, 256)), dim3(256), 0, st,
+                       sub_off, tp_off, pk_off, tiles, pk, full_off, full);
+}
+
+template <typename T>
 void launch_sub_rows(int64_t n_items, const RowItem* items, const T* inv, const T* rloc, const int32_t* dofs, T* x,
                      hipStream_t st) {
     if (n_items <= 0) return;
@@ -546,6 +587,8 @@ void launch_dense_apply(int64_t n, const double* inv, const T* r, T* x, hipStrea
                                         const T*, const T*, T*, bool, int, int, hipStream_t);                          \
     template void launch_resid_restrict<T>(int64_t, const AggItem*, const int4*, const int32_t*, const T*, const T*,  \
                                            const T*, const T*, T*, T*, int, int, hipStream_t);                         \
+    template void launch_unpack<T>(int64_t, int, const int64_t*, const int64_t*, const int64_t*, const T*, const T*,  \
+                                   const int64_t*, T*, hipStream_t);                                                   \
     template void launch_sub_rows<T>(int64_t, const RowItem*, const T*, const T*, const int32_t*, T*, hipStream_t);   \
     template void launch_prolong_agg<T>(int64_t, const AggItem*, const int4*, const T*, const T*, T*, int, int,       \
                                         hipStream_t);                                                                  \

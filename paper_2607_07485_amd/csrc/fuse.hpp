@@ -45,6 +45,11 @@ template <typename T>
 void launch_colour_step(int64_t n_sub, const SubItem* items, const int4* rows, const int32_t* col, const T* val,
                         const T* pk, const T* tiles, const T* r, T* x, bool x_zero, int pad, int row_len,
                         hipStream_t st);
+// Row-major inverses full[full_off[s] ..) of n_sub subdomains of up to max_sub DOFs from the
+// packed ones: triangles at pk_off[s] for |Omega| <= SMALL_M, else 64 x 64 tiles at tp_off[s]
+template <typename T>
+void launch_unpack(int64_t n_sub, int max_sub, const int64_t* sub_off, const int64_t* tp_off, const int64_t* pk_off,
+                   const T* tiles, const T* pk, const int64_t* full_off, T* full, hipStream_t st);
 // x[Omega] += A_Omega^{-1} rloc[Omega] (inverses unpacked, row-major)
 template <typename T>
 void launch_sub_rows(int64_t n_items, const RowItem* items, const T* inv, const T* rloc, const int32_t* dofs, T* x,

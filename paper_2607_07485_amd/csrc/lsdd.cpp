@@ -38,6 +38,17 @@ struct Error : std::runtime_error {
     Error(lsdd_status c, const std::string& m) : std::runtime_error(m), code(c) {}
 };
 
+// A call that fails with work of its own queued waits for it: the caller may go on with the
+// hierarchy on another stream, or destroy it, and host memory that copies read goes.
+struct IdleOnError {
+    hipStream_t st;
+    const int before = std::uncaught_exceptions();
+    explicit IdleOnError(hipStream_t s) : st(s) {}
+    ~IdleOnError() {
+        if (std::uncaught_exceptions() > before) (void)hipStreamSynchronize(st);
+    }
+};
+
 #define HIPCHK(x)                                                                                  \
     do {                                                                                           \
         hipError_t e_ = (x);                                                                       \
@@ -93,8 +104,11 @@ namespace lsdd {
 // of their own and go back at once.  All work of the set-up runs on one stream, so a range
 // released there may be handed out again behind the kernels that still use it; when the set-up
 // is over (seal), chunks without a live range go back, and later releases wait for the device
-// first, as hipFree does, because calls after it may use several streams.  A caller's allocator
-// (lsdd_set_allocator) gets every request as it is.
+// first, as hipFree does, because calls after it may use several streams.  What the set-up's
+// workspaces leave free in the other chunks stays with the hierarchy (Q1 48^2: 67 MB held for 32
+// in use, grad-div 40^2 1.15 GB for 0.89); pools of their own for the workspaces would give it
+// back, for 1.5 ms more of malloc and free in 73 and 0.5 in 9.6 (gradient step of Q1 48^2).  A
+// caller's allocator (lsdd_set_allocator) gets every request as it is.
 struct Arena {
     static constexpr size_t POOL_MAX = size_t(512) << 20;
     static constexpr size_t CHUNK_MIN = size_t(8) << 20, CHUNK_MAX = size_t(512) << 20;
@@ -203,11 +217,16 @@ struct Arena {
             if (prev->first + prev->second == lo) lo = prev->first;
         }
         room[lo] = (size_t)(hi - lo);
+        if (sealed) trim();
     }
     // the set-up's stream is synchronized
     void seal() {
         trim();
         sealed = true;
+        size_t pooled = 0, own = 0;
+        for (auto& q : live) (q.second.pooled ? pooled : own) += q.second.bytes;
+        vlog("memory: %.1f MB of %.1f MB in %zu chunks, %.1f MB in allocations of their own", pooled * 1e-6, held * 1e-6,
+             chunks.size(), own * 1e-6);
     }
     void clear() {
         for (auto& q : live)
@@ -374,16 +393,19 @@ struct Level {
     // FP32 cycle.  fuse: sweeps by 0 separate launches (residual rows, tiled product, partial
     // sums), 1 one launch per colour, 2 residual rows and whole rows of the unpacked inverses.
     // xfer: XFER_DOWN residual and restriction in one launch, XFER_UP prolongation by
-    // aggregates.  fuse_has: the sweep modes whose tables are there
+    // aggregates.  fuse_has, xfer_has: what the level may run; the tables are built for what it
+    // does run (need_fused) and go back when it no longer does (drop_fused)
     int fuse[2] = {0, 0}, xfer[2] = {0, 0};
-    bool fuse_has[3] = {true, false, false};
+    bool fuse_has[3] = {true, false, false}, xfer_has = false;
+    std::vector<int64_t> sw_tp_off, sw_pk_off;   // where a subdomain's packed inverse starts
+    int32_t max_sub = 0;
     SubItem* d_sitems = nullptr;      // subdomains in sweep order
     int4* d_srows = nullptr;          // their row tables, spad entries each
     AggItem* d_aitems = nullptr;
     int4* d_arows = nullptr;          // row tables of the aggregates, apad entries each
     RowItem* d_witems = nullptr;      // 16-row items in sweep order, by colour
     std::vector<int64_t> color_witem0;
-    double* d_full = nullptr;         // unpacked inverses
+    double* d_full = nullptr;         // unpacked inverses, sweep order
     float* d_full32 = nullptr;
     int32_t spad = 0, apad = 0, max_k = 0, row_len = 0;
     bool chosen[2] = {false, false};  // by the autotuner or the caller, not by the rule
@@ -919,79 +941,137 @@ void make_terminal(lsdd_hierarchy* h, Level& lv, const std::vector<int32_t>& ter
     }
 }
 
-// Bytes of a colour's unpacked inverses up to which a level keeps them: reading them
-// instead of the packed ones costs half of them at about 5 TB/s, 8 us here, and saves the
-// partial sums' launch and the tiled product's longer chain, 8 us per colour where it was
-// measured (k_sub_rows).
-constexpr double FULL_MAX_COLOUR = 80e6;
+// Bytes of the unpacked inverses (FP64) up to which a level may run on them: in a colour,
+// because reading them instead of the packed ones costs half of them at about 5 TB/s, 8 us
+// here, and saves the partial sums' launch and the tiled product's longer chain, 8 us per
+// colour where it was measured (k_sub_rows); on the level, because they stay resident
+// (27 colours of Q2 hexes 8^3: 0.72 GB beside 0.37 packed).
+constexpr double FULL_MAX_COLOUR = 80e6, FULL_MAX_LEVEL = 1e9;
+// Bytes of a table of padded rows: every subdomain has those of the largest, so one aggregate of
+// 4,096 DOFs among 100,000 small ones would ask for 6.5 GB.
+constexpr double ROWS_MAX = 256e6;
 
-// Tables of the fused single-vector kernels of a level, and the mode it starts out with.
-// inv, inv_off: the unpacked inverses (aggregate order), kept by the level in mode 2's
-// range; returns whether it took them over.  RAS masks entries of its sweep lists, which the
-// row tables cannot express.
-bool build_fused(lsdd_hierarchy* h, Level& lv, const std::vector<int64_t>& sw_tp_off,
-                 const std::vector<int64_t>& sw_pk_off, double* inv, const std::vector<int64_t>& inv_off) {
+// Builds the tables that sweep mode `mode` and transfers `xfer` of precision p need.
+void need_fused(lsdd_hierarchy* h, Level& lv, int p, int mode, int xfer) {
     Arena& ar = h->arena;
     hipStream_t st = h->st;
     const int32_t n_sub = (int32_t)lv.sweep.size();
-    const Closure& C = lv.cl;
-    if (lv.smoother == 1 || n_sub < 1) return false;
-    int32_t max_sub = 0, max_nw = 0;
-    std::vector<double> full(lv.n_colors, 0.0);
-    for (int32_t s = 0; s < n_sub; ++s) {
-        const int32_t m = (int32_t)(lv.sw_sub_off[s + 1] - lv.sw_sub_off[s]);
-        max_sub = std::max(max_sub, m);
-        full[lv.colors[lv.sweep[s]]] += 8.0 * m * m;
-        max_nw = std::max<int32_t>(max_nw, (int32_t)(C.agg_ptr[s + 1] - C.agg_ptr[s]));
-        lv.max_k = std::max(lv.max_k, lv.k[s]);
+    std::vector<AggItem> ai;
+    std::vector<SubItem> si;
+    std::vector<RowItem> wi;
+    std::vector<int64_t> off;
+    int64_t* d_off = nullptr;
+    const IdleOnError idle(st);                                   // before the vectors go
+    if (xfer && !lv.d_arows) {
+        ai.resize(n_sub);
+        for (int32_t s = 0; s < n_sub; ++s)
+            ai[s] = AggItem{(int32_t)(lv.cl.agg_ptr[s + 1] - lv.cl.agg_ptr[s]), (int32_t)lv.coff[s], lv.k[s], 0,
+                            lv.zoff[s]};
+        lv.d_aitems = ar.upload(ai, st);
+        lv.d_arows = ar.alloc<int4>((size_t)n_sub * lv.apad);
+        launch_row_table(n_sub, lv.d_agg_ptr, lv.d_agg_dofs, lv.d_rowptr, lv.d_scoff, lv.apad, lv.d_arows, st);
     }
-    lv.spad = (max_sub + 63) & ~63;
-    lv.apad = (max_nw + 63) & ~63;
-    const int64_t rows = lv.sw_sub_off[n_sub];
-    const double full_max = *std::max_element(full.begin(), full.end());
-    if (lv.nnz > INT32_MAX || rows > INT32_MAX || lv.coff[n_sub] > INT32_MAX) return false;
-    // one launch per colour reads neighbours' x while others write theirs: only where the
-    // classes are a colouring (block Jacobi has one class of aggregates that share elements)
-    lv.fuse_has[1] = lv.smoother == 0 && lv.spad <= FUSE_M;
-    lv.fuse_has[2] = full_max <= FULL_MAX_COLOUR;
-    if (!lv.fuse_has[1] && !lv.fuse_has[2]) return false;
-    lv.row_len = (int32_t)(lv.nnz / std::max<int64_t>(lv.n, 1));
-    std::vector<AggItem> ai(n_sub);
-    for (int32_t s = 0; s < n_sub; ++s)
-        ai[s] = AggItem{(int32_t)(C.agg_ptr[s + 1] - C.agg_ptr[s]), (int32_t)lv.coff[s], lv.k[s], 0, lv.zoff[s]};
-    lv.d_aitems = ar.upload(ai, st);
-    lv.d_arows = ar.alloc<int4>((size_t)n_sub * lv.apad);
-    launch_row_table(n_sub, lv.d_agg_ptr, lv.d_agg_dofs, lv.d_rowptr, lv.d_scoff, lv.apad, lv.d_arows, st);
-    if (lv.fuse_has[1]) {
-        std::vector<SubItem> si(n_sub);
+    if (mode == 1 && !lv.d_srows) {
+        si.resize(n_sub);
         for (int32_t s = 0; s < n_sub; ++s) {
             const int32_t m = (int32_t)(lv.sw_sub_off[s + 1] - lv.sw_sub_off[s]);
-            si[s] = SubItem{m, 0, m <= SMALL_M ? sw_pk_off[s] : sw_tp_off[s]};
+            si[s] = SubItem{m, 0, m <= SMALL_M ? lv.sw_pk_off[s] : lv.sw_tp_off[s]};
         }
         lv.d_sitems = ar.upload(si, st);
         lv.d_srows = ar.alloc<int4>((size_t)n_sub * lv.spad);
         launch_row_table(n_sub, lv.d_sw_sub_off, lv.d_sw_sub_dofs, lv.d_rowptr, lv.d_scoff, lv.spad, lv.d_srows, st);
     }
-    if (lv.fuse_has[2]) {
-        std::vector<RowItem> wi;
+    if (mode == 2 && !(p ? (void*)lv.d_full32 : (void*)lv.d_full)) {
+        off.assign(n_sub + 1, 0);
         lv.color_witem0.assign(lv.n_colors + 1, 0);
         for (int32_t c = 0; c < lv.n_colors; ++c) {
             for (int32_t s = lv.color_sub0[c]; s < lv.color_sub0[c + 1]; ++s) {
                 const int32_t m = (int32_t)(lv.sw_sub_off[s + 1] - lv.sw_sub_off[s]);
+                off[s + 1] = off[s] + (int64_t)m * m;
                 for (int32_t r0 = 0; r0 < m; r0 += 16)
-                    wi.push_back(RowItem{(int32_t)lv.sw_sub_off[s], m, r0, 0, inv_off[lv.sweep[s]]});
+                    wi.push_back(RowItem{(int32_t)lv.sw_sub_off[s], m, r0, 0, off[s]});
             }
             lv.color_witem0[c + 1] = (int64_t)wi.size();
         }
-        lv.d_witems = ar.upload(wi, st);
-        lv.d_full = inv;
-        if (h->prm.precision >= 1) {
-            lv.d_full32 = ar.alloc<float>(std::max<int64_t>(lv.inv_len, 1));
-            launch_to_f32(lv.inv_len, inv, lv.d_full32, st);
+        if (p) lv.d_full32 = ar.alloc<float>(off[n_sub]);
+        else lv.d_full = ar.alloc<double>(off[n_sub]);
+        if (!lv.d_witems) lv.d_witems = ar.upload(wi, st);
+        d_off = ar.upload(off, st);
+        if (p) {
+            launch_unpack<float>(n_sub, lv.max_sub, lv.d_sw_sub_off, lv.d_sw_tp_off, lv.d_sw_pk_off, lv.d_tiles32,
+                                 lv.d_pk32, d_off, lv.d_full32, st);
+        } else {
+            launch_unpack<double>(n_sub, lv.max_sub, lv.d_sw_sub_off, lv.d_sw_tp_off, lv.d_sw_pk_off, lv.d_tiles,
+                                  lv.d_pk, d_off, lv.d_full, st);
         }
     }
     HIPCHK(hipGetLastError());
-    sync(st);
+    if (!ai.empty() || !si.empty() || d_off) sync(st);            // the vectors are read until then
+    if (d_off) ar.release(d_off);
+}
+
+// Gives back the tables that no cycle of the hierarchy uses.
+void drop_fused(lsdd_hierarchy* h, Level& lv) {
+    const int np = h->prm.precision >= 1 ? 2 : 1;
+    auto used = [&](auto&& f) { return f(0) || (np > 1 && f(1)); };
+    auto drop = [&](auto*& q) {
+        if (q) h->arena.release(q);
+        q = nullptr;
+    };
+    if (!used([&](int p) { return lv.xfer[p] != 0; })) drop(lv.d_aitems), drop(lv.d_arows);
+    if (!used([&](int p) { return lv.fuse[p] == 1; })) drop(lv.d_sitems), drop(lv.d_srows);
+    if (lv.fuse[0] != 2) drop(lv.d_full);
+    if (np < 2 || lv.fuse[1] != 2) drop(lv.d_full32);
+    if (!used([&](int p) { return lv.fuse[p] == 2; })) drop(lv.d_witems);
+}
+
+// Whether the tables are there: the separate launches need none, so that a device without room
+// for more runs these.
+bool try_fused(lsdd_hierarchy* h, Level& lv, int p, int mode, int xfer) {
+    try {
+        need_fused(h, lv, p, mode, xfer);
+        return true;
+    } catch (const Error& e) {
+        if (e.code != LSDD_E_NOMEM) throw;
+        drop_fused(h, lv);
+        return false;
+    }
+}
+
+void use_kernels(lsdd_hierarchy* h, Level& lv, int p, int mode, int xfer) {
+    if (!try_fused(h, lv, p, mode, xfer))
+        throw Error(LSDD_E_NOMEM, "no room for the tables of the cycle's kernels on level " + std::to_string(lv.level));
+    lv.fuse[p] = mode;
+    lv.xfer[p] = xfer;
+}
+
+// What a level's single-vector cycle may run, and what it starts out with.  RAS masks entries of
+// its sweep lists, which the row tables cannot express.
+void init_fused(lsdd_hierarchy* h, Level& lv) {
+    const int32_t n_sub = (int32_t)lv.sweep.size();
+    const Closure& C = lv.cl;
+    if (lv.smoother == 1 || n_sub < 1) return;
+    int32_t max_nw = 0;
+    double full_level = 0.0;
+    std::vector<double> full(lv.n_colors, 0.0);
+    for (int32_t s = 0; s < n_sub; ++s) {
+        const int32_t m = (int32_t)(lv.sw_sub_off[s + 1] - lv.sw_sub_off[s]);
+        lv.max_sub = std::max(lv.max_sub, m);
+        full[lv.colors[lv.sweep[s]]] += 8.0 * m * m;
+        full_level += 8.0 * m * m;
+        max_nw = std::max<int32_t>(max_nw, (int32_t)(C.agg_ptr[s + 1] - C.agg_ptr[s]));
+        lv.max_k = std::max(lv.max_k, lv.k[s]);
+    }
+    const int32_t max_sub = lv.max_sub;
+    lv.spad = (max_sub + 63) & ~63;
+    lv.apad = (max_nw + 63) & ~63;
+    if (lv.nnz > INT32_MAX || lv.sw_sub_off[n_sub] > INT32_MAX || lv.coff[n_sub] > INT32_MAX) return;
+    // one launch per colour reads neighbours' x while others write theirs: only where the
+    // classes are a colouring (block Jacobi has one class of aggregates that share elements)
+    lv.fuse_has[1] = lv.smoother == 0 && lv.spad <= FUSE_M && 16.0 * n_sub * lv.spad <= ROWS_MAX;
+    lv.fuse_has[2] = *std::max_element(full.begin(), full.end()) <= FULL_MAX_COLOUR && full_level <= FULL_MAX_LEVEL;
+    lv.xfer_has = 16.0 * n_sub * lv.apad <= ROWS_MAX;
+    lv.row_len = (int32_t)(lv.nnz / std::max<int64_t>(lv.n, 1));
     // Until the autotuner has timed them (us per pair of sweeps in modes 0 / 1 / 2, FP64):
     // * overlaps up to 64: one launch per colour (121 of 50: 75 / 35 / 52; 4,489 a colour 284 /
     //   219), separate launches from 5,000 a colour (6,750 a colour: 241 / 259 / 383) and where
@@ -1022,11 +1102,15 @@ bool build_fused(lsdd_hierarchy* h, Level& lv, const std::vector<int64_t>& sw_tp
     };
     for (int p = 0; p < 2; ++p) {
         lv.fuse[p] = mode;
-        lv.xfer[p] = down | up(p ? 4.0 : 8.0);
+        lv.xfer[p] = lv.xfer_has ? down | up(p ? 4.0 : 8.0) : 0;
+    }
+    for (int p = 0; p < (h->prm.precision >= 1 ? 2 : 1); ++p) {
+        if (try_fused(h, lv, p, lv.fuse[p], lv.xfer[p])) continue;
+        lv.fuse[p] = lv.xfer[p] = 0;
+        drop_fused(h, lv);
     }
     vlog("level %d: single-vector mode %d, transfers %d (%.1f MB per colour, %d aggregates of up to %d DOFs and %d modes, overlaps up to %d, %d entries per row)",
          lv.level, mode, lv.xfer[0], bytes * 1e-6, n_sub, max_nw, lv.max_k, max_sub, lv.row_len);
-    return lv.fuse_has[2];
 }
 
 // Build level l+1 from level l; returns nullptr when no mode is retained.
@@ -1510,7 +1594,10 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         return (int)is_small(a) < (int)is_small(b);
     });
     std::vector<int32_t> sw_dofs, sw_dofs_w;
-    std::vector<int64_t> tp_agg(n_agg, -1), pk_agg(n_agg, -1), sw_tp_off(n_agg, -1), sw_pk_off(n_agg, -1);
+    std::vector<int64_t> tp_agg(n_agg, -1), pk_agg(n_agg, -1);
+    std::vector<int64_t>&sw_tp_off = lv.sw_tp_off, &sw_pk_off = lv.sw_pk_off;
+    sw_tp_off.assign(n_agg, -1);
+    sw_pk_off.assign(n_agg, -1);
     int64_t tiles = 0, pks = 0;
     for (int32_t i = 0; i < n_agg; ++i) {
         const int64_t m = sp_ptr[i + 1] - sp_ptr[i];
@@ -1668,8 +1755,9 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         }
         ar.release(d_tp_agg);
         ar.release(d_pk_agg);
-        if (!build_fused(h, lv, sw_tp_off, sw_pk_off, lv.d_inv, msq)) ar.release(lv.d_inv);
+        ar.release(lv.d_inv);
         lv.d_inv = nullptr;
+        init_fused(h, lv);
     }
     lv.rloc_len = (int64_t)sw_dofs.size();
     alloc_vectors(h, lv, 0);
@@ -2618,11 +2706,11 @@ void autotune_levels(lsdd_hierarchy* h) {
                 // the fastest candidate, or the one at hand if none is faster by 5 %: runs of one
                 // kernel after another find its operands in the caches, a cycle does not (the way
                 // up of 16 aggregates in FP32, 9.2 us apart against 9.4: the cycle is 3 us longer)
-                auto pick = [&](const char* what, int now, int runs, std::initializer_list<int> cand, auto&& run) {
+                auto pick = [&](const char* what, int now, int runs, const std::vector<int>& cand, auto&& run) {
                     double low = 1e300;
                     int best_c = now;
                     for (int c : cand) {
-                        double ms = time_ms(h, [&] { run(c); }, 5, runs);
+                        double ms = time_ms(h, [&] { run(c); }, runs > 1 ? 3 : 5, runs);
                         vlog("autotune level %d: %s %d: %.4f ms", lv.level, what, c, ms);
                         if (c == now) ms *= 0.95;
                         if (ms < low) low = ms, best_c = c;
@@ -2630,25 +2718,32 @@ void autotune_levels(lsdd_hierarchy* h) {
                     return best_c;
                 };
                 auto sweeps = [&](int f) {
-                    lv.fuse[p] = lv.fuse_has[f] ? f : 0;
+                    lv.fuse[p] = f;
                     sweep<T, NR>(h, lv, v.r, v.x, true, true);
                     sweep<T, NR>(h, lv, v.r, v.x, false, false);
                 };
+                // only what may win: rows of the unpacked inverses lose on small overlaps (1,849 of
+                // 50: 98 against 90 and 45 us), one launch per colour on large ones (36 of 484: 260
+                // against 114 and 65)
                 const int now = lv.fuse[p];
-                if (lv.fuse_has[1] && lv.fuse_has[2]) lv.tuned_fuse[p] = pick("sweeps, mode", now, 1, {0, 1, 2}, sweeps);
-                else if (lv.fuse_has[1]) lv.tuned_fuse[p] = pick("sweeps, mode", now, 1, {0, 1}, sweeps);
-                else if (lv.fuse_has[2]) lv.tuned_fuse[p] = pick("sweeps, mode", now, 1, {0, 2}, sweeps);
+                if (lv.fuse_has[1] && lv.max_sub <= 256) try_fused(h, lv, p, 1, 0);
+                if (lv.fuse_has[2] && lv.max_sub > SMALL_M) try_fused(h, lv, p, 2, 0);
+                std::vector<int> modes{0};
+                if (lv.d_srows) modes.push_back(1);
+                if (p ? (void*)lv.d_full32 : (void*)lv.d_full) modes.push_back(2);
+                lv.tuned_fuse[p] = pick("sweeps, mode", now, 1, modes, sweeps);
                 lv.fuse[p] = lv.tuned_fuse[p];
                 lv.tuned_xfer[p] = 0;
-                if (lv.d_arows) {
-                    lv.tuned_xfer[p] = pick("way down, fused", lv.xfer[p] & XFER_DOWN, 8, {0, XFER_DOWN}, [&](int c) {
+                if (lv.xfer_has && try_fused(h, lv, p, 0, XFER_DOWN | XFER_UP)) {
+                    lv.tuned_xfer[p] = pick("way down, fused", lv.xfer[p] & XFER_DOWN, 4, {0, XFER_DOWN}, [&](int c) {
                         if (!c) launch_zero<T>(nx.n, vn.x, h->st);
                         descend<T, NR>(h, lv, nx, v.r, v.x, c);
                     });
-                    lv.tuned_xfer[p] |= pick("way up, fused", lv.xfer[p] & XFER_UP, 8, {0, XFER_UP},
+                    lv.tuned_xfer[p] |= pick("way up, fused", lv.xfer[p] & XFER_UP, 4, {0, XFER_UP},
                                              [&](int c) { ascend<T, NR>(h, lv, nx, v.x, c); });
                 }
                 lv.xfer[p] = lv.tuned_xfer[p];
+                drop_fused(h, lv);
                 lv.chosen[p] = true;
             }
         };
@@ -2919,17 +3014,6 @@ using namespace lsdd;
 // ====================================================================== C-ABI
 
 namespace {
-
-// A call that fails with work of its own queued waits for it: the caller may go on with the
-// hierarchy on another stream, or destroy it.
-struct IdleOnError {
-    hipStream_t st;
-    const int before = std::uncaught_exceptions();
-    explicit IdleOnError(hipStream_t s) : st(s) {}
-    ~IdleOnError() {
-        if (std::uncaught_exceptions() > before) (void)hipStreamSynchronize(st);
-    }
-};
 
 // sizes of a caller's elements (checked): the largest, and whether all are of that size
 struct ElemSizes {
@@ -3551,8 +3635,7 @@ lsdd_status lsdd_set_level_tuning(lsdd_hierarchy* h, int32_t level, const int32_
     bool own = std::equal(in, in + 7, cur);
     for (auto& t : lv.tuned) own = own || std::equal(in, in + 7, t);
     if (p < 2 && std::equal(in, in + 7, lv.tuned[p])) {
-        lv.fuse[p] = lv.tuned_fuse[p];
-        lv.xfer[p] = lv.tuned_xfer[p];
+        use_kernels(h, lv, p, lv.tuned_fuse[p], lv.tuned_xfer[p]);
         lv.chosen[p] = true;
     } else if (!own) {
         for (int q = 0; q < 2; ++q) {
@@ -3571,6 +3654,7 @@ lsdd_status lsdd_set_level_tuning(lsdd_hierarchy* h, int32_t level, const int32_
         sync(h->st);
     }
     reset_graphs(h);
+    drop_fused(h, lv);
     return LSDD_OK;
     ABI_END
 }
@@ -3597,12 +3681,12 @@ lsdd_status lsdd_set_level_kernels(lsdd_hierarchy* h, int32_t level, const int32
     if (p == 2 && (in[0] || in[1]))
         throw Error(LSDD_E_UNSUPPORTED, "the mixed cycle runs in separate launches");
     if (p == 2) return LSDD_OK;
-    if (!lv.fuse_has[in[0]] || (in[1] && !lv.d_arows))
+    if (!lv.fuse_has[in[0]] || (in[1] && !lv.xfer_has))
         throw Error(LSDD_E_UNSUPPORTED, "the level does not have these kernels of the single-vector cycle");
-    lv.fuse[p] = in[0];
-    lv.xfer[p] = in[1];
+    use_kernels(h, lv, p, in[0], in[1]);
     lv.chosen[p] = true;
     reset_graphs(h);
+    drop_fused(h, lv);
     return LSDD_OK;
     ABI_END
 }

@@ -310,3 +310,107 @@ def test_every_kernel_of_the_cycle_matches_separate_launches(kind):
                     assert float((z[i] - apart[i]).norm()) <= 1e-10 * n
                     assert float((z[i + 1] - z[i]).norm()) <= 4 * float((apart[i + 1] - apart[i]).norm()) + 1e-12 * n
         assert tried >= 5
+
+
+def test_memory_of_the_kernels_is_bounded_and_reused():
+    """The tables of kernels that no precision runs go back to the hierarchy's memory, which going to and
+    fro between the kernels and tuning do not grow; a level whose padded row tables would take gigabytes does
+    without them, and solves all the same."""
+    P = _lsdd()
+
+    def used(fn):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        out = fn()
+        torch.cuda.synchronize()
+        return free - torch.cuda.mem_get_info()[0], out
+
+    prob = fegen.elasticity_q2hex(5, nu=0.3)
+    r = torch.from_numpy(np.random.default_rng(10).standard_normal(prob.n)).cuda()
+    with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2, agg_passes=1, tau_const=0.75, precision=1)) as h:
+        def to_and_fro():
+            out = []
+            for k in ((0, 0), (2, 2), (0, 3), (2, 0)):
+                for prec in (0, 1):
+                    h.set_cycle_precision(prec)
+                    h.set_level_kernels(0, *k)
+                h.set_cycle_precision(0)
+                out.append(h.vcycle(r))
+            for prec in (1, 0):
+                h.set_cycle_precision(prec)
+                h.autotune()
+            return out
+
+        z = to_and_fro()
+        for _ in range(3):
+            taken, again = used(to_and_fro)
+            assert taken <= 0
+            z += again                                      # in other orders: the tuning picks the shapes
+        assert all(float((a - z[0]).norm()) <= 1e-10 * float(z[0].norm()) for a in z)
+    # 20,000 aggregates of 2 DOFs beside one of 3,000: 20,001 x 3,008 rows of 16 bytes would be 0.96 GB
+    # beside the coarsest level's 1.61 (20,001 unknowns in packed tiles)
+    n = 43000
+    dofs = np.stack([np.arange(n - 1), np.arange(1, n)], axis=1)
+    B = np.repeat((np.array([[1.0, -1.0], [-1.0, 1.0]]) + 0.05 * np.eye(2))[None], n - 1, axis=0)
+    from fegen.common import uniform_problem
+    chain = uniform_problem(n, dofs, B, np.arange(n))
+    chain.agg_of_dof = np.where(np.arange(n) < 3000, 0, 1 + (np.arange(n) - 3000) // 2).astype(np.int32)
+    b = torch.from_numpy(np.random.default_rng(11).standard_normal(n)).cuda()
+    took, h = used(lambda: P.Hierarchy.setup_problem(chain, P.Params.default(max_levels=2, modes_fixed=1, min_coarse=1,
+                                                                             max_density=1.0, rtol=1e-8)))
+    with h:
+        assert took < 2.1e9 and h.level_kernels(0)[1] == 0
+        with pytest.raises(P.LsddError) as e:
+            h.set_level_kernels(0, 0, 3)
+        assert e.value.code == 7
+        x, info = h.solve(b)
+        A = torch.zeros(n, dtype=torch.float64, device="cuda")
+        A[:] = 2.1 * x
+        A[0] -= 1.05 * x[0]
+        A[-1] -= 1.05 * x[-1]
+        A[1:] -= x[:-1]
+        A[:-1] -= x[1:]
+        assert info[0].converged == 1 and float((A - b).norm()) <= 1.1e-8 * float(b.norm())
+
+
+def test_kernels_without_room_for_their_tables():
+    """With an allocator that refuses what the tables need, asking for the kernels is refused and changes
+    nothing, and the autotuner does without them."""
+    import ctypes as C
+
+    from paper_2607_07485_amd import lsdd as binding
+    P = _lsdd()
+    limit = [1 << 60]
+
+    def alloc(nbytes, ctx):
+        return torch.cuda.caching_allocator_alloc(int(nbytes)) if nbytes <= limit[0] else 0
+
+    def free(ptr, ctx):
+        torch.cuda.caching_allocator_delete(ptr)
+
+    fa = C.CFUNCTYPE(C.c_void_p, C.c_size_t, C.c_void_p)(alloc)
+    ff = C.CFUNCTYPE(None, C.c_void_p, C.c_void_p)(free)
+    lib = binding.lib()
+    prob = fegen.elasticity_q2hex(4, nu=0.3)
+    r = torch.from_numpy(np.random.default_rng(12).standard_normal(prob.n)).cuda()
+    try:
+        lib.lsdd_set_allocator(C.cast(fa, C.c_void_p), C.cast(ff, C.c_void_p), None)
+        with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2, agg_passes=1, tau_const=0.75)) as h:
+            z = h.vcycle(r)
+            assert h.level_kernels(0)[0] == 2
+            h.set_level_kernels(0, 0, 0)
+            apart = h.vcycle(r)
+            limit[0] = 16 << 20                         # the unpacked inverses are some 60 MB
+            with pytest.raises(P.LsddError) as e:
+                h.set_level_kernels(0, 2, 0)
+            assert e.value.code == 3 and h.level_kernels(0)[:2] == (0, 0)
+            assert torch.equal(h.vcycle(r), apart)
+            h.autotune()
+            assert h.level_kernels(0)[0] == 0
+            assert float((h.vcycle(r) - z).norm()) <= 1e-10 * float(z.norm())
+            limit[0] = 1 << 60
+            h.autotune()
+            assert float((h.vcycle(r) - z).norm()) <= 1e-10 * float(z.norm())
+            torch.cuda.synchronize()
+    finally:
+        lib.lsdd_set_allocator(None, None, None)
