@@ -1458,14 +1458,12 @@ void launch_small_sub(int64_t s0, int64_t n_sub, const int64_t* sub_off, const i
     // half the data, the row form is faster (3500 overlaps 24.3 against 26.4 us, 24 of them 8.6
     // against 9.7)
     if constexpr (NR == NB && sizeof(T) == 4)
-        if (!fact) {
+        if (!fact && (uintptr_t)x % 16 == 0) {         // a caller's allocator may align to less
             hipLaunchKernelGGL(k_small_sub_mm, dim3((unsigned)n_sub), dim3(64), lds, st, (int32_t)s0, sub_off,
                                sub_dofs, pk_off, pk, rloc, x, max_m);
             return;
         }
-    auto kern = &k_small_sub<T, NR, true>;
-    if constexpr (NR != NB || sizeof(T) != 4)
-        if (!fact) kern = &k_small_sub<T, NR, false>;
+    auto kern = fact ? &k_small_sub<T, NR, true> : &k_small_sub<T, NR, false>;
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern), 64, lds) !=
             hipSuccess ||

@@ -962,13 +962,19 @@ void need_fused(lsdd_hierarchy* h, Level& lv, int p, int mode, int xfer) {
     std::vector<int64_t> off;
     int64_t* d_off = nullptr;
     const IdleOnError idle(st);                                   // before the vectors go
+    auto row_table = [&](size_t entries) {
+        int4* q = ar.alloc<int4>(entries);
+        if (reinterpret_cast<uintptr_t>(q) % 16 == 0) return q;
+        ar.release(q);                             // a caller allocator without 16-byte alignment
+        throw Error(LSDD_E_NOMEM, "row tables need 16-byte aligned memory");
+    };
     if (xfer && !lv.d_arows) {
         ai.resize(n_sub);
         for (int32_t s = 0; s < n_sub; ++s)
             ai[s] = AggItem{(int32_t)(lv.cl.agg_ptr[s + 1] - lv.cl.agg_ptr[s]), (int32_t)lv.coff[s], lv.k[s], 0,
                             lv.zoff[s]};
         lv.d_aitems = ar.upload(ai, st);
-        lv.d_arows = ar.alloc<int4>((size_t)n_sub * lv.apad);
+        lv.d_arows = row_table((size_t)n_sub * lv.apad);
         launch_row_table(n_sub, lv.d_agg_ptr, lv.d_agg_dofs, lv.d_rowptr, lv.d_scoff, lv.apad, lv.d_arows, st);
     }
     if (mode == 1 && !lv.d_srows) {
@@ -978,7 +984,7 @@ void need_fused(lsdd_hierarchy* h, Level& lv, int p, int mode, int xfer) {
             si[s] = SubItem{m, 0, m <= SMALL_M ? lv.sw_pk_off[s] : lv.sw_tp_off[s]};
         }
         lv.d_sitems = ar.upload(si, st);
-        lv.d_srows = ar.alloc<int4>((size_t)n_sub * lv.spad);
+        lv.d_srows = row_table((size_t)n_sub * lv.spad);
         launch_row_table(n_sub, lv.d_sw_sub_off, lv.d_sw_sub_dofs, lv.d_rowptr, lv.d_scoff, lv.spad, lv.d_srows, st);
     }
     if (mode == 2 && !(p ? (void*)lv.d_full32 : (void*)lv.d_full)) {

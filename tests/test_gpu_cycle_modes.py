@@ -1,4 +1,6 @@
 """Which kernels a cycle runs, for every smoother, precision and tuning."""
+import contextlib
+import ctypes as C
 import os
 
 import numpy as np
@@ -373,28 +375,31 @@ def test_memory_of_the_kernels_is_bounded_and_reused():
         assert info[0].converged == 1 and float((A - b).norm()) <= 1.1e-8 * float(b.norm())
 
 
+@contextlib.contextmanager
+def _allocator(alloc, free):
+    """alloc(bytes) and free(pointer) behind lsdd_set_allocator."""
+    from paper_2607_07485_amd import lsdd as binding
+    fa = C.CFUNCTYPE(C.c_void_p, C.c_uint64, C.c_void_p)(lambda nbytes, ctx: alloc(nbytes))
+    ff = C.CFUNCTYPE(None, C.c_void_p, C.c_void_p)(lambda ptr, ctx: free(ptr))
+    binding.lib().lsdd_set_allocator(C.cast(fa, C.c_void_p), C.cast(ff, C.c_void_p), None)
+    try:
+        yield
+    finally:
+        binding.lib().lsdd_set_allocator(None, None, None)
+
+
 def test_kernels_without_room_for_their_tables():
     """With an allocator that refuses what the tables need, asking for the kernels is refused and changes
     nothing, and the autotuner does without them."""
-    import ctypes as C
-
-    from paper_2607_07485_amd import lsdd as binding
     P = _lsdd()
     limit = [1 << 60]
 
-    def alloc(nbytes, ctx):
+    def alloc(nbytes):
         return torch.cuda.caching_allocator_alloc(int(nbytes)) if nbytes <= limit[0] else 0
 
-    def free(ptr, ctx):
-        torch.cuda.caching_allocator_delete(ptr)
-
-    fa = C.CFUNCTYPE(C.c_void_p, C.c_size_t, C.c_void_p)(alloc)
-    ff = C.CFUNCTYPE(None, C.c_void_p, C.c_void_p)(free)
-    lib = binding.lib()
     prob = fegen.elasticity_q2hex(4, nu=0.3)
     r = torch.from_numpy(np.random.default_rng(12).standard_normal(prob.n)).cuda()
-    try:
-        lib.lsdd_set_allocator(C.cast(fa, C.c_void_p), C.cast(ff, C.c_void_p), None)
+    with _allocator(alloc, torch.cuda.caching_allocator_delete):
         with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2, agg_passes=1, tau_const=0.75)) as h:
             z = h.vcycle(r)
             assert h.level_kernels(0)[0] == 2
@@ -412,5 +417,32 @@ def test_kernels_without_room_for_their_tables():
             h.autotune()
             assert float((h.vcycle(r) - z).norm()) <= 1e-10 * float(z.norm())
             torch.cuda.synchronize()
-    finally:
-        lib.lsdd_set_allocator(None, None, None)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_allocator_with_8_byte_alignment(precision):
+    """Memory aligned to 8 bytes only: no kernel that reads 16 at a time runs on it (rows of the fused
+    kernels, blocks of right-hand sides), and the results are those of aligned memory."""
+    P = _lsdd()
+    prob = fegen.elasticity_q1(24, nu=0.3)
+    B = torch.from_numpy(np.random.default_rng(13).standard_normal((8, prob.n))).cuda()
+    prm = P.Params.default(max_levels=3, tau_const=0.75, rtol=1e-10, precision=precision)
+
+    def run():
+        with P.Hierarchy.setup_problem(prob, prm) as h:
+            out = [h.solve(B)[0], h.solve(B[0].clone())[0]]
+            kernels = _kernels(h)
+            h.autotune()
+            kernels += _kernels(h)
+            out.append(h.solve(B[0].clone())[0])
+            torch.cuda.synchronize()
+            return out, kernels
+
+    ref, kernels = run()
+    assert any(k[0] == 1 and k[1] for k in kernels)
+    with _allocator(lambda n: torch.cuda.caching_allocator_alloc(int(n) + 8) + 8,
+                    lambda p: torch.cuda.caching_allocator_delete(p - 8)):
+        out, kernels = run()
+    assert not any(k[0] == 1 or k[1] for k in kernels)
+    for a, b in zip(ref, out):
+        assert float((a - b).norm()) <= 1e-8 * float(a.norm())
