@@ -3175,11 +3175,13 @@ lsdd_status lsdd_elem_bilinear(int64_t n_elem, const int64_t* elem_ptr, const in
     const ElemSizes z = elem_sizes(n_elem, elem_ptr);
     hipStream_t st = (hipStream_t)hip_stream;
     Arena a(false);
+    std::vector<int64_t> tab;                         // read by the upload until the stream is synchronized
+    const IdleOnError idle(st);
     if (z.uniform) {
         launch_elem_bilinear(n_elem, z.n_max, z.n_max, nullptr, elem_dofs, nullptr, blocks, u, v, nrhs, ld, scale, out,
                              st);
     } else {
-        std::vector<int64_t> tab(elem_ptr, elem_ptr + n_elem + 1);
+        tab.assign(elem_ptr, elem_ptr + n_elem + 1);
         tab.resize(2 * (n_elem + 1), 0);
         int64_t* boff = tab.data() + n_elem + 1;
         for (int64_t e = 0; e < n_elem; ++e) {
