@@ -179,9 +179,10 @@ union InvSmem {
 // matrix left out, D Y^T Y D = L L^T and Y <- Y D L^{-T}, the Q that Gram-Schmidt in index
 // order gives per cluster (Y: n x bn, row-major, ld 64).  The Gram matrix runs on the matrix
 // cores, its factor and the row-wise substitution through tile64.hpp (as 2016 dependent
-// loads a row the substitution took about 1 ms a pass at n = 882).  False, with Y unchanged,
-// when a pivot falls below 1e-12, where one pass would lose orthogonality.
-__device__ inline bool batch_cholqr(InvSmem& sm, double* Y, int n, int bn, const int* cl) {
+// loads a row the substitution took about 1 ms a pass at n = 882).  0, with Y unchanged, when a
+// pivot falls below 1e-12, where one pass would lose orthogonality; 1 when one falls below
+// 1e-2; else 2: one pass leaves the members orthogonal to some 100 eps.
+__device__ inline int batch_cholqr(InvSmem& sm, double* Y, int n, int bn, const int* cl) {
     __shared__ double s_d[64], s_piv[64];
     mg::d4 acc[2][2];
     mg::zero(acc);
@@ -232,8 +233,9 @@ __device__ inline bool batch_cholqr(InvSmem& sm, double* Y, int n, int bn, const
                     for (int q = 0; q < 4; ++q) y[16 * k + 4 * q] = X[k][q];
         }
     }
+    const bool well = __all(s_piv[l] > 1e-2);
     __syncthreads();
-    return ok;
+    return ok ? 1 + (int)well : 0;
 }
 
 struct InvShared {
@@ -251,9 +253,10 @@ struct InvShared {
 // ms), a larger cluster 64 members at a time: solve every member's system on its own lane,
 // make the batch orthogonal to the cluster's earlier members, then orthonormal (Cholesky QR;
 // Gram-Schmidt member by member where that is refused).  The batch stays row-major in the
-// scratch, interleaved by lane for the solves and an operand of the matrix cores as it is;
-// its last iteration orthogonalises twice, the others once (they only have to keep the
-// members apart).
+// scratch, interleaved by lane for the solves and an operand of the matrix cores as it is.
+// The last iteration orthogonalises twice, the others once, and within the batch again where that
+// met nearly dependent members: without, factors of element blocks with 96 equal eigenvalues of
+// 128 were off by 7e-14 instead of 2e-15 (the next solve multiplies what the pass leaves).
 //
 // Convergence: from the second solve on, the iterate entering a solve has unit norm, so the
 // norm of the result is the solve's growth 1 / |lambda - shift| along the eigenvector; once it
@@ -308,9 +311,9 @@ __device__ inline void wg_invit(const double* __restrict__ d, const double* __re
             }
             __syncthreads();
             const bool last = S.conv != 0 || it == 3;
-            for (int pass = 0; pass < (last ? 2 : 1); ++pass) {
+            for (int pass = 0; pass < 2; ++pass) {
                 // against the earlier members of the cluster, 64 at a time
-                for (int q0 = qa; q0 < b0; q0 += 64) {
+                for (int q0 = qa; q0 < b0 && (last || pass == 0); q0 += 64) {
                     const double* Q = V + (int64_t)q0 * n;
                     const int qn = min(64, b0 - q0);
                     mg::d4 acc[2][2];
@@ -341,7 +344,10 @@ __device__ inline void wg_invit(const double* __restrict__ d, const double* __re
                     }
                     __syncthreads();
                 }
-                if (batch_cholqr(S.sm, Y, n, bn, S.cl)) continue;
+                if (const int c = batch_cholqr(S.sm, Y, n, bn, S.cl)) {
+                    if (c == 2 && !last) break;
+                    continue;
+                }
                 // member by member, each normalised before its use
                 for (int t = 0; t < bn; ++t) {
                     const int w = tid() >> 6, l = tid() & 63, t0 = max(0, S.cl[t] - b0);

@@ -446,3 +446,29 @@ def test_allocator_with_8_byte_alignment(precision):
     assert not any(k[0] == 1 or k[1] for k in kernels)
     for a, b in zip(ref, out):
         assert float((a - b).norm()) <= 1e-8 * float(a.norm())
+
+
+@pytest.mark.parametrize("n", [64, 81, 128])
+def test_element_factors_of_large_clusters(n):
+    """Element blocks that are projectors (three quarters of the eigenvalues equal): G^T G = A to
+    128 eps, the bound of n rounded terms; the members of so large a cluster come out nearly dependent
+    from their solves."""
+    from fegen.common import Problem
+    P = _lsdd()
+    rng = np.random.default_rng(0)
+    blocks = []
+    for _ in range(40):
+        Q = np.linalg.qr(rng.standard_normal((n, n)))[0][:, n // 4:]
+        B = Q @ Q.T
+        blocks.append(0.5 * (B + B.T))
+    N = n * len(blocks)
+    ptr = np.concatenate([n * np.arange(len(blocks) + 1), N + np.arange(1, N + 1)]).astype(np.int64)
+    prob = Problem(n=N, elem_ptr=ptr, elem_dofs=np.tile(np.arange(N, dtype=np.int32), 2),
+                   blocks=np.concatenate([b.ravel() for b in blocks] + [np.full(N, 0.1)]),
+                   node_of_dof=np.arange(N, dtype=np.int32))
+    with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=1)) as h:
+        ranks, G = h.export_gram(ptr)
+    for k, B in enumerate(blocks):
+        g = G[k * n * n:(k + 1) * n * n].reshape(n, n)
+        assert ranks[k] == n - n // 4
+        assert np.abs(g.T @ g - B).max() <= 128 * np.finfo(float).eps * np.abs(B).max()
