@@ -180,10 +180,12 @@ union InvSmem {
 // order gives per cluster (Y: n x bn, row-major, ld 64).  The Gram matrix runs on the matrix
 // cores, its factor and the row-wise substitution through tile64.hpp (as 2016 dependent
 // loads a row the substitution took about 1 ms a pass at n = 882).  0, with Y unchanged, when a
-// pivot falls below 1e-12, where one pass would lose orthogonality; 1 when one falls below
-// 1e-2; else 2: one pass leaves the members orthogonal to some 100 eps.
-__device__ inline int batch_cholqr(InvSmem& sm, double* Y, int n, int bn, const int* cl) {
+// pivot falls below 1e-12, where one pass would lose orthogonality; 2 when none falls below
+// 1e-2 and no column has lost more than 99 % of its squared norm since norm[]: nothing that
+// matters cancelled in this pass; else 1.
+__device__ inline int batch_cholqr(InvSmem& sm, double* Y, int n, int bn, const int* cl, const double* norm) {
     __shared__ double s_d[64], s_piv[64];
+    __shared__ bool s_kept[64];
     mg::d4 acc[2][2];
     mg::zero(acc);
     mg::tile_mma<mg::IMAJ, mg::IMAJ>(sm.mm, Y, 64, 0, bn, Y, 64, 0, bn, 0, n, acc);
@@ -203,6 +205,7 @@ __device__ inline int batch_cholqr(InvSmem& sm, double* Y, int n, int bn, const 
         const double g = T.t[tid()][tid()];
         s_d[tid()] = g > 0.0 ? 1.0 / sqrt(g) : 0.0;
         s_piv[tid()] = 1.0;
+        s_kept[tid()] = tid() >= bn || g > 1e-2 * norm[tid()];
     }
     __syncthreads();
 #pragma unroll
@@ -233,7 +236,7 @@ __device__ inline int batch_cholqr(InvSmem& sm, double* Y, int n, int bn, const 
                     for (int q = 0; q < 4; ++q) y[16 * k + 4 * q] = X[k][q];
         }
     }
-    const bool well = __all(s_piv[l] > 1e-2);
+    const bool well = __all(s_piv[l] > 1e-2 && s_kept[l]);
     __syncthreads();
     return ok ? 1 + (int)well : 0;
 }
@@ -243,6 +246,7 @@ struct InvShared {
     double red[LSDD_WG / 64];
     double dot[64];
     int cl[64];
+    double norm[64];                                   // squared norms of the solves' results
     int conv;
 };
 
@@ -254,9 +258,10 @@ struct InvShared {
 // make the batch orthogonal to the cluster's earlier members, then orthonormal (Cholesky QR;
 // Gram-Schmidt member by member where that is refused).  The batch stays row-major in the
 // scratch, interleaved by lane for the solves and an operand of the matrix cores as it is.
-// The last iteration orthogonalises twice, the others once, and within the batch again where that
-// met nearly dependent members: without, factors of element blocks with 96 equal eigenvalues of
-// 128 were off by 7e-14 instead of 2e-15 (the next solve multiplies what the pass leaves).
+// Every iteration orthogonalises twice, but for the last only where something cancelled in the
+// first pass: with one pass always, factors of element blocks with 96 equal eigenvalues of 128 were
+// off by 7e-14 instead of 2e-15, and the modes of aggregates of 450 to 900 DOFs orthogonal to
+// 1e-8 (geometric mean) instead of 1.1e-10 (the next solve multiplies what the pass leaves).
 //
 // Convergence: from the second solve on, the iterate entering a solve has unit norm, so the
 // norm of the result is the solve's growth 1 / |lambda - shift| along the eigenvector; once it
@@ -308,12 +313,13 @@ __device__ inline void wg_invit(const double* __restrict__ d, const double* __re
                 else tri_apply_factor(n, L);
                 const double nr = tri_back(n, L);
                 if (!(nr >= grow2)) S.conv = 0;
+                S.norm[tid()] = nr;
             }
             __syncthreads();
             const bool last = S.conv != 0 || it == 3;
             for (int pass = 0; pass < 2; ++pass) {
                 // against the earlier members of the cluster, 64 at a time
-                for (int q0 = qa; q0 < b0 && (last || pass == 0); q0 += 64) {
+                for (int q0 = qa; q0 < b0; q0 += 64) {
                     const double* Q = V + (int64_t)q0 * n;
                     const int qn = min(64, b0 - q0);
                     mg::d4 acc[2][2];
@@ -344,7 +350,7 @@ __device__ inline void wg_invit(const double* __restrict__ d, const double* __re
                     }
                     __syncthreads();
                 }
-                if (const int c = batch_cholqr(S.sm, Y, n, bn, S.cl)) {
+                if (const int c = batch_cholqr(S.sm, Y, n, bn, S.cl, S.norm)) {
                     if (c == 2 && !last) break;
                     continue;
                 }

@@ -472,3 +472,25 @@ def test_element_factors_of_large_clusters(n):
         g = G[k * n * n:(k + 1) * n * n].reshape(n, n)
         assert ranks[k] == n - n // 4
         assert np.abs(g.T @ g - B).max() <= 128 * np.finfo(float).eps * np.abs(B).max()
+
+
+def test_modes_of_large_aggregates_stay_orthogonal():
+    """Aggregates of 450 to 825 DOFs that keep all their modes, in clusters of hundreds: Z^T A_ww Z = I to
+    n eps over the clusters' distance of 1e-4 (geometric mean over the aggregates, 2e-9)."""
+    import scipy.sparse as sp
+    P = _lsdd()
+    off_by = []
+    for width in range(450, 900, 75):
+        prob = fegen.elasticity_q1(32, nu=0.3)
+        prob.agg_of_dof = (np.arange(prob.n) // width).astype(np.int32)
+        with P.Hierarchy.setup_problem(prob, P.Params.default(max_levels=2, tau_const=0.3)) as h:
+            ex = h.export_level(0)
+        A = sp.csr_matrix((ex["val"], ex["col"], ex["rowptr"]), shape=(prob.n, prob.n))
+        at = 0
+        for i in range(-(-prob.n // width)):
+            d = np.arange(i * width, min((i + 1) * width, prob.n))
+            k = int(ex["k"][i])
+            Z = ex["Z"][at:at + len(d) * k].reshape(len(d), k)
+            at += len(d) * k
+            off_by.append(np.abs(Z.T @ (A[d][:, d] @ Z) - np.eye(k)).max())
+    assert np.exp(np.mean(np.log(off_by))) <= 900 * np.finfo(float).eps / 1e-4
