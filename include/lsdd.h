@@ -379,13 +379,16 @@ lsdd_status lsdd_level_kernels(const lsdd_hierarchy* h, int32_t level, int32_t* 
  * one hierarchy what lsdd_autotune chose on another.  Values outside these -> LSDD_E_INVAL;
  * kernels the level does not have -> LSDD_E_UNSUPPORTED (sweeps: one launch per colour
  * needs a colouring and overlaps of at most 640 DOFs, rows of the unpacked inverses need
- * room for these).  Drops captured PCG graphs; changes only the order of sums. */
+ * room for these; either, and transfers, tables of at most 256 MB).  Drops captured PCG graphs; changes only the order of sums. */
 lsdd_status lsdd_set_level_kernels(lsdd_hierarchy* h, int32_t level, const int32_t* in);
 
 /* Per-kernel timing: on != 0 clears the counters and records a pair of HIP
  * events on the solve stream around every launch of the traced kernel classes
  * (csr_resid_rows, sub_symv, sub_finalize, small_sub, csr_spmv, restrict,
- * prolong, coarse_symv, pcg_spmv); on = 0 stops recording.  lsdd_trace_get reads class idx
+ * prolong, coarse_symv, pcg_spmv; sub_fact: the factor product of the mixed cycle; of the
+ * single-vector kernels of lsdd_level_kernels colour_step, sub_rows, resid_restrict and
+ * prolong_agg; coarse_dense: the unpacked coarsest inverse); on = 0 stops recording.
+ * lsdd_trace_get reads class idx
  * (0-based; LSDD_E_INVAL past the end): name (host char[name_len]), launches,
  * summed event time in ms and summed algorithmic bytes of those launches (the
  * bytes each launch must move at minimum: matrix entries, indices and vector

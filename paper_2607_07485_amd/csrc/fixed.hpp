@@ -7,10 +7,12 @@
 // in the last place of the element entries moves a V-cycle by 4e-6 to 5e-5, and so does any
 // other order of the same sums, even in the diagonal-tile steps alone; on the other elements
 // another order moves it by 1e-13 to 1.3e-10, at one size of 17 by 1e-9.  The diagonals of the
-// Hermites span 5e9 to 1e12 on meshes of 24^2 to 96^2 cells, 5.3e3 with the derivatives scaled by
-// the mesh size; those of the others at most 4.3e2, and the line is drawn halfway (in decades).
-// Such problems keep these kernels in their set-up, element factors included, bit for bit; the
-// instances of a batch are told apart.  All others take the faster ones of trd.hip, invit.hpp and tile64.hpp
+// clamped Hermites span 3e8 to 7e13 on meshes of 12^2 to 256^2 cells, 5e3 to 1.6e4 with the
+// derivatives scaled by the mesh size; those of the others at most 4.3e2, and the line is drawn
+// halfway (in decades).  It tells elements apart, not rounding: scaled Hermites without the
+// clamping span 1e2 and are on the other side.
+// Problems above the line keep these kernels in their set-up, element factors included, bit for
+// bit; the instances of a batch are told apart.  All others take those of trd.hip, invit.hpp and tile64.hpp
 // (inverse iteration for 8 matrices of up to 882 with 179 vectors 15.4 ms here, 4.6 there;
 // eigenvalues 4.9 and 1.05; a diagonal tile 48 and 17.5 us).
 #pragma once

@@ -474,7 +474,8 @@ __global__ void __launch_bounds__(256) k_dense_apply(int n, const double* __rest
 // aggregates of 81 DOFs ran 14.6 us at 1024 threads, whose workgroups fill the chip twice).
 constexpr int64_t WIDE_AGG = 256;
 
-// kernels of a launch with more than 64 KB of LDS ask for it once per device and kernel
+// a launch with more than 64 KB of LDS asks for it each time (a field of the kernel on this device
+// is set: no state of our own to keep per device and kernel)
 template <class K>
 void allow_lds(K kern, size_t bytes) {
     if (bytes > 160 * 1024) throw std::runtime_error("fused cycle kernel: more LDS than a CU has");

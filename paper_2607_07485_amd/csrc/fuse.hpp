@@ -39,8 +39,8 @@ void launch_row_table(int64_t n_sub, const int64_t* off, const int32_t* dofs, co
                       const int64_t* scoff, int pad, int4* tab, hipStream_t st);
 
 // x[Omega] += A_Omega^{-1} (r - A x)[Omega] for n_sub subdomains no two of which share an
-// element (x is read and written in one launch); rows: their row tables (pad a multiple of 64, <= FUSE_M), row_len: average entries per row of A;
-// x_zero: x is zero
+// element (x is read and written in one launch); rows: their row tables (pad a multiple of 64,
+// <= FUSE_M), row_len: average entries per row of A; x_zero: x is zero
 template <typename T>
 void launch_colour_step(int64_t n_sub, const SubItem* items, const int4* rows, const int32_t* col, const T* val,
                         const T* pk, const T* tiles, const T* r, T* x, bool x_zero, int pad, int row_len,

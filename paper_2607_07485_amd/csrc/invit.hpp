@@ -252,9 +252,9 @@ struct InvShared {
 
 // Eigenvectors of the tridiagonal (d, e) for the eigenvalues lam[0..kk) by inverse iteration,
 // to the columns of V (n x kk, column-major).  Eigenvalues closer than 1e-4 ||T|| form a
-// cluster; the workgroup takes the clusters that start at the indices [r0, r1), as many whole ones at a time as 64 lanes
-// hold (symmetric aggregates have dozens of pairs and triples; one cluster at a time took 7
-// ms), a larger cluster 64 members at a time: solve every member's system on its own lane,
+// cluster; the workgroup takes the clusters that start at the indices [r0, r1), as many whole
+// ones at a time as 64 lanes hold (symmetric aggregates have dozens of pairs and triples; one
+// cluster at a time took 7 ms), a larger cluster 64 members at a time: solve every member's system on its own lane,
 // make the batch orthogonal to the cluster's earlier members, then orthonormal (Cholesky QR;
 // Gram-Schmidt member by member where that is refused).  The batch stays row-major in the
 // scratch, interleaved by lane for the solves and an operand of the matrix cores as it is.

@@ -563,7 +563,7 @@ struct lsdd_hierarchy {
     double* d_scale0 = nullptr;
     double* d_factor = nullptr;   // scratch for lsdd_update_theta
     std::vector<char> fixed_inst; // instances set up with the order of operations of fixed.hpp
-    int32_t breakdown_bits = 0;   // cause of the last PCG breakdown (k_pcg_alpha/check/beta bits)
+    int32_t breakdown_bits = 0;   // cause of the last PCG breakdown (bits of k_pcg_update_xr/check/update_p)
     // hipGraph-captured halves of the PCG iteration: [block][cycle precision][half]
     bool use_graph = false;
     hipGraphExec_t gx[2][3][2] = {};
