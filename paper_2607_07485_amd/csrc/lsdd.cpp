@@ -405,7 +405,7 @@ struct Level {
     int4* d_arows = nullptr;          // row tables of the aggregates, apad entries each
     RowItem* d_witems = nullptr;      // 16-row items in sweep order, by colour
     std::vector<int64_t> color_witem0;
-    double* d_full = nullptr;         // unpacked inverses, sweep order
+    double* d_full = nullptr;         // unpacked inverses, aggregate order
     float* d_full32 = nullptr;
     int32_t spad = 0, apad = 0, max_k = 0, row_len = 0;
     bool chosen[2] = {false, false};  // by the autotuner or the caller, not by the rule
@@ -987,21 +987,32 @@ void need_fused(lsdd_hierarchy* h, Level& lv, int p, int mode, int xfer) {
         lv.d_srows = row_table((size_t)n_sub * lv.spad);
         launch_row_table(n_sub, lv.d_sw_sub_off, lv.d_sw_sub_dofs, lv.d_rowptr, lv.d_scoff, lv.spad, lv.d_srows, st);
     }
-    if (mode == 2 && !(p ? (void*)lv.d_full32 : (void*)lv.d_full)) {
-        off.assign(n_sub + 1, 0);
-        lv.color_witem0.assign(lv.n_colors + 1, 0);
-        for (int32_t c = 0; c < lv.n_colors; ++c) {
-            for (int32_t s = lv.color_sub0[c]; s < lv.color_sub0[c + 1]; ++s) {
-                const int32_t m = (int32_t)(lv.sw_sub_off[s + 1] - lv.sw_sub_off[s]);
-                off[s + 1] = off[s] + (int64_t)m * m;
-                for (int32_t r0 = 0; r0 < m; r0 += 16)
-                    wi.push_back(RowItem{(int32_t)lv.sw_sub_off[s], m, r0, 0, off[s]});
-            }
-            lv.color_witem0[c + 1] = (int64_t)wi.size();
+    const bool unpack = mode == 2 && !(p ? (void*)lv.d_full32 : (void*)lv.d_full);
+    if (unpack || (mode == 2 && !lv.d_witems)) {
+        std::vector<int64_t> at(n_sub + 1, 0);                    // by aggregate
+        for (int32_t s = 0; s < n_sub; ++s) {
+            const int64_t m = lv.sw_sub_off[s + 1] - lv.sw_sub_off[s];
+            at[lv.sweep[s] + 1] = m * m;
         }
-        if (p) lv.d_full32 = ar.alloc<float>(off[n_sub]);
-        else lv.d_full = ar.alloc<double>(off[n_sub]);
-        if (!lv.d_witems) lv.d_witems = ar.upload(wi, st);
+        for (int32_t a = 0; a < n_sub; ++a) at[a + 1] += at[a];
+        off.resize(n_sub);
+        for (int32_t s = 0; s < n_sub; ++s) off[s] = at[lv.sweep[s]];
+        if (!lv.d_witems) {
+            lv.color_witem0.assign(lv.n_colors + 1, 0);
+            for (int32_t c = 0; c < lv.n_colors; ++c) {
+                for (int32_t s = lv.color_sub0[c]; s < lv.color_sub0[c + 1]; ++s) {
+                    const int32_t m = (int32_t)(lv.sw_sub_off[s + 1] - lv.sw_sub_off[s]);
+                    for (int32_t r0 = 0; r0 < m; r0 += 16)
+                        wi.push_back(RowItem{(int32_t)lv.sw_sub_off[s], m, r0, 0, off[s]});
+                }
+                lv.color_witem0[c + 1] = (int64_t)wi.size();
+            }
+            lv.d_witems = ar.upload(wi, st);
+        }
+    }
+    if (unpack) {
+        if (p) lv.d_full32 = ar.alloc<float>(lv.inv_len);
+        else lv.d_full = ar.alloc<double>(lv.inv_len);
         d_off = ar.upload(off, st);
         if (p) {
             launch_unpack<float>(n_sub, lv.max_sub, lv.d_sw_sub_off, lv.d_sw_tp_off, lv.d_sw_pk_off, lv.d_tiles32,
@@ -1012,7 +1023,7 @@ void need_fused(lsdd_hierarchy* h, Level& lv, int p, int mode, int xfer) {
         }
     }
     HIPCHK(hipGetLastError());
-    if (!ai.empty() || !si.empty() || d_off) sync(st);            // the vectors are read until then
+    if (!ai.empty() || !si.empty() || !off.empty()) sync(st);     // the vectors are read until then
     if (d_off) ar.release(d_off);
 }
 
@@ -1052,7 +1063,9 @@ void use_kernels(lsdd_hierarchy* h, Level& lv, int p, int mode, int xfer) {
 }
 
 // What a level's single-vector cycle may run, and what it starts out with.  RAS masks entries of
-// its sweep lists, which the row tables cannot express.
+// its sweep lists, which the row tables cannot express.  A level that starts out with rows of
+// the unpacked inverses keeps those of the set-up (d_inv: allocating and unpacking them again
+// took 1 of the 35 ms of the set-up of Q2 hexes 8^3); else they go back before the tables come.
 void init_fused(lsdd_hierarchy* h, Level& lv) {
     const int32_t n_sub = (int32_t)lv.sweep.size();
     const Closure& C = lv.cl;
@@ -1110,6 +1123,9 @@ void init_fused(lsdd_hierarchy* h, Level& lv) {
         lv.fuse[p] = mode;
         lv.xfer[p] = lv.xfer_has ? down | up(p ? 4.0 : 8.0) : 0;
     }
+    if (lv.fuse[0] == 2) lv.d_full = lv.d_inv;
+    else h->arena.release(lv.d_inv);
+    lv.d_inv = nullptr;
     for (int p = 0; p < (h->prm.precision >= 1 ? 2 : 1); ++p) {
         if (try_fused(h, lv, p, lv.fuse[p], lv.xfer[p])) continue;
         lv.fuse[p] = lv.xfer[p] = 0;
@@ -1761,9 +1777,9 @@ std::unique_ptr<Level> coarsen(lsdd_hierarchy* h, Level& lv, const int32_t* agg_
         }
         ar.release(d_tp_agg);
         ar.release(d_pk_agg);
-        ar.release(lv.d_inv);
-        lv.d_inv = nullptr;
         init_fused(h, lv);
+        if (lv.d_inv) ar.release(lv.d_inv);
+        lv.d_inv = nullptr;
     }
     lv.rloc_len = (int64_t)sw_dofs.size();
     alloc_vectors(h, lv, 0);

@@ -494,3 +494,24 @@ def test_modes_of_large_aggregates_stay_orthogonal():
             at += len(d) * k
             off_by.append(np.abs(Z.T @ (A[d][:, d] @ Z) - np.eye(k)).max())
     assert np.exp(np.mean(np.log(off_by))) <= 900 * np.finfo(float).eps / 1e-4
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("smoother", [0, 2])
+def test_unpacked_inverses_of_the_setup_and_unpacked_again(precision, smoother):
+    """A level that starts out with rows of the unpacked inverses runs on those of its set-up; given back and
+    unpacked again they are the same, bit for bit, in either precision."""
+    P = _lsdd()
+    prob = fegen.elasticity_q2hex(4, nu=0.3)
+    prm = P.Params.default(max_levels=2, agg_passes=1, tau_const=0.75, precision=precision, smoother=smoother)
+    r = torch.from_numpy(np.random.default_rng(14).standard_normal(prob.n)).cuda()
+    with P.Hierarchy.setup_problem(prob, prm) as h:
+        for p in range(precision + 1):
+            h.set_cycle_precision(p)
+            h.set_level_kernels(0, 2, 0)
+        for p in range(precision + 1):
+            h.set_cycle_precision(p)
+            first = h.vcycle(r)
+            h.set_level_kernels(0, 0, 0)
+            h.set_level_kernels(0, 2, 0)
+            assert torch.equal(h.vcycle(r), first)
