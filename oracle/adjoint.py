@@ -1,6 +1,6 @@
 """FP64 CPU oracle of the gradient of u = A(theta)^{-1} b (test infrastructure only).
 
-Like ``oracle.lsdd`` this module is the checker, not the product: only the test
+Like ``oracle.lsdd`` this module is the oracle, not the product: only the test
 suite, the smoke entry point and the benchmark's CPU-baseline leg may import it.
 
 Setting.  The element blocks are linear in a per-element coefficient,

@@ -1,6 +1,6 @@
 """Plain FP64 CPU oracle of the LS-AMG-DD hot path (test infrastructure only).
 
-This module is the checker, not the product: only the test suite, the smoke
+This module is the oracle, not the product: only the test suite, the smoke
 entry point and the CPU-baseline leg of the benchmark may import it.  It shares
 no code with the HIP library and is deliberately slow and literal: dense LAPACK
 per element / aggregate, scipy.sparse for the assembled operators, Python loops
