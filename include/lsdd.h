@@ -360,7 +360,8 @@ lsdd_status lsdd_level_tuning(const lsdd_hierarchy* h, int32_t level, int32_t* o
  * triangles are built on first use).  Captured PCG graphs are
  * dropped and recaptured on the next solve.  The kernels of the single-vector cycle
  * (lsdd_level_kernels) follow: shapes that lsdd_autotune chose for the current cycle
- * precision bring back what it chose with them, the shapes in effect and those it chose
+ * precision bring back what it chose with them (no room for that -> LSDD_E_NOMEM, nothing
+ * changed), the shapes in effect and those it chose
  * for another precision or for blocks change nothing, and any others put the level into
  * separate launches for every precision.  Like lsdd_autotune, it changes only the
  * summation order of the sums involved. */
@@ -379,7 +380,9 @@ lsdd_status lsdd_level_kernels(const lsdd_hierarchy* h, int32_t level, int32_t* 
  * one hierarchy what lsdd_autotune chose on another.  Values outside these -> LSDD_E_INVAL;
  * kernels the level does not have -> LSDD_E_UNSUPPORTED (sweeps: one launch per colour
  * needs a colouring and overlaps of at most 640 DOFs, rows of the unpacked inverses need
- * room for these; either, and transfers, tables of at most 256 MB).  Drops captured PCG graphs; changes only the order of sums. */
+ * room for these; either, and transfers, tables of at most 256 MB); no room for what
+ * they need -> LSDD_E_NOMEM (separate launches need nothing).  On an error nothing
+ * changes.  Drops captured PCG graphs; changes only the order of sums. */
 lsdd_status lsdd_set_level_kernels(lsdd_hierarchy* h, int32_t level, const int32_t* in);
 
 /* Per-kernel timing: on != 0 clears the counters and records a pair of HIP
